@@ -165,7 +165,8 @@ adapshot_status adapshot_query_attn(adapshot_ctx* ctx, const adapshot_cache* cac
  * v_self, out, q_pos0 as in adapshot_query_attn.  Two launches besides the merge of the split partials: a small
  * one that expands the plan, and the attention.  Pools registered with ADAPSHOT_KEYS_UNROTATED only (ESTATE
  * otherwise).  bf16 models with head_dim 128 run the matrix-core kernel described above, for which a pool layer
- * must stay below 4 GiB (ECAPACITY); other shapes run a plain kernel that gathers and rotates key by key. */
+ * must stay below 4 GiB (ECAPACITY); other shapes run the streaming kernel, which gathers and rotates the keys in
+ * registers and merges its splits itself (one launch besides the plan). */
 adapshot_status adapshot_query_attn_pool(adapshot_ctx* ctx, int32_t layer, const int32_t* shot_ids,
                                          const int32_t* order, int32_t m, int64_t pos0, const void* q,
                                          const void* k_self, const void* v_self, int32_t t_q, int64_t q_pos0,
@@ -190,7 +191,7 @@ adapshot_status adapshot_assemble_batched(adapshot_ctx* ctx, adapshot_cache* cac
  * whose workgroups rotate the query rows they need themselves, and one combine grid): the context splits
  * have one common length, so
  * probes over nested prefixes of one cache read identical leading slices, and those workgroups are
- * scheduled next to each other.  Other shapes run item by item.  The outputs of distinct items must not
+ * scheduled next to each other.  Other shapes run up to 32 items per launch.  The outputs of distinct items must not
  * overlap; inputs may be shared between items.  A call whose arguments other than `layer` equal the previous
  * batched call's on this context (the same items, caches, pointers and lengths: the next layer of a forward pass)
  * reuses the tables the previous call left in device memory and only launches; nothing the caller does between
@@ -314,7 +315,7 @@ adapshot_status adapshot_set_attn_splits(adapshot_ctx* ctx, int32_t n_split);
 /* The split plan adapshot_query_attn uses for t_q query tokens over n_ctx context slots on a GPU with
  * n_compute_units compute units (host logic, nothing is launched, no GPU needed): the context is cut into
  * *n_split pieces of *keys_per_split slots (a multiple of 64; the last piece may be shorter; an empty context
- * has no piece), and the query's own tokens form one more.  EINVAL on a bad description or argument. */
+ * has no piece), and the query's own tokens form one more (bf16, head_dim 128) or go with the last piece (other shapes).  EINVAL on a bad description or argument. */
 adapshot_status adapshot_attn_split_plan(const adapshot_model_desc* desc, int32_t n_compute_units, int32_t t_q,
                                          int64_t n_ctx, int32_t* n_split, int64_t* keys_per_split);
 
@@ -326,7 +327,7 @@ adapshot_status adapshot_attn_split_plan(const adapshot_model_desc* desc, int32_
  * and their count, and forgets them.  Whole-path throughput is measured with profiling off. */
 typedef enum {
     ADAPSHOT_KERNEL_ASSEMBLE = 0,       /* fused gather + re-encode */
-    ADAPSHOT_KERNEL_ROPE_ROWS = 1,      /* rotation of the query rows and their own keys */
+    ADAPSHOT_KERNEL_ROPE_ROWS = 1,      /* rotation of the query rows (ranking); plan of a zero-copy context */
     ADAPSHOT_KERNEL_ATTN = 2,           /* split-K attention proper */
     ADAPSHOT_KERNEL_ATTN_COMBINE = 3,   /* merge of the split partials */
     ADAPSHOT_KERNEL_ENTROPY_CHUNK = 4,  /* vocabulary pass */

@@ -237,6 +237,8 @@ extern "C" adapshot_status adapshot_create(const adapshot_model_desc* desc, adap
     if (e == hipSuccess) e = hipMalloc((void**)&ctx->tab_hi, hi.size() * sizeof(float2));
     if (e == hipSuccess) e = hipMemcpy(ctx->tab_lo, lo.data(), lo.size() * sizeof(float2), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(ctx->tab_hi, hi.data(), hi.size() * sizeof(float2), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMalloc((void**)&ctx->stream_counters, kStreamUnits * sizeof(unsigned));
+    if (e == hipSuccess) e = hipMemset(ctx->stream_counters, 0, kStreamUnits * sizeof(unsigned));
     if (e == hipSuccess) e = entropy_static_scratch(&ctx->static_ent);  // set-up: the current device is the context's
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -253,7 +255,6 @@ extern "C" void adapshot_destroy(adapshot_ctx* ctx) {
     ctx->prof.release();
     ctx->tile_ring.release();
     ctx->q_rot.release();
-    ctx->k_rot.release();
     ctx->part_o.release();
     ctx->part_ml.release();
     ctx->ent_part.release();
@@ -269,6 +270,7 @@ extern "C" void adapshot_destroy(adapshot_ctx* ctx) {
     ctx->retired.clear();
     if (ctx->tab_lo) (void)hipFree(ctx->tab_lo);
     if (ctx->tab_hi) (void)hipFree(ctx->tab_hi);
+    if (ctx->stream_counters) (void)hipFree(ctx->stream_counters);
     delete ctx;
 }
 
@@ -591,14 +593,44 @@ static int64_t plan_mfma_splits(int64_t n_cu, int64_t units, int64_t key_tiles, 
     return best;
 }
 
-// Split the context of one attention call so that (kv heads x row tiles x splits) fills the chip: once for the
-// MFMA kernel (one 8-wave workgroup per compute unit), several times for the one-wave generic kernel.  Keys per
+// 16-row blocks per workgroup of the streaming kernel.  Two share the loads and the unpacking of K and V, but leave half
+// the workgroups: they pay where one block each already gives every compute unit two workgroups.
+static int32_t stream_row_blocks(const adapshot_model_desc& d, int64_t n_cu, int64_t rows) {
+    return d.head_dim == 64 && d.n_kv_heads * ((rows + 15) / 16) >= 2 * n_cu ? 2 : 1;
+}
+
+// Context splits of the streaming kernel: the count whose price is lowest.  A split of n 64-key tiles keeps each of a
+// compute unit's four matrix cores busy for n 16-key steps; a step is its matrix instructions and about 450 cycles of
+// softmax and load latency.  Splitting costs the merge: 2.2 us and a little per partial (measured: fp32, head_dim 128,
+// one query over 2300 slots: 55 us in one split, 11.8 us in 36; bf16, head_dim 64, 256 slots: 6.7 us in one, 8.0 us in 4).
+static int64_t plan_stream_splits(const adapshot_model_desc& d, int64_t n_cu, int64_t units, int64_t key_tiles, int32_t row_blocks) {
+    const int64_t pv = 4 * 32 * std::max(1, d.head_dim / 16);
+    const int64_t qk = d.dtype == ADAPSHOT_BF16 ? std::max(1, d.head_dim / 32) * 16 : d.head_dim / 4 * 32;
+    const double step_us = (double)(row_blocks * (pv + qk) + 450) / 2100.0;
+    const int64_t n_max = std::min<int64_t>(key_tiles, kStreamMaxSplits);
+    int64_t best = 1, last = 0;
+    double best_t = 1e300;
+    for (int64_t n = 1; n <= n_max; ++n) {
+        const int64_t st = (key_tiles + n - 1) / n;
+        if (st == last) continue;  // no shorter splits than with one fewer
+        last = st;
+        const int64_t rounds = (units * n + n_cu - 1) / n_cu;
+        const double t = (double)(rounds * st) * step_us + (n > 1 ? 2.2 + 0.03 * (double)n : 0.0);
+        if (t < best_t) {
+            best_t = t;
+            best = n;
+        }
+    }
+    return best;
+}
+
+// Split the context of one attention call so that (kv heads x row tiles x splits) fills the chip.  Keys per
 // split is a multiple of the 64-key tile; an empty context has no split.
 static void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t force_splits, int32_t t_q, int64_t n_ctx,
                              int64_t* n_split_out, int64_t* keys_per_split_out) {
     const bool mfma = attn_mfma_supported(d);
     const int64_t rows = (int64_t)t_q * (d.n_q_heads / d.n_kv_heads);
-    const int64_t row_tile = mfma ? kAttnRowTile : 1;
+    const int64_t row_tile = mfma ? kAttnRowTile : 16 * stream_row_blocks(d, n_cu, rows);
     const int64_t units = d.n_kv_heads * ((rows + row_tile - 1) / row_tile);
     const int64_t key_tiles = (n_ctx + 63) / 64;
     int64_t n_split = 0, keys_per_split = 64;
@@ -606,8 +638,7 @@ static void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t
         if (mfma) {
             n_split = plan_mfma_splits(n_cu, units, key_tiles, ((int64_t)t_q + 63) / 64);
         } else {
-            const int64_t target = std::max<int64_t>(1, n_cu * 8 / units);
-            n_split = std::min<int64_t>(std::min<int64_t>(target, key_tiles), 64);
+            n_split = plan_stream_splits(d, n_cu, units, key_tiles, stream_row_blocks(d, n_cu, rows));
         }
         if (force_splits > 0) n_split = std::min<int64_t>(force_splits, key_tiles);
         keys_per_split = ((key_tiles + n_split - 1) / n_split) * 64;
@@ -632,48 +663,100 @@ static adapshot_status run_query_attn(adapshot_ctx* ctx, const adapshot_cache* c
                              v_self, t_q, q_pos0, out, nullptr, nullptr, stream);
 }
 
+// One launch of the streaming kernel over up to kStreamItems problems (their keys_per_split, n_split and unit0 are set
+// here).  Every problem gets the splits that fill the chip together with the others; slot_src as in AttnFold, with one
+// problem only.
+static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t n_items, const int32_t* slot_src,
+                                  int64_t ctx_pos0, hipStream_t stream) {
+    const adapshot_model_desc& d = ctx->desc;
+    const int64_t g = d.n_q_heads / d.n_kv_heads;
+    int64_t rows = 0, tiles = 0;
+    for (int32_t i = 0; i < n_items; ++i) {
+        rows += (int64_t)items[i].t_q * g;
+        tiles = std::max<int64_t>(tiles, ((int64_t)items[i].n_ctx + 63) / 64);
+    }
+    StreamLaunch sl;
+    sl.row_blocks = stream_row_blocks(d, ctx->n_cu, rows);
+    const int64_t tr = 16 * sl.row_blocks;
+    int64_t units = 0;
+    for (int32_t i = 0; i < n_items; ++i) units += d.n_kv_heads * (((int64_t)items[i].t_q * g + tr - 1) / tr);
+    int64_t n_split = 1;
+    if (tiles > 0) n_split = plan_stream_splits(d, ctx->n_cu, units, tiles, sl.row_blocks);
+    if (ctx->force_splits > 0) n_split = std::min<int64_t>(ctx->force_splits, std::max<int64_t>(1, tiles));
+    if (units > kStreamUnits) n_split = 1;  // more units than arrival counters: the chip is full without splits
+    int64_t unit0 = 0, grid_x = 0;
+    for (int32_t i = 0; i < n_items; ++i) {
+        StreamItem& it = items[i];
+        const int64_t kt = ((int64_t)it.n_ctx + 63) / 64;
+        it.keys_per_split = (int32_t)std::max<int64_t>(64, (kt + n_split - 1) / n_split * 64);
+        it.n_split = (int32_t)std::max<int64_t>(1, ((int64_t)it.n_ctx + it.keys_per_split - 1) / it.keys_per_split);
+        const int64_t here = d.n_kv_heads * (((int64_t)it.t_q * g + tr - 1) / tr);
+        it.unit0 = (int32_t)unit0;
+        unit0 += here;
+        grid_x = std::max(grid_x, here * it.n_split);
+    }
+    if (grid_x > INT32_MAX || unit0 > INT32_MAX) return fail(ctx, ADAPSHOT_EINVAL, "query_attn: too many workgroups");
+    sl.part_o = nullptr;
+    sl.part_ml = nullptr;
+    if (n_split > 1) {
+        hipError_t e = ctx->part_o.reserve((size_t)units * n_split * tr * d.head_dim * sizeof(float), ctx->retired);
+        if (e == hipSuccess) e = ctx->part_ml.reserve((size_t)units * n_split * tr * sizeof(float2), ctx->retired);
+        if (e != hipSuccess) return fail_hip(ctx, "query_attn: workspace", e);
+        sl.part_o = (float*)ctx->part_o.p;
+        sl.part_ml = (float*)ctx->part_ml.p;
+    }
+    sl.tab_lo = ctx->tab_lo;
+    sl.tab_hi = ctx->tab_hi;
+    sl.counters = ctx->stream_counters;
+    sl.slot_src = slot_src;
+    sl.ctx_pos0 = ctx_pos0;
+    sl.n_q_heads = d.n_q_heads;
+    sl.n_kv_heads = d.n_kv_heads;
+    sl.head_dim = d.head_dim;
+    sl.dtype = d.dtype;
+    sl.max_split = (int32_t)n_split;
+    sl.pool_tokens = (int32_t)std::min<int64_t>(ctx->shot_offsets.empty() ? 0 : ctx->shot_offsets.back(), INT32_MAX);
+    sl.grid_x = (int32_t)grid_x;
+    sl.n_items = n_items;
+    sl.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
+    sl.items = items;
+    hipError_t e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN, stream, [&] { return launch_attn_stream(sl, stream); });
+    if (e != hipSuccess) return fail_hip(ctx, "query_attn: attention launch", e);
+    return ADAPSHOT_OK;
+}
+
+static StreamItem stream_item(const void* k_ctx, const void* v_ctx, int64_t n_ctx, const void* q, const void* k_self,
+                              const void* v_self, int32_t t_q, int64_t q_pos0, void* out) {
+    StreamItem it{};
+    it.q = (const char*)q;
+    it.k_self = (const char*)k_self;
+    it.v_self = (const char*)v_self;
+    it.out = (char*)out;
+    it.k_ctx = (const char*)k_ctx;
+    it.v_ctx = (const char*)v_ctx;
+    it.n_ctx = (int32_t)n_ctx;  // rows of a layer span at most 4 GiB and hold at least 32 bytes
+    it.t_q = t_q;
+    it.q_pos0 = (int32_t)q_pos0;  // below max_position <= 2^30
+    return it;
+}
+
 static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, const void* v_ctx, int64_t n_ctx,
                                          const void* q, const void* k_self, const void* v_self, int32_t t_q,
                                          int64_t q_pos0, void* out, const int32_t* slot_src, const float2* tile_rot,
                                          hipStream_t stream, int64_t ctx_pos0) {
     const adapshot_model_desc& d = ctx->desc;
+    if (!attn_mfma_supported(d)) {
+        StreamItem it = stream_item(k_ctx, v_ctx, n_ctx, q, k_self, v_self, t_q, q_pos0, out);
+        return run_stream(ctx, &it, 1, slot_src, ctx_pos0, stream);
+    }
     const int g = d.n_q_heads / d.n_kv_heads;
     const int64_t rows = (int64_t)t_q * g;
-    const bool mfma = attn_mfma_supported(d);
 
     int64_t n_split = 0, keys_per_split = 64;
     plan_single_attn(d, ctx->n_cu, ctx->force_splits, t_q, n_ctx, &n_split, &keys_per_split);
-
-    const size_t esz = (size_t)ctx->elem_bytes;
-    hipError_t e = hipSuccess;
-    const bool fold = mfma;  // the matrix-core kernels rotate the query rows (and the query's own keys) themselves
-    if (!fold) {
-        e = ctx->q_rot.reserve((size_t)t_q * d.n_q_heads * d.head_dim * esz, ctx->retired);
-        if (e == hipSuccess) e = ctx->k_rot.reserve((size_t)t_q * d.n_kv_heads * d.head_dim * esz, ctx->retired);
-    }
-    if (e == hipSuccess)
-        e = ctx->part_o.reserve((size_t)(n_split + 1) * d.n_kv_heads * rows * d.head_dim * (mfma ? 2 : 4), ctx->retired);
+    hipError_t e = ctx->part_o.reserve((size_t)(n_split + 1) * d.n_kv_heads * rows * d.head_dim * 2, ctx->retired);  // fp16 rows
     if (e == hipSuccess) e = ctx->part_ml.reserve((size_t)(n_split + 1) * d.n_kv_heads * rows * sizeof(float4), ctx->retired);
     if (e != hipSuccess) return fail_hip(ctx, "query_attn: workspace", e);
-
-    RopeRowsParams rp;
-    rp.q = q;
-    rp.k_self = k_self;
-    rp.q_rot = ctx->q_rot.p;
-    rp.k_rot = ctx->k_rot.p;
-    rp.tab_lo = ctx->tab_lo;
-    rp.tab_hi = ctx->tab_hi;
-    rp.q_pos0 = q_pos0;
-    rp.t_q = t_q;
-    rp.n_q_heads = d.n_q_heads;
-    rp.n_kv_heads = d.n_kv_heads;
-    rp.head_dim = d.head_dim;
-    rp.dtype = d.dtype;
-    rp.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
-    if (!fold) {
-        e = timed_launch(ctx, ADAPSHOT_KERNEL_ROPE_ROWS, stream, [&] { return launch_rope_rows(rp, stream); });
-        if (e != hipSuccess) return fail_hip(ctx, "query_attn: rope launch", e);
-    }
 
     AttnParams ap;
     ap.k_cache = k_ctx;
@@ -681,19 +764,17 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
     AttnFold af;
     af.slot_src = slot_src;
     af.tile_rot = tile_rot;
-    ap.q_rot = ctx->q_rot.p;
-    ap.k_self_rot = ctx->k_rot.p;
+    ap.q_rot = nullptr;
     ap.v_self = v_self;
     af.q_raw = q;
     af.k_self_raw = k_self;
     af.tab_lo = ctx->tab_lo;
     af.tab_hi = ctx->tab_hi;
     af.q_pos0 = q_pos0;
-    af.q_scale = rp.q_scale;
+    af.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
     af.pool_tokens = (int32_t)std::min<int64_t>(ctx->shot_offsets.empty() ? 0 : ctx->shot_offsets.back(), INT32_MAX);
     ap.part_o = ctx->part_o.p;
     ap.part_mlf = (float4*)ctx->part_ml.p;
-    ap.part_half = mfma ? 1 : 0;
     ap.no_self = 0;
     ap.v_blocks = 4;
     ap.split_bounds = nullptr;
@@ -707,10 +788,8 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
     ap.head_dim = d.head_dim;
     ap.dtype = d.dtype;
     ap.layer_stride_bytes = 0;
-    e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN, stream, [&] {
-        if (!mfma) return launch_attn_generic(ap, GenericPool{slot_src, ctx->tab_lo, ctx->tab_hi, ctx_pos0}, stream);
-        return slot_src ? launch_attn_mfma_pool(ap, af, stream) : launch_attn_mfma(ap, af, stream);
-    });
+    e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN, stream,
+                     [&] { return slot_src ? launch_attn_mfma_pool(ap, af, stream) : launch_attn_mfma(ap, af, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn: attention launch", e);
     e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN_COMBINE, stream, [&] { return launch_attn_combine(ap, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn: combine launch", e);
@@ -845,7 +924,7 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
         });
         if (e != hipSuccess) return fail_hip(ctx, "query_attn_batched: attention launch", e);
         e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN_COMBINE, stream,
-                         [&] { return launch_attn_combine_batched(dit, dcw, (int)ctx->batch_n_comb, d.dtype, ctx->batch_max_partials, stream); });
+                         [&] { return launch_attn_combine_batched(dit, dcw, (int)ctx->batch_n_comb, ctx->batch_max_partials, stream); });
         if (e != hipSuccess) return fail_hip(ctx, "query_attn_batched: combine launch", e);
         return ADAPSHOT_OK;
     }
@@ -939,7 +1018,6 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
             b.fold.tile_rot = nullptr;
         }
         b.attn.q_rot = nullptr;
-        b.attn.k_self_rot = nullptr;
         b.attn.v_self = it.v_self;
         b.fold.q_raw = it.q;
         b.fold.k_self_raw = it.k_self;
@@ -950,7 +1028,6 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
         b.fold.pool_tokens = (int32_t)std::min<int64_t>(ctx->shot_offsets.empty() ? 0 : ctx->shot_offsets.back(), INT32_MAX);
         b.attn.part_o = (char*)ctx->part_o.p + pl.po_off;
         b.attn.part_mlf = (float4*)((char*)ctx->part_ml.p + pl.pml_off);
-        b.attn.part_half = 1;
         b.attn.no_self = 0;
         b.attn.v_blocks = 4;
         b.attn.split_bounds = nullptr;
@@ -997,7 +1074,7 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
                      [&] { return launch_attn_mfma_batched(dit, daw, (int)n_attn, pool != nullptr, stream_tiles, layer, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn_batched: attention launch", e);
     e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN_COMBINE, stream,
-                     [&] { return launch_attn_combine_batched(dit, dcw, (int)n_comb, d.dtype, max_partials, stream); });
+                     [&] { return launch_attn_combine_batched(dit, dcw, (int)n_comb, max_partials, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn_batched: combine launch", e);
     ctx->batch_key.swap(key);
     ctx->batch_n_attn = n_attn;
@@ -1274,7 +1351,7 @@ extern "C" adapshot_status adapshot_query_attn_pool_batched(adapshot_ctx* ctx, i
     if (attn_mfma_supported(d)) {
         // with nothing but empty lists every item has its own tokens only, and the kernel never looks at the tables
         st = run_query_attn_batch(ctx, nullptr, layer, items, n_items, stream, &pb);
-    } else {  // other shapes run item by item through the generic kernel
+    } else {  // other shapes run item by item through the streaming kernel
         for (int32_t i = 0; i < n_items && st == ADAPSHOT_OK; ++i) {
             const adapshot_attn_item& it = items[i];
             st = run_query_attn_on(ctx, pb.k_layer, pb.v_layer, it.n_ctx, it.q, it.k_self, it.v_self, it.t_q, it.q_pos0, it.out,
@@ -1304,17 +1381,24 @@ extern "C" adapshot_status adapshot_query_attn_batched(adapshot_ctx* ctx, const 
             return st;
         }
     }
+    adapshot_status st = ADAPSHOT_OK;
     if (n_items > 0 && attn_mfma_supported(ctx->desc)) {
-        adapshot_status st = run_query_attn_batch(ctx, caches, layer, items, n_items, (hipStream_t)hip_stream);
-        if (st != ADAPSHOT_OK) return st;
+        st = run_query_attn_batch(ctx, caches, layer, items, n_items, (hipStream_t)hip_stream);
     } else {
-        for (int32_t i = 0; i < n_items; ++i) {
-            const adapshot_attn_item& it = items[i];
-            adapshot_status st = run_query_attn(ctx, &caches[it.cache_index], layer, it.n_ctx, it.q, it.k_self,
-                                                it.v_self, it.t_q, it.q_pos0, it.out, (hipStream_t)hip_stream);
-            if (st != ADAPSHOT_OK) return st;
+        for (int32_t i0 = 0; i0 < n_items && st == ADAPSHOT_OK; i0 += kStreamItems) {
+            StreamItem si[kStreamItems];
+            const int32_t n = std::min<int32_t>(kStreamItems, n_items - i0);
+            for (int32_t i = 0; i < n; ++i) {
+                const adapshot_attn_item& it = items[i0 + i];
+                const adapshot_cache& c = caches[it.cache_index];
+                const int64_t layer_off = (int64_t)layer * c.capacity * ctx->row_bytes;
+                si[i] = stream_item((const char*)c.k + layer_off, (const char*)c.v + layer_off, it.n_ctx, it.q, it.k_self,
+                                    it.v_self, it.t_q, it.q_pos0, it.out);
+            }
+            st = run_stream(ctx, si, n, nullptr, 0, (hipStream_t)hip_stream);
         }
     }
+    if (st != ADAPSHOT_OK) return st;
     ctx->last_error.clear();
     return ADAPSHOT_OK;
 }
@@ -1563,15 +1647,12 @@ static adapshot_status rank_shots_generic(adapshot_ctx* ctx, int32_t layer, cons
 
     RopeRowsParams rp;
     rp.q = q;
-    rp.k_self = nullptr;
     rp.q_rot = ctx->q_rot.p;
-    rp.k_rot = nullptr;
     rp.tab_lo = ctx->tab_lo;
     rp.tab_hi = ctx->tab_hi;
     rp.q_pos0 = q_pos0;
     rp.t_q = t_q;
     rp.n_q_heads = d.n_q_heads;
-    rp.n_kv_heads = d.n_kv_heads;
     rp.head_dim = d.head_dim;
     rp.dtype = d.dtype;
     rp.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
@@ -1641,15 +1722,12 @@ extern "C" adapshot_status adapshot_rank_shots(adapshot_ctx* ctx, int32_t layer,
 
     RopeRowsParams rp;  // the query rows rotated to q_pos0 + j and scaled, in a launch of their own
     rp.q = q;
-    rp.k_self = nullptr;
     rp.q_rot = ctx->q_rot.p;
-    rp.k_rot = nullptr;
     rp.tab_lo = ctx->tab_lo;
     rp.tab_hi = ctx->tab_hi;
     rp.q_pos0 = q_pos0;
     rp.t_q = t_q;
     rp.n_q_heads = d.n_q_heads;
-    rp.n_kv_heads = d.n_kv_heads;
     rp.head_dim = d.head_dim;
     rp.dtype = d.dtype;
     rp.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
@@ -1665,7 +1743,6 @@ extern "C" adapshot_status adapshot_rank_shots(adapshot_ctx* ctx, int32_t layer,
     af.slot_src = nullptr;
     af.tile_rot = nullptr;
     ap.q_rot = ctx->q_rot.p;
-    ap.k_self_rot = nullptr;
     ap.v_self = nullptr;
     af.q_raw = q;
     af.k_self_raw = nullptr;
@@ -1675,7 +1752,6 @@ extern "C" adapshot_status adapshot_rank_shots(adapshot_ctx* ctx, int32_t layer,
     af.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
     ap.part_o = ctx->part_o.p;
     ap.part_mlf = (float4*)ctx->part_ml.p;
-    ap.part_half = 1;
     ap.no_self = 1;
     ap.v_blocks = 1;  // rank_prepare closes a window after kRankWindowShots = 32 shots: one block of columns
     ap.split_bounds = ctx->rank_bounds;

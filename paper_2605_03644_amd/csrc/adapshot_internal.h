@@ -92,13 +92,11 @@ hipError_t launch_decode_append(const DecodeAppendParams& p, hipStream_t stream)
 // ---- attention --------------------------------------------------------------------
 struct RopeRowsParams {
     const void* q;       // [t_q][h_q][d]
-    const void* k_self;  // [t_q][h_kv][d]
     void* q_rot;         // [t_q][h_q][d], scaled by log2(e)/sqrt(d)
-    void* k_rot;         // [t_q][h_kv][d]
     const float2* tab_lo;
     const float2* tab_hi;
     int64_t q_pos0;
-    int32_t t_q, n_q_heads, n_kv_heads, head_dim, dtype;
+    int32_t t_q, n_q_heads, head_dim, dtype;
     float q_scale;
 };
 hipError_t launch_rope_rows(const RopeRowsParams& p, hipStream_t stream);
@@ -129,18 +127,14 @@ struct AttnFold {
 struct AttnParams {
     const void* k_cache;  // one layer [>=n_ctx][h_kv][d]
     const void* v_cache;
-    const void* q_rot;       // generic kernel: rows rotated and scaled by rope_rows
-    const void* k_self_rot;  // generic kernel: the query's own keys rotated by rope_rows
+    const void* q_rot;    // ranking: rows rotated and scaled by rope_rows (the other forms rotate their rows themselves)
     const void* v_self;
-    // Partials, indexed [n_split+1][h_kv][rows]: part_mlf = (reference maximum in log2 units, row sum l,
-    // factor f, unused) and a row O' of d values with  sum_k p_k v_k = f * O'.
-    //   part_half = 0: O' is the unnormalised fp32 accumulator, f = 1 (generic kernel);
-    //   part_half = 1: O' = accumulator / (l * a) in fp16 with a = the largest |accumulator| / l of the row,
-    //                  so |O'| <= 1 whatever the range of V, and f = l * a (MFMA kernel): half the bytes,
-    //                  error per element <= 2^-11 of the row's largest partial output.
+    // Partials, indexed [n_split+1][h_kv][rows]: part_mlf = (reference maximum in log2 units, row sum l, factor f = l * a,
+    // unused) and a row O' of d fp16 values with  sum_k p_k v_k = f * O':  O' = accumulator / (l * a), a = the largest
+    // |accumulator| / l of the row, so |O'| <= 1 whatever the range of V; error per element <= 2^-11 of the row's largest
+    // partial output.
     void* part_o;
     float4* part_mlf;
-    int32_t part_half;
     // Ranking over the pool (MFMA kernel only): context splits with explicit key bounds
     // [split_bounds[s], split_bounds[s+1]) instead of equal lengths, and no self part.
     int32_t no_self;
@@ -160,13 +154,54 @@ constexpr int kAttnRowTile = 256;  // query rows per workgroup of the MFMA kerne
 // by the memory path, not by the matrix cores: its tile loads are then marked non-temporal (when no other workgroup
 // reads the same tiles).
 constexpr int kAttnStreamRows = 128;
-struct GenericPool {  // zero-copy form of the generic kernel; slot_src == nullptr: the context is an assembled cache
-    const int32_t* slot_src;
+// ---- streaming attention (attn_stream_kernel.h): every shape the 256-row tile kernel does not cover -------------
+constexpr int kStreamWaves = 8;       // wavefronts per workgroup, each with keys of its own
+constexpr int kStreamItems = 32;      // attention problems per launch (their descriptions travel in the kernel arguments)
+constexpr int kStreamMaxSplits = 64;  // context splits per problem
+constexpr int kStreamUnits = 4096;    // (problem, row tile, kv head) units of a launch that is split: one arrival counter each
+struct StreamItem {
+    const char* q;
+    const char* k_self;
+    const char* v_self;
+    char* out;
+    const char* k_ctx;  // one layer of the context (assembled cache or pool)
+    const char* v_ctx;
+    int64_t slot0;      // zero-copy form: first entry of the context in slot_src
+    int32_t n_ctx, t_q, q_pos0;
+    int32_t keys_per_split, n_split;  // the last split also takes the query's own tokens
+    int32_t unit0;      // first unit of the problem in the workspaces
+};
+template <int NI>
+struct StreamArgs {
     const float2* tab_lo;
     const float2* tab_hi;
-    int64_t pos0;  // position of context slot 0
+    float* part_o;       // [unit][max_split][16 NR rows][d] fp32, unnormalised (launches with splits)
+    float* part_ml;      // [unit][max_split][16 NR rows] (m, l)
+    unsigned* counters;  // [unit], zero between launches
+    const int32_t* slot_src;  // zero-copy form: context slot -> pool token (null: the context is an assembled cache)
+    int64_t ctx_pos0;         // zero-copy form: position of context slot 0
+    int32_t n_q_heads, n_kv_heads, g, max_split, pool_tokens;
+    float q_scale;
+    StreamItem it[NI];
 };
-hipError_t launch_attn_generic(const AttnParams& p, const GenericPool& pool, hipStream_t stream);
+struct StreamLaunch {
+    const float2* tab_lo;
+    const float2* tab_hi;
+    float* part_o;
+    float* part_ml;
+    unsigned* counters;
+    const int32_t* slot_src;
+    int64_t ctx_pos0;
+    int32_t n_q_heads, n_kv_heads, head_dim, dtype, max_split, pool_tokens;
+    int32_t row_blocks;  // 16-row blocks per workgroup: 1 or 2
+    int32_t grid_x;      // workgroups of the largest problem
+    int32_t n_items;
+    float q_scale;
+    const StreamItem* items;
+};
+hipError_t launch_attn_stream(const StreamLaunch& s, hipStream_t stream);
+hipError_t launch_attn_stream_f32(const StreamLaunch& s, hipStream_t stream);
+hipError_t launch_attn_stream_bf16(const StreamLaunch& s, hipStream_t stream);
 hipError_t launch_attn_mfma(const AttnParams& p, const AttnFold& f, hipStream_t stream);
 hipError_t launch_attn_mfma_pool(const AttnParams& p, const AttnFold& f, hipStream_t stream);  // zero-copy form
 // Expands the per-shot segments of a zero-copy context into slot_src and builds tile_rot.
@@ -207,8 +242,8 @@ hipError_t launch_copy_table(void* dst, const void* src_pinned, size_t bytes, hi
 hipError_t launch_attn_mfma_batched(const AttnBatchItem* items, const AttnWork* work, int n_work, bool pool,
                                     bool stream_tiles, int layer, hipStream_t stream);
 // max_partials: the most partial rows that any item merges per output row (its context splits + 1)
-hipError_t launch_attn_combine_batched(const AttnBatchItem* items, const CombineWork* work, int n_work, int dtype,
-                                       int max_partials, hipStream_t stream);
+hipError_t launch_attn_combine_batched(const AttnBatchItem* items, const CombineWork* work, int n_work, int max_partials,
+                                       hipStream_t stream);
 
 // ---- relevance ranking over the pool (Eq. attention_score) ----------------------------------
 // The query attends over the locally encoded keys of ALL pool tokens at one layer with a one-hot "value"
@@ -355,10 +390,11 @@ struct adapshot_ctx {
     // tables
     float2* tab_lo = nullptr;
     float2* tab_hi = nullptr;
+    unsigned* stream_counters = nullptr;  // arrival counters of split streaming launches, zero between launches
     float* static_ent = nullptr;  // this device's copy of the static entropy scratch array (not owned)
     // scratch
     adapshot::PinnedRing tile_ring;
-    adapshot::DevBuf q_rot, k_rot, part_o, part_ml, ent_part, batch_tab, pool_src, pool_rot;
+    adapshot::DevBuf q_rot, part_o, part_ml, ent_part, batch_tab, pool_src, pool_rot;
     // What the device-side tables of the last batched attention call (batch_tab) and of the last zero-copy plan
     // (pool_src, pool_rot) were built from: a call with the same inputs -- the next layer of the same batch --
     // reuses them instead of planning and uploading again.  Empty = nothing to reuse.

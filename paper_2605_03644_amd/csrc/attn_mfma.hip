@@ -168,7 +168,7 @@ __device__ __forceinline__ T load_uniform(const T* ptr) {
 // time to land instead of two).  What a context split computes is what the plain form computes over the
 // assembled cache.
 // FOLD: the workgroup rotates its query rows (and the self split its keys) itself; otherwise rope_rows has
-// done that in a launch of its own and the kernel reads q_rot / k_self_rot.  Folding saves the launch: at the
+// done that in a launch of its own and the kernel reads q_rot.  Folding saves the launch: at the
 // headline size the rotation repeated in every context split costs the kernel 1.4 us and the launch it replaces
 // cost the step 3 us.  Ranking, whose one block of columns needs no keys of the query, keeps the launch.
 // NT: the K/V tile loads of the plain form carry the non-temporal bit (see load_lds_16).
@@ -245,8 +245,8 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
     }
 
     // ---- key range of this split
-    // context splits; a folding kernel's self split has a path of its own
-    const char* kbase = (const char*)(!FOLD && self ? p.k_self_rot : p.k_cache) + hk * kRowBytes;
+    // context splits; the self split has a path of its own
+    const char* kbase = (const char*)p.k_cache + hk * kRowBytes;
     const char* vbase = (const char*)(self ? p.v_self : p.v_cache) + hk * kRowBytes;
     const int64_t kv_stride = (int64_t)p.n_kv_heads * kRowBytes;
     int64_t k0, k1;

@@ -1,0 +1,591 @@
+// Query-over-cache attention straight from registers: the kernel for every shape that the 256-row tile kernel
+// (attn_mfma.hip) does not cover -- fp32 models, head dimensions other than 128.
+//
+// A workgroup of 8 wavefronts owns 16 * NR query rows of one KV head (rows j*g + h%g, as everywhere) and one split of
+// the context; the last split also takes the query's own tokens (causal).  The keys go to the wavefronts 16 at a
+// time, round robin, and every wavefront runs a flash-attention state of its own over its keys: no LDS, no barrier and
+// no other wavefront in the key loop.  K and V rows are loaded from global memory in exactly the lanes where the
+// matrix instructions want them, so the loop is loads, matrix instructions and a 4-value softmax:
+//
+//   S^T = K . Q^T   A = K: lane (key l%16, group l/16) holds KW consecutive columns 4*KW*j + KW*(l/16) of its key for
+//                   every j (16 bytes), B = Q in the same lanes and columns: bf16 models v_mfma_f32_16x16x32_bf16 on the
+//                   stored operands, fp32 models v_mfma_f32_16x16x4_f32.  The result leaves lane l with query row l%16
+//                   and keys 4*(l/16) .. +3.
+//   O^T += V^T.P^T  v_mfma_f32_16x16x4_f32 whatever the storage type: register r of S^T is the B operand of the k-slots
+//                   4*(l/16)+r as it stands (P is never rounded to 16 bits), and A wants V[key 4*(l/16)+r] in 16 lanes
+//                   of consecutive columns, which is a row-wise load: a lane takes VW consecutive columns (16 bytes of
+//                   a 128-wide row) and the 16 columns of MFMA block (dg, c) are 16*VW*dg + VW*i + c.  The fp32 rate is
+//                   a sixteenth of the bf16 one, but nothing has to be transposed through LDS, and these problems are
+//                   bound by latency and loads.
+//
+// The wavefronts' states meet in LDS once, at the end.  With one split the workgroup writes the output rows itself:
+// rotation, attention and merge are then one launch (the former scalar kernel: rope_rows, attention, combine).  With
+// more, each workgroup leaves its merged rows (fp32) and (m, l) in a workspace, and the workgroup that arrives last at
+// the unit's counter merges them: partials are written and read with device-scope accesses that bypass the L2 of the
+// workgroup's XCD, so no cache has to be written back or invalidated, and the counter is back at zero afterwards.  The
+// merge runs in split order whatever the order of arrival: the same inputs give the same bits.
+//
+// What bounds it: a small problem, the launch and two round trips to memory (64 slots: 6 us, 6.7 us with 256 slots of a
+// bf16 model); a large one, its steps, 1100 cycles each at two wavefronts per SIMD (bf16, head_dim 64: 544 of them
+// fp32 MFMAs of the second product, the rest the softmax and the serial order inside the wavefront).  One layer of a
+// query, rope_rows + attention + combine of the scalar kernel before it -> this launch:
+//   bf16, 32/8 heads x 64, 64 query tokens over 6.6k slots    1476 -> 37 us
+//   fp32, 8/2 heads x 128, 32 query tokens over 2.3k slots     167 -> 19 us
+//   fp32, 4/2 heads x 64, 16 query tokens over 248 slots        23 -> 8.5 us
+#pragma once
+#include <type_traits>
+
+#include "adapshot_internal.h"
+
+namespace adapshot {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned long long u64;
+
+__device__ __forceinline__ unsigned stream_pack(float lo, float hi) {
+    const f32x2 f = {lo, hi};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));  // round to nearest even
+}
+__device__ __forceinline__ void stream_store2(float* p, float a, float b) {
+    const u64 v = (u64)__float_as_uint(a) | ((u64)__float_as_uint(b) << 32);
+    __hip_atomic_store((u64*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ f32x2 stream_load2(const float* p) {
+    const u64 v = __hip_atomic_load((const u64*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const f32x2 r = {__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32))};
+    return r;
+}
+
+template <int DTYPE, int D, int NR, bool POOL, int NI>
+__global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamArgs<NI> p) {
+    constexpr int W = kStreamWaves, T = W * 64;
+    constexpr bool BF = DTYPE == ADAPSHOT_BF16;
+    constexpr int E = BF ? 2 : 4;
+    constexpr int KW = D * E >= 64 ? 16 / E : D / 4;  // consecutive columns of a lane
+    constexpr int NJ = D / (4 * KW);
+    constexpr int KR = KW * E / 4;                    // registers of one j
+    constexpr int DB = D >= 16 ? D / 16 : 1;          // 16-column blocks of the output
+    constexpr int VMAX = 16 / E;
+    constexpr int VW = DB < VMAX ? DB : VMAX;         // consecutive V columns of a lane
+    constexpr int DG = DB / VW;
+    constexpr int VR = VW * E >= 4 ? VW * E / 4 : 1;  // registers of one V piece
+    constexpr int STEP_REGS = NJ * KR + 4 * DG * VR;
+    // The next step's K and V are loaded while this one is computed (two steps ahead is no faster and costs 16 to 32
+    // registers); a step of 256 bytes per lane leaves room for its K alone, V is then loaded under the first product.
+    constexpr int NB = 2;
+    constexpr int NBV = STEP_REGS > 32 ? 1 : 2;
+    constexpr int TR = 16 * NR;
+    constexpr int NS = NR * DB;  // 1 KB pieces of a wavefront's output state
+    static_assert(D == 8 || D % 16 == 0, "head dimensions");
+
+    __shared__ f32x4 os[W][NS][64];
+    __shared__ float2 wml[W][TR];
+    __shared__ float2 sml[kStreamMaxSplits][TR];
+    __shared__ int last_flag;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, kg = lane >> 4;
+
+    const StreamItem& it = p.it[NI == 1 ? 0 : blockIdx.y];
+    const int n_split = it.n_split;
+    const int hkv = p.n_kv_heads, g = p.g;
+    const int rows = it.t_q * g;
+    const int hk = blockIdx.x % hkv;
+    const int rest = blockIdx.x / hkv;
+    const int split = rest % n_split, rt = rest / n_split;
+    const int row0 = rt * TR;
+    if (row0 >= rows) return;
+    const bool last_split = split == n_split - 1;
+
+    const int64_t stride = (int64_t)hkv * D * E;
+    const int k0 = split * it.keys_per_split;
+    int nk = it.n_ctx - k0;  // context keys of this split
+    if (nk > it.keys_per_split) nk = it.keys_per_split;
+    if (nk < 0) nk = 0;
+    const int j_last = ((row0 + TR < rows ? row0 + TR : rows) - 1) / g;
+    const int n_self = last_split ? j_last + 1 : 0;  // own tokens that any row of the tile sees
+    const int n_cs = (nk + 15) >> 4;
+    const int n_steps = n_cs + ((n_self + 15) >> 4);
+
+    const char* const kself = it.k_self + (int64_t)hk * D * E;
+    const char* const vself = it.v_self + (int64_t)hk * D * E;
+    const char* const kctx = it.k_ctx + (int64_t)hk * D * E + (POOL ? 0 : k0 * stride);
+    const char* const vctx = it.v_ctx + (int64_t)hk * D * E + (POOL ? 0 : k0 * stride);
+
+    // ---- loads of step s.  Steps past the end read one row again (all lanes the same bytes).
+    // Zero-copy form: pool tokens of the rows of the next step to load, fetched one step before the rows
+    int tok_k = 0, tok_v[4] = {0, 0, 0, 0};
+    auto pool_tok = [&](int u) __attribute__((always_inline)) -> int {
+        u = u < nk ? u : nk - 1;
+        u = u > 0 ? u : 0;
+        return p.slot_src[it.slot0 + k0 + u];
+    };
+    auto fetch_tok = [&](int s) __attribute__((always_inline)) {
+        if (POOL && nk > 0) {
+            tok_k = pool_tok(16 * s + l16);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tok_v[r] = pool_tok(16 * s + 4 * kg + r);
+        }
+    };
+    typedef typename std::conditional<POOL, uint64_t, unsigned>::type off_t;  // the rows of a context span at most 4 GiB, a pool may not
+    auto row_off = [&](bool self, bool on, int u, int lim, int tok) __attribute__((always_inline)) -> off_t {
+        int r = u < lim ? u : lim - 1;
+        if (POOL && !self) {
+            unsigned t = (unsigned)tok;
+            t = t < (unsigned)p.pool_tokens ? t : (unsigned)p.pool_tokens - 1u;  // never outside the pool
+            r = (int)t;
+        }
+        return on ? (off_t)r * (off_t)stride : (off_t)0;
+    };
+    auto load_k = [&](int s, unsigned (&dst)[NJ][KR]) __attribute__((always_inline)) {
+        const bool on = s < n_steps, self = s >= n_cs;
+        const char* base = self ? kself : kctx;
+        const int u = 16 * (self ? s - n_cs : s) + l16;
+        const char* src = base + row_off(self, on, u, self ? n_self : nk, tok_k);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            if (KR == 4) {
+                const u32x4 x = *(const u32x4*)(src + 64 * j + 16 * kg);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dst[j][i % KR] = x[i];
+            } else {
+                const uint2 x = *(const uint2*)(src + 8 * kg);
+                dst[j][0] = x.x;
+                dst[j][1 % KR] = x.y;
+            }
+        }
+    };
+    auto load_v = [&](int s, unsigned (&dst)[4][DG][VR]) __attribute__((always_inline)) {
+        const bool on = s < n_steps, self = s >= n_cs;
+        const char* base = self ? vself : vctx;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int u = 16 * (self ? s - n_cs : s) + 4 * kg + r;
+            const char* src = base + row_off(self, on, u, self ? n_self : nk, tok_v[r]);
+#pragma unroll
+            for (int dg = 0; dg < DG; ++dg) {
+                const char* q = src + (16 * VW * dg + VW * l16) * E;
+                if (VR == 4) {
+                    const u32x4 x = *(const u32x4*)q;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) dst[r][dg][i % VR] = x[i];
+                } else if (VR == 2) {
+                    const uint2 x = *(const uint2*)q;
+                    dst[r][dg][0] = x.x;
+                    dst[r][dg][1 % VR] = x.y;
+                } else if (VW * E == 4) {
+                    dst[r][dg][0] = D == 8 && l16 >= 8 ? 0u : *(const unsigned*)(D == 8 && l16 >= 8 ? src : q);
+                } else {
+                    dst[r][dg][0] = (unsigned)*(const unsigned short*)q << 16;  // bf16, one column
+                }
+            }
+        }
+    };
+    auto v_elem = [&](const unsigned (&w)[VR], int c) __attribute__((always_inline)) -> float {
+        if (!BF) return __uint_as_float(w[c % VR]);
+        if (VW == 1) return __uint_as_float(w[0]);
+        return (c & 1) ? __uint_as_float(w[(c >> 1) % VR] & 0xffff0000u) : __uint_as_float(w[(c >> 1) % VR] << 16);
+    };
+
+    // ---- rotation of a lane's pieces of a row to position a (Eq. rope_encoding), scaled; bf16 results rounded to
+    // nearest even, as a cache would hold them.  The partner of column d is d +- D/2: piece j +- NJ/2 of the same lane, or,
+    // where a row is a single piece per lane, the lane two groups on.
+    auto get = [&](const unsigned (&w)[KR], int c) __attribute__((always_inline)) -> float {
+        if (!BF) return __uint_as_float(w[c % KR]);
+        return (c & 1) ? __uint_as_float(w[(c >> 1) % KR] & 0xffff0000u) : __uint_as_float(w[(c >> 1) % KR] << 16);
+    };
+    auto put2 = [&](unsigned (&w)[KR], int c, float a, float b) __attribute__((always_inline)) {
+        if (BF) {
+            w[(c >> 1) % KR] = stream_pack(a, b);
+        } else {
+            w[c % KR] = __float_as_uint(a);
+            w[(c + 1) % KR] = __float_as_uint(b);
+        }
+    };
+    auto rotate = [&](unsigned (&x)[NJ][KR], int64_t a, float sc) __attribute__((always_inline)) {
+        const float2* th = p.tab_hi + (a >> kRopeLoBits) * (D / 2);
+        const float2* tl = p.tab_lo + (a & (kRopeLo - 1)) * (D / 2);
+        constexpr int NP = NJ > 1 ? NJ / 2 : 1;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int f0 = NJ > 1 ? 4 * KW * j + KW * kg : KW * (kg & 1);
+#pragma unroll
+            for (int c = 0; c < KW; c += 2) {
+                const f32x4 h = *(const f32x4*)(th + f0 + c), l = *(const f32x4*)(tl + f0 + c);
+                const float c0 = h[0] * l[0] - h[1] * l[1], s0 = h[1] * l[0] + h[0] * l[1];
+                const float c1 = h[2] * l[2] - h[3] * l[3], s1 = h[3] * l[2] + h[2] * l[3];
+                if (NJ > 1) {
+                    const float a0 = get(x[j], c), a1 = get(x[j], c + 1);
+                    const float b0 = get(x[(j + NP) % NJ], c), b1 = get(x[(j + NP) % NJ], c + 1);
+                    put2(x[j], c, (a0 * c0 - b0 * s0) * sc, (a1 * c1 - b1 * s1) * sc);
+                    put2(x[(j + NP) % NJ], c, (b0 * c0 + a0 * s0) * sc, (b1 * c1 + a1 * s1) * sc);
+                } else {
+                    const float a0 = get(x[0], c), a1 = get(x[0], c + 1);
+                    const float b0 = __shfl_xor(a0, 32, 64), b1 = __shfl_xor(a1, 32, 64);
+                    const float t0 = kg < 2 ? -s0 : s0, t1 = kg < 2 ? -s1 : s1;
+                    put2(x[0], c, (a0 * c0 + b0 * t0) * sc, (a1 * c1 + b1 * t1) * sc);
+                }
+            }
+        }
+    };
+
+    // ---- the first steps are requested before the query rows are rotated
+    unsigned kf[NB][NJ][KR];
+    unsigned vf[NBV][4][DG][VR];
+    fetch_tok(wave);
+#pragma unroll
+    for (int b = 0; b < NB - 1; ++b) {
+        load_k(wave + b * W, kf[b]);
+        if (NBV > 1) {
+            load_v(wave + b * W, vf[b % NBV]);
+            fetch_tok(wave + (b + 1) * W);
+        }
+    }
+
+    unsigned qf[NR][NJ][KR];
+    int jrow[NR];
+#pragma unroll
+    for (int nr = 0; nr < NR; ++nr) {
+        const int row = row0 + 16 * nr + l16;
+        const int rc = row < rows ? row : rows - 1;
+        const int j = rc / g;
+        jrow[nr] = j;
+        const char* src = it.q + (((int64_t)j * p.n_q_heads + hk * g + (rc - j * g)) * D) * E;
+#pragma unroll
+        for (int jj = 0; jj < NJ; ++jj) {
+            if (KR == 4) {
+                const u32x4 x = *(const u32x4*)(src + 64 * jj + 16 * kg);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) qf[nr][jj][i % KR] = x[i];
+            } else {
+                const uint2 x = *(const uint2*)(src + 8 * kg);
+                qf[nr][jj][0] = x.x;
+                qf[nr][jj][1 % KR] = x.y;
+            }
+        }
+        rotate(qf[nr], (int64_t)it.q_pos0 + j, p.q_scale);
+    }
+
+    f32x4 o[NR][DB];
+    float m_run[NR], l_run[NR];
+#pragma unroll
+    for (int nr = 0; nr < NR; ++nr) {
+        m_run[nr] = -INFINITY;
+        l_run[nr] = 0.f;
+#pragma unroll
+        for (int b = 0; b < DB; ++b) o[nr][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    auto compute = [&](int s, unsigned (&k)[NJ][KR], unsigned (&v)[4][DG][VR]) __attribute__((always_inline)) {
+        const bool self = s >= n_cs;  // wavefront-uniform
+        if (self) rotate(k, (int64_t)it.q_pos0 + 16 * (s - n_cs) + l16, 1.0f);
+        else if (POOL) rotate(k, p.ctx_pos0 + k0 + 16 * s + l16, 1.0f);
+        f32x4 sc[NR];
+#pragma unroll
+        for (int nr = 0; nr < NR; ++nr) sc[nr] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            if (BF && KR == 4) {
+                const u32x4 a = {k[j][0], k[j][1 % KR], k[j][2 % KR], k[j][3 % KR]};
+#pragma unroll
+                for (int nr = 0; nr < NR; ++nr) {
+                    const u32x4 b = {qf[nr][j][0], qf[nr][j][1 % KR], qf[nr][j][2 % KR], qf[nr][j][3 % KR]};
+                    sc[nr] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                                     __builtin_bit_cast(bf16x8, b), sc[nr], 0, 0, 0);
+                }
+            } else if (BF) {
+                const uint2 a = {k[j][0], k[j][1 % KR]};
+#pragma unroll
+                for (int nr = 0; nr < NR; ++nr) {
+                    const uint2 b = {qf[nr][j][0], qf[nr][j][1 % KR]};
+                    sc[nr] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a),
+                                                                       __builtin_bit_cast(s16x4, b), sc[nr], 0, 0, 0);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < KR; ++i)
+#pragma unroll
+                    for (int nr = 0; nr < NR; ++nr)
+                        sc[nr] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k[j][i]), __uint_as_float(qf[nr][j][i]),
+                                                                      sc[nr], 0, 0, 0);
+            }
+        }
+        const int u = 16 * (self ? s - n_cs : s) + 4 * kg;
+#pragma unroll
+        for (int nr = 0; nr < NR; ++nr) {
+            if (self || 16 * s + 16 > nk) {
+                const int lim = self ? jrow[nr] + 1 : nk;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (u + r >= lim) sc[nr][r] = -INFINITY;
+            }
+            float mx = fmaxf(fmaxf(sc[nr][0], sc[nr][1]), fmaxf(sc[nr][2], sc[nr][3]));
+            // the reference maximum of a row follows lazily: it moves when a score exceeds it by more than 2^8
+            if (__builtin_amdgcn_ballot_w64(mx > m_run[nr] + 8.0f)) {
+                mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                const float m_new = fmaxf(m_run[nr], mx);
+                const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run[nr] - m_new);
+                m_run[nr] = m_new;
+                l_run[nr] *= alpha;
+#pragma unroll
+                for (int b = 0; b < DB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[nr][b][r] *= alpha;
+            }
+            const float m_use = m_run[nr] == -INFINITY ? 0.f : m_run[nr];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sc[nr][r] = __builtin_amdgcn_exp2f(sc[nr][r] - m_use);
+            l_run[nr] += (sc[nr][0] + sc[nr][1]) + (sc[nr][2] + sc[nr][3]);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int dg = 0; dg < DG; ++dg)
+#pragma unroll
+                for (int c = 0; c < VW; ++c) {
+                    const float a = v_elem(v[r][dg], c);
+#pragma unroll
+                    for (int nr = 0; nr < NR; ++nr)
+                        o[nr][dg * VW + c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, sc[nr][r], o[nr][dg * VW + c], 0, 0, 0);
+                }
+    };
+
+    for (int s0 = wave; s0 < n_steps; s0 += NB * W) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int s = s0 + b * W;
+            if (s >= n_steps) break;
+            if (NBV == 1) {
+                load_v(s, vf[0]);
+                fetch_tok(s + W);
+            }
+            load_k(s + (NB - 1) * W, kf[(b + NB - 1) % NB]);
+            if (NBV > 1) {
+                load_v(s + (NB - 1) * W, vf[(b + NB - 1) % NBV]);
+                fetch_tok(s + NB * W);
+            }
+            compute(s, kf[b], vf[b % NBV]);
+        }
+    }
+
+    // ---- the wavefronts' states meet
+#pragma unroll
+    for (int nr = 0; nr < NR; ++nr) {
+        float l = l_run[nr];
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        if (kg == 0) wml[wave][16 * nr + l16] = make_float2(m_run[nr], l);
+#pragma unroll
+        for (int s = 0; s < DB; ++s) {
+            f32x4 x;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int f = 4 * (s % VW) + i;  // index in the lane's run of 4 * VW columns: column VW * r + c
+                x[i] = o[nr][(s / VW) * VW + f % VW][f / VW];
+            }
+            os[wave][nr * DB + s][lane] = x;
+        }
+    }
+    __syncthreads();
+    float wgt[NR][W], m_wg[NR], l_wg[NR];
+#pragma unroll
+    for (int nr = 0; nr < NR; ++nr) {
+        float2 ml[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) ml[w] = wml[w][16 * nr + l16];
+        float M = ml[0].x;
+#pragma unroll
+        for (int w = 1; w < W; ++w) M = fmaxf(M, ml[w].x);
+        float L = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            wgt[nr][w] = ml[w].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[w].x - M);
+            L += wgt[nr][w] * ml[w].y;
+        }
+        m_wg[nr] = M;
+        l_wg[nr] = L;
+    }
+    const int64_t unit = it.unit0 + (int64_t)rt * hkv + hk;
+    float* const po = p.part_o + (unit * p.max_split + split) * (TR * D);
+    auto store_out = [&](int row, int d0, f32x4 y) __attribute__((always_inline)) {
+        const int j = row / g;
+        const int64_t e = ((int64_t)j * p.n_q_heads + hk * g + (row - j * g)) * D + d0;
+        if (BF) *(uint2*)(it.out + e * 2) = make_uint2(stream_pack(y[0], y[1]), stream_pack(y[2], y[3]));
+        else *(f32x4*)(it.out + e * 4) = y;
+    };
+    for (int s = wave; s < NS; s += W) {
+        const int nr = s / DB, sl = s % DB;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        float Lr = 1.f;
+#pragma unroll
+        for (int n2 = 0; n2 < NR; ++n2)
+            if (n2 == nr) {
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    const f32x4 x = os[w][s][lane];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[i] += wgt[n2][w] * x[i];
+                }
+                Lr = l_wg[n2];
+            }
+        const int row = row0 + 16 * nr + l16;
+        const int d0 = 16 * VW * (sl / VW) + 4 * VW * kg + 4 * (sl % VW);
+        if (row < rows && d0 < D) {
+            if (n_split == 1) {
+                const float inv = 1.0f / Lr;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i] *= inv;
+                store_out(row, d0, acc);
+            } else {
+                float* q = po + (row - row0) * D + d0;
+                stream_store2(q, acc[0], acc[1]);
+                stream_store2(q + 2, acc[2], acc[3]);
+            }
+        }
+    }
+    if (n_split == 1) return;
+
+    // ---- merge over the splits, by the workgroup that arrives last
+    float* const pml = p.part_ml + unit * p.max_split * (TR * 2);
+    if (wave == 0 && kg == 0) {
+#pragma unroll
+        for (int nr = 0; nr < NR; ++nr) stream_store2(pml + (split * TR + 16 * nr + l16) * 2, m_wg[nr], l_wg[nr]);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's partials have reached memory
+    __syncthreads();
+    if (tid == 0) {
+        const unsigned before = __hip_atomic_fetch_add(p.counters + unit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool mine = before == (unsigned)n_split - 1u;
+        if (mine) __hip_atomic_store(p.counters + unit, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last_flag = mine ? 1 : 0;
+    }
+    __syncthreads();
+    if (!last_flag) return;
+
+    const int n_rows = rows - row0 < TR ? rows - row0 : TR;
+    const int e4 = n_rows * (D / 4);  // 16-byte pieces of the output rows
+    const float* const pu = p.part_o + unit * p.max_split * (TR * D);
+    // splits per thread: the pieces are few, so several groups of threads take the splits between them
+    int ng = T / e4;
+    ng = ng < 1 ? 1 : ng > n_split ? n_split : ng;
+    const int grp = ng > 1 ? tid / e4 : 0;
+    constexpr int PB = 8;  // splits in flight per thread
+    auto piece = [&](int e, int sp, f32x4& x) __attribute__((always_inline)) {
+        const float* q = pu + ((int64_t)sp * TR * D + 4 * e);
+        const f32x2 a = stream_load2(q), b = stream_load2(q + 2);
+        x = f32x4{a[0], a[1], b[0], b[1]};
+    };
+    for (int i = tid; i < n_split * TR; i += T) {
+        const f32x2 v = stream_load2(pml + 2 * i);
+        (&sml[0][0])[i] = make_float2(v[0], v[1]);
+    }
+    const int e_first = ng > 1 ? tid - grp * e4 : tid;
+    f32x4 x[PB];
+    const bool on0 = grp < ng && e_first < e4;
+#pragma unroll
+    for (int b = 0; b < PB; ++b) {  // the first pieces are requested with the (m, l)
+        const int sp = grp + b * ng;
+        x[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (on0 && sp < n_split) piece(e_first, sp, x[b]);
+    }
+    __syncthreads();
+    {   // weights of the splits, 16 threads per row: sml[s][row].x becomes 2^(m_s - M) / L
+        const int row = tid >> 4;
+        if (row < TR) {
+            float M = -INFINITY;
+            for (int s = l16; s < n_split; s += 16) M = fmaxf(M, sml[s][row].x);
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+            float L = 0.f;
+            for (int s = l16; s < n_split; s += 16)
+                L += sml[s][row].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sml[s][row].x - M) * sml[s][row].y;
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) L += __shfl_xor(L, off, 64);
+            const float inv = 1.0f / L;
+            for (int s = l16; s < n_split; s += 16)
+                sml[s][row].x = sml[s][row].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sml[s][row].x - M) * inv;
+        }
+    }
+    __syncthreads();
+    f32x4* const red = &os[0][0][0];  // [ng][e4], at most one piece per thread
+    for (int e = e_first; e < e4; e += T) {
+        if (grp >= ng) break;
+        const int row = e / (D / 4);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int s0 = grp; s0 < n_split; s0 += PB * ng) {
+            if (e != e_first || s0 != grp) {
+#pragma unroll
+                for (int b = 0; b < PB; ++b) {
+                    const int sp = s0 + b * ng;
+                    if (sp < n_split) piece(e, sp, x[b]);
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < PB; ++b) {
+                const int sp = s0 + b * ng;
+                if (sp < n_split) {
+                    const float w = sml[sp][row].x;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[i] += w * x[b][i];
+                }
+            }
+        }
+        if (ng == 1) store_out(row0 + row, 4 * (e - row * (D / 4)), acc);
+        else red[grp * e4 + e] = acc;
+    }
+    if (ng == 1) return;  // the same for every thread
+    __syncthreads();
+    if (tid < e4) {
+        f32x4 acc = red[tid];
+        for (int gidx = 1; gidx < ng; ++gidx) {
+            const f32x4 y = red[gidx * e4 + tid];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += y[i];
+        }
+        const int row = tid / (D / 4);
+        store_out(row0 + row, 4 * (tid - row * (D / 4)), acc);
+    }
+}
+
+template <int DTYPE, int D, int NR>
+static hipError_t launch_stream_form(const StreamLaunch& s, hipStream_t stream) {
+    auto fill = [&](auto& a) {
+        a.tab_lo = s.tab_lo;
+        a.tab_hi = s.tab_hi;
+        a.part_o = s.part_o;
+        a.part_ml = s.part_ml;
+        a.counters = s.counters;
+        a.slot_src = s.slot_src;
+        a.ctx_pos0 = s.ctx_pos0;
+        a.n_q_heads = s.n_q_heads;
+        a.n_kv_heads = s.n_kv_heads;
+        a.g = s.n_q_heads / s.n_kv_heads;
+        a.max_split = s.max_split;
+        a.pool_tokens = s.pool_tokens;
+        a.q_scale = s.q_scale;
+        for (int i = 0; i < s.n_items; ++i) a.it[i] = s.items[i];
+    };
+    const dim3 grid((unsigned)s.grid_x, (unsigned)s.n_items), block(kStreamWaves * 64);
+    if (s.n_items == 1) {
+        StreamArgs<1> a;
+        fill(a);
+        if (s.slot_src) launch_kernel((attn_stream_kernel<DTYPE, D, NR, true, 1>), grid, block, stream, a);
+        else launch_kernel((attn_stream_kernel<DTYPE, D, NR, false, 1>), grid, block, stream, a);
+    } else {
+        if (s.slot_src) return hipErrorInvalidValue;
+        StreamArgs<kStreamItems> a;
+        fill(a);
+        launch_kernel((attn_stream_kernel<DTYPE, D, NR, false, kStreamItems>), grid, block, stream, a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace adapshot
