@@ -10,7 +10,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libadapshot.so")
 SOURCES = ["adapshot_api.hip", "assemble_kernel.hip", "attn_common.hip", "attn_mfma.hip", "attn_stream_bf16.hip",
-           "attn_stream_f32.hip", "entropy_kernel.hip", "rank_kernel.hip"]
+           "attn_stream_f32.hip", "entropy_kernel.hip", "rank_kernel.hip",
+           "rank_mfma.hip"]
 
 
 def hipcc() -> str:

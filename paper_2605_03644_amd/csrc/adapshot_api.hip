@@ -262,9 +262,7 @@ extern "C" void adapshot_destroy(adapshot_ctx* ctx) {
     ctx->pool_src.release();
     ctx->pool_rot.release();
     ctx->rank_k.release();
-    ctx->rank_v.release();
     ctx->rank_w.release();
-    ctx->rank_part.release();
     ctx->rank_tab.release();
     for (void* q : ctx->retired) (void)hipFree(q);
     ctx->retired.clear();
@@ -764,7 +762,6 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
     AttnFold af;
     af.slot_src = slot_src;
     af.tile_rot = tile_rot;
-    ap.q_rot = nullptr;
     ap.v_self = v_self;
     af.q_raw = q;
     af.k_self_raw = k_self;
@@ -775,9 +772,6 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
     af.pool_tokens = (int32_t)std::min<int64_t>(ctx->shot_offsets.empty() ? 0 : ctx->shot_offsets.back(), INT32_MAX);
     ap.part_o = ctx->part_o.p;
     ap.part_mlf = (float4*)ctx->part_ml.p;
-    ap.no_self = 0;
-    ap.v_blocks = 4;
-    ap.split_bounds = nullptr;
     ap.out = out;
     ap.n_ctx = n_ctx;
     ap.keys_per_split = keys_per_split;
@@ -1017,7 +1011,6 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
             b.fold.slot_src = nullptr;
             b.fold.tile_rot = nullptr;
         }
-        b.attn.q_rot = nullptr;
         b.attn.v_self = it.v_self;
         b.fold.q_raw = it.q;
         b.fold.k_self_raw = it.k_self;
@@ -1028,9 +1021,6 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
         b.fold.pool_tokens = (int32_t)std::min<int64_t>(ctx->shot_offsets.empty() ? 0 : ctx->shot_offsets.back(), INT32_MAX);
         b.attn.part_o = (char*)ctx->part_o.p + pl.po_off;
         b.attn.part_mlf = (float4*)((char*)ctx->part_ml.p + pl.pml_off);
-        b.attn.no_self = 0;
-        b.attn.v_blocks = 4;
-        b.attn.split_bounds = nullptr;
         b.attn.out = it.out;
         b.attn.n_ctx = it.n_ctx;
         b.attn.keys_per_split = pl.keys_per_split;
@@ -1522,104 +1512,96 @@ extern "C" adapshot_status adapshot_probe_entropy_tokens(adapshot_ctx* ctx, cons
     return run_probe_entropy(ctx, logits, row_stride, n_rows, vocab, &c, entropy_out, hip_stream);
 }
 
-// Shots per window: their one-hot columns fill one 32-column block of a V row, so the second product of
-// the attention kernel needs a quarter of its matrix instructions.
-constexpr int kRankWindowShots = 32;
-
-// Ranking state of one pool layer: windows of consecutive shots (at most kRankWindowShots shots and about
-// total / (2 n_cu / n_kv_heads) keys each, so that one query makes a few rounds of workgroups), per-token
-// tables, the locally encoded keys (when the pool stores them un-rotated) and the one-hot rows.
-
+// Ranking state of one pool layer: the cut of the pool into splits and segments, and the locally encoded keys (when the
+// pool stores them un-rotated).  One split of every kv head per compute unit: queries of up to 512 rows per kv head then
+// run as one round of equal workgroups, longer ones as whole rounds; at least four 64-key tiles per split.
 static adapshot_status rank_prepare(adapshot_ctx* ctx, int32_t layer, hipStream_t stream) {
     const adapshot_model_desc& d = ctx->desc;
-    const int64_t n_tok = ctx->shot_offsets[(size_t)ctx->n_shots];
-    const int64_t target_windows = std::max<int64_t>(1, 2 * (int64_t)ctx->n_cu / d.n_kv_heads);
-    const int64_t keys_target = std::max<int64_t>(512, ((n_tok + target_windows - 1) / target_windows + 63) / 64 * 64);
-    std::vector<int64_t> bounds;
-    std::vector<int32_t> shot0;
-    std::vector<int32_t> shot_split((size_t)ctx->n_shots);
-    bounds.push_back(0);
-    shot0.push_back(0);
-    {
-        int64_t keys = 0;
-        int32_t first = 0;
-        for (int32_t i = 0; i < ctx->n_shots; ++i) {
-            const int64_t len = ctx->shot_offsets[(size_t)i + 1] - ctx->shot_offsets[(size_t)i];
-            if (i > first && (i - first >= kRankWindowShots || keys + len > keys_target)) {  // close the window before shot i
-                bounds.push_back(ctx->shot_offsets[(size_t)i]);
-                shot0.push_back(i);
-                first = i;
-                keys = 0;
-            }
-            keys += len;
-            shot_split[(size_t)i] = (int32_t)shot0.size() - 1;
-        }
-    }
-    bounds.push_back(n_tok);
-    shot0.push_back(ctx->n_shots);
-    const int32_t n_split = (int32_t)bounds.size() - 1;
+    const int64_t tok0 = ctx->shot_offsets[0], n_tok = ctx->shot_offsets[(size_t)ctx->n_shots];
+    const int64_t target = std::max<int64_t>(1, ctx->n_cu / d.n_kv_heads);
+    const int64_t kps = std::max<int64_t>(256, ((n_tok - tok0 + target - 1) / target + 63) / 64 * 64);
+    const int32_t n_split = (int32_t)((n_tok - tok0 + kps - 1) / kps);
+    const int32_t n = ctx->n_shots;
+    const size_t seg_max = (size_t)n + (size_t)n_split;
 
-    // One table blob, written into a pinned buffer and brought over by a kernel on the caller's stream:
-    // [bounds int64 | local index of every token | window column of every token | first shot of every
-    //  window | window of every shot | 1 / T_i], every part 16-byte aligned.
+    // One table blob, written into a pinned buffer and brought over by a kernel on the caller's stream, every part
+    // 16-byte aligned.
     auto up16 = [](size_t v) { return (v + 15) & ~(size_t)15; };
-    const size_t off_bounds = 0;
-    const size_t off_tok = up16(off_bounds + bounds.size() * sizeof(int64_t));
-    const size_t off_shot0 = up16(off_tok + (size_t)(2 * n_tok) * sizeof(int32_t));
-    const size_t off_split = up16(off_shot0 + shot0.size() * sizeof(int32_t));
-    const size_t off_inv = up16(off_split + shot_split.size() * sizeof(int32_t));
-    const size_t tab_bytes = up16(off_inv + (size_t)ctx->n_shots * sizeof(float));
+    const size_t off_shot = 0;
+    const size_t off_end = up16(off_shot + ((size_t)n + 1) * sizeof(int32_t));
+    const size_t off_split = up16(off_end + seg_max * sizeof(int32_t));
+    const size_t off_seg0 = up16(off_split + seg_max * sizeof(int32_t));
+    const size_t off_shot_seg = up16(off_seg0 + ((size_t)n_split + 1) * sizeof(int32_t));
+    const size_t off_inv = up16(off_shot_seg + ((size_t)n + 1) * sizeof(int32_t));
+    const size_t tab_bytes = up16(off_inv + (size_t)n * sizeof(float));
 
-    const size_t layer_bytes = (size_t)n_tok * ctx->row_bytes;
     const bool rotate = d.key_state == ADAPSHOT_KEYS_UNROTATED;
-    hipError_t e = ctx->rank_v.reserve(layer_bytes, ctx->retired);
-    if (e == hipSuccess && rotate) e = ctx->rank_k.reserve(layer_bytes, ctx->retired);
+    hipError_t e = hipSuccess;
+    if (rotate) e = ctx->rank_k.reserve((size_t)n_tok * ctx->row_bytes, ctx->retired);
     if (e == hipSuccess) e = ctx->rank_tab.reserve(tab_bytes, ctx->retired);
     if (e != hipSuccess) return fail_hip(ctx, "rank_shots: workspace", e);
     int slot = -1;
     void* host = nullptr;
     e = ctx->tile_ring.acquire(tab_bytes, &slot, &host);
     if (e != hipSuccess) return fail_hip(ctx, "rank_shots: pinned tables", e);
-    memcpy((char*)host + off_bounds, bounds.data(), bounds.size() * sizeof(int64_t));
-    int32_t* tok = (int32_t*)((char*)host + off_tok);
+    int32_t* shot_off = (int32_t*)((char*)host + off_shot);
+    int32_t* seg_end = (int32_t*)((char*)host + off_end);
+    int32_t* seg_split = (int32_t*)((char*)host + off_split);
+    int32_t* split_seg0 = (int32_t*)((char*)host + off_seg0);
+    int32_t* shot_seg0 = (int32_t*)((char*)host + off_shot_seg);
     float* inv_len = (float*)((char*)host + off_inv);
-    for (int32_t i = 0; i < ctx->n_shots; ++i) {
-        const int64_t t0 = ctx->shot_offsets[(size_t)i], len = ctx->shot_offsets[(size_t)i + 1] - t0;
-        const int32_t col = i - shot0[(size_t)shot_split[(size_t)i]];
-        inv_len[i] = len > 0 ? 1.0f / (float)len : 0.f;
-        for (int64_t t = 0; t < len; ++t) {
-            tok[t0 + t] = (int32_t)t;
-            tok[n_tok + t0 + t] = col;
+    int32_t n_seg = 0, split = 0;
+    int64_t max_len = 0, split_end = tok0 + kps;
+    split_seg0[0] = 0;
+    for (int32_t i = 0; i < n; ++i) {  // every shot holds at least one token
+        int64_t t = ctx->shot_offsets[(size_t)i];
+        const int64_t end = ctx->shot_offsets[(size_t)i + 1];
+        shot_off[i] = (int32_t)t;
+        shot_seg0[i] = n_seg;
+        inv_len[i] = 1.0f / (float)(end - t);
+        max_len = std::max(max_len, end - t);
+        while (t < end) {
+            if (t == split_end) {
+                split_seg0[++split] = n_seg;
+                split_end += kps;
+            }
+            const int64_t stop = std::min(end, split_end);
+            seg_end[n_seg] = (int32_t)stop;
+            seg_split[n_seg++] = split;
+            t = stop;
         }
     }
-    memcpy((char*)host + off_shot0, shot0.data(), shot0.size() * sizeof(int32_t));
-    memcpy((char*)host + off_split, shot_split.data(), shot_split.size() * sizeof(int32_t));
+    shot_off[n] = (int32_t)n_tok;
+    shot_seg0[n] = n_seg;
+    split_seg0[split + 1] = n_seg;
     e = launch_copy_table(ctx->rank_tab.p, host, tab_bytes, stream);
     if (e != hipSuccess) return fail_hip(ctx, "rank_shots: table copy", e);
     e = ctx->tile_ring.mark_in_use(slot, stream);
     if (e != hipSuccess) return fail_hip(ctx, "rank_shots: event record", e);
     const char* tab = (const char*)ctx->rank_tab.p;
-    ctx->rank_bounds = (const int64_t*)(tab + off_bounds);
-    ctx->rank_tok = (const int32_t*)(tab + off_tok);
-    ctx->rank_shot0 = (const int32_t*)(tab + off_shot0);
-    ctx->rank_shot_split = (const int32_t*)(tab + off_split);
+    ctx->rank_seg_end = (const int32_t*)(tab + off_end);
+    ctx->rank_seg_split = (const int32_t*)(tab + off_split);
+    ctx->rank_split_seg0 = (const int32_t*)(tab + off_seg0);
+    ctx->rank_shot_seg0 = (const int32_t*)(tab + off_shot_seg);
     ctx->rank_inv_len = (const float*)(tab + off_inv);
-
-    RankPrepareParams rp;
-    rp.k_pool = (const char*)ctx->k_pool + (int64_t)layer * ctx->pool_layer_stride_tokens * ctx->row_bytes;
-    rp.k_out = rotate ? (char*)ctx->rank_k.p : nullptr;
-    rp.v_out = (char*)ctx->rank_v.p;
-    rp.tok_local = ctx->rank_tok;
-    rp.tok_col = ctx->rank_tok + n_tok;
-    rp.tab_lo = ctx->tab_lo;
-    rp.tab_hi = ctx->tab_hi;
-    rp.n_tok = n_tok;
-    rp.n_kv_heads = d.n_kv_heads;
-    rp.head_dim = d.head_dim;
-    e = launch_rank_prepare(rp, stream);
-    if (e != hipSuccess) return fail_hip(ctx, "rank_shots: prepare launch", e);
+    if (rotate) {
+        RankPrepareParams rp;
+        rp.k_pool = (const char*)ctx->k_pool + (int64_t)layer * ctx->pool_layer_stride_tokens * ctx->row_bytes;
+        rp.k_out = (char*)ctx->rank_k.p;
+        rp.shot_off = (const int32_t*)(tab + off_shot);
+        rp.tab_lo = ctx->tab_lo;
+        rp.tab_hi = ctx->tab_hi;
+        rp.max_len = max_len;
+        rp.n_shots = n;
+        rp.n_kv_heads = d.n_kv_heads;
+        rp.head_dim = d.head_dim;
+        e = launch_rank_prepare(rp, stream);
+        if (e != hipSuccess) return fail_hip(ctx, "rank_shots: prepare launch", e);
+    }
     ctx->rank_layer = layer;
     ctx->rank_n_split = n_split;
+    ctx->rank_n_seg = n_seg;
+    ctx->rank_keys_per_split = (int32_t)kps;
     return ADAPSHOT_OK;
 }
 
@@ -1707,86 +1689,51 @@ extern "C" adapshot_status adapshot_rank_shots(adapshot_ctx* ctx, int32_t layer,
         adapshot_status st = rank_prepare(ctx, layer, stream);
         if (st != ADAPSHOT_OK) return st;
     }
-    const int g = d.n_q_heads / d.n_kv_heads;
-    const int64_t rows = (int64_t)t_q * g;
-    const int64_t n_pairs = rows * d.n_kv_heads;
+    const int64_t n_pairs = (int64_t)t_q * d.n_q_heads;
     const int32_t n_split = ctx->rank_n_split;
-    const size_t esz = (size_t)ctx->elem_bytes;
-    hipError_t e = ctx->q_rot.reserve((size_t)t_q * d.n_q_heads * d.head_dim * esz, ctx->retired);
-    if (e == hipSuccess) e = ctx->part_o.reserve((size_t)n_split * n_pairs * d.head_dim * 2, ctx->retired);
-    if (e == hipSuccess) e = ctx->part_ml.reserve((size_t)n_split * n_pairs * sizeof(float4), ctx->retired);
+    hipError_t e = ctx->part_o.reserve((size_t)ctx->rank_n_seg * n_pairs * sizeof(float), ctx->retired);
+    if (e == hipSuccess) e = ctx->part_ml.reserve((size_t)n_split * n_pairs * sizeof(float2), ctx->retired);
     if (e == hipSuccess) e = ctx->rank_w.reserve((size_t)n_split * n_pairs * sizeof(float), ctx->retired);
-    if (e == hipSuccess)
-        e = ctx->rank_part.reserve((size_t)n_split * (size_t)((n_pairs + 255) / 256) * 128 * sizeof(float), ctx->retired);
     if (e != hipSuccess) return fail_hip(ctx, "rank_shots: workspace", e);
 
-    RopeRowsParams rp;  // the query rows rotated to q_pos0 + j and scaled, in a launch of their own
-    rp.q = q;
-    rp.q_rot = ctx->q_rot.p;
-    rp.tab_lo = ctx->tab_lo;
-    rp.tab_hi = ctx->tab_hi;
-    rp.q_pos0 = q_pos0;
-    rp.t_q = t_q;
-    rp.n_q_heads = d.n_q_heads;
-    rp.head_dim = d.head_dim;
-    rp.dtype = d.dtype;
-    rp.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
-    e = timed_launch(ctx, ADAPSHOT_KERNEL_ROPE_ROWS, stream, [&] { return launch_rope_rows(rp, stream); });
-    if (e != hipSuccess) return fail_hip(ctx, "rank_shots: rope launch", e);
-
-    AttnParams ap;
-    ap.k_cache = d.key_state == ADAPSHOT_KEYS_UNROTATED
-                     ? ctx->rank_k.p
-                     : (const void*)((const char*)ctx->k_pool + (int64_t)layer * ctx->pool_layer_stride_tokens * ctx->row_bytes);
-    ap.v_cache = ctx->rank_v.p;
-    AttnFold af;
-    af.slot_src = nullptr;
-    af.tile_rot = nullptr;
-    ap.q_rot = ctx->q_rot.p;
-    ap.v_self = nullptr;
-    af.q_raw = q;
-    af.k_self_raw = nullptr;
-    af.tab_lo = ctx->tab_lo;
-    af.tab_hi = ctx->tab_hi;
-    af.q_pos0 = q_pos0;
-    af.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
-    ap.part_o = ctx->part_o.p;
-    ap.part_mlf = (float4*)ctx->part_ml.p;
-    ap.no_self = 1;
-    ap.v_blocks = 1;  // rank_prepare closes a window after kRankWindowShots = 32 shots: one block of columns
-    ap.split_bounds = ctx->rank_bounds;
-    ap.out = nullptr;
-    ap.n_ctx = n_tok;
-    ap.keys_per_split = 64;
-    ap.n_split = n_split;
-    ap.t_q = t_q;
-    ap.n_q_heads = d.n_q_heads;
-    ap.n_kv_heads = d.n_kv_heads;
-    ap.head_dim = d.head_dim;
-    ap.dtype = d.dtype;
-    ap.layer_stride_bytes = 0;
-    e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN, stream, [&] { return launch_attn_mfma(ap, af, stream); });
-    if (e != hipSuccess) return fail_hip(ctx, "rank_shots: attention launch", e);
+    RankScoreParams sp;
+    sp.k = d.key_state == ADAPSHOT_KEYS_UNROTATED
+               ? ctx->rank_k.p
+               : (const void*)((const char*)ctx->k_pool + (int64_t)layer * ctx->pool_layer_stride_tokens * ctx->row_bytes);
+    sp.q = q;
+    sp.tab_lo = ctx->tab_lo;
+    sp.tab_hi = ctx->tab_hi;
+    sp.seg_end = ctx->rank_seg_end;
+    sp.split_seg0 = ctx->rank_split_seg0;
+    sp.part = (float*)ctx->part_o.p;
+    sp.part_ml = (float2*)ctx->part_ml.p;
+    sp.q_pos0 = q_pos0;
+    sp.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
+    sp.key0 = (int32_t)ctx->shot_offsets[0];
+    sp.n_tok = (int32_t)n_tok;
+    sp.keys_per_split = ctx->rank_keys_per_split;
+    sp.n_split = n_split;
+    sp.t_q = t_q;
+    sp.n_q_heads = d.n_q_heads;
+    sp.n_kv_heads = d.n_kv_heads;
+    e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN, stream, [&] { return launch_rank_scores(sp, stream); });
+    if (e != hipSuccess) return fail_hip(ctx, "rank_shots: score launch", e);
 
     RankReduceParams rr;
-    rr.part_o = ctx->part_o.p;
-    rr.part_mlf = (const float4*)ctx->part_ml.p;
+    rr.part = (const float*)ctx->part_o.p;
+    rr.part_ml = (const float2*)ctx->part_ml.p;
     rr.weights = (float*)ctx->rank_w.p;
-    rr.block_part = (float*)ctx->rank_part.p;
     rr.scores = scores_out;
-    rr.split_shot0 = ctx->rank_shot0;
-    rr.shot_split = ctx->rank_shot_split;
+    rr.seg_split = ctx->rank_seg_split;
+    rr.shot_seg0 = ctx->rank_shot_seg0;
     rr.inv_len = ctx->rank_inv_len;
     rr.inv_rows = 1.0f / ((float)t_q * (float)d.n_q_heads);
+    rr.n_pairs = n_pairs;
     rr.n_split = n_split;
-    rr.n_pairs = (int32_t)n_pairs;
-    rr.head_dim = d.head_dim;
     rr.n_shots = ctx->n_shots;
     e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN_COMBINE, stream, [&] { return launch_rank_weights(rr, stream); });
     if (e == hipSuccess)
         e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN_COMBINE, stream, [&] { return launch_rank_reduce(rr, stream); });
-    if (e == hipSuccess)
-        e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN_COMBINE, stream, [&] { return launch_rank_finish(rr, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "rank_shots: reduce launch", e);
     ctx->last_error.clear();
     return ADAPSHOT_OK;

@@ -127,7 +127,6 @@ struct AttnFold {
 struct AttnParams {
     const void* k_cache;  // one layer [>=n_ctx][h_kv][d]
     const void* v_cache;
-    const void* q_rot;    // ranking: rows rotated and scaled by rope_rows (the other forms rotate their rows themselves)
     const void* v_self;
     // Partials, indexed [n_split+1][h_kv][rows]: part_mlf = (reference maximum in log2 units, row sum l, factor f = l * a,
     // unused) and a row O' of d fp16 values with  sum_k p_k v_k = f * O':  O' = accumulator / (l * a), a = the largest
@@ -135,11 +134,6 @@ struct AttnParams {
     // partial output.
     void* part_o;
     float4* part_mlf;
-    // Ranking over the pool (MFMA kernel only): context splits with explicit key bounds
-    // [split_bounds[s], split_bounds[s+1]) instead of equal lengths, and no self part.
-    int32_t no_self;
-    int32_t v_blocks;  // 32-column blocks of a V row that carry data: 4, or 1 when every window holds <= 32 shots
-    const int64_t* split_bounds;
     void* out;       // [t_q][h_q][d]
     int64_t n_ctx;
     int64_t keys_per_split;
@@ -246,37 +240,49 @@ hipError_t launch_attn_combine_batched(const AttnBatchItem* items, const Combine
                                        hipStream_t stream);
 
 // ---- relevance ranking over the pool (Eq. attention_score) ----------------------------------
-// The query attends over the locally encoded keys of ALL pool tokens at one layer with a one-hot "value"
-// row per token: column = the token's shot, counted from the first shot of its window of <= head_dim
-// consecutive shots.  A context split is one window, so the MFMA kernel's partial of (split, row) holds
-// the attention mass of every shot of that window; the two kernels below turn the partials into scores.
+// The query rows meet the locally encoded keys of ALL pool tokens at one layer.  The pool is cut into equal splits of
+// consecutive keys; a SEGMENT is what one split holds of one shot (a shot that a split boundary cuts has two), and the
+// key pass leaves the exponentials of every (segment, row) summed, relative to the row's reference maximum in its split.
 struct RankPrepareParams {
-    const char* k_pool;      // one layer [tokens][h_kv][d], un-rotated
-    char* k_out;             // same layout, every key rotated to its position inside its shot; null: not needed
-    char* v_out;             // one-hot rows
-    const int32_t* tok_local;  // [tokens] index of the token inside its shot
-    const int32_t* tok_col;    // [tokens] shot index inside its window
+    const char* k_pool;       // one layer [tokens][h_kv][d], un-rotated
+    char* k_out;              // same layout, every key rotated to its position inside its shot
+    const int32_t* shot_off;  // [n_shots + 1] first token of every shot
     const float2* tab_lo;
     const float2* tab_hi;
-    int64_t n_tok;
-    int32_t n_kv_heads, head_dim;
+    int64_t max_len;          // longest shot
+    int32_t n_shots, n_kv_heads, head_dim;
 };
 hipError_t launch_rank_prepare(const RankPrepareParams& p, hipStream_t stream);
+struct RankScoreParams {
+    const void* k;            // one layer [tokens][h_kv][128], keys as a cache holds them
+    const void* q;            // [t_q][h_q][128] as the caller gave it; rotated to q_pos0 + j here
+    const float2* tab_lo;
+    const float2* tab_hi;
+    const int32_t* seg_end;     // [n_seg] one past the segment's last key
+    const int32_t* split_seg0;  // [n_split + 1] first segment of every split
+    float* part;              // [n_seg][pairs], pair = kv head * rows + row
+    float2* part_ml;          // [n_split][pairs] (reference maximum in log2 units, row sum)
+    int64_t q_pos0;
+    float q_scale;
+    int32_t key0, n_tok;      // keys [key0, n_tok)
+    int32_t keys_per_split;   // multiple of 64
+    int32_t n_split, t_q, n_q_heads, n_kv_heads;
+};
+hipError_t launch_rank_scores(const RankScoreParams& p, hipStream_t stream);
 struct RankReduceParams {
-    const void* part_o;       // [n_split][pairs][d] fp16
-    const float4* part_mlf;   // [n_split][pairs]
+    const float* part;        // [n_seg][pairs]
+    const float2* part_ml;    // [n_split][pairs]
     float* weights;           // [n_split][pairs] scratch
-    float* block_part;        // [n_split][ceil(pairs / 256)][128] scratch: per-row-block sums of every shot slot
     float* scores;            // [n_shots]
-    const int32_t* split_shot0;  // [n_split + 1] first shot of every window
-    const int32_t* shot_split;   // [n_shots] window of every shot
+    const int32_t* seg_split;  // [n_seg] split of every segment
+    const int32_t* shot_seg0;  // [n_shots + 1] first segment of every shot
     const float* inv_len;     // [n_shots] 1 / T_i
     float inv_rows;           // 1 / (t_q * n_q_heads)
-    int32_t n_split, n_pairs, head_dim, n_shots;
+    int64_t n_pairs;
+    int32_t n_split, n_shots;
 };
-hipError_t launch_rank_weights(const RankReduceParams& p, hipStream_t stream);  // merge weights of the windows
-hipError_t launch_rank_reduce(const RankReduceParams& p, hipStream_t stream);   // weighted sum over blocks of rows
-hipError_t launch_rank_finish(const RankReduceParams& p, hipStream_t stream);   // row blocks added in a fixed order
+hipError_t launch_rank_weights(const RankReduceParams& p, hipStream_t stream);  // merge weights of the splits
+hipError_t launch_rank_reduce(const RankReduceParams& p, hipStream_t stream);   // weighted sums, one shot per workgroup
 
 // Ranking for the shapes the matrix-core kernel does not cover: one wavefront per (query token, head) walks the
 // whole pool layer twice (normaliser, then the mass of every shot), a second kernel adds the rows in a fixed order.
@@ -404,12 +410,12 @@ struct adapshot_ctx {
     size_t batch_attn_off = 0, batch_comb_off = 0;
     // ranking state of one pool layer, built on first use
     int32_t rank_layer = -1;
-    int32_t rank_n_split = 0;
-    adapshot::DevBuf rank_k, rank_v, rank_tab, rank_w, rank_part;
-    const int32_t* rank_tok = nullptr;       // views into rank_tab
-    const int64_t* rank_bounds = nullptr;
-    const int32_t* rank_shot0 = nullptr;
-    const int32_t* rank_shot_split = nullptr;
+    int32_t rank_n_split = 0, rank_n_seg = 0, rank_keys_per_split = 0;
+    adapshot::DevBuf rank_k, rank_tab, rank_w;
+    const int32_t* rank_seg_end = nullptr;    // views into rank_tab
+    const int32_t* rank_seg_split = nullptr;
+    const int32_t* rank_split_seg0 = nullptr;
+    const int32_t* rank_shot_seg0 = nullptr;
     const float* rank_inv_len = nullptr;
     std::vector<void*> retired;  // outgrown workspaces, freed when the context is destroyed
     adapshot::Profiler prof;

@@ -42,18 +42,9 @@
 // row is 32 bytes of a fragment and 8 bytes of an accumulator quad, and memory instructions that touch 32 rows for
 // that little each cost 5 % of the kernel when every workgroup of the grid issues them at the same moment.
 
-#include "adapshot_internal.h"
+#include "mfma_tiles.h"
 
 namespace adapshot {
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kD = 128;  // head_dim
 constexpr int kTileKeys = 64;
@@ -67,65 +58,6 @@ constexpr int kPD = 4;                             // LDS fragment reads in flig
 constexpr int kWaitVm0 = 0x0f70;  // vmcnt(0), other counters untouched
 
 bool attn_mfma_supported(const adapshot_model_desc& d) { return d.dtype == ADAPSHOT_BF16 && d.head_dim == kD; }
-
-// max / sum over the two lanes l and l^32 without going through LDS
-__device__ __forceinline__ float max_xhalf(float v) {
-    const unsigned u = __float_as_uint(v);
-    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_xhalf(float v) {
-    const unsigned u = __float_as_uint(v);
-    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-__device__ __forceinline__ unsigned pack2_bf16(float lo, float hi) {
-    f32x2 f = {lo, hi};
-    bf16x2 b = __builtin_convertvector(f, bf16x2);  // v_cvt_pk_bf16_f32, round to nearest even
-    return __builtin_bit_cast(unsigned, b);
-}
-
-// max of three in one instruction.  fmaxf() chains compile to twice as many instructions because every
-// input is first canonicalised; the scores here are MFMA outputs or -inf, never signalling NaNs.
-__device__ __forceinline__ float max3(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-// 16 bytes per lane from global memory straight into LDS: lane l's data lands at lds_base + 16*l
-// (lds_base is wave-uniform and goes through M0; the source is a uniform base plus a 32-bit lane offset).
-// Issued as inline assembly so that the key loop keeps control of the wait counters: the loads complete
-// in order and are awaited with vmcnt in barrier_keep_one_group(), tiles after they were issued.
-// NT marks the data as read once (the instruction's non-temporal bit): a launch whose workgroups stream their
-// context with one or two working wavefronts is bound by the memory path, and tiles that are not kept in the L2
-// for a reader that never comes move 10 % faster (5.9 -> 6.45 TB/s for the bare tile stream of a decode step).
-template <bool NT = false>
-__device__ __forceinline__ void load_lds_16(const char* gbase, unsigned goff, unsigned lds_base) {
-    unsigned saved_m0;
-    if (NT)
-        asm volatile(
-            "s_mov_b32 %0, m0\n\t"
-            "s_mov_b32 m0, %3\n\t"
-            "global_load_lds_dwordx4 %1, %2 nt\n\t"
-            "s_mov_b32 m0, %0"
-            : "=&s"(saved_m0)
-            : "v"(goff), "s"(gbase), "s"(lds_base)
-            : "memory");
-    else
-        asm volatile(
-            "s_mov_b32 %0, m0\n\t"
-            "s_mov_b32 m0, %3\n\t"
-            "global_load_lds_dwordx4 %1, %2\n\t"
-            "s_mov_b32 m0, %0"
-            : "=&s"(saved_m0)
-            : "v"(goff), "s"(gbase), "s"(lds_base)
-            : "memory");
-}
-__device__ __forceinline__ unsigned lds_addr(const void* p) {
-    return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
-}
 
 // Workgroup barrier of the key loop.  __syncthreads() would drain every tile load still in flight
 // (they write LDS); here only the group issued two tiles ago must have landed (the younger
@@ -154,7 +86,6 @@ __device__ __forceinline__ T load_uniform(const T* ptr) {
 
 // WAVES wavefronts, each owning NR blocks of 32 rows for the whole key loop.  BATCHED: the workgroup takes
 // its problem and its (kv head, row tile, split) from the work list instead of the launch arguments.
-// PVB: 32-column blocks of V that carry data (4 = the whole head; ranking's one-hot rows use 1).
 // POOL: the zero-copy form.  The context is not an assembled cache but the pool itself, read through the
 // table slot_src (context slot -> pool token): every 64-slot tile is gathered row by row into LDS, and its
 // keys are rotated there, in place, to the positions pos0 + slot before the first product reads them
@@ -167,12 +98,10 @@ __device__ __forceinline__ T load_uniform(const T* ptr) {
 // else); and V keeps three tiles in LDS instead of four, which pays for the tables (V(t+1) has one tile of
 // time to land instead of two).  What a context split computes is what the plain form computes over the
 // assembled cache.
-// FOLD: the workgroup rotates its query rows (and the self split its keys) itself; otherwise rope_rows has
-// done that in a launch of its own and the kernel reads q_rot.  Folding saves the launch: at the
-// headline size the rotation repeated in every context split costs the kernel 1.4 us and the launch it replaces
-// cost the step 3 us.  Ranking, whose one block of columns needs no keys of the query, keeps the launch.
+// The workgroup rotates its query rows (and the self split its keys) itself: at the headline size the rotation repeated
+// in every context split costs the kernel 1.4 us, and the launch it replaces cost the step 3 us.
 // NT: the K/V tile loads of the plain form carry the non-temporal bit (see load_lds_16).
-template <int WAVES, int NR, bool BATCHED, int PVB, bool POOL, bool FOLD, bool NT = false>
+template <int WAVES, int NR, bool BATCHED, bool POOL, bool NT = false>
 __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg, AttnFold f_arg,
                                                                int n_row_tiles_arg, const AttnBatchItem* items,
                                                                const AttnWork* work) {
@@ -226,9 +155,9 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
         split = rest / n_row_tiles_arg;
         // the self split is dispatched first: its workgroups are short, and what the grid has beyond one
         // workgroup per compute unit then starts as soon as they are done
-        if (!p.no_self) split = split == 0 ? p.n_split : split - 1;
+        split = split == 0 ? p.n_split : split - 1;
     }
-    const bool self = !p.no_self && split == p.n_split;
+    const bool self = split == p.n_split;
     // the prologue-only arguments are fetched where they are used, not held through the key loop
     auto fold = [&]() __attribute__((always_inline)) -> AttnFold {
         if (BATCHED) return load_uniform(&items[item].fold);
@@ -253,10 +182,6 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
     if (self) {
         k0 = 0;
         k1 = p.t_q;
-    } else if (p.split_bounds) {  // explicit bounds (ranking: one window of shots per split)
-        const unsigned* b = (const unsigned*)(p.split_bounds + split);
-        k0 = (int64_t)(((uint64_t)__builtin_amdgcn_readfirstlane(b[1]) << 32) | __builtin_amdgcn_readfirstlane(b[0]));
-        k1 = (int64_t)(((uint64_t)__builtin_amdgcn_readfirstlane(b[3]) << 32) | __builtin_amdgcn_readfirstlane(b[2]));
     } else {
         k0 = (int64_t)split * p.keys_per_split;
         k1 = k0 + p.keys_per_split < p.n_ctx ? k0 + p.keys_per_split : p.n_ctx;
@@ -409,7 +334,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
         *a1 = x1;
         *a2 = x2;
     };
-    if (!self || !FOLD) {
+    if (!self) {
         if (POOL) {
             // this thread's entries of the second-level table: (cos, sin)(r theta_f), f = 8 cp .. 8 cp + 7
             const f32x4* tl = (const f32x4*)(pf.tab_lo + (tid >> 3) * (kD / 2) + 8 * (tid & 7));
@@ -481,11 +406,10 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
     // same moment that cost 2 % of the kernel at the headline size.  Rows past the last one stand for it.
     bf16x8 qf[8];
     {
-        AttnFold f{};
-        if (FOLD) f = fold();
+        const AttnFold f = fold();
         const bool valid = row[0] < rows;
         const int j = valid ? jrow[0] : 0;
-        const char* qbase = (const char*)(FOLD ? f.q_raw : p.q_rot);
+        const char* qbase = (const char*)f.q_raw;
         const int r_last = rows - 1, j_last = r_last / g;
         const int jc = valid ? j : j_last, gc = valid ? row[0] - j * g : r_last - j_last * g;
         const unsigned qoff = (unsigned)(((jc * p.n_q_heads + hk * g + gc) * kD) * 2);  // the host keeps Q below 2 GiB
@@ -504,11 +428,9 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
             if (valid) {
                 x1 = *(const u32x4*)(qst + l32 * 256 + (((2 * kk + hh) ^ (l32 & 15)) << 4));
                 x2 = *(const u32x4*)(qst + l32 * 256 + (((2 * (kk + 4) + hh) ^ (l32 & 15)) << 4));
-                if (FOLD) {
-                    float c[8], sn[8];
-                    cos_sin8(f, f.q_pos0 + j, 16 * kk + 8 * hh, c, sn);
-                    rotate8(x1, x2, c, sn, f.q_scale);
-                }
+                float c[8], sn[8];
+                cos_sin8(f, f.q_pos0 + j, 16 * kk + 8 * hh, c, sn);
+                rotate8(x1, x2, c, sn, f.q_scale);
             }
             qf[kk] = __builtin_bit_cast(bf16x8, x1);
             qf[kk + 4] = __builtin_bit_cast(bf16x8, x2);
@@ -591,25 +513,23 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
         }
     };
     // O^T += V^T . P^T from V buffer `buf` (plus voff bytes, the zero-copy form's run-time ring position):
-    // 4 * PVB MFMAs, 2 transposing reads per fragment
+    // 16 MFMAs, 2 transposing reads per fragment
     auto pv_phase = [&](int buf, unsigned voff = 0u) __attribute__((always_inline)) {
-        constexpr int NPV = 4 * PVB;
-        constexpr int PD = kFD < NPV ? kFD : NPV;
         __builtin_amdgcn_s_setprio(1);
-        bf16x8 fr[PD];
+        bf16x8 fr[kFD];
 #pragma unroll
-        for (int i = 0; i < PD; ++i) fr[i] = v_frag(buf, i / PVB, i % PVB, voff);
+        for (int i = 0; i < kFD; ++i) fr[i] = v_frag(buf, i / 4, i % 4, voff);
 #pragma unroll
-        for (int i = 0; i < NPV; ++i) {  // ks = i / PVB, db = i % PVB
-            const bf16x8 a = fr[i % PD];
-            if (i + PD < NPV) fr[i % PD] = v_frag(buf, (i + PD) / PVB, (i + PD) % PVB, voff);
-            o[i % PVB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, pb[i / PVB]), o[i % PVB], 0, 0, 0);
+        for (int i = 0; i < 16; ++i) {  // ks = i / 4, db = i % 4
+            const bf16x8 a = fr[i % kFD];
+            if (i + kFD < 16) fr[i % kFD] = v_frag(buf, (i + kFD) / 4, (i + kFD) % 4, voff);
+            o[i % 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, pb[i / 4]), o[i % 4], 0, 0, 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x100, 2 * PD, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 * kFD, 0);
 #pragma unroll
-        for (int i = 0; i < NPV; ++i) {
+        for (int i = 0; i < 16; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (i + PD < NPV) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            if (i + kFD < 16) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         }
     };
     // masks + online softmax of tile t with a lazily updated reference maximum; leaves P^T(t) in pb
@@ -684,7 +604,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
     // A wavefront whose 32 rows all lie past the last query row (a decode step has fewer rows than one
     // wavefront owns) only moves tiles and keeps the barriers.
     const bool wave_idle = row_tile * kAttnRowTile + wave * NR * 32 >= rows;
-    if (self && FOLD) {
+    if (self) {
         // ---- the query's own tokens: a few tiles at most, moved through registers so that the keys can be
         // rotated to their positions q_pos0 + u on the way (the caller gives them un-rotated).  One tile at a
         // time in buffer 0, two workgroup barriers per tile.  Thread = (row r, chunk pair cp) for K, two
@@ -878,12 +798,10 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
     };
     const int row0 = row_tile * kAttnRowTile + wave * NR * 32;  // first row of this wavefront
     char* const obase = (char*)p.part_o + ((((int64_t)split * p.n_kv_heads + hk) * rows + row0) * kD) * 2;
-    // (ranking's one block of columns: the first 64 bytes of every row are written and read, nothing else)
-    constexpr int kHalves = PVB == 1 ? 1 : 2, kBlocks = PVB == 1 ? 1 : 2, kSlots = PVB == 1 ? 4 : 8;
 #pragma unroll
-    for (int half = 0; half < kHalves; ++half) {
+    for (int half = 0; half < 2; ++half) {
 #pragma unroll
-        for (int dbl = 0; dbl < kBlocks; ++dbl)
+        for (int dbl = 0; dbl < 2; ++dbl)
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq) {
                 const int db = 2 * half + dbl;
@@ -897,7 +815,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
         for (int j = 0; j < 4; ++j) {
             const int r = 8 * j + (lane >> 3), sl = lane & 7;
             const u32x4 v = *(const u32x4*)(stage_row(r) + ((sl ^ ((r >> 1) & 7)) << 4));
-            if (row0 + r < rows && sl < kSlots) *(u32x4*)(obase + (int64_t)r * (kD * 2) + half * 128 + sl * 16) = v;
+            if (row0 + r < rows) *(u32x4*)(obase + (int64_t)r * (kD * 2) + half * 128 + sl * 16) = v;
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before the second half overwrites the piece
     }
@@ -907,18 +825,14 @@ hipError_t launch_attn_mfma(const AttnParams& p, const AttnFold& f, hipStream_t 
     const int g = p.n_q_heads / p.n_kv_heads;
     const int rows = p.t_q * g;
     const int n_row_tiles = (rows + kAttnRowTile - 1) / kAttnRowTile;
-    const unsigned blocks = (unsigned)(p.n_kv_heads * n_row_tiles * (p.n_split + (p.no_self ? 0 : 1)));
+    const unsigned blocks = (unsigned)(p.n_kv_heads * n_row_tiles * (p.n_split + 1));
     if (blocks == 0) return hipSuccess;
-    if (p.v_blocks == 1)
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, 1, false, false>), dim3(blocks),
-                      dim3(kAttnWaves * 64), stream, p, f, n_row_tiles, (const AttnBatchItem*)nullptr,
-                      (const AttnWork*)nullptr);
-    else if (rows <= kAttnStreamRows)  // every tile is read by one workgroup per kv head, which has few rows to feed
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, 4, false, true, true>),
+    if (rows <= kAttnStreamRows)  // every tile is read by one workgroup per kv head, which has few rows to feed
+        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, false, true>),
                       dim3(blocks), dim3(kAttnWaves * 64), stream, p, f, n_row_tiles, (const AttnBatchItem*)nullptr,
                       (const AttnWork*)nullptr);
     else
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, 4, false, true>), dim3(blocks),
+        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, false>), dim3(blocks),
                       dim3(kAttnWaves * 64), stream, p, f, n_row_tiles, (const AttnBatchItem*)nullptr,
                       (const AttnWork*)nullptr);
     return hipGetLastError();
@@ -930,9 +844,9 @@ hipError_t launch_attn_mfma_pool(const AttnParams& p, const AttnFold& f, hipStre
     const int n_row_tiles = (rows + kAttnRowTile - 1) / kAttnRowTile;
     const unsigned blocks = (unsigned)(p.n_kv_heads * n_row_tiles * (p.n_split + 1));
     if (blocks == 0) return hipSuccess;
-    if (p.no_self || p.split_bounds || !f.slot_src || !f.tile_rot || p.keys_per_split % kTileKeys != 0)
+    if (!f.slot_src || !f.tile_rot || p.keys_per_split % kTileKeys != 0)
         return hipErrorInvalidValue;
-    launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, 4, true, true>), dim3(blocks),
+    launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, true>), dim3(blocks),
                   dim3(kAttnWaves * 64), stream, p, f, n_row_tiles, (const AttnBatchItem*)nullptr, (const AttnWork*)nullptr);
     return hipGetLastError();
 }
@@ -941,13 +855,13 @@ hipError_t launch_attn_mfma_batched(const AttnBatchItem* items, const AttnWork* 
                                     bool stream_tiles, int layer, hipStream_t stream) {
     if (n_work <= 0) return hipSuccess;
     if (pool)
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), true, 4, true, true>), dim3((unsigned)n_work),
+        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), true, true>), dim3((unsigned)n_work),
                       dim3(kAttnWaves * 64), stream, AttnParams{}, AttnFold{}, layer, items, work);
     else if (stream_tiles)
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), true, 4, false, true, true>),
+        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), true, false, true>),
                       dim3((unsigned)n_work), dim3(kAttnWaves * 64), stream, AttnParams{}, AttnFold{}, layer, items, work);
     else
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), true, 4, false, true>), dim3((unsigned)n_work),
+        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), true, false>), dim3((unsigned)n_work),
                       dim3(kAttnWaves * 64), stream, AttnParams{}, AttnFold{}, layer, items, work);
     return hipGetLastError();
 }

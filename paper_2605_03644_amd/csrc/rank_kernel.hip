@@ -1,39 +1,32 @@
-// Relevance ranking of the pool's shots for a query (Eq. attention_score, Attention-based retrieval).
-//
-// The attention itself runs in the MFMA kernel: keys = the locally encoded keys of every pool token at
-// the representative layer, "values" = one-hot rows that mark each token's shot inside its window of at
-// most head_dim consecutive shots, one context split per window, softmax normalised over the whole pool
-// when the splits are merged.  This file holds what surrounds it:
-//   rank_prepare   once per pool layer: rotate every key to its position inside its shot (a pool that
-//                  stores un-rotated keys; Eq. prefill caches them encoded) and write the one-hot rows;
-//   rank_weights   per (kv head, row): merge the splits' (m, l) into the row's global normaliser and
-//                  leave  w[s][row] = f_s 2^(m_s - M) / L  for every split;
-//   rank_reduce    per (window, block of 256 rows, shot slot): sum w[s][row] * O'[s][row][slot] over the
-//                  block's rows into a partial;
-//   rank_finish    per shot: add the row blocks' partials in a fixed order (the same query gives the same
-//                  bits every time) and scale by 1 / (T_q H_q T_i).
-#include "adapshot_internal.h"
+// Relevance ranking of the pool's shots for a query (Eq. attention_score, Attention-based retrieval): the small
+// kernels around the matrix-core pass over the keys (rank_mfma.hip), and the plain kernels of the shapes that pass does
+// not cover.
+//   rank_prepare   once per pool layer that stores un-rotated keys: every key rotated to its position inside its shot
+//                  (Eq. prefill caches them encoded);
+//   rank_weights   per (kv head, row): merge the splits' (m, l) into the row's global normaliser and leave
+//                  w[s][row] = 2^(m_s - M) / L for every split;
+//   rank_reduce    per shot: sum w[split][row] * part[segment][row] over its segments and all rows, always in the same
+//                  order (the same query gives the same bits every time), scaled by 1 / (T_q H_q T_i).
+#include <algorithm>
+
+#include "mfma_tiles.h"
 
 namespace adapshot {
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// One thread per (token, kv head, chunk pair): bf16, 8 pairs per 16-byte chunk.
+// grid = (shot, slice of the shot); one thread per (token, kv head, chunk pair): bf16, 8 pairs per 16-byte chunk.
 __global__ __launch_bounds__(256) void rank_prepare_kernel(RankPrepareParams p) {
     const int half = p.head_dim >> 1;
     const int cpr = half / 8;  // chunk pairs per head
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t n = p.n_tok * p.n_kv_heads * cpr;
-    if (idx >= n) return;
-    const int ci = (int)(idx % cpr);
-    const int64_t th = idx / cpr;
-    const int hk = (int)(th % p.n_kv_heads);
-    const int64_t u = th / p.n_kv_heads;
-    const int64_t o = ((u * p.n_kv_heads + hk) * p.head_dim + ci * 8) * 2;
-    const int64_t ho = (int64_t)half * 2;
-    if (p.k_out) {
-        const int a = p.tok_local[u];
-        const float2* thi = p.tab_hi + (int64_t)(a >> kRopeLoBits) * half + ci * 8;
+    const int64_t tok0 = p.shot_off[blockIdx.x];
+    const int64_t n = ((int64_t)p.shot_off[blockIdx.x + 1] - tok0) * p.n_kv_heads * cpr;
+    for (int64_t idx = (int64_t)blockIdx.y * 256 + threadIdx.x; idx < n; idx += (int64_t)gridDim.y * 256) {
+        const int ci = (int)(idx % cpr);
+        const int64_t th = idx / cpr;
+        const int hk = (int)(th % p.n_kv_heads);
+        const int64_t a = th / p.n_kv_heads;  // position inside the shot
+        const int64_t o = (((tok0 + a) * p.n_kv_heads + hk) * p.head_dim + ci * 8) * 2;
+        const int64_t ho = (int64_t)half * 2;
+        const float2* thi = p.tab_hi + (a >> kRopeLoBits) * half + ci * 8;
         const float2* tlo = p.tab_lo + (a & (kRopeLo - 1)) * half + ci * 8;
         u32x4 x1 = *(const u32x4*)(p.k_pool + o), x2 = *(const u32x4*)(p.k_pool + o + ho);
         float y1[8], y2[8];
@@ -48,31 +41,21 @@ __global__ __launch_bounds__(256) void rank_prepare_kernel(RankPrepareParams p) 
             y1[w] = a1 * c - a2 * s;
             y2[w] = a2 * c + a1 * s;
         }
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        typedef float f32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
         for (int w = 0; w < 8; w += 2) {
-            const f32x2 f1 = {y1[w], y1[w + 1]}, f2 = {y2[w], y2[w + 1]};
-            x1[w >> 1] = __builtin_bit_cast(unsigned, __builtin_convertvector(f1, bf16x2));  // round to nearest even
-            x2[w >> 1] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2, bf16x2));
+            x1[w >> 1] = pack2_bf16(y1[w], y1[w + 1]);
+            x2[w >> 1] = pack2_bf16(y2[w], y2[w + 1]);
         }
         *(u32x4*)(p.k_out + o) = x1;
         *(u32x4*)(p.k_out + o + ho) = x2;
     }
-    // one-hot row of this token (the same for every head): bf16 1.0 at column tok_col[u]
-    const int col = p.tok_col[u];
-    u32x4 z1 = {0u, 0u, 0u, 0u}, z2 = {0u, 0u, 0u, 0u};
-    const int e1 = col - ci * 8, e2 = col - half - ci * 8;
-    if (e1 >= 0 && e1 < 8) z1[e1 >> 1] = (e1 & 1) ? 0x3f800000u : 0x00003f80u;
-    if (e2 >= 0 && e2 < 8) z2[e2 >> 1] = (e2 & 1) ? 0x3f800000u : 0x00003f80u;
-    *(u32x4*)(p.v_out + o) = z1;
-    *(u32x4*)(p.v_out + o + ho) = z2;
 }
 
 hipError_t launch_rank_prepare(const RankPrepareParams& p, hipStream_t stream) {
-    const int64_t n = p.n_tok * p.n_kv_heads * (p.head_dim / 16);
-    if (n <= 0) return hipSuccess;
-    launch_kernel(rank_prepare_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), stream, p);
+    if (p.n_shots <= 0) return hipSuccess;
+    // a slice is 32 tokens of the longest shot, at most 64 slices
+    const int64_t slices = std::min<int64_t>(64, std::max<int64_t>(1, (p.max_len + 31) / 32));
+    launch_kernel(rank_prepare_kernel, dim3((unsigned)p.n_shots, (unsigned)slices), dim3(256), stream, p);
     return hipGetLastError();
 }
 
@@ -83,69 +66,47 @@ __global__ __launch_bounds__(256) void rank_weights_kernel(RankReduceParams p) {
     const bool on = pair < p.n_pairs;  // whole 16-lane groups are on or off together
     float M = -INFINITY;
     if (on)
-        for (int s = sl; s < p.n_split; s += 16) M = fmaxf(M, p.part_mlf[(int64_t)s * p.n_pairs + pair].x);
+        for (int s = sl; s < p.n_split; s += 16) M = fmaxf(M, p.part_ml[(int64_t)s * p.n_pairs + pair].x);
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
     float L = 0.f;
     if (on)
         for (int s = sl; s < p.n_split; s += 16) {
-            const float4 v = p.part_mlf[(int64_t)s * p.n_pairs + pair];
-            L += v.x == -INFINITY ? 0.f : exp2f(v.x - M) * v.y;
+            const float2 v = p.part_ml[(int64_t)s * p.n_pairs + pair];
+            L += exp2f(v.x - M) * v.y;
         }
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) L += __shfl_xor(L, o, 64);
     const float inv = L > 0.f ? 1.0f / L : 0.f;
     if (on)
-        for (int s = sl; s < p.n_split; s += 16) {
-            const float4 v = p.part_mlf[(int64_t)s * p.n_pairs + pair];
-            p.weights[(int64_t)s * p.n_pairs + pair] = v.x == -INFINITY ? 0.f : exp2f(v.x - M) * v.z * inv;
-        }
+        for (int s = sl; s < p.n_split; s += 16)
+            p.weights[(int64_t)s * p.n_pairs + pair] = exp2f(p.part_ml[(int64_t)s * p.n_pairs + pair].x - M) * inv;
 }
 
-// grid = (n_split, ceil(n_pairs / 256)); 256 threads = 64 row groups x 4 lanes, a lane owning 8 shot slots
-// (16 bytes of a partial row: a window holds at most 32 shots, so only the first 32 of a row's 128 columns
-// carry data, and the attention kernel writes only those).  Row group rg takes rows pair0 + rg, + 64, ...;
-// the 64 partial sums of a slot meet in LDS and leave as block_part[window][row block][slot].
+// One workgroup per shot.  VEC: whole 16-byte pieces (the number of pairs is a multiple of 4).
+template <bool VEC>
 __global__ __launch_bounds__(256) void rank_reduce_kernel(RankReduceParams p) {
-    typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-    __shared__ float red[64][33];
-    const int s = blockIdx.x;
-    const int lane4 = threadIdx.x & 3, rg = threadIdx.x >> 2;
-    const int shot0 = p.split_shot0[s];
-    const int n_here = p.split_shot0[s + 1] - shot0;
-    const int64_t pair0 = (int64_t)blockIdx.y * 256;
-    const int64_t pair1 = pair0 + 256 < p.n_pairs ? pair0 + 256 : p.n_pairs;
-    const _Float16* o = (const _Float16*)p.part_o + ((int64_t)s * p.n_pairs) * 128 + lane4 * 8;
-    const float* w = p.weights + (int64_t)s * p.n_pairs;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int64_t r = pair0 + rg; r < pair1; r += 64) {
-        const f16x8 v = __builtin_nontemporal_load((const f16x8*)(o + r * 128));
-        const float wr = w[r];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] += wr * (float)v[i];
+    __shared__ float red[4];
+    const int i = blockIdx.x;
+    float acc = 0.f;
+    for (int q = p.shot_seg0[i]; q < p.shot_seg0[i + 1]; ++q) {
+        const float* v = p.part + (int64_t)q * p.n_pairs;
+        const float* w = p.weights + (int64_t)p.seg_split[q] * p.n_pairs;
+        if (VEC) {
+#pragma unroll 4
+            for (int64_t r = threadIdx.x * 4; r < p.n_pairs; r += 1024) {
+                const f32x4 a = __builtin_nontemporal_load((const f32x4*)(v + r)), b = *(const f32x4*)(w + r);
+                acc += (a[0] * b[0] + a[1] * b[1]) + (a[2] * b[2] + a[3] * b[3]);
+            }
+        } else {
+            for (int64_t r = threadIdx.x; r < p.n_pairs; r += 256) acc += v[r] * w[r];
+        }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) red[rg][lane4 * 8 + i] = acc[i];
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    const int c = threadIdx.x;
-    if (c < 32 && c < n_here) {
-        float t = 0.f;
-#pragma unroll
-        for (int g = 0; g < 64; ++g) t += red[g][c];
-        p.block_part[((int64_t)s * gridDim.y + blockIdx.y) * 128 + c] = t;
-    }
-}
-
-// One thread per shot: its window's row-block partials added in index order.
-__global__ __launch_bounds__(256) void rank_finish_kernel(RankReduceParams p, int n_blocks) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= p.n_shots) return;
-    const int s = p.shot_split[i];
-    const int c = i - p.split_shot0[s];
-    const float* part = p.block_part + (int64_t)s * n_blocks * 128 + c;
-    float t = 0.f;
-    for (int b = 0; b < n_blocks; ++b) t += part[(int64_t)b * 128];
-    p.scores[i] = t * p.inv_rows * p.inv_len[i];
+    if (threadIdx.x == 0) p.scores[i] = ((red[0] + red[1]) + (red[2] + red[3])) * p.inv_rows * p.inv_len[i];
 }
 
 hipError_t launch_rank_weights(const RankReduceParams& p, hipStream_t stream) {
@@ -155,16 +116,9 @@ hipError_t launch_rank_weights(const RankReduceParams& p, hipStream_t stream) {
 }
 
 hipError_t launch_rank_reduce(const RankReduceParams& p, hipStream_t stream) {
-    if (p.n_split <= 0 || p.n_pairs <= 0) return hipSuccess;
-    if (p.head_dim != 128) return hipErrorInvalidValue;
-    launch_kernel(rank_reduce_kernel, dim3((unsigned)p.n_split, (unsigned)((p.n_pairs + 255) / 256)), dim3(256), stream, p);
-    return hipGetLastError();
-}
-
-hipError_t launch_rank_finish(const RankReduceParams& p, hipStream_t stream) {
-    if (p.n_split <= 0 || p.n_pairs <= 0 || p.n_shots <= 0) return hipSuccess;
-    launch_kernel(rank_finish_kernel, dim3((unsigned)((p.n_shots + 255) / 256)), dim3(256), stream, p,
-                  (int)((p.n_pairs + 255) / 256));
+    if (p.n_pairs <= 0 || p.n_shots <= 0) return hipSuccess;
+    if (p.n_pairs % 4 == 0) launch_kernel(rank_reduce_kernel<true>, dim3((unsigned)p.n_shots), dim3(256), stream, p);
+    else launch_kernel(rank_reduce_kernel<false>, dim3((unsigned)p.n_shots), dim3(256), stream, p);
     return hipGetLastError();
 }
 
