@@ -547,10 +547,12 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
                     if (32 * kb + 8 * (r >> 2) + (r & 3) >= lim_t) s[kb][r] = -INFINITY;
         }
         // s holds S - m_use; mx is relative to the reference
-        float mx = max3(s[0][0], s[1][0], s[0][1]);
+        // The first maximum is no inline assembly and reads what was multiplied last: the compiler makes it wait for the
+        // product, and max3() behind it, in whose text it sees no reader of the product, comes late enough.
+        float mx = fmaxf(s[1][0], s[0][0]);
 #pragma unroll
-        for (int r = 1; r < 15; ++r) mx = max3(mx, s[1][r], s[0][r + 1]);
-        mx = max_xhalf(fmaxf(mx, s[1][15]));
+        for (int r = 1; r < 16; ++r) mx = max3(mx, s[1][r], s[0][r]);
+        mx = max_xhalf(mx);
         if (__builtin_amdgcn_ballot_w64(mx > 8.0f || (m_run == -INFINITY && mx > -INFINITY))) {
             const float m_use_old = m_run == -INFINITY ? 0.f : m_run;  // nothing visible yet: the reference is 0
             const float m_new = fmaxf(m_run, mx + m_use_old);
