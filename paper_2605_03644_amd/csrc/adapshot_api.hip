@@ -591,32 +591,63 @@ static int64_t plan_mfma_splits(int64_t n_cu, int64_t units, int64_t key_tiles, 
     return best;
 }
 
-// 16-row blocks per workgroup of the streaming kernel.  Two share the loads and the unpacking of K and V, but leave half
-// the workgroups: they pay where one block each already gives every compute unit two workgroups.
-static int32_t stream_row_blocks(const adapshot_model_desc& d, int64_t n_cu, int64_t rows) {
-    return d.head_dim == 64 && d.n_kv_heads * ((rows + 15) / 16) >= 2 * n_cu ? 2 : 1;
+// Which kernel: the 256-row tile kernel for bf16 models of head dimension 128, unless the rows of a kv head fit one 16-row
+// block (a decode step) and the launch reads at most kStreamBytes of context: the streaming kernel is one launch instead
+// of three and keeps every wavefront busy, but draws 5.3 TB/s from the memory where the tile kernel draws 6.1.  Per layer
+// of a decode step (tile kernel / streaming kernel, us): 25 MB 27.2 / 15.6, 98 MB 34.1 / 30.7, 197 MB 48.2 / 46.5 (28 queries
+// of 4k slots, 229 MB: 56.9 / 55.6), 354 MB 73.2 / 76.8, 826 MB 153 / 167.
+constexpr int64_t kStreamBytes = 200000000;
+static bool attn_tile_kernel(const adapshot_model_desc& d, int64_t rows, int64_t context_tokens) {
+    return attn_mfma_supported(d) && (rows > 16 || context_tokens * d.n_kv_heads * d.head_dim * 4 > kStreamBytes);
 }
 
-// Context splits of the streaming kernel: the count whose price is lowest.  A split of n 64-key tiles keeps each of a
-// compute unit's four matrix cores busy for n 16-key steps; a step is its matrix instructions and about 450 cycles of
-// softmax and load latency.  Splitting costs the merge: 2.2 us and a little per partial (measured: fp32, head_dim 128,
-// one query over 2300 slots: 55 us in one split, 11.8 us in 36; bf16, head_dim 64, 256 slots: 6.7 us in one, 8.0 us in 4).
-static int64_t plan_stream_splits(const adapshot_model_desc& d, int64_t n_cu, int64_t units, int64_t key_tiles, int32_t row_blocks) {
-    const int64_t pv = 4 * 32 * std::max(1, d.head_dim / 16);
-    const int64_t qk = d.dtype == ADAPSHOT_BF16 ? std::max(1, d.head_dim / 32) * 16 : d.head_dim / 4 * 32;
-    const double step_us = (double)(row_blocks * (pv + qk) + 450) / 2100.0;
-    const int64_t n_max = std::min<int64_t>(key_tiles, kStreamMaxSplits);
-    int64_t best = 1, last = 0;
+// 16-row blocks per workgroup of the streaming kernel.  Two share the loads of K and V, but leave half the workgroups: fp32
+// models want two workgroups per compute unit with one block each before that pays, bf16 models, whose products cost
+// less, half a workgroup and a context of some length (64 query tokens of 32/8 heads, one block / two: 6.4k slots
+// 43.6 / 38.3 us, 2.3k 27.8 / 27.6, 742 20.0 / 22.6; 32 tokens, 6.4k slots 34.0 / 34.1).
+static int32_t stream_row_blocks(const adapshot_model_desc& d, int64_t n_cu, int64_t rows, int64_t key_tiles) {
+    if (d.head_dim != 64) return 1;
+    const int64_t blocks = d.n_kv_heads * ((rows + 15) / 16);
+    return blocks >= 2 * n_cu || (d.dtype == ADAPSHOT_BF16 && 2 * blocks >= n_cu && key_tiles >= 32) ? 2 : 1;
+}
+
+// Split length (in 64-key tiles) of a launch of the streaming kernel: the longest context in n equal splits, the others in
+// splits of the same length, n the count whose price is lowest.  A tile keeps each of a compute unit's four matrix cores
+// busy for a 16-key step (bf16: half a 32-key step) of matrix instructions, softmax and load latency; a decode step is
+// bound by loads, 0.8 us per tile and workgroup, 6.2 TB/s in all.  Splitting costs the merge: 2.2 us and a little per partial
+// (fp32, head_dim 128, one query over 2300 slots: 55 us in one split, 11.8 us in 36; a decode step over 16k slots: 33.6 us in
+// 8 splits, 19.5 in 32, 19.0 in 48, 21.7 in 64).
+struct StreamShape {
+    int64_t units, key_tiles;
+};
+static int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_cu, const StreamShape* shapes, int32_t n_shapes,
+                                       int32_t row_blocks) {
+    int64_t longest = 0, unit_tiles = 0;
+    for (int32_t i = 0; i < n_shapes; ++i) {
+        longest = std::max(longest, shapes[i].key_tiles);
+        unit_tiles += shapes[i].units * shapes[i].key_tiles;
+    }
+    if (longest == 0) return 1;
+    const bool bf = d.dtype == ADAPSHOT_BF16;
+    const int64_t blocks = std::max(1, d.head_dim / 16);
+    const int64_t pv = bf ? 3 * blocks * 8 : 4 * 32 * blocks;
+    const int64_t qk = bf ? std::max(1, d.head_dim / 32) * 16 : d.head_dim / 4 * 32;
+    const double tile_us = bf && d.head_dim == 128 ? 0.8 : (double)(row_blocks * (pv + qk) + 250) / 2100.0;
+    const double bytes_us = bf && d.head_dim == 128 ? (double)unit_tiles * 32768.0 / 6.2e6 : 0.0;
+    const int64_t n_max = std::min<int64_t>(longest, kStreamMaxSplits);
+    int64_t best = longest, last = 0;
     double best_t = 1e300;
     for (int64_t n = 1; n <= n_max; ++n) {
-        const int64_t st = (key_tiles + n - 1) / n;
+        const int64_t st = (longest + n - 1) / n;
         if (st == last) continue;  // no shorter splits than with one fewer
         last = st;
-        const int64_t rounds = (units * n + n_cu - 1) / n_cu;
-        const double t = (double)(rounds * st) * step_us + (n > 1 ? 2.2 + 0.03 * (double)n : 0.0);
+        int64_t wgs = 0;
+        for (int32_t i = 0; i < n_shapes; ++i) wgs += shapes[i].units * std::max<int64_t>(1, (shapes[i].key_tiles + st - 1) / st);
+        const int64_t rounds = (wgs + n_cu - 1) / n_cu;
+        const double t = std::max((double)(rounds * st) * tile_us, bytes_us) + (n > 1 ? 2.2 + 0.03 * (double)n : 0.0);
         if (t < best_t) {
             best_t = t;
-            best = n;
+            best = st;
         }
     }
     return best;
@@ -626,17 +657,20 @@ static int64_t plan_stream_splits(const adapshot_model_desc& d, int64_t n_cu, in
 // split is a multiple of the 64-key tile; an empty context has no split.
 static void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t force_splits, int32_t t_q, int64_t n_ctx,
                              int64_t* n_split_out, int64_t* keys_per_split_out) {
-    const bool mfma = attn_mfma_supported(d);
     const int64_t rows = (int64_t)t_q * (d.n_q_heads / d.n_kv_heads);
-    const int64_t row_tile = mfma ? kAttnRowTile : 16 * stream_row_blocks(d, n_cu, rows);
-    const int64_t units = d.n_kv_heads * ((rows + row_tile - 1) / row_tile);
+    const bool mfma = attn_tile_kernel(d, rows, n_ctx);
     const int64_t key_tiles = (n_ctx + 63) / 64;
+    const int32_t row_blocks = stream_row_blocks(d, n_cu, rows, key_tiles);
+    const int64_t row_tile = mfma ? kAttnRowTile : 16 * row_blocks;
+    const int64_t units = d.n_kv_heads * ((rows + row_tile - 1) / row_tile);
     int64_t n_split = 0, keys_per_split = 64;
     if (key_tiles > 0) {
         if (mfma) {
             n_split = plan_mfma_splits(n_cu, units, key_tiles, ((int64_t)t_q + 63) / 64);
         } else {
-            n_split = plan_stream_splits(d, n_cu, units, key_tiles, stream_row_blocks(d, n_cu, rows));
+            const StreamShape sh{units, key_tiles};
+            const int64_t st = plan_stream_split_tiles(d, n_cu, &sh, 1, row_blocks);
+            n_split = (key_tiles + st - 1) / st;
         }
         if (force_splits > 0) n_split = std::min<int64_t>(force_splits, key_tiles);
         keys_per_split = ((key_tiles + n_split - 1) / n_split) * 64;
@@ -674,19 +708,26 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
         tiles = std::max<int64_t>(tiles, ((int64_t)items[i].n_ctx + 63) / 64);
     }
     StreamLaunch sl;
-    sl.row_blocks = stream_row_blocks(d, ctx->n_cu, rows);
+    sl.row_blocks = stream_row_blocks(d, ctx->n_cu, rows, tiles);
     const int64_t tr = 16 * sl.row_blocks;
     int64_t units = 0;
     for (int32_t i = 0; i < n_items; ++i) units += d.n_kv_heads * (((int64_t)items[i].t_q * g + tr - 1) / tr);
-    int64_t n_split = 1;
-    if (tiles > 0) n_split = plan_stream_splits(d, ctx->n_cu, units, tiles, sl.row_blocks);
-    if (ctx->force_splits > 0) n_split = std::min<int64_t>(ctx->force_splits, std::max<int64_t>(1, tiles));
-    if (units > kStreamUnits) n_split = 1;  // more units than arrival counters: the chip is full without splits
+    int64_t st = std::max<int64_t>(1, tiles);
+    if (ctx->force_splits > 0) {
+        st = std::max<int64_t>(1, (tiles + ctx->force_splits - 1) / ctx->force_splits);
+    } else if (units <= kStreamUnits) {  // more units than arrival counters: the chip is full without splits
+        StreamShape shapes[kStreamItems];
+        for (int32_t i = 0; i < n_items; ++i)
+            shapes[i] = StreamShape{d.n_kv_heads * (((int64_t)items[i].t_q * g + tr - 1) / tr), ((int64_t)items[i].n_ctx + 63) / 64};
+        st = plan_stream_split_tiles(d, ctx->n_cu, shapes, n_items, sl.row_blocks);
+    }
+    if (units > kStreamUnits) st = std::max<int64_t>(1, tiles);
+    st = std::max<int64_t>(st, (tiles + kStreamMaxSplits - 1) / kStreamMaxSplits);
+    const int64_t n_split = tiles > 0 ? (tiles + st - 1) / st : 1;
     int64_t unit0 = 0, grid_x = 0;
     for (int32_t i = 0; i < n_items; ++i) {
         StreamItem& it = items[i];
-        const int64_t kt = ((int64_t)it.n_ctx + 63) / 64;
-        it.keys_per_split = (int32_t)std::max<int64_t>(64, (kt + n_split - 1) / n_split * 64);
+        it.keys_per_split = (int32_t)(st * 64);
         it.n_split = (int32_t)std::max<int64_t>(1, ((int64_t)it.n_ctx + it.keys_per_split - 1) / it.keys_per_split);
         const int64_t here = d.n_kv_heads * (((int64_t)it.t_q * g + tr - 1) / tr);
         it.unit0 = (int32_t)unit0;
@@ -743,7 +784,7 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
                                          int64_t q_pos0, void* out, const int32_t* slot_src, const float2* tile_rot,
                                          hipStream_t stream, int64_t ctx_pos0) {
     const adapshot_model_desc& d = ctx->desc;
-    if (!attn_mfma_supported(d)) {
+    if (!attn_tile_kernel(d, (int64_t)t_q * (d.n_q_heads / d.n_kv_heads), n_ctx) && !(slot_src && attn_mfma_supported(d))) {
         StreamItem it = stream_item(k_ctx, v_ctx, n_ctx, q, k_self, v_self, t_q, q_pos0, out);
         return run_stream(ctx, &it, 1, slot_src, ctx_pos0, stream);
     }
@@ -1353,6 +1394,22 @@ extern "C" adapshot_status adapshot_query_attn_pool_batched(adapshot_ctx* ctx, i
     return st;
 }
 
+// Batches that the streaming kernel takes from the tile kernel (attn_tile_kernel): every context is read by one item --
+// items that share one find its tiles in the L2 when the tile kernel orders them by cache and split.
+static bool streams_batch(const adapshot_ctx* ctx, const adapshot_attn_item* items, int32_t n_items) {
+    const int32_t g = ctx->desc.n_q_heads / ctx->desc.n_kv_heads;
+    std::vector<int32_t> seen;
+    seen.reserve((size_t)n_items);
+    int64_t tokens = 0;
+    for (int32_t i = 0; i < n_items; ++i) {
+        tokens += items[i].n_ctx;
+        if (attn_tile_kernel(ctx->desc, (int64_t)items[i].t_q * g, tokens)) return false;
+        if (items[i].n_ctx > 0) seen.push_back(items[i].cache_index);
+    }
+    std::sort(seen.begin(), seen.end());
+    return std::adjacent_find(seen.begin(), seen.end()) == seen.end();
+}
+
 extern "C" adapshot_status adapshot_query_attn_batched(adapshot_ctx* ctx, const adapshot_cache* caches,
                                                        int32_t n_caches, int32_t layer,
                                                        const adapshot_attn_item* items, int32_t n_items,
@@ -1372,7 +1429,7 @@ extern "C" adapshot_status adapshot_query_attn_batched(adapshot_ctx* ctx, const 
         }
     }
     adapshot_status st = ADAPSHOT_OK;
-    if (n_items > 0 && attn_mfma_supported(ctx->desc)) {
+    if (n_items > 0 && attn_mfma_supported(ctx->desc) && !streams_batch(ctx, items, n_items)) {
         st = run_query_attn_batch(ctx, caches, layer, items, n_items, (hipStream_t)hip_stream);
     } else {
         for (int32_t i0 = 0; i0 < n_items && st == ADAPSHOT_OK; i0 += kStreamItems) {

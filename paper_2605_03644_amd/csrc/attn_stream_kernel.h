@@ -1,37 +1,41 @@
-// Query-over-cache attention straight from registers: the kernel for every shape that the 256-row tile kernel
-// (attn_mfma.hip) does not cover -- fp32 models, head dimensions other than 128.
+// Query-over-cache attention straight from registers: the kernel for the shapes that the 256-row tile kernel
+// (attn_mfma.hip) does not cover -- fp32 models, head dimensions other than 128 -- and for its decode steps, whose
+// query rows (at most 16 per KV head) would leave seven of that kernel's eight wavefronts idle.
 //
 // A workgroup of 8 wavefronts owns 16 * NR query rows of one KV head (rows j*g + h%g, as everywhere) and one split of
-// the context; the last split also takes the query's own tokens (causal).  The keys go to the wavefronts 16 at a
-// time, round robin, and every wavefront runs a flash-attention state of its own over its keys: no LDS, no barrier and
-// no other wavefront in the key loop.  K and V rows are loaded from global memory in exactly the lanes where the
-// matrix instructions want them, so the loop is loads, matrix instructions and a 4-value softmax:
+// the context; the last split also takes the query's own tokens (causal).  The keys go to the wavefronts in steps of 16
+// (bf16 models: 32), round robin, and every wavefront runs a flash-attention state of its own over its keys: no LDS, no
+// barrier and no other wavefront in the key loop.  K and V rows are loaded from global memory in exactly the lanes where
+// the matrix instructions want them, so the loop is loads, matrix instructions and a softmax of 4 or 8 values:
 //
 //   S^T = K . Q^T   A = K: lane (key l%16, group l/16) holds KW consecutive columns 4*KW*j + KW*(l/16) of its key for
 //                   every j (16 bytes), B = Q in the same lanes and columns: bf16 models v_mfma_f32_16x16x32_bf16 on the
 //                   stored operands, fp32 models v_mfma_f32_16x16x4_f32.  The result leaves lane l with query row l%16
-//                   and keys 4*(l/16) .. +3.
-//   O^T += V^T.P^T  v_mfma_f32_16x16x4_f32 whatever the storage type: register r of S^T is the B operand of the k-slots
-//                   4*(l/16)+r as it stands (P is never rounded to 16 bits), and A wants V[key 4*(l/16)+r] in 16 lanes
-//                   of consecutive columns, which is a row-wise load: a lane takes VW consecutive columns (16 bytes of
-//                   a 128-wide row) and the 16 columns of MFMA block (dg, c) are 16*VW*dg + VW*i + c.  The fp32 rate is
-//                   a sixteenth of the bf16 one, but nothing has to be transposed through LDS, and these problems are
-//                   bound by latency and loads.
+//                   and keys 4*(l/16) .. +3 of every 16.
+//   O^T += V^T.P^T  A lane loads the V rows of just those keys, VW consecutive columns each (a row-wise load of 16 lanes);
+//                   the 16 columns of MFMA block (dg, c) are 16*VW*dg + VW*i + c.  fp32 models: v_mfma_f32_16x16x4_f32,
+//                   register r of S^T as it stands.  bf16 models: v_mfma_f32_16x16x32_bf16, column c of a lane's 8 rows
+//                   picked together by byte permutes, and P in three bf16 pieces -- the upper 8 of its 24 bits, the
+//                   next 8, the last 8, exactly -- so that P is not rounded: three instructions of 16 cycles for 32 keys
+//                   where the fp32 product took eight of 32.  Head dimension 128 rounds P to one bf16, as the tile kernel
+//                   that computes the larger problems of those models does.
 //
 // The wavefronts' states meet in LDS once, at the end.  With one split the workgroup writes the output rows itself:
-// rotation, attention and merge are then one launch (the former scalar kernel: rope_rows, attention, combine).  With
-// more, each workgroup leaves its merged rows (fp32) and (m, l) in a workspace, and the workgroup that arrives last at
-// the unit's counter merges them: partials are written and read with device-scope accesses that bypass the L2 of the
-// workgroup's XCD, so no cache has to be written back or invalidated, and the counter is back at zero afterwards.  The
-// merge runs in split order whatever the order of arrival: the same inputs give the same bits.
+// rotation, attention and merge are then one launch.  With more, each workgroup leaves its merged rows (fp32) and (m, l)
+// in a workspace, and the workgroup that arrives last at the unit's counter merges them: partials are written and read
+// with device-scope accesses that bypass the L2 of the workgroup's XCD, so no cache has to be written back or invalidated,
+// and the counter is back at zero afterwards.  The merge runs in split order whatever the order of arrival: the same
+// inputs give the same bits.
 //
-// What bounds it: a small problem, the launch and two round trips to memory (64 slots: 6 us, 6.7 us with 256 slots of a
-// bf16 model); a large one, its steps, 1100 cycles each at two wavefronts per SIMD (bf16, head_dim 64: 544 of them
-// fp32 MFMAs of the second product, the rest the softmax and the serial order inside the wavefront).  One layer of a
-// query, rope_rows + attention + combine of the scalar kernel before it -> this launch:
-//   bf16, 32/8 heads x 64, 64 query tokens over 6.6k slots    1476 -> 37 us
-//   fp32, 8/2 heads x 128, 32 query tokens over 2.3k slots     167 -> 19 us
-//   fp32, 4/2 heads x 64, 16 query tokens over 248 slots        23 -> 8.5 us
+// What bounds it: a small problem, the launch and three round trips to memory (keys and query rows, arrival, partials);
+// a larger one, what a compute unit gets from beyond its L1, 45 to 48 GB/s whatever is in flight (64 or 128 KB), which is
+// why the loads are shared by two row blocks where there are rows enough.  A decode step of one query over 16k slots (4 KV
+// heads, 42 splits) spends 7 us on its keys and values, 1.5 on the wavefronts meeting, 1.5 on the arrival and 5.5 on
+// 150 KB of partials per KV head (more of them in flight, or cached loads behind an acquire, change nothing).  One layer:
+//   bf16, 32/8 heads x 64, 64 query tokens over 6.6k slots     fp32 second product 37 us -> 24 us
+//   bf16, 28/4 heads x 128, decode step over 16k slots          table copy + tile kernel + combine 29.6 us -> 19 us
+//   fp32, 8/2 heads x 128, 32 query tokens over 2.3k slots      19 us
+//   fp32, 4/2 heads x 64, 16 query tokens over 248 slots        8.9 us
 #pragma once
 #include <type_traits>
 
@@ -65,6 +69,7 @@ template <int DTYPE, int D, int NR, bool POOL, int NI>
 __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamArgs<NI> p) {
     constexpr int W = kStreamWaves, T = W * 64;
     constexpr bool BF = DTYPE == ADAPSHOT_BF16;
+    constexpr bool NT = BF && D == 128;  // decode steps: the context is read by one workgroup per KV head, once
     constexpr int E = BF ? 2 : 4;
     constexpr int KW = D * E >= 64 ? 16 / E : D / 4;  // consecutive columns of a lane
     constexpr int NJ = D / (4 * KW);
@@ -74,11 +79,15 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     constexpr int VW = DB < VMAX ? DB : VMAX;         // consecutive V columns of a lane
     constexpr int DG = DB / VW;
     constexpr int VR = VW * E >= 4 ? VW * E / 4 : 1;  // registers of one V piece
+    constexpr int NK = BF && D <= 128 ? 2 : 1;        // 16-key blocks of a step
+    constexpr int SK = 16 * NK;                       // keys of a step
+    constexpr int NV = 4 * NK;                        // V rows of a lane
+    constexpr int NP = BF ? (D == 128 ? 1 : 3) : 0;   // bf16 pieces of a softmax weight (fp32 models: as it is)
     constexpr int STEP_REGS = NJ * KR + 4 * DG * VR;
     // The next step's K and V are loaded while this one is computed (two steps ahead is no faster and costs 16 to 32
     // registers); a step of 256 bytes per lane leaves room for its K alone, V is then loaded under the first product.
     constexpr int NB = 2;
-    constexpr int NBV = STEP_REGS > 32 ? 1 : 2;
+    constexpr int NBV = STEP_REGS > (BF ? 48 : 32) ? 1 : 2;
     constexpr int TR = 16 * NR;
     constexpr int NS = NR * DB;  // 1 KB pieces of a wavefront's output state
     static_assert(D == 8 || D % 16 == 0, "head dimensions");
@@ -111,8 +120,8 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     if (nk < 0) nk = 0;
     const int j_last = ((row0 + TR < rows ? row0 + TR : rows) - 1) / g;
     const int n_self = last_split ? j_last + 1 : 0;  // own tokens that any row of the tile sees
-    const int n_cs = (nk + 15) >> 4;
-    const int n_steps = n_cs + ((n_self + 15) >> 4);
+    const int n_cs = (nk + SK - 1) / SK;
+    const int n_steps = n_cs + (n_self + SK - 1) / SK;
 
     const char* const kself = it.k_self + (int64_t)hk * D * E;
     const char* const vself = it.v_self + (int64_t)hk * D * E;
@@ -121,7 +130,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
 
     // ---- loads of step s.  Steps past the end read one row again (all lanes the same bytes).
     // Zero-copy form: pool tokens of the rows of the next step to load, fetched one step before the rows
-    int tok_k = 0, tok_v[4] = {0, 0, 0, 0};
+    int tok_k[NK] = {}, tok_v[NV] = {};
     auto pool_tok = [&](int u) __attribute__((always_inline)) -> int {
         u = u < nk ? u : nk - 1;
         u = u > 0 ? u : 0;
@@ -129,9 +138,10 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     };
     auto fetch_tok = [&](int s) __attribute__((always_inline)) {
         if (POOL && nk > 0) {
-            tok_k = pool_tok(16 * s + l16);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) tok_v[r] = pool_tok(16 * s + 4 * kg + r);
+            for (int b = 0; b < NK; ++b) tok_k[b] = pool_tok(SK * s + 16 * b + l16);
+#pragma unroll
+            for (int r = 0; r < NV; ++r) tok_v[r] = pool_tok(SK * s + 16 * (r >> 2) + 4 * kg + (r & 3));
         }
     };
     typedef typename std::conditional<POOL, uint64_t, unsigned>::type off_t;  // the rows of a context span at most 4 GiB, a pool may not
@@ -144,36 +154,43 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         }
         return on ? (off_t)r * (off_t)stride : (off_t)0;
     };
-    auto load_k = [&](int s, unsigned (&dst)[NJ][KR]) __attribute__((always_inline)) {
+    // A context that one workgroup per KV head reads once is not kept in the caches (NT).
+    auto ld4 = [&](const char* q, bool self) __attribute__((always_inline)) -> u32x4 {
+        return NT && !self ? __builtin_nontemporal_load((const u32x4*)q) : *(const u32x4*)q;
+    };
+    auto load_k = [&](int s, unsigned (&dst)[NK][NJ][KR]) __attribute__((always_inline)) {
         const bool on = s < n_steps, self = s >= n_cs;
         const char* base = self ? kself : kctx;
-        const int u = 16 * (self ? s - n_cs : s) + l16;
-        const char* src = base + row_off(self, on, u, self ? n_self : nk, tok_k);
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            if (KR == 4) {
-                const u32x4 x = *(const u32x4*)(src + 64 * j + 16 * kg);
+        for (int b = 0; b < NK; ++b) {
+            const int u = SK * (self ? s - n_cs : s) + 16 * b + l16;
+            const char* src = base + row_off(self, on, u, self ? n_self : nk, tok_k[b]);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) dst[j][i % KR] = x[i];
-            } else {
-                const uint2 x = *(const uint2*)(src + 8 * kg);
-                dst[j][0] = x.x;
-                dst[j][1 % KR] = x.y;
+            for (int j = 0; j < NJ; ++j) {
+                if (KR == 4) {
+                    const u32x4 x = ld4(src + 64 * j + 16 * kg, self);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) dst[b][j][i % KR] = x[i];
+                } else {
+                    const uint2 x = *(const uint2*)(src + 8 * kg);
+                    dst[b][j][0] = x.x;
+                    dst[b][j][1 % KR] = x.y;
+                }
             }
         }
     };
-    auto load_v = [&](int s, unsigned (&dst)[4][DG][VR]) __attribute__((always_inline)) {
+    auto load_v = [&](int s, unsigned (&dst)[NV][DG][VR]) __attribute__((always_inline)) {
         const bool on = s < n_steps, self = s >= n_cs;
         const char* base = self ? vself : vctx;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int u = 16 * (self ? s - n_cs : s) + 4 * kg + r;
+        for (int r = 0; r < NV; ++r) {
+            const int u = SK * (self ? s - n_cs : s) + 16 * (r >> 2) + 4 * kg + (r & 3);
             const char* src = base + row_off(self, on, u, self ? n_self : nk, tok_v[r]);
 #pragma unroll
             for (int dg = 0; dg < DG; ++dg) {
                 const char* q = src + (16 * VW * dg + VW * l16) * E;
                 if (VR == 4) {
-                    const u32x4 x = *(const u32x4*)q;
+                    const u32x4 x = ld4(q, self);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) dst[r][dg][i % VR] = x[i];
                 } else if (VR == 2) {
@@ -188,10 +205,10 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
             }
         }
     };
-    auto v_elem = [&](const unsigned (&w)[VR], int c) __attribute__((always_inline)) -> float {
-        if (!BF) return __uint_as_float(w[c % VR]);
-        if (VW == 1) return __uint_as_float(w[0]);
-        return (c & 1) ? __uint_as_float(w[(c >> 1) % VR] & 0xffff0000u) : __uint_as_float(w[(c >> 1) % VR] << 16);
+    // bf16: column c of two V rows in one register, the first in the low half
+    auto v_pair = [&](const unsigned (&x)[VR], const unsigned (&y)[VR], int c) __attribute__((always_inline)) -> unsigned {
+        const unsigned a = x[(c >> 1) % VR], b = y[(c >> 1) % VR];
+        return __builtin_amdgcn_perm(b, a, (c & 1) || VW == 1 ? 0x07060302u : 0x05040100u);
     };
 
     // ---- rotation of a lane's pieces of a row to position a (Eq. rope_encoding), scaled; bf16 results rounded to
@@ -237,8 +254,8 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     };
 
     // ---- the first steps are requested before the query rows are rotated
-    unsigned kf[NB][NJ][KR];
-    unsigned vf[NBV][4][DG][VR];
+    unsigned kf[NB][NK][NJ][KR];
+    unsigned vf[NBV][NV][DG][VR];
     fetch_tok(wave);
 #pragma unroll
     for (int b = 0; b < NB - 1; ++b) {
@@ -283,50 +300,57 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         for (int b = 0; b < DB; ++b) o[nr][b] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    auto compute = [&](int s, unsigned (&k)[NJ][KR], unsigned (&v)[4][DG][VR]) __attribute__((always_inline)) {
+    auto compute = [&](int s, unsigned (&k)[NK][NJ][KR], unsigned (&v)[NV][DG][VR]) __attribute__((always_inline)) {
         const bool self = s >= n_cs;  // wavefront-uniform
-        if (self) rotate(k, (int64_t)it.q_pos0 + 16 * (s - n_cs) + l16, 1.0f);
-        else if (POOL) rotate(k, p.ctx_pos0 + k0 + 16 * s + l16, 1.0f);
-        f32x4 sc[NR];
+        f32x4 sc[NK][NR];
 #pragma unroll
-        for (int nr = 0; nr < NR; ++nr) sc[nr] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int kb = 0; kb < NK; ++kb) {
+            if (self) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16, 1.0f);
+            else if (POOL) rotate(k[kb], p.ctx_pos0 + k0 + SK * s + 16 * kb + l16, 1.0f);
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            if (BF && KR == 4) {
-                const u32x4 a = {k[j][0], k[j][1 % KR], k[j][2 % KR], k[j][3 % KR]};
+            for (int nr = 0; nr < NR; ++nr) sc[kb][nr] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int nr = 0; nr < NR; ++nr) {
-                    const u32x4 b = {qf[nr][j][0], qf[nr][j][1 % KR], qf[nr][j][2 % KR], qf[nr][j][3 % KR]};
-                    sc[nr] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                                     __builtin_bit_cast(bf16x8, b), sc[nr], 0, 0, 0);
+            for (int j = 0; j < NJ; ++j) {
+                if (BF && KR == 4) {
+                    const u32x4 a = {k[kb][j][0], k[kb][j][1 % KR], k[kb][j][2 % KR], k[kb][j][3 % KR]};
+#pragma unroll
+                    for (int nr = 0; nr < NR; ++nr) {
+                        const u32x4 b = {qf[nr][j][0], qf[nr][j][1 % KR], qf[nr][j][2 % KR], qf[nr][j][3 % KR]};
+                        sc[kb][nr] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                                             __builtin_bit_cast(bf16x8, b), sc[kb][nr], 0, 0, 0);
+                    }
+                } else if (BF) {
+                    const uint2 a = {k[kb][j][0], k[kb][j][1 % KR]};
+#pragma unroll
+                    for (int nr = 0; nr < NR; ++nr) {
+                        const uint2 b = {qf[nr][j][0], qf[nr][j][1 % KR]};
+                        sc[kb][nr] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a),
+                                                                               __builtin_bit_cast(s16x4, b), sc[kb][nr], 0, 0, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < KR; ++i)
+#pragma unroll
+                        for (int nr = 0; nr < NR; ++nr)
+                            sc[kb][nr] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k[kb][j][i]), __uint_as_float(qf[nr][j][i]),
+                                                                              sc[kb][nr], 0, 0, 0);
                 }
-            } else if (BF) {
-                const uint2 a = {k[j][0], k[j][1 % KR]};
-#pragma unroll
-                for (int nr = 0; nr < NR; ++nr) {
-                    const uint2 b = {qf[nr][j][0], qf[nr][j][1 % KR]};
-                    sc[nr] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a),
-                                                                       __builtin_bit_cast(s16x4, b), sc[nr], 0, 0, 0);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < KR; ++i)
-#pragma unroll
-                    for (int nr = 0; nr < NR; ++nr)
-                        sc[nr] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(k[j][i]), __uint_as_float(qf[nr][j][i]),
-                                                                      sc[nr], 0, 0, 0);
             }
         }
-        const int u = 16 * (self ? s - n_cs : s) + 4 * kg;
+        const int u = SK * (self ? s - n_cs : s) + 4 * kg;
 #pragma unroll
         for (int nr = 0; nr < NR; ++nr) {
-            if (self || 16 * s + 16 > nk) {
+            if (self || SK * s + SK > nk) {
                 const int lim = self ? jrow[nr] + 1 : nk;
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (u + r >= lim) sc[nr][r] = -INFINITY;
+                for (int kb = 0; kb < NK; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (u + 16 * kb + r >= lim) sc[kb][nr][r] = -INFINITY;
             }
-            float mx = fmaxf(fmaxf(sc[nr][0], sc[nr][1]), fmaxf(sc[nr][2], sc[nr][3]));
+            float mx = fmaxf(fmaxf(sc[0][nr][0], sc[0][nr][1]), fmaxf(sc[0][nr][2], sc[0][nr][3]));
+            if (NK == 2)
+                mx = fmaxf(mx, fmaxf(fmaxf(sc[NK - 1][nr][0], sc[NK - 1][nr][1]), fmaxf(sc[NK - 1][nr][2], sc[NK - 1][nr][3])));
             // the reference maximum of a row follows lazily: it moves when a score exceeds it by more than 2^8
             if (__builtin_amdgcn_ballot_w64(mx > m_run[nr] + 8.0f)) {
                 mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
@@ -342,20 +366,68 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
             }
             const float m_use = m_run[nr] == -INFINITY ? 0.f : m_run[nr];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) sc[nr][r] = __builtin_amdgcn_exp2f(sc[nr][r] - m_use);
-            l_run[nr] += (sc[nr][0] + sc[nr][1]) + (sc[nr][2] + sc[nr][3]);
-        }
+            for (int kb = 0; kb < NK; ++kb) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+                for (int r = 0; r < 4; ++r) sc[kb][nr][r] = __builtin_amdgcn_exp2f(sc[kb][nr][r] - m_use);
+                l_run[nr] += (sc[kb][nr][0] + sc[kb][nr][1]) + (sc[kb][nr][2] + sc[kb][nr][3]);
+            }
+        }
+        if constexpr (BF) {
+            // pb[nr][i]: piece i of the weights, slot 4*kb + r of a lane = key 16*kb + 4*kg + r, as V has them
+            unsigned pb[NR][NP][2 * NK];
+#pragma unroll
+            for (int nr = 0; nr < NR; ++nr)
+#pragma unroll
+                for (int w = 0; w < 2 * NK; ++w) {
+                    float x = sc[w >> 1][nr][2 * (w & 1)], y = sc[w >> 1][nr][2 * (w & 1) + 1];
+                    if (NP == 1) {
+                        pb[nr][0][w] = stream_pack(x, y);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < NP; ++i) {  // the upper 8 of the bits that are left, exactly
+                            pb[nr][i][w] = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
+                            x -= __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+                            y -= __uint_as_float(__float_as_uint(y) & 0xffff0000u);
+                        }
+                    }
+                }
 #pragma unroll
             for (int dg = 0; dg < DG; ++dg)
 #pragma unroll
                 for (int c = 0; c < VW; ++c) {
-                    const float a = v_elem(v[r][dg], c);
+                    unsigned a[2 * NK];
 #pragma unroll
-                    for (int nr = 0; nr < NR; ++nr)
-                        o[nr][dg * VW + c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, sc[nr][r], o[nr][dg * VW + c], 0, 0, 0);
+                    for (int w = 0; w < 2 * NK; ++w) a[w] = v_pair(v[2 * w][dg], v[2 * w + 1][dg], c);
+#pragma unroll
+                    for (int i = 0; i < NP; ++i)
+#pragma unroll
+                        for (int nr = 0; nr < NR; ++nr) {
+                            f32x4& acc = o[nr][dg * VW + c];
+                            if (NK == 2) {
+                                const u32x4 av = {a[0], a[1], a[2 % (2 * NK)], a[3 % (2 * NK)]};
+                                const u32x4 bv = {pb[nr][i][0], pb[nr][i][1], pb[nr][i][2 % (2 * NK)], pb[nr][i][3 % (2 * NK)]};
+                                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv),
+                                                                              acc, 0, 0, 0);
+                            } else {
+                                const uint2 av = {a[0], a[1]}, bv = {pb[nr][i][0], pb[nr][i][1]};
+                                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, av), __builtin_bit_cast(s16x4, bv),
+                                                                                acc, 0, 0, 0);
+                            }
+                        }
                 }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int dg = 0; dg < DG; ++dg)
+#pragma unroll
+                    for (int c = 0; c < VW; ++c) {
+                        const float a = __uint_as_float(v[r][dg][c % VR]);
+#pragma unroll
+                        for (int nr = 0; nr < NR; ++nr)
+                            o[nr][dg * VW + c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, sc[0][nr][r], o[nr][dg * VW + c], 0, 0, 0);
+                    }
+        }
     };
 
     for (int s0 = wave; s0 < n_steps; s0 += NB * W) {
@@ -577,8 +649,10 @@ static hipError_t launch_stream_form(const StreamLaunch& s, hipStream_t stream) 
     if (s.n_items == 1) {
         StreamArgs<1> a;
         fill(a);
-        if (s.slot_src) launch_kernel((attn_stream_kernel<DTYPE, D, NR, true, 1>), grid, block, stream, a);
-        else launch_kernel((attn_stream_kernel<DTYPE, D, NR, false, 1>), grid, block, stream, a);
+        if (s.slot_src) {
+            if constexpr (DTYPE == ADAPSHOT_BF16 && D == 128) return hipErrorInvalidValue;  // the tile kernel's zero-copy form
+            else launch_kernel((attn_stream_kernel<DTYPE, D, NR, true, 1>), grid, block, stream, a);
+        } else launch_kernel((attn_stream_kernel<DTYPE, D, NR, false, 1>), grid, block, stream, a);
     } else {
         if (s.slot_src) return hipErrorInvalidValue;
         StreamArgs<kStreamItems> a;
