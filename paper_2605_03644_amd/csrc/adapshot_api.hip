@@ -747,6 +747,7 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
     sl.tab_lo = ctx->tab_lo;
     sl.tab_hi = ctx->tab_hi;
     sl.counters = ctx->stream_counters;
+    sl.counter_stride = counter_stride(units);
     sl.slot_src = slot_src;
     sl.ctx_pos0 = ctx_pos0;
     sl.n_q_heads = d.n_q_heads;
@@ -1464,6 +1465,8 @@ static adapshot_status plan_probe_entropy(adapshot_ctx* ctx, const float* logits
     p.logits = logits;
     p.out = const_cast<float*>(entropy_out);
     p.partials = nullptr;
+    p.counters = nullptr;
+    p.counter_stride = 1;
     p.row_stride = row_stride;
     p.n_rows = n_rows;
     p.vocab = vocab;
@@ -1490,20 +1493,19 @@ static adapshot_status run_probe_entropy(adapshot_ctx* ctx, const float* logits,
         return ADAPSHOT_OK;
     }
     hipStream_t stream = (hipStream_t)hip_stream;
-    if (n_rows >= ctx->entropy_rows_min && vocab >= 16384) {  // enough rows of at least one full step for one workgroup each: one launch, no partials
-        hipError_t e1 = timed_launch(ctx, ADAPSHOT_KERNEL_ENTROPY_CHUNK, stream, [&] { return launch_entropy_rows(p, answer, stream); });
-        if (e1 != hipSuccess) return fail_hip(ctx, "probe_entropy: launch", e1);
-        ctx->last_error.clear();
-        return ADAPSHOT_OK;
+    // Enough rows of at least one full step for one workgroup each: no partials.  (Also where there are more rows than
+    // arrival counters and a row has several chunks.)
+    hipError_t e = hipSuccess;
+    if ((n_rows >= ctx->entropy_rows_min && vocab >= 16384) || (n_rows > kStreamUnits && p.n_chunks > 1)) {
+        e = timed_launch(ctx, ADAPSHOT_KERNEL_ENTROPY_CHUNK, stream, [&] { return launch_entropy_rows(p, answer, stream); });
+    } else {
+        e = ctx->ent_part.reserve((size_t)n_rows * p.n_chunks * 3 * sizeof(float), ctx->retired);
+        if (e != hipSuccess) return fail_hip(ctx, "probe_entropy: workspace", e);
+        p.partials = (float*)ctx->ent_part.p;
+        p.counters = ctx->stream_counters;
+        p.counter_stride = counter_stride(n_rows);
+        e = timed_launch(ctx, ADAPSHOT_KERNEL_ENTROPY_CHUNK, stream, [&] { return launch_entropy_fused(p, answer, stream); });
     }
-    hipError_t e = ctx->ent_part.reserve((size_t)n_rows * p.n_chunks * 3 * sizeof(float), ctx->retired);
-    if (e != hipSuccess) return fail_hip(ctx, "probe_entropy: workspace", e);
-    p.partials = (float*)ctx->ent_part.p;
-    e = timed_launch(ctx, ADAPSHOT_KERNEL_ENTROPY_CHUNK, stream, [&] { return launch_entropy_chunk(p, stream); });
-    if (e == hipSuccess)
-        e = timed_launch(ctx, ADAPSHOT_KERNEL_ENTROPY_FINISH, stream, [&] {
-            return answer ? launch_entropy_finish_tokens(p, *answer, stream) : launch_entropy_finish(p, stream);
-        });
     if (e != hipSuccess) return fail_hip(ctx, "probe_entropy: launch", e);
     ctx->last_error.clear();
     return ADAPSHOT_OK;
@@ -1516,8 +1518,8 @@ extern "C" adapshot_status adapshot_probe_entropy(adapshot_ctx* ctx, const float
     return run_probe_entropy(ctx, logits, row_stride, n_rows, vocab, nullptr, entropy_out, hip_stream);
 }
 
-// The same two kernels over the file-scope device array instead of a workspace of the context: no
-// allocation of any kind on this path (no hipMalloc, no event creation: the launches are not profiled).
+// Chunks and their merge as two kernels over the file-scope device array instead of a workspace and counters of the
+// context: no allocation of any kind on this path (no hipMalloc, no event creation: the launches are not profiled).
 extern "C" adapshot_status adapshot_probe_entropy_static(adapshot_ctx* ctx, const float* logits, int64_t row_stride,
                                                          int32_t n_rows, int32_t vocab, float* entropy_out,
                                                          void* hip_stream) {

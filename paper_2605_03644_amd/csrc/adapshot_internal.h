@@ -153,6 +153,12 @@ constexpr int kStreamWaves = 8;       // wavefronts per workgroup, each with key
 constexpr int kStreamItems = 32;      // attention problems per launch (their descriptions travel in the kernel arguments)
 constexpr int kStreamMaxSplits = 64;  // context splits per problem
 constexpr int kStreamUnits = 4096;    // (problem, row tile, kv head) units of a launch that is split: one arrival counter each
+// Distance of the arrival counters of n units (of an entropy call: rows), in counters: up to a 128-byte line each.  Atomics
+// on one line follow each other at about 14 ns whatever counter they name (16 rows x 126 arrivals in one line: 29 us, a line
+// for every row: 10 us).
+inline int32_t counter_stride(int64_t n) {
+    return (int32_t)(n >= kStreamUnits ? 1 : kStreamUnits / n < 32 ? kStreamUnits / n : 32);
+}
 struct StreamItem {
     const char* q;
     const char* k_self;
@@ -171,10 +177,10 @@ struct StreamArgs {
     const float2* tab_hi;
     float* part_o;       // [unit][max_split][16 NR rows][d] fp32, unnormalised (launches with splits)
     float* part_ml;      // [unit][max_split][16 NR rows] (m, l)
-    unsigned* counters;  // [unit], zero between launches
+    unsigned* counters;  // [unit * counter_stride], zero between launches
     const int32_t* slot_src;  // zero-copy form: context slot -> pool token (null: the context is an assembled cache)
     int64_t ctx_pos0;         // zero-copy form: position of context slot 0
-    int32_t n_q_heads, n_kv_heads, g, max_split, pool_tokens;
+    int32_t n_q_heads, n_kv_heads, g, max_split, pool_tokens, counter_stride;
     float q_scale;
     StreamItem it[NI];
 };
@@ -186,7 +192,7 @@ struct StreamLaunch {
     unsigned* counters;
     const int32_t* slot_src;
     int64_t ctx_pos0;
-    int32_t n_q_heads, n_kv_heads, head_dim, dtype, max_split, pool_tokens;
+    int32_t n_q_heads, n_kv_heads, head_dim, dtype, max_split, pool_tokens, counter_stride;
     int32_t row_blocks;  // 16-row blocks per workgroup: 1 or 2
     int32_t grid_x;      // workgroups of the largest problem
     int32_t n_items;
@@ -303,8 +309,9 @@ struct EntropyParams {
     const float* logits;
     float* out;
     float* partials;  // [n_rows][n_chunks][3] = (max, sum exp, sum (z-max) exp)
+    unsigned* counters;  // [n_rows * counter_stride], zero between launches (the one-launch form)
     int64_t row_stride;
-    int32_t n_rows, vocab, chunk, n_chunks;
+    int32_t n_rows, vocab, chunk, n_chunks, counter_stride;
 };
 // The file-scope device array behind adapshot_probe_entropy_static: room for this many (row, chunk) partials.
 constexpr int kStaticEntropyPartials = 65536;
@@ -319,7 +326,8 @@ struct AnswerTokens {
     int32_t mode;  // ADAPSHOT_ENTROPY_FULL_P / ADAPSHOT_ENTROPY_RENORMALISED
     int32_t id[kMaxAnswerTokens];
 };
-hipError_t launch_entropy_finish_tokens(const EntropyParams& p, const AnswerTokens& c, hipStream_t stream);
+// Chunks and their merge in one launch; c == nullptr: the vocabulary-wide entropy.
+hipError_t launch_entropy_fused(const EntropyParams& p, const AnswerTokens* c, hipStream_t stream);
 // Whole rows in one launch (one workgroup per row); c == nullptr: the vocabulary-wide entropy.
 hipError_t launch_entropy_rows(const EntropyParams& p, const AnswerTokens* c, hipStream_t stream);
 

@@ -534,9 +534,9 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's partials have reached memory
     __syncthreads();
     if (tid == 0) {
-        const unsigned before = __hip_atomic_fetch_add(p.counters + unit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned before = __hip_atomic_fetch_add(p.counters + unit * p.counter_stride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const bool mine = before == (unsigned)n_split - 1u;
-        if (mine) __hip_atomic_store(p.counters + unit, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (mine) __hip_atomic_store(p.counters + unit * p.counter_stride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         last_flag = mine ? 1 : 0;
     }
     __syncthreads();
@@ -641,6 +641,7 @@ static hipError_t launch_stream_form(const StreamLaunch& s, hipStream_t stream) 
         a.n_kv_heads = s.n_kv_heads;
         a.g = s.n_q_heads / s.n_kv_heads;
         a.max_split = s.max_split;
+        a.counter_stride = s.counter_stride;
         a.pool_tokens = s.pool_tokens;
         a.q_scale = s.q_scale;
         for (int i = 0; i < s.n_items; ++i) a.it[i] = s.items[i];

@@ -3,7 +3,7 @@
 // With m = max z, e_v = exp(z_v - m), s = sum e_v, t = sum (z_v - m) e_v:
 //     H = ln s - t / s.
 // One HBM pass: a workgroup reduces one chunk of one row to (m, s, t) with an online
-// rescale per 16-element batch; a second tiny kernel merges the chunks of a row.
+// rescale per 16-element batch; the workgroup that arrives last merges the chunks of its row.
 // Partials re-base as  s' = s * exp(m - M),  t' = (t + (m - M) * s) * exp(m - M).
 #include <mutex>
 
@@ -125,13 +125,11 @@ __device__ __forceinline__ void mst_add_batch(Mst& acc, const float (&z)[N]) {
     acc.t += t;
 }
 
-// grid = n_rows * n_chunks workgroups (chunk fastest), 256 threads.  VEC: rows are 16-byte aligned -> float4 loads.
+// (m, s, t) of one chunk of a row, by 256 threads; the result is thread 0's.  VEC: rows are 16-byte aligned -> float4 loads.
 template <bool VEC>
-__global__ __launch_bounds__(256) void entropy_chunk_kernel(EntropyParams p) {
+__device__ __forceinline__ Mst reduce_chunk(const EntropyParams& p, int row, int chunk) {
     __shared__ Mst red[4];
     const int tid = threadIdx.x;
-    const int row = blockIdx.x / p.n_chunks;
-    const int chunk = blockIdx.x - row * p.n_chunks;
     const float* z = p.logits + (int64_t)row * p.row_stride;
     const int c0 = chunk * p.chunk;
     const int c1 = min(c0 + p.chunk, p.vocab);
@@ -195,13 +193,100 @@ __global__ __launch_bounds__(256) void entropy_chunk_kernel(EntropyParams p) {
     acc = mst_wave_reduce(acc);
     if ((tid & 63) == 0) red[tid >> 6] = acc;
     __syncthreads();
-    if (tid == 0) {
-        Mst r = mst_merge(mst_merge(red[0], red[1]), mst_merge(red[2], red[3]));
+    return mst_merge(mst_merge(red[0], red[1]), mst_merge(red[2], red[3]));
+}
+
+// The entropy of a row from its (m, s, t), by one wavefront (all lanes hold r).  TOKENS: Eq. (entropy) as printed, summed over
+// the answer tokens C only; lane c < |C| holds token c.
+//   full-p reading:      H = -sum_c p_c ln p_c,  ln p_c = z_c - lse
+//   renormalised reading: the same with the log-sum-exp taken over C
+// A term with p_c = 0 contributes 0.
+template <bool TOKENS>
+__device__ __forceinline__ void finish_row(const EntropyParams& p, const AnswerTokens& c, int row, Mst r, int lane) {
+    if (!TOKENS) {
+        if (lane == 0) {
+            float h;
+            if (r.m == -INFINITY || r.m == INFINITY) h = NAN;  // no finite logit, or a +inf logit
+            else h = logf(r.s) - r.t / r.s;                   // NaN sums propagate
+            p.out[row] = h;
+        }
+        return;
+    }
+    const bool row_bad = r.m == -INFINITY || r.m == INFINITY || r.s != r.s;  // as in the full entropy
+    const float zc = lane < c.n ? p.logits[(int64_t)row * p.row_stride + c.id[lane]] : -INFINITY;
+    float lse;
+    if (c.mode == ADAPSHOT_ENTROPY_FULL_P) {
+        lse = r.m + logf(r.s);
+    } else {
+        float mc = zc;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mc = fmaxf(mc, __shfl_xor(mc, o, 64));
+        float sc = mc == -INFINITY ? 0.f : expf(zc - mc);  // lanes past |C| hold -inf: 0
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sc += __shfl_xor(sc, o, 64);
+        lse = mc + logf(sc);
+        if (mc == -INFINITY) lse = NAN;  // all of C at -inf
+    }
+    const float lp = zc - lse;
+    const float pc = expf(lp);
+    float h = (lane < c.n && pc > 0.f) ? -pc * lp : 0.f;
+    if (lse != lse) h = NAN;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) h += __shfl_xor(h, o, 64);
+    if (lane == 0) p.out[row] = row_bad ? NAN : h;
+}
+
+// grid = n_rows * n_chunks workgroups (chunk fastest), 256 threads.
+template <bool VEC>
+__global__ __launch_bounds__(256) void entropy_chunk_kernel(EntropyParams p) {
+    const int row = blockIdx.x / p.n_chunks;
+    const Mst r = reduce_chunk<VEC>(p, row, blockIdx.x - row * p.n_chunks);
+    if (threadIdx.x == 0) {
         float* o = p.partials + (int64_t)blockIdx.x * 3;
         o[0] = r.m;
         o[1] = r.s;
         o[2] = r.t;
     }
+}
+
+// The same, and the workgroup that arrives last at its row's counter merges the row's chunks (in chunk order, whatever the
+// order of arrival): one launch.  Partials go past the L2 of the workgroup's XCD and are waited for before the arrival, so
+// no cache is written back or invalidated; the counter is zero again afterwards.  What it has to avoid is counters that
+// share a line (counter_stride).  Call after call, this / chunks and merge in two launches (us): 16 rows of 1000 logits 8.4 /
+// 11.6, 1 row of 128256 8.2 / 11.5, 48 rows 9.0 / 11.1, 128 rows 14.7 / 15.3 (below 9 us the host's call is what is timed).
+template <bool VEC, bool TOKENS>
+__global__ __launch_bounds__(256) void entropy_fused_kernel(EntropyParams p, AnswerTokens c) {
+    __shared__ int last_flag;
+    const int tid = threadIdx.x;
+    const int row = blockIdx.x / p.n_chunks;
+    Mst r = reduce_chunk<VEC>(p, row, blockIdx.x - row * p.n_chunks);  // the same in every thread
+    if (p.n_chunks > 1) {
+        if (tid == 0) {
+            float* o = p.partials + (int64_t)blockIdx.x * 3;
+            __hip_atomic_store(o, r.m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(o + 1, r.s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(o + 2, r.t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the partial has reached memory
+            const unsigned before = __hip_atomic_fetch_add(p.counters + row * p.counter_stride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const bool mine = before == (unsigned)p.n_chunks - 1u;
+            if (mine) __hip_atomic_store(p.counters + row * p.counter_stride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last_flag = mine ? 1 : 0;
+        }
+        __syncthreads();
+        if (!last_flag) return;
+        if (tid >= 64) return;
+        r = Mst{-INFINITY, 0.f, 0.f};
+        for (int k = tid; k < p.n_chunks; k += 64) {
+            const float* o = p.partials + ((int64_t)row * p.n_chunks + k) * 3;
+            Mst b;
+            b.m = __hip_atomic_load(o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            b.s = __hip_atomic_load(o + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            b.t = __hip_atomic_load(o + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            r = mst_merge(r, b);
+        }
+        r = mst_wave_reduce(r);
+    }
+    if (tid < 64) finish_row<TOKENS>(p, c, row, r, tid);
 }
 
 // Whole rows in one launch: a workgroup of 1024 threads reduces one row and writes its entropy (or, with answer
@@ -278,38 +363,7 @@ __global__ __launch_bounds__(1024) void entropy_row_kernel(EntropyParams p, Answ
     Mst r = {-INFINITY, 0.f, 0.f};
     if (lane < 16) r = red[lane];
     r = mst_wave_reduce(r);
-    if (!TOKENS) {
-        if (lane == 0) {
-            float h;
-            if (r.m == -INFINITY || r.m == INFINITY) h = NAN;  // no finite logit, or a +inf logit
-            else h = logf(r.s) - r.t / r.s;                   // NaN sums propagate
-            p.out[row] = h;
-        }
-        return;
-    }
-    // Eq. (entropy) over the answer tokens, as in entropy_finish_tokens_kernel
-    const bool row_bad = r.m == -INFINITY || r.m == INFINITY || r.s != r.s;
-    const float zc = lane < c.n ? z[c.id[lane]] : -INFINITY;
-    float lse;
-    if (c.mode == ADAPSHOT_ENTROPY_FULL_P) {
-        lse = r.m + logf(r.s);
-    } else {
-        float mc = zc;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mc = fmaxf(mc, __shfl_xor(mc, o, 64));
-        float sc = mc == -INFINITY ? 0.f : expf(zc - mc);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sc += __shfl_xor(sc, o, 64);
-        lse = mc + logf(sc);
-        if (mc == -INFINITY) lse = NAN;
-    }
-    const float lp = zc - lse;
-    const float pc = expf(lp);
-    float h = (lane < c.n && pc > 0.f) ? -pc * lp : 0.f;
-    if (lse != lse) h = NAN;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) h += __shfl_xor(h, o, 64);
-    if (lane == 0) p.out[row] = row_bad ? NAN : h;
+    finish_row<TOKENS>(p, c, row, r, lane);
 }
 
 hipError_t launch_entropy_rows(const EntropyParams& p, const AnswerTokens* c, hipStream_t stream) {
@@ -326,31 +380,8 @@ hipError_t launch_entropy_rows(const EntropyParams& p, const AnswerTokens* c, hi
     return hipGetLastError();
 }
 
-// One wavefront per row merges its chunk partials and writes H.
+// One wavefront per row merges its chunk partials and writes H (the entry point that has no counters).
 __global__ __launch_bounds__(64) void entropy_finish_kernel(EntropyParams p) {
-    const int row = blockIdx.x;
-    const int lane = threadIdx.x;
-    Mst acc = {-INFINITY, 0.f, 0.f};
-    for (int c = lane; c < p.n_chunks; c += 64) {
-        const float* o = p.partials + ((int64_t)row * p.n_chunks + c) * 3;
-        Mst b = {o[0], o[1], o[2]};
-        acc = mst_merge(acc, b);
-    }
-    acc = mst_wave_reduce(acc);
-    if (lane == 0) {
-        float h;
-        if (acc.m == -INFINITY || acc.m == INFINITY) h = NAN;  // no finite logit, or a +inf logit
-        else h = logf(acc.s) - acc.t / acc.s;                 // NaN sums propagate
-        p.out[row] = h;
-    }
-}
-
-// Eq. (entropy) as printed, summed over the answer tokens C only.  One wavefront per row merges the
-// chunk partials into the vocabulary-wide log-sum-exp; lane c < |C| then holds token c.
-//   full-p reading:      H = -sum_c p_c ln p_c,  ln p_c = z_c - lse
-//   renormalised reading: the same with the log-sum-exp taken over C
-// A term with p_c = 0 contributes 0.
-__global__ __launch_bounds__(64) void entropy_finish_tokens_kernel(EntropyParams p, AnswerTokens c) {
     const int row = blockIdx.x;
     const int lane = threadIdx.x;
     Mst acc = {-INFINITY, 0.f, 0.f};
@@ -360,32 +391,21 @@ __global__ __launch_bounds__(64) void entropy_finish_tokens_kernel(EntropyParams
         acc = mst_merge(acc, b);
     }
     acc = mst_wave_reduce(acc);
-    const bool row_bad = acc.m == -INFINITY || acc.m == INFINITY || acc.s != acc.s;  // as in the full entropy
-    const float z = lane < c.n ? p.logits[(int64_t)row * p.row_stride + c.id[lane]] : -INFINITY;
-    float lse;
-    if (c.mode == ADAPSHOT_ENTROPY_FULL_P) {
-        lse = acc.m + logf(acc.s);
-    } else {
-        float mc = z;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mc = fmaxf(mc, __shfl_xor(mc, o, 64));
-        float sc = mc == -INFINITY ? 0.f : expf(z - mc);  // lanes past |C| hold -inf: 0
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sc += __shfl_xor(sc, o, 64);
-        lse = mc + logf(sc);  // all of C at -inf: -inf + (-inf) -> handled below
-        if (mc == -INFINITY) lse = NAN;
-    }
-    const float lp = z - lse;
-    const float pc = expf(lp);
-    float h = (lane < c.n && pc > 0.f) ? -pc * lp : 0.f;
-    if (lse != lse) h = NAN;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) h += __shfl_xor(h, o, 64);
-    if (lane == 0) p.out[row] = row_bad ? NAN : h;
+    finish_row<false>(p, AnswerTokens{}, row, acc, lane);
 }
 
-hipError_t launch_entropy_finish_tokens(const EntropyParams& p, const AnswerTokens& c, hipStream_t stream) {
-    launch_kernel(entropy_finish_tokens_kernel, dim3((unsigned)p.n_rows), dim3(64), stream, p, c);
+hipError_t launch_entropy_fused(const EntropyParams& p, const AnswerTokens* c, hipStream_t stream) {
+    if ((int64_t)p.n_chunks * p.n_rows > INT32_MAX) return hipErrorInvalidValue;  // the host checks this first
+    const bool vec = (((uintptr_t)p.logits & 15u) == 0) && (p.row_stride % 4 == 0);
+    const dim3 grid((unsigned)(p.n_chunks * p.n_rows)), block(256);
+    const AnswerTokens none{};
+    if (c) {
+        if (vec) launch_kernel((entropy_fused_kernel<true, true>), grid, block, stream, p, *c);
+        else launch_kernel((entropy_fused_kernel<false, true>), grid, block, stream, p, *c);
+    } else {
+        if (vec) launch_kernel((entropy_fused_kernel<true, false>), grid, block, stream, p, none);
+        else launch_kernel((entropy_fused_kernel<false, false>), grid, block, stream, p, none);
+    }
     return hipGetLastError();
 }
 
