@@ -6,7 +6,9 @@
 #include <string.h>
 
 #include <algorithm>
+#include <functional>
 #include <new>
+#include <numeric>
 
 #include "adapshot_internal.h"
 
@@ -897,6 +899,73 @@ static int64_t plan_batch_split_tiles(int64_t n_cu, const std::vector<BatchShape
     return best_st;
 }
 
+// The same for a batch that keeps the matrix cores busy (not a decode step): its items differ in length by design
+// (nested prefixes), and equal splits of the longest one fit the others badly.  Candidates are also the lengths that
+// give every compute unit k workgroups of equal work, with some slack for the remainders; each is dealt out the way the
+// hardware does it (longest first, to the compute unit that is free first) and priced as that finish time plus 0.13
+// tiles per workgroup.  That price is fitted to the two rounds of the probe sweep (8 queries; split length: time per
+// layer): prefixes of 128-512 shots 859: 1120 us, 430: 780, 375: 750, 193: 763, 94: 780, 61: 806; prefixes of 16-64 shots
+// 110: 170 us, 56: 124, 50: 128, 28: 137, 8: 190.  (The chip clocks lower the fewer compute units idle, so a better
+// balance gives about half of what it promises, which the price per workgroup accounts for.)  Only from 32 tiles per
+// compute unit on: below that a launch is mostly prologues, and the equal splits lose less (2 queries, prefixes of 11-91
+// shots, 13 tiles: a pass of 150 us against 172; 1 query, prefixes of 27-221, 16 tiles: 204 against 228).
+constexpr int64_t kBalancedTiles = 32;
+static int64_t plan_balanced_split_tiles(int64_t n_cu, const std::vector<BatchShape>& shapes) {
+    const double fixed = 2.5, per_wg = 0.13;
+    int64_t longest = 1, total = 0, g = n_cu;
+    for (const BatchShape& b : shapes) {
+        longest = std::max(longest, b.key_tiles);
+        total += b.units * b.key_tiles;
+        g = std::gcd(g, b.units);
+    }
+    if (total < kBalancedTiles * n_cu) return plan_batch_split_tiles(n_cu, shapes, 0);
+    const int64_t bins = n_cu / g;  // every class of workgroups comes g-fold: one compute unit of g stands for all
+    const int64_t floor_tiles = std::min<int64_t>(8, longest);  // shorter splits are all prologue
+    std::vector<int64_t> cand;
+    for (int n : {1, 2, 3, 4, 6, 8}) cand.push_back((longest + n - 1) / n);
+    for (int k : {1, 2, 3, 4})
+        for (double f : {1.02, 1.05, 1.1}) cand.push_back((int64_t)ceil((double)total * f / (double)(k * n_cu)));
+    for (int64_t& st : cand) st = std::min(longest, std::max(floor_tiles, st));
+    std::sort(cand.begin(), cand.end(), std::greater<int64_t>());
+    cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
+    struct Class {
+        double cost;
+        int64_t count;
+    };
+    std::vector<Class> cls;
+    std::vector<double> busy;
+    int64_t best_st = longest;
+    double best_t = 1e300;
+    for (int64_t st : cand) {
+        cls.clear();
+        int64_t n_wg = 0;
+        for (const BatchShape& b : shapes) {
+            const int64_t full = b.key_tiles / st, rem = b.key_tiles - full * st, u = b.units / g;
+            if (full > 0) cls.push_back(Class{(double)st + fixed, full * u});
+            if (rem > 0) cls.push_back(Class{(double)rem + fixed, u});
+            cls.push_back(Class{(double)b.self_tiles + fixed, u});
+            n_wg += (full + (rem > 0) + 1) * u;
+        }
+        if (n_wg > 64 * bins) continue;  // many rounds: any of the longer candidates is as good, and cheaper to price
+        std::sort(cls.begin(), cls.end(), [](const Class& x, const Class& y) { return x.cost > y.cost; });
+        busy.assign((size_t)bins, 0.0);  // a heap, the compute unit that is free first on top
+        double t = 0.0;
+        for (const Class& c : cls)
+            for (int64_t i = 0; i < c.count; ++i) {
+                std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
+                busy.back() += c.cost;
+                t = std::max(t, busy.back());
+                std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+            }
+        t += per_wg * (double)(n_wg * g);
+        if (t < best_t) {
+            best_t = t;
+            best_st = st;
+        }
+    }
+    return best_st;
+}
+
 // All items of a batch in two launches: one MFMA attention grid over the work list of all (item, kv head,
 // row tile, split) workgroups (each rotates the query rows it needs itself), one combine grid.  Items are validated
 // by the caller.  The context is cut into splits of one common length (plan_batch_split_tiles: whole rounds of
@@ -974,7 +1043,9 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
         shapes[(size_t)i].key_tiles = (items[i].n_ctx + 63) / 64;
         shapes[(size_t)i].self_tiles = ((int64_t)items[i].t_q + 63) / 64;
     }
-    const int64_t split_tiles_common = plan_batch_split_tiles(ctx->n_cu, shapes, ctx->force_splits);
+    const int64_t split_tiles_common = stream_tiles || ctx->force_splits > 0
+                                           ? plan_batch_split_tiles(ctx->n_cu, shapes, ctx->force_splits)
+                                           : plan_balanced_split_tiles(ctx->n_cu, shapes);
 
     struct Plan {
         int64_t rows, n_row_tiles, n_split, keys_per_split;
