@@ -598,9 +598,15 @@ static int64_t plan_mfma_splits(int64_t n_cu, int64_t units, int64_t key_tiles, 
 // of three and keeps every wavefront busy, but draws 5.3 TB/s from the memory where the tile kernel draws 6.1.  Per layer
 // of a decode step (tile kernel / streaming kernel, us): 25 MB 27.2 / 15.6, 98 MB 34.1 / 30.7, 197 MB 48.2 / 46.5 (28 queries
 // of 4k slots, 229 MB: 56.9 / 55.6), 354 MB 73.2 / 76.8, 826 MB 153 / 167.
+// A single call has no table to copy, so the tile kernel is two launches there, and with more than 8 rows the partials of
+// a context that needs splits cost the streaming kernel what the second launch costs (32/8 heads, 4 tokens = 16 rows, over
+// 244 / 900 / 2.5k / 6.8k slots: 11.3 / 12.3 / 14.5 / 16.6 us by tiles, 10.4 / 11.9 / 14.8 / 17.5 by streaming; 1 token = 4 rows:
+// 11.5 / 12.4 / 14.6 / 16.7 and 9.7 / 10.2 / 11.0 / 12.9).
 constexpr int64_t kStreamBytes = 200000000;
-static bool attn_tile_kernel(const adapshot_model_desc& d, int64_t rows, int64_t context_tokens) {
-    return attn_mfma_supported(d) && (rows > 16 || context_tokens * d.n_kv_heads * d.head_dim * 4 > kStreamBytes);
+static bool attn_tile_kernel(const adapshot_model_desc& d, int64_t rows, int64_t context_tokens, bool single) {
+    if (!attn_mfma_supported(d)) return false;
+    return rows > 16 || (single && rows > 8 && context_tokens > 1024) ||
+           context_tokens * d.n_kv_heads * d.head_dim * 4 > kStreamBytes;
 }
 
 // 16-row blocks per workgroup of the streaming kernel.  Two share the loads of K and V, but leave half the workgroups: fp32
@@ -616,14 +622,17 @@ static int32_t stream_row_blocks(const adapshot_model_desc& d, int64_t n_cu, int
 // Split length (in 64-key tiles) of a launch of the streaming kernel: the longest context in n equal splits, the others in
 // splits of the same length, n the count whose price is lowest.  A tile keeps each of a compute unit's four matrix cores
 // busy for a 16-key step (bf16: half a 32-key step) of matrix instructions, softmax and load latency; a decode step is
-// bound by loads, 0.8 us per tile and workgroup, 6.2 TB/s in all.  Splitting costs the merge: 2.2 us and a little per partial
+// bound by loads, 0.85 us per tile and workgroup, 6.2 TB/s in all.  Splitting costs the merge: 2.2 us, a little per
+// partial, and 0.8 us for every round of loads after the first (8 splits in flight per thread, a thread per 16 bytes)
 // (fp32, head_dim 128, one query over 2300 slots: 55 us in one split, 11.8 us in 36; a decode step over 16k slots: 33.6 us in
 // 8 splits, 19.5 in 32, 19.0 in 48, 21.7 in 64).
 struct StreamShape {
-    int64_t units, key_tiles;
+    int64_t units, key_tiles, rows;
 };
 static int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_cu, const StreamShape* shapes, int32_t n_shapes,
                                        int32_t row_blocks) {
+    int64_t unit_rows = 0;  // of the fullest unit
+    for (int32_t i = 0; i < n_shapes; ++i) unit_rows = std::max(unit_rows, std::min<int64_t>(shapes[i].rows, 16 * row_blocks));
     int64_t longest = 0, unit_tiles = 0;
     for (int32_t i = 0; i < n_shapes; ++i) {
         longest = std::max(longest, shapes[i].key_tiles);
@@ -634,8 +643,10 @@ static int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_c
     const int64_t blocks = std::max(1, d.head_dim / 16);
     const int64_t pv = bf ? 3 * blocks * 8 : 4 * 32 * blocks;
     const int64_t qk = bf ? std::max(1, d.head_dim / 32) * 16 : d.head_dim / 4 * 32;
-    const double tile_us = bf && d.head_dim == 128 ? 0.8 : (double)(row_blocks * (pv + qk) + 250) / 2100.0;
+    const double tile_us = bf && d.head_dim == 128 ? 0.85 : (double)(row_blocks * (pv + qk) + 250) / 2100.0;
     const double bytes_us = bf && d.head_dim == 128 ? (double)unit_tiles * 32768.0 / 6.2e6 : 0.0;
+    const int64_t pieces = std::max<int64_t>(1, unit_rows * d.head_dim / 4);  // 16-byte pieces of a unit's rows, one per thread
+    const int64_t round_splits = 8 * std::max<int64_t>(1, 64 * kStreamWaves / pieces);
     const int64_t n_max = std::min<int64_t>(longest, kStreamMaxSplits);
     int64_t best = longest, last = 0;
     double best_t = 1e300;
@@ -646,7 +657,8 @@ static int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_c
         int64_t wgs = 0;
         for (int32_t i = 0; i < n_shapes; ++i) wgs += shapes[i].units * std::max<int64_t>(1, (shapes[i].key_tiles + st - 1) / st);
         const int64_t rounds = (wgs + n_cu - 1) / n_cu;
-        const double t = std::max((double)(rounds * st) * tile_us, bytes_us) + (n > 1 ? 2.2 + 0.03 * (double)n : 0.0);
+        const double merge = 2.2 + 0.03 * (double)n + 0.8 * (double)((n - 1) / round_splits);
+        const double t = std::max((double)(rounds * st) * tile_us, bytes_us) + (n > 1 ? merge : 0.0);
         if (t < best_t) {
             best_t = t;
             best = st;
@@ -660,7 +672,7 @@ static int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_c
 static void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t force_splits, int32_t t_q, int64_t n_ctx,
                              int64_t* n_split_out, int64_t* keys_per_split_out) {
     const int64_t rows = (int64_t)t_q * (d.n_q_heads / d.n_kv_heads);
-    const bool mfma = attn_tile_kernel(d, rows, n_ctx);
+    const bool mfma = attn_tile_kernel(d, rows, n_ctx, true);
     const int64_t key_tiles = (n_ctx + 63) / 64;
     const int32_t row_blocks = stream_row_blocks(d, n_cu, rows, key_tiles);
     const int64_t row_tile = mfma ? kAttnRowTile : 16 * row_blocks;
@@ -670,7 +682,7 @@ static void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t
         if (mfma) {
             n_split = plan_mfma_splits(n_cu, units, key_tiles, ((int64_t)t_q + 63) / 64);
         } else {
-            const StreamShape sh{units, key_tiles};
+            const StreamShape sh{units, key_tiles, rows};
             const int64_t st = plan_stream_split_tiles(d, n_cu, &sh, 1, row_blocks);
             n_split = (key_tiles + st - 1) / st;
         }
@@ -720,7 +732,8 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
     } else if (units <= kStreamUnits) {  // more units than arrival counters: the chip is full without splits
         StreamShape shapes[kStreamItems];
         for (int32_t i = 0; i < n_items; ++i)
-            shapes[i] = StreamShape{d.n_kv_heads * (((int64_t)items[i].t_q * g + tr - 1) / tr), ((int64_t)items[i].n_ctx + 63) / 64};
+            shapes[i] = StreamShape{d.n_kv_heads * (((int64_t)items[i].t_q * g + tr - 1) / tr), ((int64_t)items[i].n_ctx + 63) / 64,
+                                    (int64_t)items[i].t_q * g};
         st = plan_stream_split_tiles(d, ctx->n_cu, shapes, n_items, sl.row_blocks);
     }
     if (units > kStreamUnits) st = std::max<int64_t>(1, tiles);
@@ -787,7 +800,7 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
                                          int64_t q_pos0, void* out, const int32_t* slot_src, const float2* tile_rot,
                                          hipStream_t stream, int64_t ctx_pos0) {
     const adapshot_model_desc& d = ctx->desc;
-    if (!attn_tile_kernel(d, (int64_t)t_q * (d.n_q_heads / d.n_kv_heads), n_ctx) && !(slot_src && attn_mfma_supported(d))) {
+    if (!attn_tile_kernel(d, (int64_t)t_q * (d.n_q_heads / d.n_kv_heads), n_ctx, true) && !(slot_src && attn_mfma_supported(d))) {
         StreamItem it = stream_item(k_ctx, v_ctx, n_ctx, q, k_self, v_self, t_q, q_pos0, out);
         return run_stream(ctx, &it, 1, slot_src, ctx_pos0, stream);
     }
@@ -1475,7 +1488,7 @@ static bool streams_batch(const adapshot_ctx* ctx, const adapshot_attn_item* ite
     int64_t tokens = 0;
     for (int32_t i = 0; i < n_items; ++i) {
         tokens += items[i].n_ctx;
-        if (attn_tile_kernel(ctx->desc, (int64_t)items[i].t_q * g, tokens)) return false;
+        if (attn_tile_kernel(ctx->desc, (int64_t)items[i].t_q * g, tokens, false)) return false;
         if (items[i].n_ctx > 0) seen.push_back(items[i].cache_index);
     }
     std::sort(seen.begin(), seen.end());
