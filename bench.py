@@ -131,7 +131,7 @@ def extras(ad, dev) -> dict:
     n_tok = int(off[-1])
     out["rank_shots"] = {"workload": f"{w.n_shots} shots, {n_tok} pool tokens, {w.t_q} query tokens",
                          "us_per_query": dt * 1e6, "pool_tokens_per_s": n_tok / dt,
-                         "mfma_tflops_both_products": 4.0 * w.n_q_heads * w.head_dim * w.t_q * n_tok / dt * 1e-12}
+                         "mfma_tflops_score_product": 2.0 * w.n_q_heads * w.head_dim * w.t_q * n_tok / dt * 1e-12}
     ctx.close()
     del k_pool, v_pool
 
@@ -234,7 +234,7 @@ def extras(ad, dev) -> dict:
         it = iter(range(10 ** 9))
         dt = wall(lambda: ctx.probe_entropy(views[next(it) % 8], out=ho), 20)
         ent[str(rows)] = {"us": dt * 1e6, "gbps": rows * w.vocab * 4 / dt * 1e-9}
-    out["probe_entropy_by_rows"] = {"workload": f"{w.vocab}-way fp32 logits, wall clock per call (chunks + merge; one launch from 256 rows on)", **ent}
+    out["probe_entropy_by_rows"] = {"workload": f"{w.vocab}-way fp32 logits, wall clock per call (one launch: chunks merged by the row's last workgroup, from 256 rows on a workgroup per row)", **ent}
     ctx.close()
     del big, views
     torch.cuda.empty_cache()
