@@ -191,7 +191,8 @@ adapshot_status adapshot_assemble_batched(adapshot_ctx* ctx, adapshot_cache* cac
  * whose workgroups rotate the query rows they need themselves, and one combine grid): the context splits
  * have one common length, so
  * probes over nested prefixes of one cache read identical leading slices, and those workgroups are
- * scheduled next to each other.  Other shapes run up to 32 items per launch.  The outputs of distinct items must not
+ * scheduled next to each other.  Other shapes, and decode steps of such models (at most 16 query rows per kv head,
+ * contexts of their own, up to 200 MB of them), run up to 32 items per launch.  The outputs of distinct items must not
  * overlap; inputs may be shared between items.  A call whose arguments other than `layer` equal the previous
  * batched call's on this context (the same items, caches, pointers and lengths: the next layer of a forward pass)
  * reuses the tables the previous call left in device memory and only launches; nothing the caller does between

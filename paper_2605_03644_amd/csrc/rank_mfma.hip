@@ -20,9 +20,10 @@
 // and vector ALU busy together 14 % of the time, now 29 %), and every branch in the run costs more than what it saves.
 // A tile stays in LDS for one tile longer than its products need it, for the second look.
 //
-// What bounds it: matrix cores busy 51 % and vector ALU 57 % of the SIMD cycles at 1.83 GHz; every variant that overlapped
-// them better ran at a lower clock (2.0 GHz at 8 % less work at once), so what counts is the number of vector
-// instructions per score: one exponential, one addition and 0.5 of everything else.  128 query tokens, 32/8 heads, 209k
+// What bounds it: matrix cores busy 51 % and vector ALU 57 % of the SIMD cycles, at 1.83 GHz.  The better a variant overlapped
+// the two, the lower the chip clocked (2.0 GHz with 8 % of the cycles shared, 1.78 with 26 % and four wavefronts per SIMD), so
+// what counts is the number of vector instructions per score: one exponential, one addition and half of everything
+// else.  128 query tokens, 32/8 heads, 209k
 // tokens: 223 us when the GPU was idle before, 250 us back to back (0.88 PFLOP/s of the one product); through the attention
 // kernel with one-hot value rows 339 / 369 us.
 #include <type_traits>
