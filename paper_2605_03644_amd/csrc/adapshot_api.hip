@@ -6,9 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
-#include <functional>
 #include <new>
-#include <numeric>
 
 #include "adapshot_internal.h"
 
@@ -556,144 +554,6 @@ static adapshot_status check_query_attn(adapshot_ctx* ctx, const adapshot_cache*
     return ADAPSHOT_OK;
 }
 
-// Split count of one MFMA attention launch.  The grid is `units` (kv head, row tile) pairs times the context
-// splits, plus one workgroup per unit for the query's own tokens; one workgroup occupies a compute unit, and
-// the self workgroups are dispatched first.  A handful of candidate counts -- everything in one round beside
-// the self workgroups, one context split per compute unit with the last of them starting when the self
-// workgroups are done, and two to four rounds of that -- are priced in 64-key tiles plus a fixed
-// per-workgroup cost, and the cheapest wins (the smaller count on a tie).  A short context fits everything into
-// one round (26k tokens, 16 units: 15 splits of 29 tiles beside the 16 self workgroups); a long one does not
-// leave the self workgroups' compute units idle (127k tokens, 64 units: 4 splits of 495 tiles, not 3 of 660).
-static int64_t plan_mfma_splits(int64_t n_cu, int64_t units, int64_t key_tiles, int64_t self_tiles) {
-    const double fixed = 2.5;  // launch, first tile round trip and partial write-out of a workgroup, in tiles
-    const int64_t s_max = std::min<int64_t>(key_tiles, 64);
-    const double ls = (double)self_tiles + fixed;
-    auto price = [&](int64_t s) {
-        const double l = (double)((key_tiles + s - 1) / s) + fixed;
-        const int64_t n = units * s;
-        double t;
-        if (units + n <= n_cu) t = std::max(l, ls);          // one round
-        else if (n <= n_cu && units <= n_cu) t = ls + l;      // the context workgroups that do not fit wait for the self ones
-        else t = ceil(((double)n * l + (double)units * ls) / ((double)n_cu * l)) * l;  // whole rounds
-        return t + 0.02 * (double)s;                           // partials cost a little too
-    };
-    const int64_t one_round = (n_cu - units) / units, per_cu = n_cu / units;
-    const int64_t cand[6] = {1, one_round, per_cu, 2 * per_cu, 3 * per_cu, 4 * per_cu};
-    int64_t best = 1;
-    double best_t = price(1);
-    for (int64_t c : cand) {
-        int64_t sc = std::max<int64_t>(1, std::min<int64_t>(c, s_max));
-        sc = (key_tiles + ((key_tiles + sc - 1) / sc) - 1) / ((key_tiles + sc - 1) / sc);  // the count this split length gives
-        const double t = price(sc);
-        if (t < best_t - 1e-9 || (t < best_t + 1e-9 && sc < best)) {
-            best = sc;
-            best_t = t;
-        }
-    }
-    return best;
-}
-
-// Which kernel: the 256-row tile kernel for bf16 models of head dimension 128, unless the rows of a kv head fit one 16-row
-// block (a decode step) and the launch reads at most kStreamBytes of context: the streaming kernel is one launch instead
-// of three and keeps every wavefront busy, but draws 5.3 TB/s from the memory where the tile kernel draws 6.1.  Per layer
-// of a decode step (tile kernel / streaming kernel, us): 25 MB 27.2 / 15.6, 98 MB 34.1 / 30.7, 197 MB 48.2 / 46.5 (28 queries
-// of 4k slots, 229 MB: 56.9 / 55.6), 354 MB 73.2 / 76.8, 826 MB 153 / 167.
-// A single call has no table to copy, so the tile kernel is two launches there, and with more than 8 rows the partials of
-// a context that needs splits cost the streaming kernel what the second launch costs (32/8 heads, 4 tokens = 16 rows, over
-// 244 / 900 / 2.5k / 6.8k slots: 11.3 / 12.3 / 14.5 / 16.6 us by tiles, 10.4 / 11.9 / 14.8 / 17.5 by streaming; 1 token = 4 rows:
-// 11.5 / 12.4 / 14.6 / 16.7 and 9.7 / 10.2 / 11.0 / 12.9).
-constexpr int64_t kStreamBytes = 200000000;
-static bool attn_tile_kernel(const adapshot_model_desc& d, int64_t rows, int64_t context_tokens, bool single) {
-    if (!attn_mfma_supported(d)) return false;
-    return rows > 16 || (single && rows > 8 && context_tokens > 1024) ||
-           context_tokens * d.n_kv_heads * d.head_dim * 4 > kStreamBytes;
-}
-
-// 16-row blocks per workgroup of the streaming kernel.  Two share the loads of K and V, but leave half the workgroups: fp32
-// models want two workgroups per compute unit with one block each before that pays, bf16 models, whose products cost
-// less, half a workgroup and a context of some length (64 query tokens of 32/8 heads, one block / two: 6.4k slots
-// 43.6 / 38.3 us, 2.3k 27.8 / 27.6, 742 20.0 / 22.6; 32 tokens, 6.4k slots 34.0 / 34.1).
-static int32_t stream_row_blocks(const adapshot_model_desc& d, int64_t n_cu, int64_t rows, int64_t key_tiles) {
-    if (d.head_dim != 64) return 1;
-    const int64_t blocks = d.n_kv_heads * ((rows + 15) / 16);
-    return blocks >= 2 * n_cu || (d.dtype == ADAPSHOT_BF16 && 2 * blocks >= n_cu && key_tiles >= 32) ? 2 : 1;
-}
-
-// Split length (in 64-key tiles) of a launch of the streaming kernel: the longest context in n equal splits, the others in
-// splits of the same length, n the count whose price is lowest.  A tile keeps each of a compute unit's four matrix cores
-// busy for a 16-key step (bf16: half a 32-key step) of matrix instructions, softmax and load latency; a decode step is
-// bound by loads, 0.85 us per tile and workgroup, 6.2 TB/s in all.  Splitting costs the merge: 2.2 us, a little per
-// partial, and 0.8 us for every round of loads after the first (8 splits in flight per thread, a thread per 16 bytes)
-// (fp32, head_dim 128, one query over 2300 slots: 55 us in one split, 11.8 us in 36; a decode step over 16k slots: 33.6 us in
-// 8 splits, 19.5 in 32, 19.0 in 48, 21.7 in 64).
-struct StreamShape {
-    int64_t units, key_tiles, rows;
-};
-static int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_cu, const StreamShape* shapes, int32_t n_shapes,
-                                       int32_t row_blocks) {
-    int64_t unit_rows = 0;  // of the fullest unit
-    for (int32_t i = 0; i < n_shapes; ++i) unit_rows = std::max(unit_rows, std::min<int64_t>(shapes[i].rows, 16 * row_blocks));
-    int64_t longest = 0, unit_tiles = 0;
-    for (int32_t i = 0; i < n_shapes; ++i) {
-        longest = std::max(longest, shapes[i].key_tiles);
-        unit_tiles += shapes[i].units * shapes[i].key_tiles;
-    }
-    if (longest == 0) return 1;
-    const bool bf = d.dtype == ADAPSHOT_BF16;
-    const int64_t blocks = std::max(1, d.head_dim / 16);
-    const int64_t pv = bf ? 3 * blocks * 8 : 4 * 32 * blocks;
-    const int64_t qk = bf ? std::max(1, d.head_dim / 32) * 16 : d.head_dim / 4 * 32;
-    const double tile_us = bf && d.head_dim == 128 ? 0.85 : (double)(row_blocks * (pv + qk) + 250) / 2100.0;
-    const double bytes_us = bf && d.head_dim == 128 ? (double)unit_tiles * 32768.0 / 6.2e6 : 0.0;
-    const int64_t pieces = std::max<int64_t>(1, unit_rows * d.head_dim / 4);  // 16-byte pieces of a unit's rows, one per thread
-    const int64_t round_splits = 8 * std::max<int64_t>(1, 64 * kStreamWaves / pieces);
-    const int64_t n_max = std::min<int64_t>(longest, kStreamMaxSplits);
-    int64_t best = longest, last = 0;
-    double best_t = 1e300;
-    for (int64_t n = 1; n <= n_max; ++n) {
-        const int64_t st = (longest + n - 1) / n;
-        if (st == last) continue;  // no shorter splits than with one fewer
-        last = st;
-        int64_t wgs = 0;
-        for (int32_t i = 0; i < n_shapes; ++i) wgs += shapes[i].units * std::max<int64_t>(1, (shapes[i].key_tiles + st - 1) / st);
-        const int64_t rounds = (wgs + n_cu - 1) / n_cu;
-        const double merge = 2.2 + 0.03 * (double)n + 0.8 * (double)((n - 1) / round_splits);
-        const double t = std::max((double)(rounds * st) * tile_us, bytes_us) + (n > 1 ? merge : 0.0);
-        if (t < best_t) {
-            best_t = t;
-            best = st;
-        }
-    }
-    return best;
-}
-
-// Split the context of one attention call so that (kv heads x row tiles x splits) fills the chip.  Keys per
-// split is a multiple of the 64-key tile; an empty context has no split.
-static void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t force_splits, int32_t t_q, int64_t n_ctx,
-                             int64_t* n_split_out, int64_t* keys_per_split_out) {
-    const int64_t rows = (int64_t)t_q * (d.n_q_heads / d.n_kv_heads);
-    const bool mfma = attn_tile_kernel(d, rows, n_ctx, true);
-    const int64_t key_tiles = (n_ctx + 63) / 64;
-    const int32_t row_blocks = stream_row_blocks(d, n_cu, rows, key_tiles);
-    const int64_t row_tile = mfma ? kAttnRowTile : 16 * row_blocks;
-    const int64_t units = d.n_kv_heads * ((rows + row_tile - 1) / row_tile);
-    int64_t n_split = 0, keys_per_split = 64;
-    if (key_tiles > 0) {
-        if (mfma) {
-            n_split = plan_mfma_splits(n_cu, units, key_tiles, ((int64_t)t_q + 63) / 64);
-        } else {
-            const StreamShape sh{units, key_tiles, rows};
-            const int64_t st = plan_stream_split_tiles(d, n_cu, &sh, 1, row_blocks);
-            n_split = (key_tiles + st - 1) / st;
-        }
-        if (force_splits > 0) n_split = std::min<int64_t>(force_splits, key_tiles);
-        keys_per_split = ((key_tiles + n_split - 1) / n_split) * 64;
-        n_split = (n_ctx + keys_per_split - 1) / keys_per_split;
-    }
-    *n_split_out = n_split;
-    *keys_per_split_out = keys_per_split;
-}
-
 // k_ctx / v_ctx: one layer of the context the rows attend over -- the assembled cache, or, for the zero-copy form
 // (slot_src and tile_rot given), one layer of the pool.
 static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, const void* v_ctx, int64_t n_ctx,
@@ -845,138 +705,6 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
     e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN_COMBINE, stream, [&] { return launch_attn_combine(ap, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn: combine launch", e);
     return ADAPSHOT_OK;
-}
-
-// Common split length (in 64-key tiles) of a batch.  The longest item is cut into n equal splits, every other item
-// into splits of that length plus a remainder; n is the candidate whose work list finishes first when the
-// workgroups, sorted longest first, are dealt round-robin over the compute units (the first workgroup of every
-// round is the longest of that round, so the finish time is the sum of those), or rather the fewest splits that come
-// within 12 % of it: whole rounds of equal workgroups win
-// over an average that leaves a few compute units one workgroup more (32 queries x 4 kv heads x 16k tokens: 4 splits,
-// 512 workgroups in two rounds, 199 us; the 4-or-5 splits of an average-based length: 210 us; 3 splits: 230 us).
-struct BatchShape {
-    int64_t units, key_tiles, self_tiles;
-};
-static int64_t plan_batch_split_tiles(int64_t n_cu, const std::vector<BatchShape>& shapes, int32_t force_splits) {
-    int64_t longest = 1;
-    for (const BatchShape& b : shapes) longest = std::max(longest, b.key_tiles);
-    if (force_splits > 0) return (longest + force_splits - 1) / force_splits;
-    const double fixed = 2.5;  // launch, first tile round trip and partial write-out of a workgroup, in tiles
-    struct Class {
-        double cost;
-        int64_t count;
-    };
-    std::vector<Class> cls;
-    int64_t best_st = longest;
-    double best_t = 1e300;
-    static const int kCand[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 16, 20, 24, 32, 48, 64};
-    int64_t cand_st[sizeof(kCand) / sizeof(kCand[0])];
-    double cand_t[sizeof(kCand) / sizeof(kCand[0])];
-    int n_cand = 0;
-    int64_t last_st = -1;
-    for (int n : kCand) {
-        int64_t st = (longest + n - 1) / n;
-        if (st < 8 && longest >= 8) st = 8;  // shorter splits are all prologue
-        if (st == last_st) continue;
-        last_st = st;
-        cls.clear();
-        int64_t partials = 0;
-        for (const BatchShape& b : shapes) {
-            const int64_t full = b.key_tiles / st, rem = b.key_tiles - full * st;
-            if (full > 0) cls.push_back(Class{(double)st + fixed, full * b.units});
-            if (rem > 0) cls.push_back(Class{(double)rem + fixed, b.units});
-            cls.push_back(Class{(double)b.self_tiles + fixed, b.units});
-            partials += (full + (rem > 0)) * b.units;
-        }
-        std::sort(cls.begin(), cls.end(), [](const Class& a, const Class& b) { return a.cost > b.cost; });
-        // finish time of the compute unit that gets the first workgroup of every round
-        double t = 0.0;
-        int64_t rank = 0, next_pick = 0;  // workgroups dealt so far; rank of the next round's first workgroup
-        for (const Class& c : cls) {
-            while (next_pick < rank + c.count) {
-                t += c.cost;
-                next_pick += n_cu;
-            }
-            rank += c.count;
-        }
-        t += 0.0005 * (double)partials;  // the partials are written and merged too
-        cand_st[n_cand] = st;
-        cand_t[n_cand++] = t;
-        best_t = std::min(best_t, t);
-    }
-    // The fewest splits within 12 % of the best: the chip clocks higher while some compute units idle, so a finer
-    // cut gains less than its balance promises, and every extra workgroup has a prologue, an epilogue and a
-    // partial of its own (the probe sweep's 48 items: 4-5 splits of the longest item 850 us, 8-16 splits 872-887 us).
-    for (int i = 0; i < n_cand; ++i)
-        if (cand_t[i] <= 1.12 * best_t) return cand_st[i];
-    return best_st;
-}
-
-// The same for a batch that keeps the matrix cores busy (not a decode step): its items differ in length by design
-// (nested prefixes), and equal splits of the longest one fit the others badly.  Candidates are also the lengths that
-// give every compute unit k workgroups of equal work, with some slack for the remainders; each is dealt out the way the
-// hardware does it (longest first, to the compute unit that is free first) and priced as that finish time plus 0.13
-// tiles per workgroup.  That price is fitted to the two rounds of the probe sweep (8 queries; split length: time per
-// layer): prefixes of 128-512 shots 859: 1120 us, 430: 780, 375: 750, 193: 763, 94: 780, 61: 806; prefixes of 16-64 shots
-// 110: 170 us, 56: 124, 50: 128, 28: 137, 8: 190.  (The chip clocks lower the fewer compute units idle, so a better
-// balance gives about half of what it promises, which the price per workgroup accounts for.)  Only from 32 tiles per
-// compute unit on: below that a launch is mostly prologues, and the equal splits lose less (2 queries, prefixes of 11-91
-// shots, 13 tiles: a pass of 150 us against 172; 1 query, prefixes of 27-221, 16 tiles: 204 against 228).
-constexpr int64_t kBalancedTiles = 32;
-static int64_t plan_balanced_split_tiles(int64_t n_cu, const std::vector<BatchShape>& shapes) {
-    const double fixed = 2.5, per_wg = 0.13;
-    int64_t longest = 1, total = 0, g = n_cu;
-    for (const BatchShape& b : shapes) {
-        longest = std::max(longest, b.key_tiles);
-        total += b.units * b.key_tiles;
-        g = std::gcd(g, b.units);
-    }
-    if (total < kBalancedTiles * n_cu) return plan_batch_split_tiles(n_cu, shapes, 0);
-    const int64_t bins = n_cu / g;  // every class of workgroups comes g-fold: one compute unit of g stands for all
-    const int64_t floor_tiles = std::min<int64_t>(8, longest);  // shorter splits are all prologue
-    std::vector<int64_t> cand;
-    for (int n : {1, 2, 3, 4, 6, 8}) cand.push_back((longest + n - 1) / n);
-    for (int k : {1, 2, 3, 4})
-        for (double f : {1.02, 1.05, 1.1}) cand.push_back((int64_t)ceil((double)total * f / (double)(k * n_cu)));
-    for (int64_t& st : cand) st = std::min(longest, std::max(floor_tiles, st));
-    std::sort(cand.begin(), cand.end(), std::greater<int64_t>());
-    cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
-    struct Class {
-        double cost;
-        int64_t count;
-    };
-    std::vector<Class> cls;
-    std::vector<double> busy;
-    int64_t best_st = longest;
-    double best_t = 1e300;
-    for (int64_t st : cand) {
-        cls.clear();
-        int64_t n_wg = 0;
-        for (const BatchShape& b : shapes) {
-            const int64_t full = b.key_tiles / st, rem = b.key_tiles - full * st, u = b.units / g;
-            if (full > 0) cls.push_back(Class{(double)st + fixed, full * u});
-            if (rem > 0) cls.push_back(Class{(double)rem + fixed, u});
-            cls.push_back(Class{(double)b.self_tiles + fixed, u});
-            n_wg += (full + (rem > 0) + 1) * u;
-        }
-        if (n_wg > 64 * bins) continue;  // many rounds: any of the longer candidates is as good, and cheaper to price
-        std::sort(cls.begin(), cls.end(), [](const Class& x, const Class& y) { return x.cost > y.cost; });
-        busy.assign((size_t)bins, 0.0);  // a heap, the compute unit that is free first on top
-        double t = 0.0;
-        for (const Class& c : cls)
-            for (int64_t i = 0; i < c.count; ++i) {
-                std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
-                busy.back() += c.cost;
-                t = std::max(t, busy.back());
-                std::push_heap(busy.begin(), busy.end(), std::greater<double>());
-            }
-        t += per_wg * (double)(n_wg * g);
-        if (t < best_t) {
-            best_t = t;
-            best_st = st;
-        }
-    }
-    return best_st;
 }
 
 // All items of a batch in two launches: one MFMA attention grid over the work list of all (item, kv head,

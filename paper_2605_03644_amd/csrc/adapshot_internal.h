@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "adapshot.h"
+#include "attn_plan.h"
 
 namespace adapshot {
 
@@ -143,22 +144,7 @@ struct AttnParams {
     // layer, so that the tables of a batch serve every layer of a model (0 for single calls).
     int64_t layer_stride_bytes;
 };
-constexpr int kAttnRowTile = 256;  // query rows per workgroup of the MFMA kernel
-// With at most this many rows per kv head half of a workgroup's wavefronts only move tiles and the launch is bound
-// by the memory path, not by the matrix cores: its tile loads are then marked non-temporal (when no other workgroup
-// reads the same tiles).
-constexpr int kAttnStreamRows = 128;
 // ---- streaming attention (attn_stream_kernel.h): every shape the 256-row tile kernel does not cover -------------
-constexpr int kStreamWaves = 8;       // wavefronts per workgroup, each with keys of its own
-constexpr int kStreamItems = 32;      // attention problems per launch (their descriptions travel in the kernel arguments)
-constexpr int kStreamMaxSplits = 64;  // context splits per problem
-constexpr int kStreamUnits = 4096;    // (problem, row tile, kv head) units of a launch that is split: one arrival counter each
-// Distance of the arrival counters of n units (of an entropy call: rows), in counters: up to a 128-byte line each.  Atomics
-// on one line follow each other at about 14 ns whatever counter they name (16 rows x 126 arrivals in one line: 29 us, a line
-// for every row: 10 us).
-inline int32_t counter_stride(int64_t n) {
-    return (int32_t)(n >= kStreamUnits ? 1 : kStreamUnits / n < 32 ? kStreamUnits / n : 32);
-}
 struct StreamItem {
     const char* q;
     const char* k_self;
@@ -218,7 +204,6 @@ struct PoolPlanParams {
     int32_t n_segs, n_tiles, head_dim;
 };
 hipError_t launch_pool_plan(const PoolPlanParams& p, hipStream_t stream);
-bool attn_mfma_supported(const adapshot_model_desc& d);
 hipError_t launch_attn_combine(const AttnParams& p, hipStream_t stream);
 
 // ---- a batch of attention problems in two launches (attend, combine) ------------------------

@@ -57,8 +57,6 @@ constexpr int kPD = 4;                             // LDS fragment reads in flig
 // s_waitcnt immediates (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
 constexpr int kWaitVm0 = 0x0f70;  // vmcnt(0), other counters untouched
 
-bool attn_mfma_supported(const adapshot_model_desc& d) { return d.dtype == ADAPSHOT_BF16 && d.head_dim == kD; }
-
 // Workgroup barrier of the key loop.  __syncthreads() would drain every tile load still in flight
 // (they write LDS); here only the group issued two tiles ago must have landed (the younger
 // group stays outstanding), this wave's own LDS reads must be complete, and the
