@@ -144,6 +144,8 @@ adapshot_status adapshot_assemble(adapshot_ctx* ctx, adapshot_cache* cache, cons
  * grows with the spread of the scores.  With N(0,1) queries, keys and values the outputs stay within
  * 2e-2 (max-abs) of the exact result; keys three times as large were measured at 1.9e-2, eight times
  * as large at 6e-2.  Accumulation, maxima and sums are fp32 throughout.
+ * A value of v_self that is not finite reaches only the rows that attend to its token.  Exception: bf16 models with
+ * head_dim 128 in calls of more than 8 query rows per kv head, where it can make NaN of every row of the call.
  * Errors, all found before anything is launched (out is then untouched): EINVAL (null or
  * misaligned pointer, t_q < 1, layer out of range, n_ctx < 0, q_pos0 < 0, a q of 2 GiB or more, or a
  * context or query whose K/V rows span more than 4 GiB in one layer), ESTATE (n_ctx beyond

@@ -292,15 +292,19 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
 
     f32x4 o[NR][DB];
     float m_run[NR], l_run[NR];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int nr = 0; nr < NR; ++nr) {
-        m_run[nr] = -INFINITY;
-        l_run[nr] = 0.f;
+        for (int nr = 0; nr < NR; ++nr) {
+            m_run[nr] = -INFINITY;
+            l_run[nr] = 0.f;
 #pragma unroll
-        for (int b = 0; b < DB; ++b) o[nr][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+            for (int b = 0; b < DB; ++b) o[nr][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    clear();
 
-    auto compute = [&](int s, unsigned (&k)[NK][NJ][KR], unsigned (&v)[NV][DG][VR]) __attribute__((always_inline)) {
+    // key_by_key: the second product without matrix instructions (for values that are not finite, see below)
+    auto compute = [&](int s, unsigned (&k)[NK][NJ][KR], unsigned (&v)[NV][DG][VR], auto key_by_key) __attribute__((always_inline)) {
         const bool self = s >= n_cs;  // wavefront-uniform
         f32x4 sc[NK][NR];
 #pragma unroll
@@ -372,7 +376,35 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
                 l_run[nr] += (sc[kb][nr][0] + sc[kb][nr][1]) + (sc[kb][nr][2] + sc[kb][nr][3]);
             }
         }
-        if constexpr (BF) {
+        if constexpr (decltype(key_by_key)::value) {
+#pragma unroll 1
+            for (int kq = 0; kq < 4; ++kq)
+#pragma unroll
+                for (int kr = 0; kr < NV; ++kr) {  // key 16 * (kr / 4) + 4 * kq + kr % 4 of the step
+                    const int key = SK * (self ? s - n_cs : s) + 16 * (kr >> 2) + 4 * kq + (kr & 3);
+                    float w[NR];
+#pragma unroll
+                    for (int nr = 0; nr < NR; ++nr) w[nr] = __shfl(sc[kr >> 2][nr][kr & 3], 16 * kq + l16, 64);
+#pragma unroll
+                    for (int dg = 0; dg < DG; ++dg)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)  // a lane's columns 16 * VW * dg + VW * (4 * kg + i) + c
+#pragma unroll
+                            for (int x = 0; x < VR; ++x) {
+                                const unsigned y = __shfl(v[kr][dg][x], 16 * kq + 4 * kg + i, 64);
+                                constexpr int CX = BF && VW > 1 ? 2 : 1;  // columns of a register
+#pragma unroll
+                                for (int c = 0; c < CX; ++c) {
+                                    const float val = __uint_as_float(CX == 1 ? y : c == 0 ? y << 16 : y & 0xffff0000u);
+#pragma unroll
+                                    for (int nr = 0; nr < NR; ++nr) {
+                                        f32x4& acc = o[nr][dg * VW + CX * x + c];
+                                        acc[i] = key < (self ? jrow[nr] + 1 : nk) ? fmaf(w[nr], val, acc[i]) : acc[i];
+                                    }
+                                }
+                            }
+                }
+        } else if constexpr (BF) {
             // pb[nr][i]: piece i of the weights, slot 4*kb + r of a lane = key 16*kb + 4*kg + r, as V has them
             unsigned pb[NR][NP][2 * NK];
 #pragma unroll
@@ -444,7 +476,29 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
                 load_v(s + (NB - 1) * W, vf[(b + NB - 1) % NBV]);
                 fetch_tok(s + NB * W);
             }
-            compute(s, kf[b], vf[b % NBV]);
+            compute(s, kf[b], vf[b % NBV], std::false_type{});
+        }
+    }
+
+    // A matrix product multiplies every V row of its step with every query row: a V that is not finite makes NaN of the
+    // rows that must not see its token (weight 0) and, where P is in pieces, an infinite one of those whose weight leaves
+    // a piece 0 (a weight of 1 leaves two).  A wavefront whose sums hold a NaN therefore takes its keys a second time, one
+    // by one, each only for the rows that see it.  Looking for NaN costs a call without any 0.2 to 0.5 us (64 query tokens of
+    // 32/8 heads x 64 over 6.6k slots, two layers: 75.0 -> 75.5 us).
+    bool nan = false;
+#pragma unroll
+    for (int nr = 0; nr < NR; ++nr)
+#pragma unroll
+        for (int b = 0; b < DB; ++b)
+            nan |= __builtin_isunordered(o[nr][b][0], o[nr][b][1]) || __builtin_isunordered(o[nr][b][2], o[nr][b][3]);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(nan) != 0, 0)) {
+        clear();
+#pragma unroll 1
+        for (int s = wave; s < n_steps; s += W) {
+            fetch_tok(s);
+            load_k(s, kf[0]);
+            load_v(s, vf[0]);
+            compute(s, kf[0], vf[0], std::true_type{});
         }
     }
 
