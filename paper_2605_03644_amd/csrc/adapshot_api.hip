@@ -660,7 +660,7 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
                                          int64_t q_pos0, void* out, const int32_t* slot_src, const float2* tile_rot,
                                          hipStream_t stream, int64_t ctx_pos0) {
     const adapshot_model_desc& d = ctx->desc;
-    if (!attn_tile_kernel(d, (int64_t)t_q * (d.n_q_heads / d.n_kv_heads), n_ctx, true) && !(slot_src && attn_mfma_supported(d))) {
+    if (!single_by_tiles(d, t_q, n_ctx, slot_src != nullptr)) {
         StreamItem it = stream_item(k_ctx, v_ctx, n_ctx, q, k_self, v_self, t_q, q_pos0, out);
         return run_stream(ctx, &it, 1, slot_src, ctx_pos0, stream);
     }
@@ -668,7 +668,7 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
     const int64_t rows = (int64_t)t_q * g;
 
     int64_t n_split = 0, keys_per_split = 64;
-    plan_single_attn(d, ctx->n_cu, ctx->force_splits, t_q, n_ctx, &n_split, &keys_per_split);
+    plan_single_attn(d, ctx->n_cu, ctx->force_splits, t_q, n_ctx, slot_src != nullptr, &n_split, &keys_per_split);
     hipError_t e = ctx->part_o.reserve((size_t)(n_split + 1) * d.n_kv_heads * rows * d.head_dim * 2, ctx->retired);  // fp16 rows
     if (e == hipSuccess) e = ctx->part_ml.reserve((size_t)(n_split + 1) * d.n_kv_heads * rows * sizeof(float4), ctx->retired);
     if (e != hipSuccess) return fail_hip(ctx, "query_attn: workspace", e);
@@ -1655,7 +1655,7 @@ extern "C" adapshot_status adapshot_attn_split_plan(const adapshot_model_desc* d
     if (!desc || !n_split || !keys_per_split || n_compute_units < 1 || t_q < 1 || n_ctx < 0) return ADAPSHOT_EINVAL;
     if (check_desc(*desc) != nullptr) return ADAPSHOT_EINVAL;
     int64_t ns = 0, kps = 64;
-    plan_single_attn(*desc, n_compute_units, 0, t_q, n_ctx, &ns, &kps);
+    plan_single_attn(*desc, n_compute_units, 0, t_q, n_ctx, false, &ns, &kps);
     *n_split = (int32_t)ns;
     *keys_per_split = kps;
     return ADAPSHOT_OK;

@@ -144,12 +144,19 @@ inline int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_c
     return best;
 }
 
+// The kernel of a single call: zero-copy calls of the tile kernel's shapes always run it (the streaming kernel has no gathered
+// form of head dimension 128 in bf16).
+inline bool single_by_tiles(const adapshot_model_desc& d, int32_t t_q, int64_t n_ctx, bool zero_copy) {
+    return (zero_copy && attn_mfma_supported(d)) || attn_tile_kernel(d, (int64_t)t_q * (d.n_q_heads / d.n_kv_heads), n_ctx, true);
+}
+
 // Split the context of one attention call so that (kv heads x row tiles x splits) fills the chip.  Keys per
-// split is a multiple of the 64-key tile; an empty context has no split.
+// split is a multiple of the 64-key tile; an empty context has no split.  (A zero-copy query of 32/8 heads and one token
+// over 26k slots: 30 splits of 14 tiles 35.7 us, 21 of 20, as the streaming kernel would want them, 43.8 us.)
 inline void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t force_splits, int32_t t_q, int64_t n_ctx,
-                             int64_t* n_split_out, int64_t* keys_per_split_out) {
+                             bool zero_copy, int64_t* n_split_out, int64_t* keys_per_split_out) {
     const int64_t rows = (int64_t)t_q * (d.n_q_heads / d.n_kv_heads);
-    const bool mfma = attn_tile_kernel(d, rows, n_ctx, true);
+    const bool mfma = single_by_tiles(d, t_q, n_ctx, zero_copy);
     const int64_t key_tiles = (n_ctx + 63) / 64;
     const int32_t row_blocks = stream_row_blocks(d, n_cu, rows, key_tiles);
     const int64_t row_tile = mfma ? kAttnRowTile : 16 * row_blocks;

@@ -1,0 +1,59 @@
+"""How attention calls are cut into workgroups (csrc/attn_plan.h): host logic over sizes, compiled here with the host compiler
+and called directly.  No GPU, no HIP."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2605_03644_amd import binding as ad
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHIM = r"""
+#include "attn_plan.h"
+using namespace adapshot;
+extern "C" void single(const adapshot_model_desc* d, int64_t n_cu, int32_t t_q, int64_t n_ctx, int32_t zero_copy, int64_t* out) {
+    out[0] = single_by_tiles(*d, t_q, n_ctx, zero_copy != 0);
+    plan_single_attn(*d, n_cu, 0, t_q, n_ctx, zero_copy != 0, out + 1, out + 2);
+}
+extern "C" int64_t tile_splits(int64_t n_cu, int64_t units, int64_t key_tiles, int64_t self_tiles) {
+    return plan_mfma_splits(n_cu, units, key_tiles, self_tiles);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("plan") / "plan.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2605_03644_amd", "csrc"), "-x", "c++", "-", "-o", so], input=SHIM.encode(), check=True)
+    lib = ctypes.CDLL(so)
+    lib.tile_splits.restype = ctypes.c_int64
+    return lib
+
+
+def _desc(hq, hkv, d, dtype):
+    return ad.ModelDesc(1, hq, hkv, d, 5.0e5, dtype, ad.KEYS_UNROTATED, 1 << 20)
+
+
+def _single(plan, desc, t_q, n_ctx, zero_copy, n_cu=256):
+    """(runs the tile kernel, splits, keys per split)"""
+    out = (ctypes.c_int64 * 3)()
+    plan.single(ctypes.byref(desc), ctypes.c_int64(n_cu), ctypes.c_int32(t_q), ctypes.c_int64(n_ctx), ctypes.c_int32(zero_copy), out)
+    return tuple(out)
+
+
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (28, 4), (64, 8), (4, 4)])
+@pytest.mark.parametrize("t_q", [1, 2, 4, 64])
+@pytest.mark.parametrize("n_ctx", [64, 600, 2500, 16000, 26000, 60000])
+def test_a_zero_copy_call_is_planned_for_the_kernel_it_runs(plan, hq, hkv, t_q, n_ctx):
+    """bf16 / head_dim 128: the tile kernel, however few rows there are."""
+    tiles, n_split, keys = _single(plan, _desc(hq, hkv, 128, ad.BF16), t_q, n_ctx, 1)
+    assert tiles
+    units, key_tiles = hkv * -(-t_q * (hq // hkv) // 256), -(-n_ctx // 64)
+    want = plan.tile_splits(ctypes.c_int64(256), ctypes.c_int64(units), ctypes.c_int64(key_tiles), ctypes.c_int64(-(-t_q // 64)))
+    assert keys == -(-key_tiles // want) * 64 and n_split == -(-n_ctx // keys)
+    # other shapes have a gathered form of the streaming kernel, and are planned like a call over a cache
+    for d, dtype in ((64, ad.BF16), (128, ad.F32)):
+        assert _single(plan, _desc(hq, hkv, d, dtype), t_q, n_ctx, 1) == _single(plan, _desc(hq, hkv, d, dtype), t_q, n_ctx, 0)
+        assert not _single(plan, _desc(hq, hkv, d, dtype), t_q, n_ctx, 1)[0]

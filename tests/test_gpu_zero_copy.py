@@ -328,3 +328,24 @@ def test_zero_copy_plan_kept_for_the_next_layer(ad):
     assert torch.equal(o.view(torch.int16), ref.view(torch.int16))
     c2.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("t_q", [1, 2])
+def test_zero_copy_of_few_rows_is_cut_like_the_tile_kernel_wants_it(ad, t_q):
+    """A few-row call over 160 shots gives the bits of the split count that a call of 16 rows per kv head over as many
+    slots gets (the tile kernel's plan depends on the row tiles, not on the rows in them)."""
+    w = wl.WORKLOADS["llama8b_1layer"]
+    k_pool, v_pool, off = wl.make_pool(w, "cuda", n_layers=1)
+    ids = wl.selection(w)[0][:160]
+    total = int(np.sum(off[ids + 1] - off[ids]))
+    ctx = ad.Context.for_workload(w, n_layers=1)
+    ctx.pool_register(k_pool, v_pool, off)
+    q, ks, vs = wl.make_query(w, "cuda", t_q=t_q)
+    auto = ctx.query_attn_pool(0, ids, None, q, ks, vs, total)
+    n_split, _ = ad.attn_split_plan(w.n_q_heads, w.n_kv_heads, 128, ad.BF16, torch.cuda.get_device_properties(0).multi_processor_count,
+                                    4, total)
+    ctx.set_attn_splits(n_split)
+    assert torch.equal(auto, ctx.query_attn_pool(0, ids, None, q, ks, vs, total))
+    ctx.set_attn_splits(n_split - 8)                   # another split count rounds elsewhere: the comparison sees it
+    assert not torch.equal(auto, ctx.query_attn_pool(0, ids, None, q, ks, vs, total))
+    ctx.close()
