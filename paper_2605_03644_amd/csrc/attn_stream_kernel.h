@@ -462,43 +462,46 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         }
     };
 
-    for (int s0 = wave; s0 < n_steps; s0 += NB * W) {
+    if (wave < n_steps) {  // (said once for both loops: what only they need is then computed under it)
+        for (int s0 = wave; s0 < n_steps; s0 += NB * W) {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int s = s0 + b * W;
-            if (s >= n_steps) break;
-            if (NBV == 1) {
-                load_v(s, vf[0]);
-                fetch_tok(s + W);
+            for (int b = 0; b < NB; ++b) {
+                const int s = s0 + b * W;
+                if (s >= n_steps) break;
+                if (NBV == 1) {
+                    load_v(s, vf[0]);
+                    fetch_tok(s + W);
+                }
+                load_k(s + (NB - 1) * W, kf[(b + NB - 1) % NB]);
+                if (NBV > 1) {
+                    load_v(s + (NB - 1) * W, vf[(b + NB - 1) % NBV]);
+                    fetch_tok(s + NB * W);
+                }
+                compute(s, kf[b], vf[b % NBV], std::false_type{});
             }
-            load_k(s + (NB - 1) * W, kf[(b + NB - 1) % NB]);
-            if (NBV > 1) {
-                load_v(s + (NB - 1) * W, vf[(b + NB - 1) % NBV]);
-                fetch_tok(s + NB * W);
-            }
-            compute(s, kf[b], vf[b % NBV], std::false_type{});
         }
-    }
 
-    // A matrix product multiplies every V row of its step with every query row: a V that is not finite makes NaN of the
-    // rows that must not see its token (weight 0) and, where P is in pieces, an infinite one of those whose weight leaves
-    // a piece 0 (a weight of 1 leaves two).  A wavefront whose sums hold a NaN therefore takes its keys a second time, one
-    // by one, each only for the rows that see it.  Looking for NaN costs a call without any 0.2 to 0.5 us (64 query tokens of
-    // 32/8 heads x 64 over 6.6k slots, two layers: 75.0 -> 75.5 us).
-    bool nan = false;
+        // A matrix product multiplies every V row of its step with every query row: a V that is not finite makes NaN of the
+        // rows that must not see its token (weight 0) and, where P is in pieces, an infinite one of those whose weight
+        // leaves a piece 0 (a weight of 1 leaves two).  A wavefront whose sums hold a NaN therefore takes its keys a second
+        // time, one by one, each only for the rows that see it.  Looking for NaN costs a call without any 0.1 to 0.2 us
+        // (kernel alone: 64 query tokens of 32/8 heads x 64 over 6.6k slots 22.2 -> 22.5 us; head dimension 256, where the
+        // second loop's registers spill, up to 0.6 us of 11 to 19).
+        bool nan = false;
 #pragma unroll
-    for (int nr = 0; nr < NR; ++nr)
+        for (int nr = 0; nr < NR; ++nr)
 #pragma unroll
-        for (int b = 0; b < DB; ++b)
-            nan |= __builtin_isunordered(o[nr][b][0], o[nr][b][1]) || __builtin_isunordered(o[nr][b][2], o[nr][b][3]);
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(nan) != 0, 0)) {
-        clear();
+            for (int b = 0; b < DB; ++b)
+                nan |= __builtin_isunordered(o[nr][b][0], o[nr][b][1]) || __builtin_isunordered(o[nr][b][2], o[nr][b][3]);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(nan) != 0, 0)) {
+            clear();
 #pragma unroll 1
-        for (int s = wave; s < n_steps; s += W) {
-            fetch_tok(s);
-            load_k(s, kf[0]);
-            load_v(s, vf[0]);
-            compute(s, kf[0], vf[0], std::true_type{});
+            for (int s = wave; s < n_steps; s += W) {
+                fetch_tok(s);
+                load_k(s, kf[0]);
+                load_v(s, vf[0]);
+                compute(s, kf[0], vf[0], std::true_type{});
+            }
         }
     }
 
