@@ -576,24 +576,21 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
                                   int64_t ctx_pos0, hipStream_t stream) {
     const adapshot_model_desc& d = ctx->desc;
     const int64_t g = d.n_q_heads / d.n_kv_heads;
-    int64_t rows = 0, tiles = 0;
+    StreamShape shapes[kStreamItems];
+    int64_t tiles = 0;
     for (int32_t i = 0; i < n_items; ++i) {
-        rows += (int64_t)items[i].t_q * g;
-        tiles = std::max<int64_t>(tiles, ((int64_t)items[i].n_ctx + 63) / 64);
+        shapes[i] = StreamShape{(int64_t)items[i].t_q * g, ((int64_t)items[i].n_ctx + 63) / 64};
+        tiles = std::max(tiles, shapes[i].key_tiles);
     }
     StreamLaunch sl;
-    sl.row_blocks = stream_row_blocks(d, ctx->n_cu, rows, tiles);
+    sl.row_blocks = stream_row_blocks(d, ctx->n_cu, shapes, n_items);
     const int64_t tr = 16 * sl.row_blocks;
     int64_t units = 0;
-    for (int32_t i = 0; i < n_items; ++i) units += d.n_kv_heads * (((int64_t)items[i].t_q * g + tr - 1) / tr);
+    for (int32_t i = 0; i < n_items; ++i) units += stream_units(d, shapes[i], sl.row_blocks);
     int64_t st = std::max<int64_t>(1, tiles);
     if (ctx->force_splits > 0) {
         st = std::max<int64_t>(1, (tiles + ctx->force_splits - 1) / ctx->force_splits);
     } else if (units <= kStreamUnits) {  // more units than arrival counters: the chip is full without splits
-        StreamShape shapes[kStreamItems];
-        for (int32_t i = 0; i < n_items; ++i)
-            shapes[i] = StreamShape{d.n_kv_heads * (((int64_t)items[i].t_q * g + tr - 1) / tr), ((int64_t)items[i].n_ctx + 63) / 64,
-                                    (int64_t)items[i].t_q * g};
         st = plan_stream_split_tiles(d, ctx->n_cu, shapes, n_items, sl.row_blocks);
     }
     if (units > kStreamUnits) st = std::max<int64_t>(1, tiles);
@@ -604,7 +601,7 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
         StreamItem& it = items[i];
         it.keys_per_split = (int32_t)(st * 64);
         it.n_split = (int32_t)std::max<int64_t>(1, ((int64_t)it.n_ctx + it.keys_per_split - 1) / it.keys_per_split);
-        const int64_t here = d.n_kv_heads * (((int64_t)it.t_q * g + tr - 1) / tr);
+        const int64_t here = stream_units(d, shapes[i], sl.row_blocks);
         it.unit0 = (int32_t)unit0;
         unit0 += here;
         grid_x = std::max(grid_x, here * it.n_split);

@@ -89,11 +89,27 @@ inline bool attn_tile_kernel(const adapshot_model_desc& d, int64_t rows, int64_t
 // 16-row blocks per workgroup of the streaming kernel.  Two share the loads of K and V, but leave half the workgroups: fp32
 // models want two workgroups per compute unit with one block each before that pays, bf16 models, whose products cost
 // less, half a workgroup and a context of some length (64 query tokens of 32/8 heads, one block / two: 6.4k slots
-// 43.6 / 38.3 us, 2.3k 27.8 / 27.6, 742 20.0 / 22.6; 32 tokens, 6.4k slots 34.0 / 34.1).
-inline int32_t stream_row_blocks(const adapshot_model_desc& d, int64_t n_cu, int64_t rows, int64_t key_tiles) {
+// 43.6 / 38.3 us, 2.3k 27.8 / 27.6, 742 20.0 / 22.6; 32 tokens, 6.4k slots 34.0 / 34.1).  And the second blocks have to hold
+// rows, at least half of them: problems share no workgroup (32 queries of 16 rows over 2k / 4k slots: two blocks, the second
+// one empty, 27.2 / 49.8 us, one 24.8 / 47.3).
+struct StreamShape {
+    int64_t rows, key_tiles;  // query rows per kv head, 64-key tiles of context
+};
+inline int32_t stream_row_blocks(const adapshot_model_desc& d, int64_t n_cu, const StreamShape* shapes, int32_t n_shapes) {
     if (d.head_dim != 64) return 1;
-    const int64_t blocks = d.n_kv_heads * ((rows + 15) / 16);
+    int64_t blocks = 0, pairs = 0, key_tiles = 0;
+    for (int32_t i = 0; i < n_shapes; ++i) {
+        blocks += (shapes[i].rows + 15) / 16;
+        pairs += (shapes[i].rows + 31) / 32;
+        key_tiles = std::max(key_tiles, shapes[i].key_tiles);
+    }
+    if (4 * pairs > 3 * blocks) return 1;
+    blocks *= d.n_kv_heads;
     return blocks >= 2 * n_cu || (d.dtype == ADAPSHOT_BF16 && 2 * blocks >= n_cu && key_tiles >= 32) ? 2 : 1;
+}
+// (problem, row tile, kv head) units of a problem
+inline int64_t stream_units(const adapshot_model_desc& d, const StreamShape& s, int32_t row_blocks) {
+    return d.n_kv_heads * ((s.rows + 16 * row_blocks - 1) / (16 * row_blocks));
 }
 
 // Split length (in 64-key tiles) of a launch of the streaming kernel: the longest context in n equal splits, the others in
@@ -103,9 +119,6 @@ inline int32_t stream_row_blocks(const adapshot_model_desc& d, int64_t n_cu, int
 // partial, and 0.8 us for every round of loads after the first (8 splits in flight per thread, a thread per 16 bytes)
 // (fp32, head_dim 128, one query over 2300 slots: 55 us in one split, 11.8 us in 36; a decode step over 16k slots: 33.6 us in
 // 8 splits, 19.5 in 32, 19.0 in 48, 21.7 in 64).
-struct StreamShape {
-    int64_t units, key_tiles, rows;
-};
 inline int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_cu, const StreamShape* shapes, int32_t n_shapes,
                                        int32_t row_blocks) {
     int64_t unit_rows = 0;  // of the fullest unit
@@ -113,7 +126,7 @@ inline int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_c
     int64_t longest = 0, unit_tiles = 0;
     for (int32_t i = 0; i < n_shapes; ++i) {
         longest = std::max(longest, shapes[i].key_tiles);
-        unit_tiles += shapes[i].units * shapes[i].key_tiles;
+        unit_tiles += stream_units(d, shapes[i], row_blocks) * shapes[i].key_tiles;
     }
     if (longest == 0) return 1;
     const bool bf = d.dtype == ADAPSHOT_BF16;
@@ -132,7 +145,7 @@ inline int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_c
         if (st == last) continue;  // no shorter splits than with one fewer
         last = st;
         int64_t wgs = 0;
-        for (int32_t i = 0; i < n_shapes; ++i) wgs += shapes[i].units * std::max<int64_t>(1, (shapes[i].key_tiles + st - 1) / st);
+        for (int32_t i = 0; i < n_shapes; ++i) wgs += stream_units(d, shapes[i], row_blocks) * std::max<int64_t>(1, (shapes[i].key_tiles + st - 1) / st);
         const int64_t rounds = (wgs + n_cu - 1) / n_cu;
         const double merge = 2.2 + 0.03 * (double)n + 0.8 * (double)((n - 1) / round_splits);
         const double t = std::max((double)(rounds * st) * tile_us, bytes_us) + (n > 1 ? merge : 0.0);
@@ -158,7 +171,8 @@ inline void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t
     const int64_t rows = (int64_t)t_q * (d.n_q_heads / d.n_kv_heads);
     const bool mfma = single_by_tiles(d, t_q, n_ctx, zero_copy);
     const int64_t key_tiles = (n_ctx + 63) / 64;
-    const int32_t row_blocks = stream_row_blocks(d, n_cu, rows, key_tiles);
+    const StreamShape sh{rows, key_tiles};
+    const int32_t row_blocks = stream_row_blocks(d, n_cu, &sh, 1);
     const int64_t row_tile = mfma ? kAttnRowTile : 16 * row_blocks;
     const int64_t units = d.n_kv_heads * ((rows + row_tile - 1) / row_tile);
     int64_t n_split = 0, keys_per_split = 64;
@@ -166,7 +180,6 @@ inline void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t
         if (mfma) {
             n_split = plan_mfma_splits(n_cu, units, key_tiles, ((int64_t)t_q + 63) / 64);
         } else {
-            const StreamShape sh{units, key_tiles, rows};
             const int64_t st = plan_stream_split_tiles(d, n_cu, &sh, 1, row_blocks);
             n_split = (key_tiles + st - 1) / st;
         }

@@ -19,6 +19,11 @@ extern "C" void single(const adapshot_model_desc* d, int64_t n_cu, int32_t t_q, 
 extern "C" int64_t tile_splits(int64_t n_cu, int64_t units, int64_t key_tiles, int64_t self_tiles) {
     return plan_mfma_splits(n_cu, units, key_tiles, self_tiles);
 }
+extern "C" int32_t row_blocks(const adapshot_model_desc* d, int64_t n_cu, const int64_t* rows, const int64_t* tiles, int32_t n) {
+    std::vector<StreamShape> s;
+    for (int32_t i = 0; i < n; ++i) s.push_back(StreamShape{rows[i], tiles[i]});
+    return stream_row_blocks(*d, n_cu, s.data(), n);
+}
 """
 
 
@@ -57,3 +62,26 @@ def test_a_zero_copy_call_is_planned_for_the_kernel_it_runs(plan, hq, hkv, t_q, 
     for d, dtype in ((64, ad.BF16), (128, ad.F32)):
         assert _single(plan, _desc(hq, hkv, d, dtype), t_q, n_ctx, 1) == _single(plan, _desc(hq, hkv, d, dtype), t_q, n_ctx, 0)
         assert not _single(plan, _desc(hq, hkv, d, dtype), t_q, n_ctx, 1)[0]
+
+
+def _row_blocks(plan, desc, rows, tiles, n_cu=256):
+    arr = lambda x: (ctypes.c_int64 * len(x))(*x)  # noqa: E731
+    return plan.row_blocks(ctypes.byref(desc), ctypes.c_int64(n_cu), arr(rows), arr(tiles), ctypes.c_int32(len(rows)))
+
+
+@pytest.mark.parametrize("dtype", [ad.BF16, ad.F32])
+def test_two_row_blocks_only_where_the_problems_fill_them(plan, dtype):
+    """Many problems of one 16-row block each are many rows, but no workgroup of two blocks would have a second one."""
+    d = _desc(32, 8, 64, dtype)
+    for n in (1, 16, 32):
+        for rows in (1, 4, 16):
+            assert _row_blocks(plan, d, [rows] * n, [63] * n) == 1
+    assert _row_blocks(plan, d, [16] * 31 + [32], [63] * 32) == 1
+    assert _row_blocks(plan, d, [32] * 32, [63] * 32) == 2
+    assert _row_blocks(plan, d, [48] * 32, [63] * 32) == 2
+    assert _row_blocks(plan, _desc(128, 128, 64, dtype), [16], [63]) == 1
+    # what one problem alone gets: two blocks from half a workgroup (fp32: two) per compute unit on
+    assert _row_blocks(plan, d, [256], [63]) == (2 if dtype == ad.BF16 else 1)
+    assert _row_blocks(plan, d, [240], [63]) == 1
+    assert _row_blocks(plan, d, [1024], [2]) == 2
+    assert _row_blocks(plan, _desc(32, 8, 128, ad.F32), [1024], [63]) == 1
