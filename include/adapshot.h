@@ -23,8 +23,8 @@
  *     the GPU.  A context owns device scratch (RoPE tables, tile descriptors,
  *     split partials), so calls on ONE context must be issued in stream order on
  *     one stream at a time; use one context per concurrent stream.
- *   - Allocation and waiting.  adapshot_create allocates the RoPE tables (hipMalloc and two
- *     blocking copies).  adapshot_query_attn, adapshot_query_attn_pool, the batched attention calls, adapshot_probe_entropy,
+ *   - Allocation and waiting.  adapshot_create allocates the RoPE tables and 16 KiB of arrival counters
+ *     (hipMalloc, blocking copies, and a wait for them).  adapshot_query_attn, adapshot_query_attn_pool, the batched attention calls, adapshot_probe_entropy,
  *     adapshot_probe_entropy_tokens and adapshot_rank_shots keep grow-only workspaces: a call that
  *     needs more than any earlier call on the context calls hipMalloc (an outgrown buffer is kept
  *     until adapshot_destroy, never freed in a call, so no call waits for the device); a call that

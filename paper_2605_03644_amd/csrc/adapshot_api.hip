@@ -238,7 +238,11 @@ extern "C" adapshot_status adapshot_create(const adapshot_model_desc* desc, adap
     if (e == hipSuccess) e = hipMemcpy(ctx->tab_lo, lo.data(), lo.size() * sizeof(float2), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(ctx->tab_hi, hi.data(), hi.size() * sizeof(float2), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc((void**)&ctx->stream_counters, kStreamUnits * sizeof(unsigned));
-    if (e == hipSuccess) e = hipMemset(ctx->stream_counters, 0, kStreamUnits * sizeof(unsigned));
+    const std::vector<unsigned> zeros(kStreamUnits, 0u);
+    if (e == hipSuccess) e = hipMemcpy(ctx->stream_counters, zeros.data(), zeros.size() * sizeof(unsigned), hipMemcpyHostToDevice);
+    // The caller's streams need not be ordered behind the null stream, and a counter that is not zero when a first launch
+    // counts on it would never be again: everything above has landed before the context is handed out.
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e == hipSuccess) e = entropy_static_scratch(&ctx->static_ent);  // set-up: the current device is the context's
     if (e != hipSuccess) {
         (void)hipGetLastError();
