@@ -581,29 +581,15 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
     const adapshot_model_desc& d = ctx->desc;
     const int64_t g = d.n_q_heads / d.n_kv_heads;
     StreamShape shapes[kStreamItems];
-    int64_t tiles = 0;
-    for (int32_t i = 0; i < n_items; ++i) {
-        shapes[i] = StreamShape{(int64_t)items[i].t_q * g, ((int64_t)items[i].n_ctx + 63) / 64};
-        tiles = std::max(tiles, shapes[i].key_tiles);
-    }
+    for (int32_t i = 0; i < n_items; ++i) shapes[i] = StreamShape{(int64_t)items[i].t_q * g, ((int64_t)items[i].n_ctx + 63) / 64};
+    const StreamPlan plan = plan_stream(d, ctx->n_cu, ctx->force_splits, shapes, n_items);
+    const int64_t units = plan.units, n_split = plan.n_split, tr = 16 * plan.row_blocks;
     StreamLaunch sl;
-    sl.row_blocks = stream_row_blocks(d, ctx->n_cu, shapes, n_items);
-    const int64_t tr = 16 * sl.row_blocks;
-    int64_t units = 0;
-    for (int32_t i = 0; i < n_items; ++i) units += stream_units(d, shapes[i], sl.row_blocks);
-    int64_t st = std::max<int64_t>(1, tiles);
-    if (ctx->force_splits > 0) {
-        st = std::max<int64_t>(1, (tiles + ctx->force_splits - 1) / ctx->force_splits);
-    } else if (units <= kStreamUnits) {  // more units than arrival counters: the chip is full without splits
-        st = plan_stream_split_tiles(d, ctx->n_cu, shapes, n_items, sl.row_blocks);
-    }
-    if (units > kStreamUnits) st = std::max<int64_t>(1, tiles);
-    st = std::max<int64_t>(st, (tiles + kStreamMaxSplits - 1) / kStreamMaxSplits);
-    const int64_t n_split = tiles > 0 ? (tiles + st - 1) / st : 1;
+    sl.row_blocks = plan.row_blocks;
     int64_t unit0 = 0, grid_x = 0;
     for (int32_t i = 0; i < n_items; ++i) {
         StreamItem& it = items[i];
-        it.keys_per_split = (int32_t)(st * 64);
+        it.keys_per_split = (int32_t)(plan.split_tiles * 64);
         it.n_split = (int32_t)std::max<int64_t>(1, ((int64_t)it.n_ctx + it.keys_per_split - 1) / it.keys_per_split);
         const int64_t here = stream_units(d, shapes[i], sl.row_blocks);
         it.unit0 = (int32_t)unit0;

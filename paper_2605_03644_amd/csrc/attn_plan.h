@@ -157,6 +157,31 @@ inline int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_c
     return best;
 }
 
+// One launch of the streaming kernel.  More units than arrival counters: the chip is full without splits, and none are made.
+struct StreamPlan {
+    int32_t row_blocks;
+    int64_t units;        // of all problems
+    int64_t split_tiles;  // 64-key tiles of a split
+    int64_t n_split;      // of the longest problem (an empty one: 1)
+};
+inline StreamPlan plan_stream(const adapshot_model_desc& d, int64_t n_cu, int32_t force_splits, const StreamShape* shapes,
+                              int32_t n_shapes) {
+    StreamPlan p;
+    p.row_blocks = stream_row_blocks(d, n_cu, shapes, n_shapes);
+    p.units = 0;
+    int64_t tiles = 1;
+    for (int32_t i = 0; i < n_shapes; ++i) {
+        p.units += stream_units(d, shapes[i], p.row_blocks);
+        tiles = std::max(tiles, shapes[i].key_tiles);
+    }
+    if (p.units > kStreamUnits) p.split_tiles = tiles;
+    else if (force_splits > 0) p.split_tiles = (tiles + force_splits - 1) / force_splits;
+    else p.split_tiles = plan_stream_split_tiles(d, n_cu, shapes, n_shapes, p.row_blocks);
+    p.split_tiles = std::max(p.split_tiles, (tiles + kStreamMaxSplits - 1) / kStreamMaxSplits);
+    p.n_split = (tiles + p.split_tiles - 1) / p.split_tiles;
+    return p;
+}
+
 // The kernel of a single call: zero-copy calls of the tile kernel's shapes always run it (the streaming kernel has no gathered
 // form of head dimension 128 in bf16).
 inline bool single_by_tiles(const adapshot_model_desc& d, int32_t t_q, int64_t n_ctx, bool zero_copy) {
@@ -169,22 +194,18 @@ inline bool single_by_tiles(const adapshot_model_desc& d, int32_t t_q, int64_t n
 inline void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t force_splits, int32_t t_q, int64_t n_ctx,
                              bool zero_copy, int64_t* n_split_out, int64_t* keys_per_split_out) {
     const int64_t rows = (int64_t)t_q * (d.n_q_heads / d.n_kv_heads);
-    const bool mfma = single_by_tiles(d, t_q, n_ctx, zero_copy);
     const int64_t key_tiles = (n_ctx + 63) / 64;
-    const StreamShape sh{rows, key_tiles};
-    const int32_t row_blocks = stream_row_blocks(d, n_cu, &sh, 1);
-    const int64_t row_tile = mfma ? kAttnRowTile : 16 * row_blocks;
-    const int64_t units = d.n_kv_heads * ((rows + row_tile - 1) / row_tile);
     int64_t n_split = 0, keys_per_split = 64;
     if (key_tiles > 0) {
-        if (mfma) {
-            n_split = plan_mfma_splits(n_cu, units, key_tiles, ((int64_t)t_q + 63) / 64);
+        if (single_by_tiles(d, t_q, n_ctx, zero_copy)) {
+            const int64_t units = d.n_kv_heads * ((rows + kAttnRowTile - 1) / kAttnRowTile);
+            n_split = force_splits > 0 ? std::min<int64_t>(force_splits, key_tiles)
+                                       : plan_mfma_splits(n_cu, units, key_tiles, ((int64_t)t_q + 63) / 64);
+            keys_per_split = ((key_tiles + n_split - 1) / n_split) * 64;
         } else {
-            const int64_t st = plan_stream_split_tiles(d, n_cu, &sh, 1, row_blocks);
-            n_split = (key_tiles + st - 1) / st;
+            const StreamShape sh{rows, key_tiles};
+            keys_per_split = plan_stream(d, n_cu, force_splits, &sh, 1).split_tiles * 64;
         }
-        if (force_splits > 0) n_split = std::min<int64_t>(force_splits, key_tiles);
-        keys_per_split = ((key_tiles + n_split - 1) / n_split) * 64;
         n_split = (n_ctx + keys_per_split - 1) / keys_per_split;
     }
     *n_split_out = n_split;

@@ -24,6 +24,13 @@ extern "C" int32_t row_blocks(const adapshot_model_desc* d, int64_t n_cu, const 
     for (int32_t i = 0; i < n; ++i) s.push_back(StreamShape{rows[i], tiles[i]});
     return stream_row_blocks(*d, n_cu, s.data(), n);
 }
+extern "C" void stream(const adapshot_model_desc* d, int64_t n_cu, int32_t force, const int64_t* rows, const int64_t* tiles,
+                       int32_t n, int64_t* out) {
+    std::vector<StreamShape> s;
+    for (int32_t i = 0; i < n; ++i) s.push_back(StreamShape{rows[i], tiles[i]});
+    const StreamPlan p = plan_stream(*d, n_cu, force, s.data(), n);
+    out[0] = p.row_blocks, out[1] = p.units, out[2] = p.split_tiles, out[3] = p.n_split;
+}
 """
 
 
@@ -85,3 +92,33 @@ def test_two_row_blocks_only_where_the_problems_fill_them(plan, dtype):
     assert _row_blocks(plan, d, [240], [63]) == 1
     assert _row_blocks(plan, d, [1024], [2]) == 2
     assert _row_blocks(plan, _desc(32, 8, 128, ad.F32), [1024], [63]) == 1
+
+
+def _stream(plan, desc, rows, tiles, force=0, n_cu=256):
+    """(row blocks, units, tiles per split, splits of the longest problem)"""
+    arr = lambda x: (ctypes.c_int64 * len(x))(*x)  # noqa: E731
+    out = (ctypes.c_int64 * 4)()
+    plan.stream(ctypes.byref(desc), ctypes.c_int64(n_cu), ctypes.c_int32(force), arr(rows), arr(tiles), ctypes.c_int32(len(rows)), out)
+    return tuple(out)
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(32, 8, 64, ad.F32), (32, 8, 64, ad.BF16), (8, 8, 128, ad.F32), (28, 4, 128, ad.BF16)])
+def test_the_public_plan_is_the_launch_s_plan(plan, hq, hkv, d, dtype):
+    """adapshot_attn_split_plan names the splits that the launch makes, also beyond 4096 units, where it makes none."""
+    desc, g = _desc(hq, hkv, d, dtype), hq // hkv
+    beyond = 0
+    for t_q in (1, 2, 100, 2048, 4130, 9000):
+        for n_ctx in (1, 64, 700, 6400, 40000):
+            if dtype == ad.BF16 and d == 128 and t_q > 1:     # the tile kernel
+                continue
+            n_split, keys = ad.attn_split_plan(hq, hkv, d, dtype, 256, t_q, n_ctx)
+            _, units, tiles, splits = _stream(plan, desc, [t_q * g], [-(-n_ctx // 64)])
+            assert (n_split, keys) == (splits, tiles * 64)
+            assert splits == 1 or units <= 4096
+            assert splits <= 64 and splits * keys >= n_ctx > (splits - 1) * keys
+            beyond += units > 4096
+            forced = _stream(plan, desc, [t_q * g], [-(-n_ctx // 64)], force=100)
+            assert forced[3] <= (64 if units <= 4096 else 1)
+    assert beyond or (dtype == ad.BF16 and d == 128)
+    assert ad.attn_split_plan(hq, hkv, d, dtype, 256, 1, 0) == (0, 64)
+    assert _stream(plan, desc, [g], [0])[2:] == (1, 1)

@@ -117,3 +117,33 @@ def test_stream_gathered_context(ad, oracle_mod, dtype, d, m, t_q, splits):
                                 29 + total)
     H.check_attention(out.float().cpu().numpy(), ref, **BARS[dtype])
     ctx.close()
+
+
+@pytest.mark.parametrize("form", ["cache", "pool"])
+@pytest.mark.parametrize("dtype,hq,hkv,t_q,n_ctx", [("f32", 32, 8, 256, 350), ("bf16", 32, 8, 64, 2150), ("f32", 32, 8, 4130, 150)])
+def test_stream_two_row_blocks_and_many_units(ad, oracle_mod, dtype, hq, hkv, t_q, n_ctx, form):
+    """Two row blocks in both element types, over a cache and gathered (bf16: with several splits), and more units than
+    arrival counters; 300 sampled outputs."""
+    w = _model(dtype, 64, hq, hkv)
+    ctx = ad.Context.for_workload(w, max_position=1 << 14)
+    c = _full_cache(ad, ctx, w, n_ctx, 3)
+    q, ks, vs = _random(w, 5, t_q, hq, 64), _random(w, 6, t_q, hkv, 64), _random(w, 7, t_q, hkv, 64)
+    if form == "cache":
+        out = ctx.query_attn(c, 0, n_ctx, q, ks, vs, n_ctx)
+        kc, vc = H.to_storage(c.k[0]), H.to_storage(c.v[0])
+    else:
+        off = np.arange(0, n_ctx + 1, 50).astype(np.int64)
+        ids = np.random.default_rng(1).permutation(n_ctx // 50).astype(np.int32)
+        ctx.pool_register(c.k, c.v, off)
+        out = ctx.query_attn_pool(0, ids, None, q, ks, vs, n_ctx)
+        pl = oracle_mod.plan(off, ids, np.arange(len(ids), dtype=np.int32), slot0=0, pos0=0)
+        ko, vo, _ = oracle_mod.assemble(H.to_storage(c.k), H.to_storage(c.v), dtype, w.rope_theta, 0, pl, 0, n_ctx)
+        kc, vc = ko[0], vo[0]
+    rng = np.random.default_rng(2)
+    pairs = np.stack([rng.integers(0, t_q, 300), rng.integers(0, hq, 300)], axis=1).astype(np.int32)
+    pairs[0], pairs[1] = (0, 0), (t_q - 1, hq - 1)
+    ref = oracle_mod.query_attn(kc, vc, dtype, n_ctx, H.to_storage(q), H.to_storage(ks), H.to_storage(vs), w.rope_theta, n_ctx,
+                                pairs=pairs)
+    got = np.stack([out[j, h].float().cpu().numpy() for j, h in pairs])
+    H.check_attention(got, ref, **BARS[dtype])
+    ctx.close()
