@@ -1292,18 +1292,23 @@ static adapshot_status run_probe_entropy(adapshot_ctx* ctx, const float* logits,
         return ADAPSHOT_OK;
     }
     hipStream_t stream = (hipStream_t)hip_stream;
-    // Enough rows of at least one full step for one workgroup each: no partials.  (Also where there are more rows than
-    // arrival counters and a row has several chunks.)
+    // Enough rows of at least one full step for one workgroup each: no partials.
     hipError_t e = hipSuccess;
-    if ((n_rows >= ctx->entropy_rows_min && vocab >= 16384) || (n_rows > kStreamUnits && p.n_chunks > 1)) {
+    if (n_rows >= ctx->entropy_rows_min && vocab >= 16384) {
         e = timed_launch(ctx, ADAPSHOT_KERNEL_ENTROPY_CHUNK, stream, [&] { return launch_entropy_rows(p, answer, stream); });
     } else {
         e = ctx->ent_part.reserve((size_t)n_rows * p.n_chunks * 3 * sizeof(float), ctx->retired);
         if (e != hipSuccess) return fail_hip(ctx, "probe_entropy: workspace", e);
         p.partials = (float*)ctx->ent_part.p;
-        p.counters = ctx->stream_counters;
-        p.counter_stride = counter_stride(n_rows);
-        e = timed_launch(ctx, ADAPSHOT_KERNEL_ENTROPY_CHUNK, stream, [&] { return launch_entropy_fused(p, answer, stream); });
+        if (n_rows > kEntropyFusedRows && p.n_chunks > 1) {
+            e = timed_launch(ctx, ADAPSHOT_KERNEL_ENTROPY_CHUNK, stream, [&] { return launch_entropy_chunk(p, stream); });
+            if (e == hipSuccess)
+                e = timed_launch(ctx, ADAPSHOT_KERNEL_ENTROPY_FINISH, stream, [&] { return launch_entropy_finish(p, answer, stream); });
+        } else {
+            p.counters = ctx->stream_counters;
+            p.counter_stride = counter_stride(n_rows);
+            e = timed_launch(ctx, ADAPSHOT_KERNEL_ENTROPY_CHUNK, stream, [&] { return launch_entropy_fused(p, answer, stream); });
+        }
     }
     if (e != hipSuccess) return fail_hip(ctx, "probe_entropy: launch", e);
     ctx->last_error.clear();
@@ -1340,7 +1345,7 @@ extern "C" adapshot_status adapshot_probe_entropy_static(adapshot_ctx* ctx, cons
     p.partials = ctx->static_ent;  // every (row, chunk) triple is written by the first kernel before the second reads it
     hipStream_t stream = (hipStream_t)hip_stream;
     hipError_t e = launch_entropy_chunk(p, stream);
-    if (e == hipSuccess) e = launch_entropy_finish(p, stream);
+    if (e == hipSuccess) e = launch_entropy_finish(p, nullptr, stream);
     if (e != hipSuccess) return fail_hip(ctx, "probe_entropy_static: launch", e);
     ctx->last_error.clear();
     return ADAPSHOT_OK;

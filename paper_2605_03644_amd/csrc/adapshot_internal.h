@@ -303,7 +303,6 @@ constexpr int kStaticEntropyPartials = 65536;
 // Device address of that array on the CURRENT device (looked up once per device, then remembered).
 hipError_t entropy_static_scratch(float** out);
 hipError_t launch_entropy_chunk(const EntropyParams& p, hipStream_t stream);
-hipError_t launch_entropy_finish(const EntropyParams& p, hipStream_t stream);
 // Eq. (entropy) over a set C of answer tokens, from the same vocabulary-wide partials.
 constexpr int kMaxAnswerTokens = 16;
 struct AnswerTokens {
@@ -311,6 +310,12 @@ struct AnswerTokens {
     int32_t mode;  // ADAPSHOT_ENTROPY_FULL_P / ADAPSHOT_ENTROPY_RENORMALISED
     int32_t id[kMaxAnswerTokens];
 };
+hipError_t launch_entropy_finish(const EntropyParams& p, const AnswerTokens* c, hipStream_t stream);
+// Up to this many rows of several chunks merge in the launch that reduces the chunks.  More rows have counters closer than
+// a line and arrivals that cost what a second launch does (one launch / two, us: 600 x 16000 12.1 / 12.7, 1000 x 10000 13.8 /
+// 14.4, 2000 x 10000 22.0 / 21.4, 4096 x 16383 49.4 / 47.8; a workgroup per row / two launches: 5000 x 16001 74.4 / 67.4,
+// 20000 x 9000 177 / 147).
+constexpr int32_t kEntropyFusedRows = 1024;
 // Chunks and their merge in one launch; c == nullptr: the vocabulary-wide entropy.
 hipError_t launch_entropy_fused(const EntropyParams& p, const AnswerTokens* c, hipStream_t stream);
 // Whole rows in one launch (one workgroup per row); c == nullptr: the vocabulary-wide entropy.

@@ -380,8 +380,9 @@ hipError_t launch_entropy_rows(const EntropyParams& p, const AnswerTokens* c, hi
     return hipGetLastError();
 }
 
-// One wavefront per row merges its chunk partials and writes H (the entry point that has no counters).
-__global__ __launch_bounds__(64) void entropy_finish_kernel(EntropyParams p) {
+// One wavefront per row merges its chunk partials and writes H: calls of many rows, and the entry point that has no counters.
+template <bool TOKENS>
+__global__ __launch_bounds__(64) void entropy_finish_kernel(EntropyParams p, AnswerTokens c) {
     const int row = blockIdx.x;
     const int lane = threadIdx.x;
     Mst acc = {-INFINITY, 0.f, 0.f};
@@ -391,7 +392,7 @@ __global__ __launch_bounds__(64) void entropy_finish_kernel(EntropyParams p) {
         acc = mst_merge(acc, b);
     }
     acc = mst_wave_reduce(acc);
-    finish_row<false>(p, AnswerTokens{}, row, acc, lane);
+    finish_row<TOKENS>(p, c, row, acc, lane);
 }
 
 hipError_t launch_entropy_fused(const EntropyParams& p, const AnswerTokens* c, hipStream_t stream) {
@@ -420,8 +421,9 @@ hipError_t launch_entropy_chunk(const EntropyParams& p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t launch_entropy_finish(const EntropyParams& p, hipStream_t stream) {
-    launch_kernel(entropy_finish_kernel, dim3((unsigned)p.n_rows), dim3(64), stream, p);
+hipError_t launch_entropy_finish(const EntropyParams& p, const AnswerTokens* c, hipStream_t stream) {
+    if (c) launch_kernel(entropy_finish_kernel<true>, dim3((unsigned)p.n_rows), dim3(64), stream, p, *c);
+    else launch_kernel(entropy_finish_kernel<false>, dim3((unsigned)p.n_rows), dim3(64), stream, p, AnswerTokens{});
     return hipGetLastError();
 }
 
