@@ -6,7 +6,7 @@
 
 #include <algorithm>
 #include <functional>
-#include <numeric>
+#include <utility>
 #include <vector>
 
 #include "adapshot.h"
@@ -277,27 +277,32 @@ inline int64_t plan_batch_split_tiles(int64_t n_cu, const std::vector<BatchShape
     return best_st;
 }
 
-// The same for a batch that keeps the matrix cores busy (not a decode step): its items differ in length by design
-// (nested prefixes), and equal splits of the longest one fit the others badly.  Candidates are also the lengths that
-// give every compute unit k workgroups of equal work, with some slack for the remainders; each is dealt out the way the
-// hardware does it (longest first, to the compute unit that is free first) and priced as that finish time plus 0.13
-// tiles per workgroup.  That price is fitted to the two rounds of the probe sweep (8 queries; split length: time per
-// layer): prefixes of 128-512 shots 859: 1120 us, 430: 780, 375: 750, 193: 763, 94: 780, 61: 806; prefixes of 16-64 shots
-// 110: 170 us, 56: 124, 50: 128, 28: 137, 8: 190.  (The chip clocks lower the fewer compute units idle, so a better
-// balance gives about half of what it promises, which the price per workgroup accounts for.)  Only from 32 tiles per
-// compute unit on: below that a launch is mostly prologues, and the equal splits lose less (2 queries, prefixes of 11-91
-// shots, 13 tiles: a pass of 150 us against 172; 1 query, prefixes of 27-221, 16 tiles: 204 against 228).
+// The same where the items do not stream their contexts (kAttnStreamRows): items differ in length by design (nested
+// prefixes), and equal splits of the longest one fit the others badly.  Candidates are also the lengths that give every
+// compute unit k workgroups of equal work, with some slack for the remainders; each is dealt out the way the hardware does it
+// (longest first, to the compute unit that is free first) and priced as that finish time plus 0.13 tiles per workgroup.
+// That price is fitted to the two rounds of one probe sweep (8 queries; split length: time per layer): prefixes of 128-512
+// shots 859: 1120 us, 430: 780, 375: 750, 193: 763, 94: 780, 61: 806; prefixes of 16-64 shots 110: 170 us, 56: 124, 50: 128, 28:
+// 137, 8: 190.  (The chip clocks lower the fewer compute units idle, so a better balance gives about half of what it
+// promises, which the price per workgroup accounts for.)  Away from that sweep (equal splits / these): 8 queries, 5 nested
+// prefixes of 25k tokens, 32/8 heads, 8 / 16 / 33 tokens over caches 253 / 215, 261 / 225, 335 / 309 us, over the pool 360 / 308,
+// 368 / 317, 415 / 365, 28/4 heads, 8 tokens 137 / 123 and 192 / 168; zero-copy decode of 32 contexts of 16k slots 208 / 205.  Only
+// from 32 tiles per compute unit on: below that a launch is mostly prologues, and the equal splits lose less (2 queries,
+// prefixes of 11-91 shots, 13 tiles: a pass of 150 us against 172; 1 query, prefixes of 27-221, 16 tiles: 204 against 228).
+//
+// Compute units that are free at the same time are dealt to together, so that a plan costs the host what the batch has
+// in distinct workgroups, not in workgroups (24 / 64 / 256 items of 7 KV heads: 33 / 157 / 471 us; one workgroup after the other
+// 329 / 842 / 2067; equal splits 16 / 53 / 385).
 constexpr int64_t kBalancedTiles = 32;
 inline int64_t plan_balanced_split_tiles(int64_t n_cu, const std::vector<BatchShape>& shapes) {
-    const double fixed = 2.5, per_wg = 0.13;
-    int64_t longest = 1, total = 0, g = n_cu;
+    const int64_t fixed2 = 5;  // half tiles: 2.5 tiles of launch, first tile round trip and partial write-out of a workgroup
+    const double per_wg = 0.13;
+    int64_t longest = 1, total = 0;
     for (const BatchShape& b : shapes) {
         longest = std::max(longest, b.key_tiles);
         total += b.units * b.key_tiles;
-        g = std::gcd(g, b.units);
     }
     if (total < kBalancedTiles * n_cu) return plan_batch_split_tiles(n_cu, shapes, 0);
-    const int64_t bins = n_cu / g;  // every class of workgroups comes g-fold: one compute unit of g stands for all
     const int64_t floor_tiles = std::min<int64_t>(8, longest);  // shorter splits are all prologue
     std::vector<int64_t> cand;
     for (int n : {1, 2, 3, 4, 6, 8}) cand.push_back((longest + n - 1) / n);
@@ -306,36 +311,48 @@ inline int64_t plan_balanced_split_tiles(int64_t n_cu, const std::vector<BatchSh
     for (int64_t& st : cand) st = std::min(longest, std::max(floor_tiles, st));
     std::sort(cand.begin(), cand.end(), std::greater<int64_t>());
     cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
-    struct Class {
-        double cost;
-        int64_t count;
-    };
-    std::vector<Class> cls;
-    std::vector<double> busy;
+    typedef std::pair<int64_t, int64_t> Class;  // (cost in half tiles, workgroups); of compute units: (time they are free, how many)
+    std::vector<Class> cls, level;
     int64_t best_st = longest;
     double best_t = 1e300;
     for (int64_t st : cand) {
         cls.clear();
-        int64_t n_wg = 0;
+        int64_t n_full = 0, n_wg = 0;
         for (const BatchShape& b : shapes) {
-            const int64_t full = b.key_tiles / st, rem = b.key_tiles - full * st, u = b.units / g;
-            if (full > 0) cls.push_back(Class{(double)st + fixed, full * u});
-            if (rem > 0) cls.push_back(Class{(double)rem + fixed, u});
-            cls.push_back(Class{(double)b.self_tiles + fixed, u});
-            n_wg += (full + (rem > 0) + 1) * u;
+            const int64_t full = b.key_tiles / st, rem = b.key_tiles - full * st;
+            n_full += full * b.units;
+            if (rem > 0) cls.push_back(Class(2 * rem + fixed2, b.units));
+            cls.push_back(Class(2 * b.self_tiles + fixed2, b.units));
+            n_wg += (full + (rem > 0) + 1) * b.units;
         }
-        if (n_wg > 64 * bins) continue;  // many rounds: any of the longer candidates is as good, and cheaper to price
-        std::sort(cls.begin(), cls.end(), [](const Class& x, const Class& y) { return x.cost > y.cost; });
-        busy.assign((size_t)bins, 0.0);  // a heap, the compute unit that is free first on top
-        double t = 0.0;
-        for (const Class& c : cls)
-            for (int64_t i = 0; i < c.count; ++i) {
-                std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
-                busy.back() += c.cost;
-                t = std::max(t, busy.back());
-                std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+        if (n_wg > 64 * n_cu) continue;  // many rounds: any of the longer candidates is as good, and cheaper to price
+        if (n_full > 0) cls.push_back(Class(2 * st + fixed2, n_full));
+        std::sort(cls.begin(), cls.end(), std::greater<Class>());
+        level.assign(1, Class(0, n_cu));  // a heap, the compute units that are free first on top
+        int64_t t2 = 0;
+        for (size_t c = 0; c < cls.size();) {
+            int64_t left = 0;
+            const int64_t cost = cls[c].first;
+            while (c < cls.size() && cls[c].first == cost) left += cls[c++].second;
+            while (left > 0) {
+                Class now(level.front().first, 0);
+                while (!level.empty() && level.front().first == now.first) {
+                    now.second += level.front().second;
+                    std::pop_heap(level.begin(), level.end(), std::greater<Class>());
+                    level.pop_back();
+                }
+                const int64_t n = std::min(now.second, left);
+                left -= n;
+                level.push_back(Class(now.first + cost, n));
+                std::push_heap(level.begin(), level.end(), std::greater<Class>());
+                if (n < now.second) {
+                    level.push_back(Class(now.first, now.second - n));
+                    std::push_heap(level.begin(), level.end(), std::greater<Class>());
+                }
+                t2 = std::max(t2, now.first + cost);
             }
-        t += per_wg * (double)(n_wg * g);
+        }
+        const double t = 0.5 * (double)t2 + per_wg * (double)n_wg;
         if (t < best_t) {
             best_t = t;
             best_st = st;

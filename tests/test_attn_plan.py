@@ -1,8 +1,12 @@
 """How attention calls are cut into workgroups (csrc/attn_plan.h): host logic over sizes, compiled here with the host compiler
 and called directly.  No GPU, no HIP."""
 import ctypes
+import heapq
+import math
 import os
+import random
 import subprocess
+import time
 
 import pytest
 
@@ -31,6 +35,13 @@ extern "C" void stream(const adapshot_model_desc* d, int64_t n_cu, int32_t force
     const StreamPlan p = plan_stream(*d, n_cu, force, s.data(), n);
     out[0] = p.row_blocks, out[1] = p.units, out[2] = p.split_tiles, out[3] = p.n_split;
 }
+static std::vector<BatchShape> batch(const int64_t* shapes, int32_t n) {
+    std::vector<BatchShape> s;
+    for (int32_t i = 0; i < n; ++i) s.push_back(BatchShape{shapes[3 * i], shapes[3 * i + 1], shapes[3 * i + 2]});
+    return s;
+}
+extern "C" int64_t balanced(int64_t n_cu, const int64_t* shapes, int32_t n) { return plan_balanced_split_tiles(n_cu, batch(shapes, n)); }
+extern "C" int64_t equal_splits(int64_t n_cu, const int64_t* shapes, int32_t n) { return plan_batch_split_tiles(n_cu, batch(shapes, n), 0); }
 """
 
 
@@ -40,7 +51,7 @@ def plan(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I",
                     os.path.join(ROOT, "paper_2605_03644_amd", "csrc"), "-x", "c++", "-", "-o", so], input=SHIM.encode(), check=True)
     lib = ctypes.CDLL(so)
-    lib.tile_splits.restype = ctypes.c_int64
+    lib.tile_splits.restype = lib.balanced.restype = lib.equal_splits.restype = ctypes.c_int64
     return lib
 
 
@@ -122,3 +133,61 @@ def test_the_public_plan_is_the_launch_s_plan(plan, hq, hkv, d, dtype):
     assert beyond or (dtype == ad.BF16 and d == 128)
     assert ad.attn_split_plan(hq, hkv, d, dtype, 256, 1, 0) == (0, 64)
     assert _stream(plan, desc, [g], [0])[2:] == (1, 1)
+
+
+def _batch(f, shapes, n_cu=256):
+    flat = [x for s in shapes for x in s]
+    return f(ctypes.c_int64(n_cu), (ctypes.c_int64 * len(flat))(*flat), ctypes.c_int32(len(shapes)))
+
+
+def _balanced_by_dealing(shapes, n_cu):
+    """The rule of plan_balanced_split_tiles, every workgroup dealt by itself."""
+    longest, total = max([1] + [t for _, t, _ in shapes]), sum(u * t for u, t, _ in shapes)
+    cand = [-(-longest // n) for n in (1, 2, 3, 4, 6, 8)]
+    cand += [math.ceil(total * f / (k * n_cu)) for k in (1, 2, 3, 4) for f in (1.02, 1.05, 1.1)]
+    best, best_t = longest, math.inf
+    for st in sorted({min(longest, max(min(8, longest), c)) for c in cand}, reverse=True):
+        wgs = []
+        for units, tiles, own in shapes:
+            wgs += ([st + 2.5] * (tiles // st) + [tiles % st + 2.5] * (tiles % st > 0) + [own + 2.5]) * units
+        if len(wgs) > 64 * n_cu:
+            continue
+        busy, end = [0.0] * n_cu, 0.0
+        for w in sorted(wgs, reverse=True):
+            t = heapq.heappop(busy) + w
+            heapq.heappush(busy, t)
+            end = max(end, t)
+        if end + 0.13 * len(wgs) < best_t:
+            best, best_t = st, end + 0.13 * len(wgs)
+    return best
+
+
+def test_balanced_split_length(plan):
+    rng = random.Random(3)
+    for _ in range(60):
+        hkv = rng.choice([1, 2, 3, 4, 5, 7, 8])
+        shapes = [(hkv * rng.randint(1, 2), rng.randint(0, 500), rng.randint(1, 2)) for _ in range(rng.randint(1, 20))]
+        n_cu = rng.choice([64, 104, 256])
+        if sum(u * t for u, t, _ in shapes) < 32 * n_cu:
+            assert _batch(plan.balanced, shapes, n_cu) == _batch(plan.equal_splits, shapes, n_cu)
+        else:
+            assert _batch(plan.balanced, shapes, n_cu) == _balanced_by_dealing(shapes, n_cu)
+
+
+@pytest.mark.parametrize("hkv", [1, 3, 4, 5, 7, 8])
+def test_balanced_split_length_costs_what_the_items_cost(plan, hkv):
+    """The host's time for a plan follows the items, not the workgroups: a few times that of the equal splits' plan, whatever
+    the number of KV heads (dealt one by one, 64 items of 5 or 7 KV heads took 13 to 16 times as long)."""
+    rng = random.Random(hkv)
+    shapes = [(hkv, rng.randint(100, 700), 1) for _ in range(64)]
+
+    def best(f):
+        t = math.inf
+        for _ in range(15):
+            t0 = time.perf_counter()
+            for _ in range(4):
+                _batch(f, shapes)
+            t = min(t, time.perf_counter() - t0)
+        return t
+
+    assert best(plan.balanced) < 7 * best(plan.equal_splits)
