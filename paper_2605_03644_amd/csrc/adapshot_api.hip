@@ -998,7 +998,7 @@ extern "C" adapshot_status adapshot_query_attn_pool(adapshot_ctx* ctx, int32_t l
     }
     ctx->pool_key.clear();  // the tables are about to be rewritten, and a batch's tables point into them
     ctx->batch_key.clear();
-    const int64_t n_tiles = (total + 63) / 64;
+    const int64_t n_tiles = attn_mfma_supported(d) ? (total + 63) / 64 : 0;  // the streaming kernel needs no tile_rot
     hipError_t e = ctx->pool_src.reserve((size_t)(total + 256) * sizeof(int32_t), ctx->retired);  // the kernel reads it 1 KB at a time
     if (e == hipSuccess) e = ctx->pool_rot.reserve((size_t)n_tiles * (d.head_dim / 2) * sizeof(float2), ctx->retired);
     if (e != hipSuccess) return fail_hip(ctx, "query_attn_pool: workspace", e);
@@ -1140,7 +1140,7 @@ extern "C" adapshot_status adapshot_query_attn_pool_batched(adapshot_ctx* ctx, i
     } else if (longest > 0) {
         ctx->pool_key.clear();
         ctx->batch_key.clear();  // its tables point into what is rewritten now
-        const int64_t n_tiles = (longest + 63) / 64;
+        const int64_t n_tiles = attn_mfma_supported(d) ? (longest + 63) / 64 : 0;  // the streaming kernel needs no tile_rot
         hipError_t e = ctx->pool_src.reserve((size_t)(list_base[(size_t)n_lists] + 256) * sizeof(int32_t), ctx->retired);
         if (e == hipSuccess) e = ctx->pool_rot.reserve((size_t)n_tiles * (d.head_dim / 2) * sizeof(float2), ctx->retired);
         if (e != hipSuccess) return fail_hip(ctx, "query_attn_pool_batched: workspace", e);

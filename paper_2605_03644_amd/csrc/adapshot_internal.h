@@ -152,7 +152,6 @@ struct StreamItem {
     char* out;
     const char* k_ctx;  // one layer of the context (assembled cache or pool)
     const char* v_ctx;
-    int64_t slot0;      // zero-copy form: first entry of the context in slot_src
     int32_t n_ctx, t_q, q_pos0;
     int32_t keys_per_split, n_split;  // the last split also takes the query's own tokens
     int32_t unit0;      // first unit of the problem in the workspaces

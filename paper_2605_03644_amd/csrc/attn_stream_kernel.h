@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     auto pool_tok = [&](int u) __attribute__((always_inline)) -> int {
         u = u < nk ? u : nk - 1;
         u = u > 0 ? u : 0;
-        return p.slot_src[it.slot0 + k0 + u];
+        return p.slot_src[k0 + u];
     };
     auto fetch_tok = [&](int s) __attribute__((always_inline)) {
         if (POOL && nk > 0) {
