@@ -639,7 +639,7 @@ def test_two_contexts_on_two_streams(ad, oracle_mod):
 def test_other_head_shapes(ad, oracle_mod, dtype, d, hq, hkv):
     """Every head_dim the library accepts besides the workloads' own (fp32: 8..128, bf16: 16..256 in powers of
     two), with grouped, ungrouped and single kv heads: assemble in both key states, then attention over the
-    result (the one-wavefront kernel serves every shape the matrix-core kernel does not)."""
+    result (the streaming kernel serves every shape that the tile kernel does not)."""
     import dataclasses
     w = dataclasses.replace(wl.WORKLOADS["tiny_fp32"], name=f"shape_{dtype}_{d}", n_q_heads=hq, n_kv_heads=hkv,
                             head_dim=d, dtype=dtype, rope_theta=5.0e5)

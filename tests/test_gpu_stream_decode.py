@@ -81,18 +81,28 @@ def test_decode_ragged_batch(ad, oracle_mod):
     ctx.query_attn_batched(caches, 0, two)
     torch.cuda.synchronize()
     assert torch.equal(two[0][6], two[1][6])
-    assert float((two[0][6].float() - items[2][6].float()).abs().max()) <= 2e-2
+    # the two kernels round P and the partials differently; relative to the output, as everywhere, so that a split that is
+    # left out is seen (1/79 of 5000 keys: 0.11)
+    H.check_attention(two[0][6].float().cpu().numpy(), items[2][6].double().cpu().numpy(), **BAR)
     ctx.close()
 
 
 def test_decode_beyond_the_streaming_share(ad):
-    """Contexts on either side of the border (200 MB) agree: the last slots' keys are those of the shorter one."""
+    """Contexts on either side of the border between the two kernels (200 MB), each against a float32 reference.  The bar is
+    relative to the output (means over 49k keys are small): one of 64 splits left out would be 0.12 of it."""
     w = _model(32, 8)
     n = 49152   # 201 MB
     ctx = ad.Context.for_workload(w, max_position=1 << 17)
     c = _cache(ad, ctx, w, n, 9)
     q, ks, vs = _random(w, 5, 1, 32, 128), _random(w, 6, 1, 8, 128), _random(w, 7, 1, 8, 128)
-    outs = [ctx.query_attn(c, 0, m, q, ks, vs, n).float() for m in (n, n - 512)]
+    outs = []
+    for m, merges in ((n, 1), (n - 512, 0)):           # the tile kernel has a merge of its own
+        ctx.profile_enable(True)
+        outs.append(ctx.query_attn(c, 0, m, q, ks, vs, n).float())
+        torch.cuda.synchronize()
+        prof = ctx.profile_read()
+        ctx.profile_enable(False)
+        assert (prof["query_attn"][1], prof["attn_combine"][1]) == (1, merges)
     kf, vf = c.k[0].float(), c.v[0].float()
     for m, out in zip((n, n - 512), outs):
         got = out[0].view(8, 4, 128)
@@ -104,5 +114,5 @@ def test_decode_beyond_the_streaming_share(ad):
         for hk in range(8):
             keys, vals = torch.cat([kf[:m, hk], kr[hk:hk + 1]]), torch.cat([vf[:m, hk], vs[0].float()[hk:hk + 1]])
             p = torch.softmax(qr[hk] @ keys.T / 128.0 ** 0.5, dim=-1)
-            assert float((got[hk] - p @ vals).abs().max()) <= 2e-2
+            H.check_attention(got[hk].cpu().numpy(), (p @ vals).double().cpu().numpy(), **BAR)
     ctx.close()

@@ -99,8 +99,7 @@ def test_zero_copy_llama70b_128k_sampled(ad, oracle_mod):
 
 
 def test_zero_copy_generic_kernel_fp32(ad, oracle_mod):
-    """The fp32 / head_dim 64 workload goes through the generic kernel, which gathers and rotates on the way into the
-    score: single calls (with an order, a position base, a duplicate) and a batch over two lists."""
+    """The fp32 / head_dim 64 workload goes through the streaming kernel, which gathers and rotates the keys in registers: single calls (with an order, a position base, a duplicate) and a batch over two lists."""
     w = wl.WORKLOADS["tiny_fp32"]
     ids, order = wl.selection(w)
     _case(ad, oracle_mod, w, ids, order, w.t_q)
