@@ -1396,7 +1396,9 @@ static adapshot_status rank_prepare(adapshot_ctx* ctx, int32_t layer, hipStream_
     const size_t off_seg0 = up16(off_split + seg_max * sizeof(int32_t));
     const size_t off_shot_seg = up16(off_seg0 + ((size_t)n_split + 1) * sizeof(int32_t));
     const size_t off_inv = up16(off_shot_seg + ((size_t)n + 1) * sizeof(int32_t));
-    const size_t tab_bytes = up16(off_inv + (size_t)n * sizeof(float));
+    const size_t off_bits = up16(off_inv + (size_t)n * sizeof(float));
+    const size_t bit_words = (size_t)((n_tok - tok0 + 31) / 32);
+    const size_t tab_bytes = up16(off_bits + bit_words * sizeof(uint32_t));
 
     const bool rotate = d.key_state == ADAPSHOT_KEYS_UNROTATED;
     hipError_t e = hipSuccess;
@@ -1413,6 +1415,8 @@ static adapshot_status rank_prepare(adapshot_ctx* ctx, int32_t layer, hipStream_
     int32_t* split_seg0 = (int32_t*)((char*)host + off_seg0);
     int32_t* shot_seg0 = (int32_t*)((char*)host + off_shot_seg);
     float* inv_len = (float*)((char*)host + off_inv);
+    uint32_t* end_bits = (uint32_t*)((char*)host + off_bits);
+    memset(end_bits, 0, bit_words * sizeof(uint32_t));
     int32_t n_seg = 0, split = 0;
     int64_t max_len = 0, split_end = tok0 + kps;
     split_seg0[0] = 0;
@@ -1430,6 +1434,7 @@ static adapshot_status rank_prepare(adapshot_ctx* ctx, int32_t layer, hipStream_
             }
             const int64_t stop = std::min(end, split_end);
             seg_end[n_seg] = (int32_t)stop;
+            end_bits[(stop - 1 - tok0) / 32] |= 1u << ((stop - 1 - tok0) & 31);
             seg_split[n_seg++] = split;
             t = stop;
         }
@@ -1447,6 +1452,7 @@ static adapshot_status rank_prepare(adapshot_ctx* ctx, int32_t layer, hipStream_
     ctx->rank_split_seg0 = (const int32_t*)(tab + off_seg0);
     ctx->rank_shot_seg0 = (const int32_t*)(tab + off_shot_seg);
     ctx->rank_inv_len = (const float*)(tab + off_inv);
+    ctx->rank_end_bits = (const uint32_t*)(tab + off_bits);
     if (rotate) {
         RankPrepareParams rp;
         rp.k_pool = (const char*)ctx->k_pool + (int64_t)layer * ctx->pool_layer_stride_tokens * ctx->row_bytes;
@@ -1568,6 +1574,8 @@ extern "C" adapshot_status adapshot_rank_shots(adapshot_ctx* ctx, int32_t layer,
     sp.tab_hi = ctx->tab_hi;
     sp.seg_end = ctx->rank_seg_end;
     sp.split_seg0 = ctx->rank_split_seg0;
+    sp.end_bits = ctx->rank_end_bits;
+    sp.n_seg = ctx->rank_n_seg;
     sp.part = (float*)ctx->part_o.p;
     sp.part_ml = (float2*)ctx->part_ml.p;
     sp.q_pos0 = q_pos0;

@@ -250,6 +250,7 @@ struct RankScoreParams {
     const float2* tab_hi;
     const int32_t* seg_end;     // [n_seg] one past the segment's last key
     const int32_t* split_seg0;  // [n_split + 1] first segment of every split
+    const uint32_t* end_bits;   // a bit per key from key0 on: a segment ends with it
     float* part;              // [n_seg][pairs], pair = kv head * rows + row
     float2* part_ml;          // [n_split][pairs] (reference maximum in log2 units, row sum)
     int64_t q_pos0;
@@ -257,6 +258,7 @@ struct RankScoreParams {
     int32_t key0, n_tok;      // keys [key0, n_tok)
     int32_t keys_per_split;   // multiple of 64
     int32_t n_split, t_q, n_q_heads, n_kv_heads;
+    int32_t n_seg;
 };
 hipError_t launch_rank_scores(const RankScoreParams& p, hipStream_t stream);
 struct RankReduceParams {
@@ -413,6 +415,7 @@ struct adapshot_ctx {
     const int32_t* rank_seg_split = nullptr;
     const int32_t* rank_split_seg0 = nullptr;
     const int32_t* rank_shot_seg0 = nullptr;
+    const uint32_t* rank_end_bits = nullptr;
     const float* rank_inv_len = nullptr;
     std::vector<void*> retired;  // outgrown workspaces, freed when the context is destroyed
     adapshot::Profiler prof;

@@ -26,6 +26,21 @@
 // else.  128 query tokens, 32/8 heads, 209k
 // tokens: 223 us when the GPU was idle before, 250 us back to back (0.88 PFLOP/s of the one product); through the attention
 // kernel with one-hot value rows 339 / 369 us.
+//
+// That is for N(0,1) queries and keys.  A wavefront leaves the interleaved loop for the rest of its split once a row of its 64
+// has a first maximum beyond 2^+-40 or a sum beyond 2^80.  A whole ranking, this / one-hot value rows (us): keys 3 / 8 / 12 times
+// as large 241 / 360, 255 / 380, 335 / 392 (there every wavefront leaves at its first block); every shot's first key 12 times as
+// large (an attention sink) 265 / 387; a mean of 2 common to queries and keys 259 / 357.
+//
+// Short shots: a segment that ends inside a block costs about 0.25 us a wavefront by factors, whatever its length, and a block of
+// many ends about 1.1 us by the one-hot product (short_sums; its 16 fp32 instructions take 1024 cycles).  30000 tokens in
+// shots of 1 / 2 / 4 / 6 / 8 / 10, a whole ranking, us; one-hot value rows -- one-hot product -- factors:
+//   16 query tokens   240  127   83   63   56   49      89   71   61   58   57   56     270  150   89   69   58   52
+//   64 (256 rows)     313  162  107   81   72   64     131  100   87   83   82   80     302  171  111   86   74   68
+//   128 (512 rows)    576  280  166  128  116   99     223  158  135  129  125  122     385  215  137  107   95   89
+// so the product is taken up to a mean of 6 keys a segment, with two row blocks up to 4.  (With up to 64 query tokens shots of 7 to
+// 12 tokens stay 3 to 7 % behind the one-hot value rows; from 15 tokens on this is never slower.)  A segment's end is fetched
+// a segment ahead: 1 to 3 % for shots of ten tokens.
 #include <type_traits>
 
 #include "mfma_tiles.h"
@@ -40,11 +55,13 @@ constexpr int kTileBytes = kTileKeys * kRowBytes;
 constexpr int kBuf = 4;    // K tiles in LDS
 constexpr int kWaves = 8;
 constexpr int kFrag = 4;   // LDS fragment reads in flight
+constexpr int kShortKeys[2] = {6, 4};  // mean keys of a segment up to which the short form is taken: one, two row blocks
 constexpr float kLimit = 1.2089258196146292e24f;  // 2^80
 constexpr float kUnset = -3.0e38f;                // reference of a row that has seen no key: everything exceeds it
 }  // namespace
 
-template <int NR>
+// SHORT: the form for short shots, which sums the segments that end in a block by matrix instructions (see short_sums).
+template <int NR, bool SHORT>
 __global__ __launch_bounds__(kWaves * 64) void rank_scores_kernel(RankScoreParams p, int n_row_tiles) {
     constexpr int PASSES = kTileBytes / (kWaves * 1024);  // 1 KB blocks of a tile per wavefront
     __shared__ __attribute__((aligned(16384))) char k_s[kBuf][kTileBytes];
@@ -159,7 +176,12 @@ __global__ __launch_bounds__(kWaves * 64) void rank_scores_kernel(RankScoreParam
     const table_t seg_end = (table_t)(uintptr_t)p.seg_end, seg0 = (table_t)(uintptr_t)p.split_seg0;
     const int seg_first = seg0[split], seg_stop = seg0[split + 1];
     int seg = seg_first;
-    int next_end = seg_end[seg] - k0;
+    // end of the segment (relative to k0; behind the split's last: none) -- `after`, the next one's, is fetched a segment ahead
+    auto end_of = [&](int q) __attribute__((always_inline)) -> int {
+        const int e = seg_end[q < seg_stop ? q : seg_stop - 1] - k0;
+        return q < seg_stop ? e : 0x7fffffff;
+    };
+    int next_end = end_of(seg), after = end_of(seg + 1);
     const int64_t n_pairs = (int64_t)rows * p.n_kv_heads;
     const int my_row = row_base + (NR == 2 ? lane : l32);  // the row this lane stores
     const bool store_on = my_row < rows && (NR == 2 || hh == 0);
@@ -180,10 +202,12 @@ __global__ __launch_bounds__(kWaves * 64) void rank_scores_kernel(RankScoreParam
     block_t s0, s1;
     float m[NR], acc[NR];
     float l_run = 0.f;  // of my_row
+    float l_short[NR];  // SHORT: of row l32 of every row block, what this half of the lanes has stored
 #pragma unroll
     for (int rb = 0; rb < NR; ++rb) {
         m[rb] = 0.f;
         acc[rb] = 0.f;
+        l_short[rb] = 0.f;
     }
 
     // Pointers to the fragments of tile t
@@ -295,6 +319,7 @@ __global__ __launch_bounds__(kWaves * 64) void rank_scores_kernel(RankScoreParam
             alpha[rb] = __builtin_amdgcn_exp2f(m[rb] - m_new);
             m[rb] = m_new;
             acc[rb] *= alpha[rb];
+            if (SHORT) l_short[rb] *= alpha[rb];
         }
         const float al = NR == 2 && hh ? alpha[NR - 1] : alpha[0];
         l_run *= al;
@@ -307,10 +332,92 @@ __global__ __launch_bounds__(kWaves * 64) void rank_scores_kernel(RankScoreParam
         if (NR == 2) o |= !(x[NR - 1] <= kLimit);
         return __builtin_amdgcn_ballot_w64(o) != 0;
     };
+    // The segments that end in the block, all of them at once: sums = one-hot . P with v_mfma_f32_32x32x2_f32.  Register r of a
+    // block is the B operand as it stands (lane = row, key 2r + l/32); the A operand's lane holds 1 where that key belongs to
+    // the segment l%32 of the block.  Products with 0 and 1 and sums in fp32.  Row i of the result, in the lanes of half
+    // (i/4)%2, is the sum of the block's segment i; the one behind the last end is carried on.
+    auto short_sums = [&](unsigned ends, const block_t& s) __attribute__((always_inline)) {
+        constexpr int CH = NR == 1 ? 2 : 1;  // chains of products: two row blocks are two already
+        const int n_end = __builtin_popcount(ends);  // >= 1
+        f32x16 d[NR][CH];
+#pragma unroll
+        for (int rb = 0; rb < NR; ++rb) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+                d[rb][c] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            const float c = sum_xhalf(acc[rb]);  // what the first segment has from the blocks before
+            d[rb][0][0] = hh ? 0.f : c;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int before = __builtin_popcount(__builtin_amdgcn_ubfe(ends, 0, 2 * r + hh));  // the key's segment
+            const float one = before == l32 ? 1.f : 0.f;
+#pragma unroll
+            for (int rb = 0; rb < NR; ++rb)
+                d[rb][r % CH] = __builtin_amdgcn_mfma_f32_32x32x2f32(one, s[rb][r], d[rb][r % CH], 0, 0, 0);
+        }
+        if (CH == 2) d[0][0] += d[0][CH - 1];
+        float* out[NR];
+        int lim[NR];
+#pragma unroll
+        for (int rb = 0; rb < NR; ++rb) {
+            const int row = row_base + 32 * rb + l32;
+            out[rb] = p.part + (int64_t)(seg + 4 * hh) * n_pairs + (int64_t)hk * rows + row;
+            lim[rb] = row < rows ? n_end - 4 * hh : 0;
+        }
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4)
+            if (8 * i4 < n_end) {
+#pragma unroll
+                for (int i = 4 * i4; i < 4 * i4 + 4; ++i) {
+                    const int first = 8 * i4 + (i & 3);
+#pragma unroll
+                    for (int rb = 0; rb < NR; ++rb)
+                        if (first < lim[rb]) {
+                            l_short[rb] += d[rb][0][i];
+                            out[rb][first * n_pairs] = d[rb][0][i];
+                        }
+                }
+            }
+        const int i_rest = (n_end >> 3) * 4 + (n_end & 3);
+        const bool here = n_end < 32 && hh == ((n_end >> 2) & 1);
+#pragma unroll
+        for (int rb = 0; rb < NR; ++rb) {
+            const f32x16 v = d[rb][0];
+            const float x = v[i_rest & 15];
+            acc[rb] = here ? x : 0.f;
+        }
+        seg += n_end;
+    };
+    // The bits of the segment ends in the block that begins at key_b: 0 behind the last key
+    auto block_ends = [&](int key_b) __attribute__((always_inline)) -> unsigned {
+        const int b = key_b < n_keys ? key_b : 0;
+        const unsigned w = ((table_t)(uintptr_t)p.end_bits)[(split * p.keys_per_split + b) >> 5];
+        return key_b < n_keys ? w : 0u;
+    };
+    unsigned ends_here = SHORT ? block_ends(0) : 0u;  // of the next block to sum, fetched a block ahead
     // Sums of a block whose exponentials are in s.  `moved`: references other than 0 are in use, and moved where that is
     // needed; without it the result says whether the sums were in range, and nothing has changed where they were not.
     auto sums = [&](int t, int kb, block_t& s, bool moved) __attribute__((always_inline)) -> bool {
         const int key_b = t * kTileKeys + kb * 32;  // first key of the block
+        if constexpr (SHORT) {
+            float a[NR];
+            whole_sums(s, a);
+            if (__builtin_expect(is_over(a), 0)) {
+                if (!moved) return false;
+                move_references(t, kb, s);
+                whole_sums(s, a);
+            }
+            const unsigned ends = ends_here;
+            ends_here = block_ends(key_b + 32);
+            if (ends) {
+                short_sums(ends, s);
+            } else {
+#pragma unroll
+                for (int rb = 0; rb < NR; ++rb) acc[rb] = a[rb];
+            }
+            return true;
+        }
         // a: the sum of the segment that ends here (or with the whole block, nothing ending), b: of what lies behind it
         float a[NR], b[NR];
         if (__builtin_expect(next_end > key_b + 32, 1)) {
@@ -338,7 +445,8 @@ __global__ __launch_bounds__(kWaves * 64) void rank_scores_kernel(RankScoreParam
         flush(a);
         ++seg;
         int done = next_end - key_b;  // keys of the block whose segments have left
-        next_end = seg < seg_stop ? seg_end[seg] - k0 : 0x7fffffff;
+        next_end = after;
+        after = end_of(seg + 1);
         while (next_end <= key_b + 32) {  // short segments that begin and end in this block: 0 / 1 factors
             const float lo = (float)(done - hh), hi = (float)(next_end - key_b - hh);
 #pragma unroll
@@ -356,7 +464,8 @@ __global__ __launch_bounds__(kWaves * 64) void rank_scores_kernel(RankScoreParam
             flush(a);
             ++seg;
             done = next_end - key_b;
-            next_end = seg < seg_stop ? seg_end[seg] - k0 : 0x7fffffff;
+            next_end = after;
+            after = end_of(seg + 1);
         }
 #pragma unroll
         for (int rb = 0; rb < NR; ++rb) acc[rb] = b[rb];
@@ -415,6 +524,10 @@ __global__ __launch_bounds__(kWaves * 64) void rank_scores_kernel(RankScoreParam
             sums(t, 1, s1, true);
         }
     }
+    if (SHORT) {
+        const float l0 = sum_xhalf(l_short[0]), l1 = sum_xhalf(l_short[NR - 1]);
+        l_run += NR == 2 && hh ? l1 : l0;
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the loads past the end must land before LDS is released
     if (!wave_idle && store_on)
         p.part_ml[(int64_t)split * n_pairs + (int64_t)hk * rows + my_row] = make_float2(NR == 2 && hh ? m[NR - 1] : m[0], l_run);
@@ -424,12 +537,18 @@ hipError_t launch_rank_scores(const RankScoreParams& p, hipStream_t stream) {
     const int rows = p.t_q * (p.n_q_heads / p.n_kv_heads);
     // Two row blocks per wavefront halve the LDS reads per product (512 rows: 223 us against 230 us in two tiles of 256); up
     // to 256 rows they would leave wavefronts idle.
-        const int tile = rows > 256 ? 512 : 256;
+    const int tile = rows > 256 ? 512 : 256;
     const int n_row_tiles = (rows + tile - 1) / tile;
     const unsigned blocks = (unsigned)(p.n_kv_heads * n_row_tiles * p.n_split);
     if (blocks == 0) return hipSuccess;
-    if (tile == 512) launch_kernel(rank_scores_kernel<2>, dim3(blocks), dim3(kWaves * 64), stream, p, n_row_tiles);
-    else launch_kernel(rank_scores_kernel<1>, dim3(blocks), dim3(kWaves * 64), stream, p, n_row_tiles);
+    const bool short_segments = (int64_t)p.n_seg * kShortKeys[tile == 512] >= p.n_tok - p.key0;
+    if (tile == 512) {
+        if (short_segments) launch_kernel((rank_scores_kernel<2, true>), dim3(blocks), dim3(kWaves * 64), stream, p, n_row_tiles);
+        else launch_kernel((rank_scores_kernel<2, false>), dim3(blocks), dim3(kWaves * 64), stream, p, n_row_tiles);
+    } else {
+        if (short_segments) launch_kernel((rank_scores_kernel<1, true>), dim3(blocks), dim3(kWaves * 64), stream, p, n_row_tiles);
+        else launch_kernel((rank_scores_kernel<1, false>), dim3(blocks), dim3(kWaves * 64), stream, p, n_row_tiles);
+    }
     return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
 """The key pass of relevance ranking (bf16, head_dim 128) where it can go wrong: shots that begin, end or lie inside a block
-of 32 keys, shots cut by a split, partial row tiles of both widths, and score ranges that move the rows' references."""
+of 32 keys, many of them in one, shots cut by a split, partial row tiles of both widths, and score ranges that move the rows'
+references."""
 import numpy as np
 import pytest
 import torch
@@ -24,6 +25,11 @@ LENGTHS = {
     "whole_blocks": [32, 64, 96, 256, 512] * 2,
     "one_long": [1500],
     "mixed": [700, 1, 48, 160, 33, 290, 2, 2, 2, 129],
+    # few keys a segment: the form that sums a block's segments by matrix instructions
+    "short": [1, 2, 3, 4, 5, 31, 1, 1, 2, 7, 33, 1] * 19,
+    "fours": [4] * 300,
+    "tens": [10] * 150,
+    "long_then_ones": [300] + [1] * 70 + [65] + [1, 1, 2] * 30,
 }
 # factor of key u's length, of n keys: the usual range; a range that grows or shrinks by hundreds of log2 units inside a
 # split; scores that lie far from 0 from the first key on
@@ -89,4 +95,23 @@ def test_rank_wide_row_tiles_against_oracle(ad, oracle_mod, key_state, t_q, h_q,
     err = np.abs(got - want)   # the rotated query is rounded to bf16 on the GPU, not in the oracle
     assert float(err.max()) <= 2e-2 * want.max() and float((err / want).mean()) < 5e-3
     assert abs(float((got * np.diff(off)).sum()) - 1.0) < 1e-5   # fp32 sums: all attention mass is accounted for
+    ctx.close()
+
+
+@pytest.mark.parametrize("t_q", [3, 80])
+def test_rank_short_shots_in_a_pool_that_begins_late(ad, oracle_mod, t_q):
+    """Shots of one to five tokens, un-rotated keys, the first shot at token 5, one and two row blocks per wavefront."""
+    rng = np.random.default_rng(t_q)
+    off = (np.concatenate([[0], np.cumsum(rng.integers(1, 6, 700))]) + 5).astype(np.int64)
+    g = torch.Generator(device="cuda"); g.manual_seed(t_q)
+    k = torch.randn(1, int(off[-1]), 4, 128, device="cuda", generator=g).bfloat16()
+    q = torch.randn(t_q, 28, 128, device="cuda", generator=g).bfloat16()
+    ctx = ad.Context(1, 28, 4, 128, 5.0e5, ad.BF16, key_state=ad.KEYS_UNROTATED, max_position=1 << 12)
+    ctx.pool_register(k, k.clone(), off)
+    got = ctx.rank_shots(0, q, q_pos0=9).cpu().numpy().astype(np.float64)
+    want = oracle_mod.rank_scores(H.to_storage(k[:, 5:].contiguous())[0], "bf16", off - 5, H.to_storage(q), 5.0e5,
+                                  ad.KEYS_UNROTATED, q_pos0=9)
+    err = np.abs(got - want)   # the bars of the wide-tile test above, for the same reason
+    assert float(err.max()) <= 2e-2 * want.max() and float((err / want).mean()) < 5e-3
+    assert abs(float((got * np.diff(off)).sum()) - 1.0) < 1e-5
     ctx.close()
