@@ -136,16 +136,17 @@ adapshot_status adapshot_assemble(adapshot_ctx* ctx, adapshot_cache* cache, cons
  * v_self (DEVICE) are given WITHOUT rotation: the library rotates row j of q and
  * k_self to position q_pos0 + j.  n_ctx <= cache->len.  out: DEVICE
  * [t_q][n_q_heads][head_dim] in desc.dtype.  Scores and the online softmax are kept
- * in fp32; bf16 models use bf16 MFMA for q k^T and p v with fp32 accumulation, and the
- * partial outputs of the context splits are exchanged as fp16 rows scaled by their
- * largest element (error <= 2^-11 of that element, below the bf16 rounding of out).
+ * in fp32; bf16 models use bf16 MFMA for q k^T and p v with fp32 accumulation.  The partial outputs of
+ * the context splits are exchanged in fp32, or, by bf16 models with head_dim 128 beyond decode steps, as fp16
+ * rows scaled by their largest element (error <= 2^-11 of that element, below the bf16 rounding of out).
  * Accuracy of the bf16 path depends on the data: the rotated, pre-scaled query and the keys are bf16
  * matrix operands, so a score carries about 2^-9 of its own magnitude as error and the output error
  * grows with the spread of the scores.  With N(0,1) queries, keys and values the outputs stay within
  * 2e-2 (max-abs) of the exact result; keys three times as large were measured at 1.9e-2, eight times
  * as large at 6e-2.  Accumulation, maxima and sums are fp32 throughout.
  * A value of v_self that is not finite reaches only the rows that attend to its token.  Exception: bf16 models with
- * head_dim 128 in calls of more than 8 query rows per kv head, where it can make NaN of every row of the call.
+ * head_dim 128 in calls beyond decode steps (more than 8 query rows per kv head, or more than 200 MB of context; zero-copy
+ * calls always), where it can make NaN of every row of the call.
  * Errors, all found before anything is launched (out is then untouched): EINVAL (null or
  * misaligned pointer, t_q < 1, layer out of range, n_ctx < 0, q_pos0 < 0, a q of 2 GiB or more, or a
  * context or query whose K/V rows span more than 4 GiB in one layer), ESTATE (n_ctx beyond
@@ -221,7 +222,7 @@ adapshot_status adapshot_query_attn_batched(adapshot_ctx* ctx, const adapshot_ca
  * n_ctx is a token count, at most the list's length: the probes of one query over nested prefixes of its ranked
  * list (Probe-based Dynamic Evaluation) are items of one list, and no shot is copied for a prefix that the stopping
  * rule then rejects.  Out[i] is what adapshot_query_attn_batched gives over caches assembled from the same lists
- * (same kernels' arithmetic; parity bar of adapshot_query_attn).  Three launches (two when the lists equal
+ * up to rounding (parity bar of adapshot_query_attn; decode steps over caches may run another kernel).  Three launches (two when the lists equal
  * the previous call's: the plan is kept for the next layer): the plan of all lists, the attention grid over
  * all items, the merge of the partials (bf16 models with head_dim 128, for which a pool layer
  * must stay below 4 GiB, ECAPACITY; other shapes run item by item).  Pools registered with ADAPSHOT_KEYS_UNROTATED
@@ -248,8 +249,8 @@ adapshot_status adapshot_probe_entropy(adapshot_ctx* ctx, const float* logits, i
                                        void* hip_stream);
 
 /* adapshot_probe_entropy for callers that cannot allocate device memory: code under HIP graph capture,
- * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels, same results; the
- * chunk partials go to a 768 KiB array that lives in the library's code object on every GPU it runs on
+ * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same arithmetic, always two kernels
+ * (chunks, then their merge); the chunk partials go to a 768 KiB array that lives in the library's code object on every GPU it runs on
  * (held until the process ends) instead of a workspace of the context, and nothing is allocated, freed or
  * waited for, on the host or the device.  The array holds 65536 partials, one per (row, chunk of a row);
  * rows are cut into chunks of 8192 logits, or of 4096, 2048 or 1024 while that leaves fewer than four
@@ -283,14 +284,13 @@ adapshot_status adapshot_probe_entropy_tokens(adapshot_ctx* ctx, const float* lo
  * The softmax runs over the whole pool (read inside one shot only, as printed, every row sums to 1 and
  * the average is 1 / T_i whatever the content).  Keys are taken as a cache holds them: encoded at their
  * position inside the shot (Eq. prefill); for a pool registered with ADAPSHOT_KEYS_UNROTATED the library
- * builds that encoding of the layer once and keeps it, together with one more layer-sized buffer, until
- * another layer is ranked, the pool is registered again or the context is destroyed.  The kept state is
+ * builds that encoding of the layer once and keeps it (a layer-sized buffer) until another layer is ranked, the pool is registered again or the context is destroyed.  The kept state is
  * tied to the registration, not to the bytes: after rewriting pool contents in place, call
  * adapshot_pool_register again before ranking.  The query is encoded on its own: token j at position
  * q_pos0 + j.  The reduction order is fixed: the same inputs give bit-identical scores.
  * q: DEVICE [t_q][n_q_heads][head_dim] without rotation; scores_out: DEVICE fp32 [n_shots].
- * Every shot must hold at least one token.  bf16 models with head_dim 128 run the matrix-core attention kernel
- * over the pool (a pool layer must stay below 4 GiB, ECAPACITY); other shapes run a plain kernel (one wavefront
+ * Every shot must hold at least one token.  bf16 models with head_dim 128 run a matrix-core kernel of
+ * their own over the pool (a pool layer must stay below 4 GiB, ECAPACITY); other shapes run a plain kernel (one wavefront
  * per query token and head over the whole layer: for small models and checks, not tuned), head_dim <= 1024. */
 adapshot_status adapshot_rank_shots(adapshot_ctx* ctx, int32_t layer, const void* q, int32_t t_q, int64_t q_pos0,
                                     float* scores_out, void* hip_stream);
@@ -334,7 +334,8 @@ typedef enum {
     ADAPSHOT_KERNEL_ATTN = 2,           /* split-K attention proper */
     ADAPSHOT_KERNEL_ATTN_COMBINE = 3,   /* merge of the split partials */
     ADAPSHOT_KERNEL_ENTROPY_CHUNK = 4,  /* vocabulary pass */
-    ADAPSHOT_KERNEL_ENTROPY_FINISH = 5, /* merge of the chunk partials */
+    ADAPSHOT_KERNEL_ENTROPY_FINISH = 5, /* merge of the chunk partials where it has a launch of its own (more
+                                         * than 1024 rows of several chunks) */
     ADAPSHOT_KERNEL_KINDS = 6
 } adapshot_kernel_kind;
 adapshot_status adapshot_profile_enable(adapshot_ctx* ctx, int32_t enable);

@@ -252,8 +252,9 @@ __global__ __launch_bounds__(256) void entropy_chunk_kernel(EntropyParams p) {
 // The same, and the workgroup that arrives last at its row's counter merges the row's chunks (in chunk order, whatever the
 // order of arrival): one launch.  Partials go past the L2 of the workgroup's XCD and are waited for before the arrival, so
 // no cache is written back or invalidated; the counter is zero again afterwards.  What it has to avoid is counters that
-// share a line (counter_stride).  Call after call, this / chunks and merge in two launches (us): 16 rows of 1000 logits 8.4 /
-// 11.6, 1 row of 128256 8.2 / 11.5, 48 rows 9.0 / 11.1, 128 rows 14.7 / 15.3 (below 9 us the host's call is what is timed).
+// share a line (counter_stride).  Call after call over logits that no cache holds, this / chunks and merge in two launches
+// (us): 1 row of 128256 8.8 / 11.6, 48 rows 9.6 / 11.5, 128 rows 15.5 / 15.8, 255 rows 25.3 / 25.4; 128 rows of 50257 11.0 / 11.6
+// (below 9 us the host's call is what is timed).
 template <bool VEC, bool TOKENS>
 __global__ __launch_bounds__(256) void entropy_fused_kernel(EntropyParams p, AnswerTokens c) {
     __shared__ int last_flag;
