@@ -39,22 +39,12 @@
 #pragma once
 #include <type_traits>
 
-#include "adapshot_internal.h"
+#include "mfma_tiles.h"
 
 namespace adapshot {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned long long u64;
 
-__device__ __forceinline__ unsigned stream_pack(float lo, float hi) {
-    const f32x2 f = {lo, hi};
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));  // round to nearest even
-}
 __device__ __forceinline__ void stream_store2(float* p, float a, float b) {
     const u64 v = (u64)__float_as_uint(a) | ((u64)__float_as_uint(b) << 32);
     __hip_atomic_store((u64*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -220,7 +210,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     };
     auto put2 = [&](unsigned (&w)[KR], int c, float a, float b) __attribute__((always_inline)) {
         if (BF) {
-            w[(c >> 1) % KR] = stream_pack(a, b);
+            w[(c >> 1) % KR] = pack2_bf16(a, b);
         } else {
             w[c % KR] = __float_as_uint(a);
             w[(c + 1) % KR] = __float_as_uint(b);
@@ -413,7 +403,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
                 for (int w = 0; w < 2 * NK; ++w) {
                     float x = sc[w >> 1][nr][2 * (w & 1)], y = sc[w >> 1][nr][2 * (w & 1) + 1];
                     if (NP == 1) {
-                        pb[nr][0][w] = stream_pack(x, y);
+                        pb[nr][0][w] = pack2_bf16(x, y);
                     } else {
 #pragma unroll
                         for (int i = 0; i < NP; ++i) {  // the upper 8 of the bits that are left, exactly
@@ -547,7 +537,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     auto store_out = [&](int row, int d0, f32x4 y) __attribute__((always_inline)) {
         const int j = row / g;
         const int64_t e = ((int64_t)j * p.n_q_heads + hk * g + (row - j * g)) * D + d0;
-        if (BF) *(uint2*)(it.out + e * 2) = make_uint2(stream_pack(y[0], y[1]), stream_pack(y[2], y[3]));
+        if (BF) *(uint2*)(it.out + e * 2) = make_uint2(pack2_bf16(y[0], y[1]), pack2_bf16(y[2], y[3]));
         else *(f32x4*)(it.out + e * 4) = y;
     };
     for (int s = wave; s < NS; s += W) {

@@ -1,4 +1,4 @@
-// Device helpers shared by the matrix-core kernels whose tiles come straight into LDS (attention, ranking).
+// Device helpers shared by the matrix-core kernels (attention, streaming attention, ranking).
 #pragma once
 #include "adapshot_internal.h"
 
