@@ -23,6 +23,9 @@ constexpr int kStreamWaves = 8;       // wavefronts per workgroup, each with key
 constexpr int kStreamItems = 32;      // attention problems per launch (their descriptions travel in the kernel arguments)
 constexpr int kStreamMaxSplits = 64;  // context splits per problem
 constexpr int kStreamUnits = 4096;    // (problem, row tile, kv head) units of a launch that is split: one arrival counter each
+// How long a workgroup waits for the others of its unit before it leaves the merge to the last one, in ticks of 10 ns.  Those
+// of a launch that has the chip to itself arrive within 1 to 3 us of each other.
+constexpr int32_t kStreamWaitTicks = 1000;
 // Distance of the arrival counters of n units (of an entropy call: rows), in counters: up to a 128-byte line each.  Atomics
 // on one line follow each other at about 14 ns whatever counter they name (16 rows x 126 arrivals in one line: 29 us, a line
 // for every row: 10 us).
@@ -110,6 +113,20 @@ inline int32_t stream_row_blocks(const adapshot_model_desc& d, int64_t n_cu, con
 // (problem, row tile, kv head) units of a problem
 inline int64_t stream_units(const adapshot_model_desc& d, const StreamShape& s, int32_t row_blocks) {
     return d.n_kv_heads * ((s.rows + 16 * row_blocks - 1) / (16 * row_blocks));
+}
+
+// Keys of a step of one wavefront.
+inline int64_t stream_step_keys(const adapshot_model_desc& d) { return d.dtype == ADAPSHOT_BF16 && d.head_dim <= 128 ? 32 : 16; }
+// Splits of a problem whose context is cut into pieces of split_tiles 64-key tiles.  The last one also takes the query's own
+// tokens, unless these would give its wavefronts another step to run than the other splits have: then they are a
+// split of their own.
+inline int64_t stream_splits(const adapshot_model_desc& d, int64_t n_ctx, int64_t t_q, int64_t split_tiles) {
+    const int64_t keys = split_tiles * 64, n = (n_ctx + keys - 1) / keys;
+    if (n <= 1) return 1;
+    if (n >= kStreamMaxSplits) return n;
+    const int64_t sk = stream_step_keys(d), rest = n_ctx - (n - 1) * keys;
+    const int64_t last = (rest + sk - 1) / sk + (t_q + sk - 1) / sk;
+    return (last + kStreamWaves - 1) / kStreamWaves > (keys / sk + kStreamWaves - 1) / kStreamWaves ? n + 1 : n;
 }
 
 // Split length (in 64-key tiles) of a launch of the streaming kernel: the longest context in n equal splits, the others in

@@ -22,23 +22,25 @@
 //
 // The wavefronts' states meet in LDS once, at the end.  With one split the workgroup writes the output rows itself:
 // rotation, attention and merge are then one launch.  With more, each workgroup leaves its merged rows (fp32) and (m, l)
-// in a workspace, and the workgroup that arrives last at the unit's counter merges them: partials are written and read
+// in a workspace and arrives at the unit's counter; where the whole launch fits the chip all workgroups of the unit then
+// merge a share of its rows each, elsewhere the one that arrived last merges them all.  Partials are written and read
 // with device-scope accesses that bypass the L2 of the workgroup's XCD, so no cache has to be written back or invalidated,
 // and the counter is back at zero afterwards.  The merge runs in split order whatever the order of arrival: the same
 // inputs give the same bits.
 //
 // What bounds it: a small problem, the launch and three round trips to memory (keys and query rows, arrival, partials);
 // a larger one, what a compute unit gets from beyond its L1, 45 to 48 GB/s whatever is in flight (64 or 128 KB), which is
-// why the loads are shared by two row blocks where there are rows enough.  A decode step of one query over 16k slots (4 KV
-// heads, 42 splits) spends 7 us on its keys and values, 1.5 on the wavefronts meeting, 1.5 on the arrival and 5.5 on
-// 150 KB of partials per KV head (more of them in flight, or cached loads behind an acquire, change nothing).  One layer:
-//   bf16, 32/8 heads x 64, 64 query tokens over 6.6k slots     fp32 second product 37 us -> 24 us
-//   bf16, 28/4 heads x 128, decode step over 16k slots          table copy + tile kernel + combine 29.6 us -> 19 us
-//   fp32, 8/2 heads x 128, 32 query tokens over 2.3k slots      19 us
-//   fp32, 4/2 heads x 64, 16 query tokens over 248 slots        8.9 us
+// why the loads are shared by two row blocks where there are rows enough, and why a single compute unit took 5 to 6 us for
+// the 100 to 250 KB of partials of a unit.  One layer, kernel time:
+//   bf16, 28/4 heads x 128, decode step over 16k slots, 42 splits   merged by the last to arrive 17.9 us, by all 15.1 us
+//     (of which 4 us to the first product, 5 the key loop, 3.5 wavefronts meeting, storing and arriving, 2.5 merging)
+//   fp32, 8/2 heads x 128, 32 query tokens over 2.3k slots, 12 splits                     18.2 us          17.2 us
+//   bf16, 32/8 heads x 64, 64 query tokens over 6.6k slots, 4 splits                      22.4 us          22.2 us
+//   fp32, 4/2 heads x 64, 16 query tokens over 248 slots                                   8.9 us
 #pragma once
 #include <type_traits>
 
+#include "arrival.h"
 #include "mfma_tiles.h"
 
 namespace adapshot {
@@ -84,8 +86,8 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
 
     __shared__ f32x4 os[W][NS][64];
     __shared__ float2 wml[W][TR];
-    __shared__ float2 sml[kStreamMaxSplits][TR];
-    __shared__ int last_flag;
+    __shared__ float sw[kStreamMaxSplits][TR];
+    __shared__ int role;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -533,7 +535,8 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         l_wg[nr] = L;
     }
     const int64_t unit = it.unit0 + (int64_t)rt * hkv + hk;
-    float* const po = p.part_o + (unit * p.max_split + split) * (TR * D);
+    // partials of the unit, [split][row][column]: at most 64 splits of 64 rows of 256 columns
+    const buf_rsrc parts = make_buffer(p.part_o + unit * p.max_split * (TR * D), (unsigned)(n_split * (TR * D) * 4));
     auto store_out = [&](int row, int d0, f32x4 y) __attribute__((always_inline)) {
         const int j = row / g;
         const int64_t e = ((int64_t)j * p.n_q_heads + hk * g + (row - j * g)) * D + d0;
@@ -564,15 +567,19 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
                 for (int i = 0; i < 4; ++i) acc[i] *= inv;
                 store_out(row, d0, acc);
             } else {
-                float* q = po + (row - row0) * D + d0;
-                stream_store2(q, acc[0], acc[1]);
-                stream_store2(q + 2, acc[2], acc[3]);
+                buf_store_16<kCacheDevice>(parts, (unsigned)((split * TR + row - row0) * D + d0) * 4u, __builtin_bit_cast(u32x4, acc));
             }
         }
     }
     if (n_split == 1) return;
 
-    // ---- merge over the splits, by the workgroup that arrives last
+    // ---- merge over the splits.  A workgroup that has left its partial arrives at the unit's counter.  Where all workgroups
+    // of the launch fit the chip at once (p.wait > 0) it then waits for the others, and every one of them merges its share of
+    // the unit's rows: the partials of a unit are 100 to 250 KB, which a single compute unit draws in 4 to 6 us.  The wait
+    // is bounded, because other launches may hold the compute units that a late workgroup needs: a workgroup that has
+    // waited p.wait ticks leaves, and says so in the counter; if anybody left before the last one arrived, that one merges
+    // everything, as it does where nobody waits.  Once all have arrived the counter does not change any more, so all see
+    // the same.  Whoever merges adds the splits in the same order: the same inputs give the same bits.
     float* const pml = p.part_ml + unit * p.max_split * (TR * 2);
     if (wave == 0 && kg == 0) {
 #pragma unroll
@@ -580,97 +587,112 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's partials have reached memory
     __syncthreads();
+    unsigned* const word = p.counters + unit * p.counter_stride;
+    unsigned* const exits = word + kStreamUnits;
+    unsigned n_exits = 0;
     if (tid == 0) {
-        const unsigned before = __hip_atomic_fetch_add(p.counters + unit * p.counter_stride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool mine = before == (unsigned)n_split - 1u;
-        if (mine) __hip_atomic_store(p.counters + unit * p.counter_stride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        last_flag = mine ? 1 : 0;
+        unsigned seen = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+        const bool last = arrived_all(seen, n_split);
+        if (p.wait > 0) {
+            const u64 t0 = __builtin_amdgcn_s_memrealtime();
+            while (!arrived_all(seen, n_split)) {
+                if (__builtin_amdgcn_s_memrealtime() - t0 < (u64)p.wait) {
+                    __builtin_amdgcn_s_sleep(2);
+                    seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else if (__hip_atomic_compare_exchange_strong(word, &seen, seen + kArrivalLeft, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT)) {
+                    break;  // (a failed exchange has read the word again; it changes at most twice per workgroup)
+                }
+            }
+            // the counter is not looked at again: the last workgroup to say so puts both words back to zero
+            n_exits = __hip_atomic_fetch_add(exits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+        } else if (last) {
+            __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        role = merge_role(seen, n_split, last, p.wait > 0);
     }
     __syncthreads();
-    if (!last_flag) return;
+    const int what = role;
+    if (tid == 0 && n_exits == (unsigned)n_split) {
+        __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(exits, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (what == kMergeNothing) return;
 
     const int n_rows = rows - row0 < TR ? rows - row0 : TR;
     const int e4 = n_rows * (D / 4);  // 16-byte pieces of the output rows
-    const float* const pu = p.part_o + unit * p.max_split * (TR * D);
-    // splits per thread: the pieces are few, so several groups of threads take the splits between them
-    int ng = T / e4;
-    ng = ng < 1 ? 1 : ng > n_split ? n_split : ng;
-    const int grp = ng > 1 ? tid / e4 : 0;
+    const int e_lo = what == kMergeShare ? e4 * split / n_split : 0;
+    const int e_hi = what == kMergeShare ? e4 * (split + 1) / n_split : e4;
+    if (e_lo >= e_hi) return;
     constexpr int PB = 8;  // splits in flight per thread
+    // The pieces are few, so ng groups of threads take the splits of a piece between them, up to 8 splits each; their number
+    // depends on the sizes only, not on who merges.
+    int ng = T / (p.wait > 0 ? (e4 + n_split - 1) / n_split : e4);
+    const int ng_max = (n_split + PB - 1) / PB;
+    ng = ng < 1 ? 1 : ng > ng_max ? ng_max : ng;
+    const int pe = T / ng < e_hi - e_lo ? T / ng : e_hi - e_lo;  // pieces of a pass
+    const int grp = tid / pe, ei = tid - grp * pe;
     auto piece = [&](int e, int sp, f32x4& x) __attribute__((always_inline)) {
-        const float* q = pu + ((int64_t)sp * TR * D + 4 * e);
-        const f32x2 a = stream_load2(q), b = stream_load2(q + 2);
-        x = f32x4{a[0], a[1], b[0], b[1]};
+        x = __builtin_bit_cast(f32x4, buf_load_16<kCacheDevice>(parts, (unsigned)(sp * (TR * D) + 4 * e) * 4u));
     };
-    for (int i = tid; i < n_split * TR; i += T) {
-        const f32x2 v = stream_load2(pml + 2 * i);
-        (&sml[0][0])[i] = make_float2(v[0], v[1]);
-    }
-    const int e_first = ng > 1 ? tid - grp * e4 : tid;
+    // weights of the splits, a wavefront per row and a lane per split: sw[s][row] = 2^(m_s - M) / L
+    const int r_lo = e_lo / (D / 4), r_hi = (e_hi - 1) / (D / 4);
+    f32x2 ml = {-INFINITY, 0.f};
+    if (r_lo + wave <= r_hi && lane < n_split) ml = stream_load2(pml + (lane * TR + r_lo + wave) * 2);
     f32x4 x[PB];
-    const bool on0 = grp < ng && e_first < e4;
 #pragma unroll
-    for (int b = 0; b < PB; ++b) {  // the first pieces are requested with the (m, l)
+    for (int b = 0; b < PB; ++b) {  // the first pieces are requested with the first (m, l)
         const int sp = grp + b * ng;
         x[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (on0 && sp < n_split) piece(e_first, sp, x[b]);
+        if (grp < ng && e_lo + ei < e_hi && sp < n_split) piece(e_lo + ei, sp, x[b]);
+    }
+    for (int row = r_lo + wave; row <= r_hi; row += W) {
+        if (row != r_lo + wave) ml = lane < n_split ? stream_load2(pml + (lane * TR + row) * 2) : f32x2{-INFINITY, 0.f};
+        const float M = wave_max(ml[0]);
+        const float w = ml[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[0] - M);
+        const float L = wave_sum(w == 0.f ? 0.f : w * ml[1]);
+        if (lane < n_split) sw[lane][row] = w == 0.f ? 0.f : w * (1.0f / L);
     }
     __syncthreads();
-    {   // weights of the splits, 16 threads per row: sml[s][row].x becomes 2^(m_s - M) / L
-        const int row = tid >> 4;
-        if (row < TR) {
-            float M = -INFINITY;
-            for (int s = l16; s < n_split; s += 16) M = fmaxf(M, sml[s][row].x);
-#pragma unroll
-            for (int off = 8; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
-            float L = 0.f;
-            for (int s = l16; s < n_split; s += 16)
-                L += sml[s][row].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sml[s][row].x - M) * sml[s][row].y;
-#pragma unroll
-            for (int off = 8; off > 0; off >>= 1) L += __shfl_xor(L, off, 64);
-            const float inv = 1.0f / L;
-            for (int s = l16; s < n_split; s += 16)
-                sml[s][row].x = sml[s][row].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sml[s][row].x - M) * inv;
-        }
-    }
-    __syncthreads();
-    f32x4* const red = &os[0][0][0];  // [ng][e4], at most one piece per thread
-    for (int e = e_first; e < e4; e += T) {
-        if (grp >= ng) break;
+    f32x4* const red = &os[0][0][0];  // [ng][pe], at most one piece per thread
+    for (int e0 = e_lo; e0 < e_hi; e0 += pe) {
+        const int e = e0 + ei;
         const int row = e / (D / 4);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int s0 = grp; s0 < n_split; s0 += PB * ng) {
-            if (e != e_first || s0 != grp) {
+        if (grp < ng && e < e_hi) {
+            for (int s0 = grp; s0 < n_split; s0 += PB * ng) {
+                if (e0 != e_lo || s0 != grp) {
+#pragma unroll
+                    for (int b = 0; b < PB; ++b) {
+                        const int sp = s0 + b * ng;
+                        if (sp < n_split) piece(e, sp, x[b]);
+                    }
+                }
 #pragma unroll
                 for (int b = 0; b < PB; ++b) {
                     const int sp = s0 + b * ng;
-                    if (sp < n_split) piece(e, sp, x[b]);
+                    if (sp < n_split) {
+                        const float w = sw[sp][row];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[i] += w * x[b][i];
+                    }
                 }
             }
+            if (ng == 1) store_out(row0 + row, 4 * (e - row * (D / 4)), acc);
+            else red[grp * pe + ei] = acc;
+        }
+        if (ng == 1) continue;  // the same for every thread
+        __syncthreads();
+        if (tid < pe && e < e_hi) {
+            acc = red[tid];
+            for (int gidx = 1; gidx < ng; ++gidx) {
+                const f32x4 y = red[gidx * pe + tid];
 #pragma unroll
-            for (int b = 0; b < PB; ++b) {
-                const int sp = s0 + b * ng;
-                if (sp < n_split) {
-                    const float w = sml[sp][row].x;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[i] += w * x[b][i];
-                }
+                for (int i = 0; i < 4; ++i) acc[i] += y[i];
             }
+            store_out(row0 + row, 4 * (e - row * (D / 4)), acc);
         }
-        if (ng == 1) store_out(row0 + row, 4 * (e - row * (D / 4)), acc);
-        else red[grp * e4 + e] = acc;
-    }
-    if (ng == 1) return;  // the same for every thread
-    __syncthreads();
-    if (tid < e4) {
-        f32x4 acc = red[tid];
-        for (int gidx = 1; gidx < ng; ++gidx) {
-            const f32x4 y = red[gidx * e4 + tid];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] += y[i];
-        }
-        const int row = tid / (D / 4);
-        store_out(row0 + row, 4 * (tid - row * (D / 4)), acc);
+        __syncthreads();
     }
 }
 
@@ -689,6 +711,7 @@ static hipError_t launch_stream_form(const StreamLaunch& s, hipStream_t stream) 
         a.g = s.n_q_heads / s.n_kv_heads;
         a.max_split = s.max_split;
         a.counter_stride = s.counter_stride;
+        a.wait = s.wait;
         a.pool_tokens = s.pool_tokens;
         a.q_scale = s.q_scale;
         for (int i = 0; i < s.n_items; ++i) a.it[i] = s.items[i];

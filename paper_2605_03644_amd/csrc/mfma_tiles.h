@@ -25,6 +25,38 @@ __device__ __forceinline__ float sum_xhalf(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// max / sum over the 64 lanes, the same in every lane
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    const int u = (int)__float_as_uint(v);
+    return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(u, u, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float max_xrow(float v) {  // lanes l and l^16
+    const unsigned u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_xrow(float v) {
+    const unsigned u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppHalfMirror = 0x141, kDppMirror = 0x140;  // quad_perm, row_half_mirror, row_mirror
+__device__ __forceinline__ float wave_max(float v) {
+    v = fmaxf(v, dpp<kDppXor1>(v));
+    v = fmaxf(v, dpp<kDppXor2>(v));
+    v = fmaxf(v, dpp<kDppHalfMirror>(v));
+    v = fmaxf(v, dpp<kDppMirror>(v));
+    return max_xhalf(max_xrow(v));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    v += dpp<kDppXor1>(v);
+    v += dpp<kDppXor2>(v);
+    v += dpp<kDppHalfMirror>(v);
+    v += dpp<kDppMirror>(v);
+    return sum_xhalf(sum_xrow(v));
+}
+
 __device__ __forceinline__ unsigned pack2_bf16(float lo, float hi) {
     f32x2 f = {lo, hi};
     bf16x2 b = __builtin_convertvector(f, bf16x2);  // v_cvt_pk_bf16_f32, round to nearest even
@@ -37,6 +69,22 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
     float r;
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
+}
+
+// ---- buffer accesses: a base and a size in scalar registers, a 32-bit byte offset per lane.  Reads past the size return zero.
+constexpr int kCacheNT = 2;       // read once: not kept in the caches
+constexpr int kCacheDevice = 16;  // past the L2 of the workgroup's XCD, for data that other workgroups of the launch write or read
+typedef __amdgpu_buffer_rsrc_t buf_rsrc;
+__device__ __forceinline__ buf_rsrc make_buffer(const void* base, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);  // raw, 32-bit data
+}
+template <int CACHE = 0>
+__device__ __forceinline__ u32x4 buf_load_16(buf_rsrc r, unsigned off) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, CACHE));
+}
+template <int CACHE = 0>
+__device__ __forceinline__ void buf_store_16(buf_rsrc r, unsigned off, u32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, CACHE);
 }
 
 // 16 bytes per lane from global memory straight into LDS: lane l's data lands at lds_base + 16*l
