@@ -28,15 +28,16 @@
 // and the counter is back at zero afterwards.  The merge runs in split order whatever the order of arrival: the same
 // inputs give the same bits.
 //
-// What bounds it: a small problem, the launch and three round trips to memory (keys and query rows, arrival, partials);
-// a larger one, what a compute unit gets from beyond its L1, 45 to 48 GB/s whatever is in flight (64 or 128 KB), which is
-// why the loads are shared by two row blocks where there are rows enough, and why a single compute unit took 5 to 6 us for
-// the 100 to 250 KB of partials of a unit.  One layer, kernel time:
-//   bf16, 28/4 heads x 128, decode step over 16k slots, 42 splits   merged by the last to arrive 17.9 us, by all 15.1 us
-//     (of which 4 us to the first product, 5 the key loop, 3.5 wavefronts meeting, storing and arriving, 2.5 merging)
-//   fp32, 8/2 heads x 128, 32 query tokens over 2.3k slots, 12 splits                     18.2 us          17.2 us
-//   bf16, 32/8 heads x 64, 64 query tokens over 6.6k slots, 4 splits                      22.4 us          22.2 us
-//   fp32, 4/2 heads x 64, 16 query tokens over 248 slots                                   8.9 us
+// What bounds it: a small problem, the launch, two or three round trips to memory (keys and query rows, arrival, partials)
+// and the instructions between them, 4 cycles each and two wavefronts per SIMD: loads therefore go through buffers (no
+// address arithmetic) and the query rows are rotated once per workgroup and handed out through LDS.  A larger problem,
+// what a compute unit gets from beyond its L1, 45 to 48 GB/s whatever is in flight (64 or 128 KB), which is why the loads are
+// shared by two row blocks where there are rows enough, and why a single compute unit took 5 to 6 us for the 100 to 250 KB
+// of partials of a unit.  One layer, kernel time: the last to arrive merges, addresses by lane / all merge / buffers
+//   bf16, 28/4 heads x 128, decode step over 16k slots, 42 splits  18.2 / 15.1 / 13.7 us
+//   fp32, 8/2 heads x 128, 32 query tokens over 2.3k slots         18.2 / 17.2 / 13.9
+//   bf16, 32/8 heads x 64, 64 query tokens over 6.6k slots         22.4 / 22.2 / 18.9
+//   fp32, 4/2 heads x 64, 16 query tokens over 248 slots, 1 split   8.7 /  8.8 /  6.5
 #pragma once
 #include <type_traits>
 
@@ -61,11 +62,11 @@ template <int DTYPE, int D, int NR, bool POOL, int NI>
 __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamArgs<NI> p) {
     constexpr int W = kStreamWaves, T = W * 64;
     constexpr bool BF = DTYPE == ADAPSHOT_BF16;
-    constexpr bool NT = BF && D == 128;  // decode steps: the context is read by one workgroup per KV head, once
     constexpr int E = BF ? 2 : 4;
     constexpr int KW = D * E >= 64 ? 16 / E : D / 4;  // consecutive columns of a lane
     constexpr int NJ = D / (4 * KW);
     constexpr int KR = KW * E / 4;                    // registers of one j
+    constexpr int KP = 16 / E;                        // elements of a 16-byte chunk
     constexpr int DB = D >= 16 ? D / 16 : 1;          // 16-column blocks of the output
     constexpr int VMAX = 16 / E;
     constexpr int VW = DB < VMAX ? DB : VMAX;         // consecutive V columns of a lane
@@ -86,6 +87,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
 
     __shared__ f32x4 os[W][NS][64];
     __shared__ float2 wml[W][TR];
+    __shared__ __attribute__((aligned(16))) char qs[TR * D * E];
     __shared__ float sw[kStreamMaxSplits][TR];
     __shared__ int role;
 
@@ -120,7 +122,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     const char* const kctx = it.k_ctx + (int64_t)hk * D * E + (POOL ? 0 : k0 * stride);
     const char* const vctx = it.v_ctx + (int64_t)hk * D * E + (POOL ? 0 : k0 * stride);
 
-    // ---- loads of step s.  Steps past the end read one row again (all lanes the same bytes).
+    // ---- loads of step s.  Steps past the end read no rows (the zero-copy form: one row again, all lanes the same bytes).
     // Zero-copy form: pool tokens of the rows of the next step to load, fetched one step before the rows
     int tok_k[NK] = {}, tok_v[NV] = {};
     auto pool_tok = [&](int u) __attribute__((always_inline)) -> int {
@@ -136,63 +138,109 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
             for (int r = 0; r < NV; ++r) tok_v[r] = pool_tok(SK * s + 16 * (r >> 2) + 4 * kg + (r & 3));
         }
     };
-    typedef typename std::conditional<POOL, uint64_t, unsigned>::type off_t;  // the rows of a context span at most 4 GiB, a pool may not
-    auto row_off = [&](bool self, bool on, int u, int lim, int tok) __attribute__((always_inline)) -> off_t {
-        int r = u < lim ? u : lim - 1;
-        if (POOL && !self) {
-            unsigned t = (unsigned)tok;
-            t = t < (unsigned)p.pool_tokens ? t : (unsigned)p.pool_tokens - 1u;  // never outside the pool
-            r = (int)t;
-        }
-        return on ? (off_t)r * (off_t)stride : (off_t)0;
+    auto row_off = [&](bool on, int tok) __attribute__((always_inline)) -> uint64_t {  // the rows of a pool may span more than 4 GiB
+        unsigned t = (unsigned)tok;
+        t = t < (unsigned)p.pool_tokens ? t : (unsigned)p.pool_tokens - 1u;  // never outside the pool
+        return on ? (uint64_t)t * (uint64_t)stride : 0;
     };
-    // A context that one workgroup per KV head reads once is not kept in the caches (NT).
-    auto ld4 = [&](const char* q, bool self) __attribute__((always_inline)) -> u32x4 {
-        return NT && !self ? __builtin_nontemporal_load((const u32x4*)q) : *(const u32x4*)q;
-    };
+    // An assembled context, and the query's own tokens, are read through buffers of exactly the split's rows: a lane's offset is its
+    // place in the step plus the step's (a scalar), rows past the end read as zero without a trip to memory, and nothing is
+    // clamped.  Addresses and clamps as vector arithmetic were 250 of the 700 instructions of a decode step's key step, at 4
+    // cycles each and two wavefronts per SIMD.  The loads are cached ones also where no other workgroup reads the rows: an
+    // instruction takes half a line of each of 16 keys, the next one the other half (non-temporal: 31 splits of 16k slots
+    // 18.2 us, cached 13.5; with every layer's keys cold 18.2 and 16.5).
+    const unsigned row_end = (unsigned)(D * E);
+    const unsigned ctx_bytes = POOL || nk == 0 ? 0u : (unsigned)((nk - 1) * stride) + row_end;
+    const unsigned self_bytes = n_self == 0 ? 0u : (unsigned)((n_self - 1) * stride) + row_end;
+    const unsigned k_lane = (unsigned)(l16 * stride) + 16u * (unsigned)kg;         // KR == 4; else 8 bytes per group
+    const unsigned v_lane = (unsigned)(4 * kg * stride) + (unsigned)(VW * l16 * E);
     auto load_k = [&](int s, unsigned (&dst)[NK][NJ][KR]) __attribute__((always_inline)) {
         const bool on = s < n_steps, self = s >= n_cs;
-        const char* base = self ? kself : kctx;
+        if (POOL && !self) {
+#pragma unroll
+            for (int b = 0; b < NK; ++b) {
+                const char* src = kctx + row_off(on, tok_k[b]);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    if (KR == 4) {
+                        const u32x4 x = *(const u32x4*)(src + 64 * j + 16 * kg);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) dst[b][j][i % KR] = x[i];
+                    } else {
+                        const uint2 x = *(const uint2*)(src + 8 * kg);
+                        dst[b][j][0] = x.x;
+                        dst[b][j][1 % KR] = x.y;
+                    }
+                }
+            }
+            return;
+        }
+        const buf_rsrc rows_k = make_buffer(self ? kself : kctx, on ? (self ? self_bytes : ctx_bytes) : 0u);
+        const unsigned step = (unsigned)(SK * (self ? s - n_cs : s)) * (unsigned)stride;
 #pragma unroll
         for (int b = 0; b < NK; ++b) {
-            const int u = SK * (self ? s - n_cs : s) + 16 * b + l16;
-            const char* src = base + row_off(self, on, u, self ? n_self : nk, tok_k[b]);
+            const unsigned at = k_lane + step + (unsigned)(16 * b) * (unsigned)stride;
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 if (KR == 4) {
-                    const u32x4 x = ld4(src + 64 * j + 16 * kg, self);
+                    const u32x4 x = buf_load_16(rows_k, at + 64u * j);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) dst[b][j][i % KR] = x[i];
                 } else {
-                    const uint2 x = *(const uint2*)(src + 8 * kg);
-                    dst[b][j][0] = x.x;
-                    dst[b][j][1 % KR] = x.y;
+                    const u32x2 x = buf_load_8(rows_k, at - 8u * (unsigned)kg);
+                    dst[b][j][0] = x[0];
+                    dst[b][j][1 % KR] = x[1];
                 }
             }
         }
     };
     auto load_v = [&](int s, unsigned (&dst)[NV][DG][VR]) __attribute__((always_inline)) {
         const bool on = s < n_steps, self = s >= n_cs;
-        const char* base = self ? vself : vctx;
+        if (POOL && !self) {
+#pragma unroll
+            for (int r = 0; r < NV; ++r) {
+                const char* src = vctx + row_off(on, tok_v[r]);
+#pragma unroll
+                for (int dg = 0; dg < DG; ++dg) {
+                    const char* q = src + (16 * VW * dg + VW * l16) * E;
+                    if (VR == 4) {
+                        const u32x4 x = *(const u32x4*)q;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) dst[r][dg][i % VR] = x[i];
+                    } else if (VR == 2) {
+                        const uint2 x = *(const uint2*)q;
+                        dst[r][dg][0] = x.x;
+                        dst[r][dg][1 % VR] = x.y;
+                    } else if (VW * E == 4) {
+                        dst[r][dg][0] = D == 8 && l16 >= 8 ? 0u : *(const unsigned*)(D == 8 && l16 >= 8 ? src : q);
+                    } else {
+                        dst[r][dg][0] = (unsigned)*(const unsigned short*)q << 16;  // bf16, one column
+                    }
+                }
+            }
+            return;
+        }
+        const buf_rsrc rows_v = make_buffer(self ? vself : vctx, on ? (self ? self_bytes : ctx_bytes) : 0u);
+        const unsigned step = (unsigned)(SK * (self ? s - n_cs : s)) * (unsigned)stride;
 #pragma unroll
         for (int r = 0; r < NV; ++r) {
-            const int u = SK * (self ? s - n_cs : s) + 16 * (r >> 2) + 4 * kg + (r & 3);
-            const char* src = base + row_off(self, on, u, self ? n_self : nk, tok_v[r]);
+            const unsigned at = v_lane + step + (unsigned)(16 * (r >> 2) + (r & 3)) * (unsigned)stride;
 #pragma unroll
             for (int dg = 0; dg < DG; ++dg) {
-                const char* q = src + (16 * VW * dg + VW * l16) * E;
+                const unsigned q = at + (unsigned)(16 * VW * dg * E);
                 if (VR == 4) {
-                    const u32x4 x = ld4(q, self);
+                    const u32x4 x = buf_load_16(rows_v, q);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) dst[r][dg][i % VR] = x[i];
                 } else if (VR == 2) {
-                    const uint2 x = *(const uint2*)q;
-                    dst[r][dg][0] = x.x;
-                    dst[r][dg][1 % VR] = x.y;
+                    const u32x2 x = buf_load_8(rows_v, q);
+                    dst[r][dg][0] = x[0];
+                    dst[r][dg][1 % VR] = x[1];
                 } else if (VW * E == 4) {
-                    dst[r][dg][0] = D == 8 && l16 >= 8 ? 0u : *(const unsigned*)(D == 8 && l16 >= 8 ? src : q);
+                    const unsigned x = buf_load_4(rows_v, q);
+                    dst[r][dg][0] = D == 8 && l16 >= 8 ? 0u : x;
                 } else {
-                    dst[r][dg][0] = (unsigned)*(const unsigned short*)q << 16;  // bf16, one column
+                    dst[r][dg][0] = (unsigned)buf_load_2(rows_v, q) << 16;  // bf16, one column
                 }
             }
         }
@@ -203,7 +251,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         return __builtin_amdgcn_perm(b, a, (c & 1) || VW == 1 ? 0x07060302u : 0x05040100u);
     };
 
-    // ---- rotation of a lane's pieces of a row to position a (Eq. rope_encoding), scaled; bf16 results rounded to
+    // ---- rotation of a lane's pieces of a key to position a (Eq. rope_encoding); bf16 results rounded to
     // nearest even, as a cache would hold them.  The partner of column d is d +- D/2: piece j +- NJ/2 of the same lane, or,
     // where a row is a single piece per lane, the lane two groups on.
     auto get = [&](const unsigned (&w)[KR], int c) __attribute__((always_inline)) -> float {
@@ -218,7 +266,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
             w[(c + 1) % KR] = __float_as_uint(b);
         }
     };
-    auto rotate = [&](unsigned (&x)[NJ][KR], int64_t a, float sc) __attribute__((always_inline)) {
+    auto rotate = [&](unsigned (&x)[NJ][KR], int64_t a) __attribute__((always_inline)) {
         const float2* th = p.tab_hi + (a >> kRopeLoBits) * (D / 2);
         const float2* tl = p.tab_lo + (a & (kRopeLo - 1)) * (D / 2);
         constexpr int NP = NJ > 1 ? NJ / 2 : 1;
@@ -233,53 +281,99 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
                 if (NJ > 1) {
                     const float a0 = get(x[j], c), a1 = get(x[j], c + 1);
                     const float b0 = get(x[(j + NP) % NJ], c), b1 = get(x[(j + NP) % NJ], c + 1);
-                    put2(x[j], c, (a0 * c0 - b0 * s0) * sc, (a1 * c1 - b1 * s1) * sc);
-                    put2(x[(j + NP) % NJ], c, (b0 * c0 + a0 * s0) * sc, (b1 * c1 + a1 * s1) * sc);
+                    put2(x[j], c, a0 * c0 - b0 * s0, a1 * c1 - b1 * s1);
+                    put2(x[(j + NP) % NJ], c, b0 * c0 + a0 * s0, b1 * c1 + a1 * s1);
                 } else {
                     const float a0 = get(x[0], c), a1 = get(x[0], c + 1);
                     const float b0 = __shfl_xor(a0, 32, 64), b1 = __shfl_xor(a1, 32, 64);
                     const float t0 = kg < 2 ? -s0 : s0, t1 = kg < 2 ? -s1 : s1;
-                    put2(x[0], c, (a0 * c0 + b0 * t0) * sc, (a1 * c1 + b1 * t1) * sc);
+                    put2(x[0], c, a0 * c0 + b0 * t0, a1 * c1 + b1 * t1);
                 }
             }
         }
     };
 
-    // ---- the first steps are requested before the query rows are rotated
+    // ---- query rows: rotated once per workgroup (a thread per pair of 16-byte chunks, halves of a head apart), through LDS into the
+    // fragments of every wavefront; the first steps' keys and values are requested behind them
+    constexpr int CH = D * E / 32, NCH = 2 * CH;  // 16-byte chunks of half a head, of a head
+    constexpr int QI = (TR * CH + T - 1) / T;
+    auto q_chunk = [&](int row, int c) __attribute__((always_inline)) -> char* { return qs + (row * NCH + (c ^ (row & (NCH - 1)))) * 16; };
+    u32x4 qa[QI], qb[QI];
+    f32x4 th[QI][KP / 2], tl[QI][KP / 2];
+#pragma unroll
+    for (int i = 0; i < QI; ++i) {
+        if (wave * 64 + i * T >= TR * CH) break;
+        const int r = (tid + i * T) / CH < TR ? (tid + i * T) / CH : TR - 1, c = tid % CH;
+        const int rc = row0 + r < rows ? row0 + r : rows - 1;
+        const int j = rc / g;
+        const char* src = it.q + (((int64_t)j * p.n_q_heads + hk * g + (rc - j * g)) * D) * E + 16 * c;
+        qa[i] = *(const u32x4*)src;
+        qb[i] = *(const u32x4*)(src + 16 * CH);
+        const int64_t a = (int64_t)it.q_pos0 + j;
+        const f32x4* h4 = (const f32x4*)(p.tab_hi + (a >> kRopeLoBits) * (D / 2) + KP * c);
+        const f32x4* l4 = (const f32x4*)(p.tab_lo + (a & (kRopeLo - 1)) * (D / 2) + KP * c);
+#pragma unroll
+        for (int e = 0; e < KP / 2; ++e) {
+            th[i][e] = h4[e];
+            tl[i][e] = l4[e];
+        }
+    }
     unsigned kf[NB][NK][NJ][KR];
     unsigned vf[NBV][NV][DG][VR];
     fetch_tok(wave);
+    load_k(wave, kf[0]);
+    if (NBV > 1) {
+        load_v(wave, vf[0]);
+        fetch_tok(wave + W);
+    }
 #pragma unroll
-    for (int b = 0; b < NB - 1; ++b) {
-        load_k(wave + b * W, kf[b]);
-        if (NBV > 1) {
-            load_v(wave + b * W, vf[b % NBV]);
-            fetch_tok(wave + (b + 1) * W);
+    for (int i = 0; i < QI; ++i) {
+        if (wave * 64 + i * T >= TR * CH) break;
+#pragma unroll
+        for (int e = 0; e < KP / 2; ++e) {  // frequencies 2e and 2e + 1 of the chunk
+            const f32x4 h = th[i][e], l = tl[i][e];
+            const float c0 = h[0] * l[0] - h[1] * l[1], s0 = h[1] * l[0] + h[0] * l[1];
+            const float c1 = h[2] * l[2] - h[3] * l[3], s1 = h[3] * l[2] + h[2] * l[3];
+            if (BF) {
+                const float a0 = __uint_as_float(qa[i][e] << 16), a1 = __uint_as_float(qa[i][e] & 0xffff0000u);
+                const float b0 = __uint_as_float(qb[i][e] << 16), b1 = __uint_as_float(qb[i][e] & 0xffff0000u);
+                qa[i][e] = pack2_bf16((a0 * c0 - b0 * s0) * p.q_scale, (a1 * c1 - b1 * s1) * p.q_scale);
+                qb[i][e] = pack2_bf16((b0 * c0 + a0 * s0) * p.q_scale, (b1 * c1 + a1 * s1) * p.q_scale);
+            } else {
+                const float a0 = __uint_as_float(qa[i][2 * e % 4]), a1 = __uint_as_float(qa[i][(2 * e + 1) % 4]);
+                const float b0 = __uint_as_float(qb[i][2 * e % 4]), b1 = __uint_as_float(qb[i][(2 * e + 1) % 4]);
+                qa[i][2 * e % 4] = __float_as_uint((a0 * c0 - b0 * s0) * p.q_scale);
+                qa[i][(2 * e + 1) % 4] = __float_as_uint((a1 * c1 - b1 * s1) * p.q_scale);
+                qb[i][2 * e % 4] = __float_as_uint((b0 * c0 + a0 * s0) * p.q_scale);
+                qb[i][(2 * e + 1) % 4] = __float_as_uint((b1 * c1 + a1 * s1) * p.q_scale);
+            }
+        }
+        if (tid + i * T < TR * CH) {
+            const int r = (tid + i * T) / CH, c = tid % CH;
+            *(u32x4*)q_chunk(r, c) = qa[i];
+            *(u32x4*)q_chunk(r, c + CH) = qb[i];
         }
     }
-
+    // (a barrier that leaves the loads of keys and values in flight)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     unsigned qf[NR][NJ][KR];
     int jrow[NR];
 #pragma unroll
     for (int nr = 0; nr < NR; ++nr) {
         const int row = row0 + 16 * nr + l16;
-        const int rc = row < rows ? row : rows - 1;
-        const int j = rc / g;
-        jrow[nr] = j;
-        const char* src = it.q + (((int64_t)j * p.n_q_heads + hk * g + (rc - j * g)) * D) * E;
+        jrow[nr] = (row < rows ? row : rows - 1) / g;
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
             if (KR == 4) {
-                const u32x4 x = *(const u32x4*)(src + 64 * jj + 16 * kg);
+                const u32x4 x = *(const u32x4*)q_chunk(16 * nr + l16, 4 * jj + kg);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) qf[nr][jj][i % KR] = x[i];
             } else {
-                const uint2 x = *(const uint2*)(src + 8 * kg);
-                qf[nr][jj][0] = x.x;
-                qf[nr][jj][1 % KR] = x.y;
+                const u32x2 x = *(const u32x2*)(q_chunk(16 * nr + l16, kg >> 1) + 8 * (kg & 1));
+                qf[nr][jj][0] = x[0];
+                qf[nr][jj][1 % KR] = x[1];
             }
         }
-        rotate(qf[nr], (int64_t)it.q_pos0 + j, p.q_scale);
     }
 
     f32x4 o[NR][DB];
@@ -301,8 +395,8 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         f32x4 sc[NK][NR];
 #pragma unroll
         for (int kb = 0; kb < NK; ++kb) {
-            if (self) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16, 1.0f);
-            else if (POOL) rotate(k[kb], p.ctx_pos0 + k0 + SK * s + 16 * kb + l16, 1.0f);
+            if (self) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16);
+            else if (POOL) rotate(k[kb], p.ctx_pos0 + k0 + SK * s + 16 * kb + l16);
 #pragma unroll
             for (int nr = 0; nr < NR; ++nr) sc[kb][nr] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -349,8 +443,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
                 mx = fmaxf(mx, fmaxf(fmaxf(sc[NK - 1][nr][0], sc[NK - 1][nr][1]), fmaxf(sc[NK - 1][nr][2], sc[NK - 1][nr][3])));
             // the reference maximum of a row follows lazily: it moves when a score exceeds it by more than 2^8
             if (__builtin_amdgcn_ballot_w64(mx > m_run[nr] + 8.0f)) {
-                mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                mx = max_xhalf(max_xrow(mx));
                 const float m_new = fmaxf(m_run[nr], mx);
                 const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run[nr] - m_new);
                 m_run[nr] = m_new;
@@ -455,22 +548,30 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     };
 
     if (wave < n_steps) {  // (said once for both loops: what only they need is then computed under it)
-        for (int s0 = wave; s0 < n_steps; s0 += NB * W) {
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int s = s0 + b * W;
-                if (s >= n_steps) break;
-                if (NBV == 1) {
-                    load_v(s, vf[0]);
-                    fetch_tok(s + W);
-                }
-                load_k(s + (NB - 1) * W, kf[(b + NB - 1) % NB]);
-                if (NBV > 1) {
-                    load_v(s + (NB - 1) * W, vf[(b + NB - 1) % NBV]);
-                    fetch_tok(s + NB * W);
-                }
-                compute(s, kf[b], vf[b % NBV], std::false_type{});
+        // Steps in pairs, one buffer each, and the odd one behind the loop: a loop that could be left between the two has the
+        // compiler wait at its head for loads that only that way out leaves behind, and a wavefront with one step loads no
+        // second one (one step per wavefront: 7.2 -> 6.6 us of a call, 10.3 -> 9.6).
+        int s = wave;
+        auto step = [&](int b) __attribute__((always_inline)) {
+            if (NBV == 1) {
+                load_v(s, vf[0]);
+                fetch_tok(s + W);
             }
+            load_k(s + W, kf[1 - b]);
+            if (NBV > 1) {
+                load_v(s + W, vf[(1 - b) % NBV]);
+                fetch_tok(s + 2 * W);
+            }
+            compute(s, kf[b], vf[b % NBV], std::false_type{});
+            s += W;
+        };
+        while (s + W < n_steps) {
+            step(0);
+            step(1);
+        }
+        if (s < n_steps) {
+            if (NBV == 1) load_v(s, vf[0]);
+            compute(s, kf[0], vf[0], std::false_type{});
         }
 
         // A matrix product multiplies every V row of its step with every query row: a V that is not finite makes NaN of the
@@ -501,8 +602,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
 #pragma unroll
     for (int nr = 0; nr < NR; ++nr) {
         float l = l_run[nr];
-        l += __shfl_xor(l, 16, 64);
-        l += __shfl_xor(l, 32, 64);
+        l = sum_xhalf(sum_xrow(l));
         if (kg == 0) wml[wave][16 * nr + l16] = make_float2(m_run[nr], l);
 #pragma unroll
         for (int s = 0; s < DB; ++s) {

@@ -5,6 +5,7 @@
 namespace adapshot {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -72,7 +73,6 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
 }
 
 // ---- buffer accesses: a base and a size in scalar registers, a 32-bit byte offset per lane.  Reads past the size return zero.
-constexpr int kCacheNT = 2;       // read once: not kept in the caches
 constexpr int kCacheDevice = 16;  // past the L2 of the workgroup's XCD, for data that other workgroups of the launch write or read
 typedef __amdgpu_buffer_rsrc_t buf_rsrc;
 __device__ __forceinline__ buf_rsrc make_buffer(const void* base, unsigned bytes) {
@@ -82,6 +82,11 @@ template <int CACHE = 0>
 __device__ __forceinline__ u32x4 buf_load_16(buf_rsrc r, unsigned off) {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, CACHE));
 }
+__device__ __forceinline__ u32x2 buf_load_8(buf_rsrc r, unsigned off) {
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ unsigned buf_load_4(buf_rsrc r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0); }
+__device__ __forceinline__ unsigned short buf_load_2(buf_rsrc r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0); }
 template <int CACHE = 0>
 __device__ __forceinline__ void buf_store_16(buf_rsrc r, unsigned off, u32x4 v) {
     __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, CACHE);
