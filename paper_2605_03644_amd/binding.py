@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Optional, Sequence
 
 import numpy as np
@@ -135,8 +136,11 @@ def attn_split_plan(n_q_heads: int, n_kv_heads: int, head_dim: int, dtype: int, 
 
 
 def _stream_ptr(stream: Optional[torch.cuda.Stream] = None) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    """The hipStream_t of a stream, or of the current one of the current device.  (torch.cuda.current_stream() makes a Python
+    object for it, 2.5 us of the 7 us that a call took; the handle alone is 0.1 us.)"""
+    if stream is not None:
+        return int(stream.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _torch_dtype(dtype: int) -> torch.dtype:
@@ -325,10 +329,7 @@ class Context:
     #    advanced lengths are copied back
     @staticmethod
     def _pack_caches(caches):
-        arr = (CacheStruct * len(caches))()
-        for i, c in enumerate(caches):
-            arr[i] = c.c
-        return arr
+        return (CacheStruct * len(caches))(*[c.c for c in caches])
 
     @staticmethod
     def _unpack_lens(caches, arr):
@@ -356,11 +357,12 @@ class Context:
     def pack_attn_items(items):
         """The C array of a list of (cache_index, n_ctx, q, k_self, v_self, q_pos0, out); reusable across calls
         as long as the tensors stay alive and the lengths do not change."""
-        its = (AttnItem * len(items))()
-        for i, (ci, n_ctx, q, ks, vs, q_pos0, out) in enumerate(items):
+        fields = []
+        for ci, n_ctx, q, ks, vs, q_pos0, out in items:
             assert q.is_contiguous() and ks.is_contiguous() and vs.is_contiguous() and out.is_contiguous()
-            its[i] = AttnItem(q.data_ptr(), ks.data_ptr(), vs.data_ptr(), out.data_ptr(), n_ctx, q_pos0, q.shape[0], ci)
-        return its
+            fields += (q.data_ptr(), ks.data_ptr(), vs.data_ptr(), out.data_ptr(), n_ctx, q_pos0, q.size(0), ci)
+        # all items at once: a ctypes structure per item, field by field, was 7 of its 8 us
+        return (AttnItem * len(items)).from_buffer(bytearray(struct.pack("@" + "PPPPqqii" * len(items), *fields)))
 
     def query_attn_batched(self, caches, layer: int, items, stream: Optional[torch.cuda.Stream] = None) -> None:
         """items: a list of (cache_index, n_ctx, q, k_self, v_self, q_pos0, out), or what pack_attn_items made of one."""
