@@ -369,8 +369,21 @@ struct AssembleJob {
     int64_t total, n_tiles;
 };
 
+static AssembleDst assemble_dst(const adapshot_ctx* ctx, const adapshot_cache& c, int64_t pos0) {
+    AssembleDst d;
+    d.k_out = (char*)c.k;
+    d.v_out = (char*)c.v;
+    d.slot_shot = c.slot_shot;
+    d.slot_tok = c.slot_tok;
+    d.slot_pos = c.slot_pos;
+    d.layer_stride_bytes = c.capacity * ctx->row_bytes;
+    d.pos0 = pos0;
+    return d;
+}
+
 // Plan (prefix sums -> tile descriptors) and launch of validated assemble jobs: one launch per group of
-// up to kAssembleBatch caches, the tiles of a group's caches in one descriptor list.
+// up to kAssembleBatch caches, the tiles of a group's caches in one descriptor list.  A group of one cache and few shots
+// needs no descriptors: its shot list is a kernel argument.
 static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_t n_jobs, int64_t pos0,
                                     hipStream_t stream) {
     const bool local = ctx->desc.key_state == ADAPSHOT_KEYS_ROTATED_LOCAL;
@@ -379,6 +392,35 @@ static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_
         int64_t group_tiles = 0;
         for (int32_t b = j0; b < j1; ++b) group_tiles += jobs[b].n_tiles;
         if (group_tiles == 0) continue;
+        if (j1 - j0 == 1 && jobs[j0].m <= kAssembleShots) {
+            const AssembleJob& jb = jobs[j0];
+            AssembleShotsParams p;
+            p.k_pool = (const char*)ctx->k_pool;
+            p.v_pool = (const char*)ctx->v_pool;
+            p.tab_lo = ctx->tab_lo;
+            p.tab_hi = ctx->tab_hi;
+            p.pool_layer_stride_bytes = ctx->pool_layer_stride_tokens * ctx->row_bytes;
+            p.dst = assemble_dst(ctx, *jb.cache, pos0);
+            p.slot0 = (int32_t)jb.cache->len;
+            p.n_tokens = (int32_t)jb.total;
+            p.n_shots = jb.m;
+            p.n_layers = ctx->desc.n_layers;
+            p.wg_tok = ctx->assemble_wg_tok;
+            p.local = local ? 1 : 0;
+            p.n_kv_heads = ctx->desc.n_kv_heads;
+            p.head_dim = ctx->desc.head_dim;
+            p.dtype = ctx->desc.dtype;
+            int32_t slot = 0;
+            for (int32_t j = 0; j < jb.m; ++j) {
+                const int32_t s = jb.shot_ids[jb.order ? jb.order[j] : j];
+                p.shots[j] = ShotRun{slot, (int32_t)ctx->shot_offsets[s], s};
+                slot += (int32_t)(ctx->shot_offsets[s + 1] - ctx->shot_offsets[s]);
+            }
+            const hipError_t e = timed_launch(ctx, ADAPSHOT_KERNEL_ASSEMBLE, stream, [&] { return launch_assemble_shots(p, stream); });
+            if (e != hipSuccess) return fail_hip(ctx, "assemble: launch", e);
+            jb.cache->len += jb.total;
+            continue;
+        }
         if (group_tiles > INT32_MAX / kTileTok) return fail(ctx, ADAPSHOT_EINVAL, "assemble: too many tiles");
         int slot;
         void* host;
@@ -390,14 +432,7 @@ static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_
         int64_t nt = 0, n_tok_group = 0;
         for (int32_t b = j0; b < j1; ++b) {
             const AssembleJob& jb = jobs[b];
-            AssembleDst& dc = p.dst[b - j0];
-            dc.k_out = (char*)jb.cache->k;
-            dc.v_out = (char*)jb.cache->v;
-            dc.slot_shot = jb.cache->slot_shot;
-            dc.slot_tok = jb.cache->slot_tok;
-            dc.slot_pos = jb.cache->slot_pos;
-            dc.layer_stride_bytes = jb.cache->capacity * ctx->row_bytes;
-            dc.pos0 = pos0;
+            p.dst[b - j0] = assemble_dst(ctx, *jb.cache, pos0);
             // slot group j starts at off_j = sum of the lengths before it
             int64_t slot0 = jb.cache->len;
             for (int32_t j = 0; j < jb.m; ++j) {

@@ -69,6 +69,31 @@ struct AssembleParams {
 };
 hipError_t launch_assemble(const AssembleParams& p, hipStream_t stream);
 
+// The same for one cache and up to kAssembleShots shots, whose list travels in the kernel arguments: workgroups are cut by
+// cache slots, wg_tok consecutive ones each, and look their shots up in the list.
+constexpr int kAssembleShots = 320;
+struct ShotRun {
+    int32_t slot;     // first slot of the shot, counted from the call's first slot; not decreasing
+    int32_t src_tok;  // its first pool token
+    int32_t shot;     // pool shot id
+};
+struct AssembleShotsParams {
+    const char* k_pool;
+    const char* v_pool;
+    const float2* tab_lo;
+    const float2* tab_hi;
+    int64_t pool_layer_stride_bytes;
+    AssembleDst dst;
+    int32_t slot0;    // first slot of the call
+    int32_t n_tokens, n_shots, n_layers;
+    int32_t wg_tok;   // a power of two <= kTileTok
+    int32_t local;    // 1: keys rotated at local positions (angle = position of the shot's first slot), 0: un-rotated (angle = position)
+    int32_t n_kv_heads, head_dim, dtype;
+    ShotRun shots[kAssembleShots];
+};
+static_assert(sizeof(AssembleShotsParams) <= 4096, "kernel arguments");
+hipError_t launch_assemble_shots(const AssembleShotsParams& p, hipStream_t stream);
+
 // One decode step: cache i of this launch receives token row [layer][first + i] of k_new / v_new at
 // slot[i], the key rotated to pos[i].  Pointer tables travel in the kernel arguments.
 constexpr int kDecodeBatch = 32;

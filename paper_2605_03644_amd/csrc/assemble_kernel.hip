@@ -78,66 +78,62 @@ __device__ __forceinline__ void rotate_chunks(u32x4& a, u32x4& b, const float2* 
     }
 }
 
+// Where the rows of a workgroup's tokens lie in a pool layer (byte offsets): one run of consecutive tokens, or
+// a row each (a workgroup whose slots span several shots).
+struct DenseRows {
+    int64_t base, row_bytes;
+    __device__ __forceinline__ int64_t row(int tau) const { return base + tau * row_bytes; }
+    __device__ __forceinline__ int64_t chunk(int i) const { return base + ((int64_t)i << 4); }  // 16-byte chunk i of all rows together
+};
+struct GatheredRows {
+    const int32_t* tok;  // LDS
+    int64_t row_bytes;
+    __device__ __forceinline__ int64_t row(int tau) const { return tok[tau] * row_bytes; }
+    __device__ __forceinline__ int64_t chunk(int i) const {
+        const int c = (int)(row_bytes >> 4), tau = i / c;
+        return tok[tau] * row_bytes + ((int64_t)(i - tau * c) << 4);
+    }
+};
+
+// V: dense copy of n_tok rows, one step (4 x 16 bytes per lane) ahead
+template <bool NT, typename Rows>
+__device__ __forceinline__ void copy_v(const char* pool, const Rows& rows, char* dst, int n_tok, int64_t row_bytes) {
+    const int tid = threadIdx.x;
+    const int n16 = (int)((n_tok * row_bytes) >> 4);
+    auto vload = [&](int i0, u32x4(&r)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i0 + 256 * u < n16) r[u] = ld16(pool + rows.chunk(i0 + 256 * u));
+    };
+    auto vstore = [&](int i0, u32x4(&r)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i0 + 256 * u < n16) st16<NT>(dst + ((int64_t)(i0 + 256 * u) << 4), r[u]);
+    };
+    u32x4 cur[4];
+    vload(tid, cur);
+    for (int i0 = tid; i0 - tid < n16; i0 += 1024) {
+        const bool more = i0 + 1024 - tid < n16;  // workgroup-uniform
+        u32x4 nxt[4];
+        if (more) vload(i0 + 1024, nxt);
+        vstore(i0, cur);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
+    }
+}
+
+// K: n_tok rows, each rotated by its angle.  cs: LDS, kTileTok * HALF entries.
 // DTYPE: element type; CH: 16-byte chunks per half head (head_dim/2 * elem / 16).
-template <int DTYPE, int CH, bool NT>
-__global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p) {
+template <int DTYPE, int CH, bool NT, typename Rows, typename Angle>
+__device__ __forceinline__ void rotate_k(const char* pool, const Rows& rows, char* dst, int n_tok, int n_kv_heads,
+                                         const float2* tab_lo, const float2* tab_hi, float2* cs, Angle&& angle) {
     constexpr int E = DTYPE == ADAPSHOT_BF16 ? 2 : 4;
     constexpr int NP = 16 / E;            // pairs per chunk
     constexpr int HALF = CH * NP;         // head_dim / 2
     constexpr int HEAD_BYTES = 2 * CH * 16;
-    __shared__ float2 cs[kTileTok * HALF];
-
     const int tid = threadIdx.x;
-    const int parts = kTileTok / p.wg_tok;
-    const TileDesc td = p.tiles[blockIdx.x / parts];
-    const int t_first = (int)(blockIdx.x % parts) * p.wg_tok;  // this workgroup's tokens of the tile: t_first .. t_first + n_tok - 1
-    const int n_tok = td.n_tok - t_first < p.wg_tok ? td.n_tok - t_first : p.wg_tok;
-    if (n_tok <= 0) return;  // a ragged tile's last parts are empty (workgroup-uniform)
-    // the first cache's entry is read without waiting for the descriptor: a launch for one cache needs no other
-    AssembleDst dc = p.dst[0];
-    if (p.n_dst != 1) dc = p.dst[__builtin_amdgcn_readfirstlane(td.cache)];
-    const int64_t row_bytes = (int64_t)p.n_kv_heads * HEAD_BYTES;
-    const int64_t src_off = (int64_t)(td.src_tok + t_first) * row_bytes;
-    const int64_t dst_off = (int64_t)(td.dst_slot + t_first) * row_bytes;
-
-    if (blockIdx.z == 1) {
-        // ---- V: dense copy of n_tok rows per layer, one step (4 x 16 bytes per lane) ahead ----
-        const int n16 = (int)((n_tok * row_bytes) >> 4);
-        auto vload = [&](int l, int i0, u32x4(&r)[4]) __attribute__((always_inline)) {
-            const char* src = p.v_pool + (int64_t)l * p.pool_layer_stride_bytes + src_off;
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (i0 + 256 * u < n16) r[u] = ld16(src + ((int64_t)(i0 + 256 * u) << 4));
-        };
-        auto vstore = [&](int l, int i0, u32x4(&r)[4]) __attribute__((always_inline)) {
-            char* dst = dc.v_out + (int64_t)l * dc.layer_stride_bytes + dst_off;
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (i0 + 256 * u < n16) st16<NT>(dst + ((int64_t)(i0 + 256 * u) << 4), r[u]);
-        };
-        const int l = blockIdx.y;
-        u32x4 cur[4];
-        vload(l, tid, cur);
-        for (int i0 = tid; i0 - tid < n16; i0 += 1024) {
-            const bool more = i0 + 1024 - tid < n16;  // workgroup-uniform
-            u32x4 nxt[4];
-            if (more) vload(l, i0 + 1024, nxt);
-            vstore(l, i0, cur);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
-        }
-        return;
-    }
-
-    // ---- K ----
-    if (blockIdx.y == 0 && tid < n_tok) {
-        const int slot = td.dst_slot + t_first + tid;
-        if (dc.slot_shot) dc.slot_shot[slot] = td.shot;
-        if (dc.slot_tok) dc.slot_tok[slot] = td.tok0 + t_first + tid;
-        if (dc.slot_pos) dc.slot_pos[slot] = dc.pos0 + slot;
-    }
-
-    const int rpt = p.n_kv_heads * CH;  // lane items per token: (head, chunk)
+    const int64_t row_bytes = (int64_t)n_kv_heads * HEAD_BYTES;
+    const int rpt = n_kv_heads * CH;  // lane items per token: (head, chunk)
     const int n_items = n_tok * rpt;
     // One step of the K stream: up to KI (head, chunk) items per lane, both pair partners of each
     // (2 * KI 16-byte loads in flight per lane, the same as a V step).
@@ -147,7 +143,7 @@ __global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p
         int64_t off[KI];
         int csi[KI];
     };
-    auto load_step = [&](const char* src, int base, Step& st) __attribute__((always_inline)) {
+    auto load_step = [&](int base, Step& st) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < KI; ++u) {
             const int f = base + u * 256 + tid;
@@ -156,14 +152,16 @@ __global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p
                 const int r = f - tau * rpt;
                 const int h = r / CH;
                 const int c = r - h * CH;
-                st.off[u] = (int64_t)tau * row_bytes + h * HEAD_BYTES + c * 16;
+                const int within = h * HEAD_BYTES + c * 16;
+                st.off[u] = (int64_t)tau * row_bytes + within;
                 st.csi[u] = tau * HALF + c * NP;
-                st.a[u] = ld16(src + st.off[u]);
-                st.b[u] = ld16(src + st.off[u] + CH * 16);
+                const char* src = pool + rows.row(tau) + within;
+                st.a[u] = ld16(src);
+                st.b[u] = ld16(src + CH * 16);
             }
         }
     };
-    auto store_step = [&](char* dst, int base, Step& st) __attribute__((always_inline)) {
+    auto store_step = [&](int base, Step& st) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < KI; ++u) {
             const int f = base + u * 256 + tid;
@@ -176,19 +174,16 @@ __global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p
     };
     // The first keys are requested before the angle table is built, so that the table's own loads and
     // arithmetic run under their latency.
-    const int l = blockIdx.y;
-    const char* ksrc = p.k_pool + (int64_t)l * p.pool_layer_stride_bytes + src_off;
-    char* kdst = dc.k_out + (int64_t)l * dc.layer_stride_bytes + dst_off;
     Step first;
-    load_step(ksrc, 0, first);
+    load_step(0, first);
 
-    // cos/sin of every (token, frequency) of the tile, two frequencies per step.
+    // cos/sin of every (token, frequency), two frequencies per step.
     for (int it = tid; it < n_tok * (HALF / 2); it += 256) {
         const int tau = it / (HALF / 2);
         const int f2 = it - tau * (HALF / 2);
-        const int a = td.angle0 + (t_first + tau) * td.angle_step;
-        const f32x4 h = *(const f32x4*)(p.tab_hi + (int64_t)(a >> kRopeLoBits) * HALF + 2 * f2);
-        const f32x4 l = *(const f32x4*)(p.tab_lo + (a & (kRopeLo - 1)) * HALF + 2 * f2);
+        const int a = angle(tau);
+        const f32x4 h = *(const f32x4*)(tab_hi + (int64_t)(a >> kRopeLoBits) * HALF + 2 * f2);
+        const f32x4 l = *(const f32x4*)(tab_lo + (a & (kRopeLo - 1)) * HALF + 2 * f2);
         f32x4 r;
         r[0] = h[0] * l[0] - h[1] * l[1];  // cos(A+B)
         r[1] = h[1] * l[0] + h[0] * l[1];  // sin(A+B)
@@ -204,10 +199,112 @@ __global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p
     for (int base = 0; base < n_items; base += KI * 256) {
         const bool more = base + KI * 256 < n_items;
         Step nxt;
-        if (more) load_step(ksrc, base + KI * 256, nxt);
-        store_step(kdst, base, cur);
+        if (more) load_step(base + KI * 256, nxt);
+        store_step(base, cur);
         cur = nxt;
     }
+}
+
+template <int DTYPE, int CH, bool NT>
+__global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p) {
+    constexpr int HALF = CH * (DTYPE == ADAPSHOT_BF16 ? 8 : 4);
+    __shared__ float2 cs[kTileTok * HALF];
+
+    const int tid = threadIdx.x;
+    const int parts = kTileTok / p.wg_tok;
+    const TileDesc td = p.tiles[blockIdx.x / parts];
+    const int t_first = (int)(blockIdx.x % parts) * p.wg_tok;  // this workgroup's tokens of the tile: t_first .. t_first + n_tok - 1
+    const int n_tok = td.n_tok - t_first < p.wg_tok ? td.n_tok - t_first : p.wg_tok;
+    if (n_tok <= 0) return;  // a ragged tile's last parts are empty (workgroup-uniform)
+    // the first cache's entry is read without waiting for the descriptor: a launch for one cache needs no other
+    AssembleDst dc = p.dst[0];
+    if (p.n_dst != 1) dc = p.dst[__builtin_amdgcn_readfirstlane(td.cache)];
+    const int64_t row_bytes = (int64_t)p.n_kv_heads * (2 * CH * 16);
+    const DenseRows rows{(int64_t)(td.src_tok + t_first) * row_bytes, row_bytes};
+    const int64_t dst_off = (int64_t)(td.dst_slot + t_first) * row_bytes + (int64_t)blockIdx.y * dc.layer_stride_bytes;
+    const int64_t pool_off = (int64_t)blockIdx.y * p.pool_layer_stride_bytes;
+
+    if (blockIdx.z == 1) {
+        copy_v<NT>(p.v_pool + pool_off, rows, dc.v_out + dst_off, n_tok, row_bytes);
+        return;
+    }
+    if (blockIdx.y == 0 && tid < n_tok) {
+        const int slot = td.dst_slot + t_first + tid;
+        if (dc.slot_shot) dc.slot_shot[slot] = td.shot;
+        if (dc.slot_tok) dc.slot_tok[slot] = td.tok0 + t_first + tid;
+        if (dc.slot_pos) dc.slot_pos[slot] = dc.pos0 + slot;
+    }
+    rotate_k<DTYPE, CH, NT>(p.k_pool + pool_off, rows, dc.k_out + dst_off, n_tok, p.n_kv_heads, p.tab_lo, p.tab_hi, cs,
+                            [&](int tau) __attribute__((always_inline)) { return td.angle0 + (t_first + tau) * td.angle_step; });
+}
+
+// One cache, the shot list in the kernel arguments (a read there takes 0.25 us, one of a descriptor in host memory 1.3 to 1.8
+// us, and 4.5 once thousands of workgroups ask), and workgroups cut by cache slots: none of them is empty or ragged.  Every
+// wavefront finds the shots of its workgroup's first and last slot by itself: the list's starts a lane each, and the
+// number of starts at or before a slot from ballots.  Where the two differ (one in ten at 100 tokens a shot and 8 a
+// workgroup) the rows are looked up one by one.  Bound by the launch and three round trips below 1000 tokens, by the copy's
+// rate from 10000 on.  Descriptors / this list, kernel (call after call, with the event that guards the descriptors), us:
+//   fp32 4/2 x 64, 225 tokens 4.2 / 4.1 (7.5 / 6.0)              bf16 32/8 x 128, 644 tokens 4.8 / 4.3 (8.0 / 5.5)
+//   the same, 3.2k tokens 8.0 / 6.4 (10.4 / 6.6)                 32/8 x 64, 2 layers of 6.5k 15.0 / 12.3 (18.4 / 13.0)
+//   32/8 x 128, 25.5k tokens 36.4 / 35.8 (41.1 / 36.9)           28 layers of 26.5k 1088 / 1041 (5.6 / 5.8 TB/s)
+template <int DTYPE, int CH, bool NT>
+__global__ __launch_bounds__(256) void assemble_shots_kernel(AssembleShotsParams p) {
+    constexpr int HALF = CH * (DTYPE == ADAPSHOT_BF16 ? 8 : 4);
+    __shared__ float2 cs[kTileTok * HALF];
+    __shared__ int32_t row_tok[kTileTok], row_angle[kTileTok];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int s0 = (int)blockIdx.x * p.wg_tok;  // this workgroup's slots, counted from the call's first: s0 .. s0 + n_tok - 1
+    const int n_tok = p.n_tokens - s0 < p.wg_tok ? p.n_tokens - s0 : p.wg_tok;
+    int i0 = -1, i1 = -1;  // shots of the first and the last slot: one less than the number of starts at or before it
+    for (int b = 0; b < p.n_shots; b += 64) {
+        const int start = b + lane < p.n_shots ? p.shots[b + lane].slot : INT32_MAX;
+        const int n0 = (int)__popcll(__builtin_amdgcn_ballot_w64(start <= s0));
+        const int n1 = (int)__popcll(__builtin_amdgcn_ballot_w64(start <= s0 + n_tok - 1));
+        i0 += n0;
+        i1 += n1;
+        if (n1 < 64) break;  // starts do not decrease
+    }
+    i0 = __builtin_amdgcn_readfirstlane(i0);
+    i1 = __builtin_amdgcn_readfirstlane(i1);
+    const ShotRun first = p.shots[i0];
+    const int64_t row_bytes = (int64_t)p.n_kv_heads * (2 * CH * 16);
+    const int64_t dst_off = (int64_t)(p.slot0 + s0) * row_bytes + (int64_t)blockIdx.y * p.dst.layer_stride_bytes;
+    const char* const pool = (blockIdx.z == 1 ? p.v_pool : p.k_pool) + (int64_t)blockIdx.y * p.pool_layer_stride_bytes;
+    char* const out = (blockIdx.z == 1 ? p.dst.v_out : p.dst.k_out) + dst_off;
+    const int pos = (int)p.dst.pos0 + p.slot0 + s0;  // of the first slot (below max_position <= 2^30)
+    const bool one = i0 == i1;
+    const DenseRows dense{(int64_t)(first.src_tok + s0 - first.slot) * row_bytes, row_bytes};
+    const GatheredRows gathered{row_tok, row_bytes};
+    if (!one || (blockIdx.y == 0 && blockIdx.z == 0)) {
+        if (tid < n_tok) {
+            int i = i0;
+            while (i < i1 && p.shots[i + 1].slot <= s0 + tid) ++i;
+            const ShotRun run = p.shots[i];
+            const int t = s0 + tid - run.slot;
+            row_tok[tid] = run.src_tok + t;
+            row_angle[tid] = p.local ? pos - s0 + run.slot : pos + tid;
+            if (blockIdx.y == 0 && blockIdx.z == 0) {
+                const int slot = p.slot0 + s0 + tid;
+                if (p.dst.slot_shot) p.dst.slot_shot[slot] = run.shot;
+                if (p.dst.slot_tok) p.dst.slot_tok[slot] = t;
+                if (p.dst.slot_pos) p.dst.slot_pos[slot] = p.dst.pos0 + slot;
+            }
+        }
+        if (!one) __syncthreads();
+    }
+    if (blockIdx.z == 1) {
+        if (one) copy_v<NT>(pool, dense, out, n_tok, row_bytes);
+        else copy_v<NT>(pool, gathered, out, n_tok, row_bytes);
+        return;
+    }
+    const int angle0 = p.local ? pos - s0 + first.slot : pos, step = p.local ? 0 : 1;
+    if (one)
+        rotate_k<DTYPE, CH, NT>(pool, dense, out, n_tok, p.n_kv_heads, p.tab_lo, p.tab_hi, cs,
+                                [&](int tau) __attribute__((always_inline)) { return angle0 + tau * step; });
+    else
+        rotate_k<DTYPE, CH, NT>(pool, gathered, out, n_tok, p.n_kv_heads, p.tab_lo, p.tab_hi, cs,
+                                [&](int tau) __attribute__((always_inline)) { return row_angle[tau]; });
 }
 
 template <int DTYPE, int CH>
@@ -223,12 +320,22 @@ static hipError_t launch_t(const AssembleParams& p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t launch_assemble(const AssembleParams& p, hipStream_t stream) {
+template <int DTYPE, int CH>
+static hipError_t launch_t(const AssembleShotsParams& p, hipStream_t stream) {
+    const dim3 grid((unsigned)((p.n_tokens + p.wg_tok - 1) / p.wg_tok), (unsigned)p.n_layers, 2);
+    const int64_t e = DTYPE == ADAPSHOT_BF16 ? 2 : 4;
+    if (2 * (int64_t)p.n_tokens * p.n_kv_heads * p.head_dim * e * p.n_layers > kAssembleStreamBytes)
+        launch_kernel((assemble_shots_kernel<DTYPE, CH, true>), grid, dim3(256), stream, p);
+    else
+        launch_kernel((assemble_shots_kernel<DTYPE, CH, false>), grid, dim3(256), stream, p);
+    return hipGetLastError();
+}
+
+template <typename P>
+static hipError_t launch_by_shape(const P& p, hipStream_t stream) {
     const int e = p.dtype == ADAPSHOT_BF16 ? 2 : 4;
     const int ch = p.head_dim / 2 * e / 16;
-    if (p.n_tiles <= 0) return hipSuccess;
     if (p.wg_tok < 1 || p.wg_tok > kTileTok || (p.wg_tok & (p.wg_tok - 1)) != 0) return hipErrorInvalidValue;
-    if ((int64_t)p.n_tiles * (kTileTok / p.wg_tok) > INT32_MAX) return hipErrorInvalidValue;
     if (p.dtype == ADAPSHOT_BF16) {
         switch (ch) {
             case 1: return launch_t<ADAPSHOT_BF16, 1>(p, stream);
@@ -247,6 +354,18 @@ hipError_t launch_assemble(const AssembleParams& p, hipStream_t stream) {
         }
     }
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_assemble(const AssembleParams& p, hipStream_t stream) {
+    if (p.n_tiles <= 0) return hipSuccess;
+    if (p.wg_tok > 0 && (int64_t)p.n_tiles * (kTileTok / p.wg_tok) > INT32_MAX) return hipErrorInvalidValue;
+    return launch_by_shape(p, stream);
+}
+
+hipError_t launch_assemble_shots(const AssembleShotsParams& p, hipStream_t stream) {
+    if (p.n_tokens <= 0) return hipSuccess;
+    if (p.n_shots < 1 || p.n_shots > kAssembleShots || p.shots[0].slot != 0) return hipErrorInvalidValue;
+    return launch_by_shape(p, stream);
 }
 
 // ---- decode append ------------------------------------------------------------------------------
