@@ -622,10 +622,15 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
     StreamLaunch sl;
     sl.row_blocks = plan.row_blocks;
     int64_t unit0 = 0, grid_x = 0, n_split = 1, wgs = 0;
+    // own tokens in splits of their own as long as the workgroups fit the chip
+    int64_t own = 0;
+    for (int32_t i = 0; i < n_items; ++i)
+        own += stream_units(d, shapes[i], sl.row_blocks) * stream_splits(d, items[i].n_ctx, items[i].t_q, plan.split_tiles);
     for (int32_t i = 0; i < n_items; ++i) {
         StreamItem& it = items[i];
         it.keys_per_split = (int32_t)(plan.split_tiles * 64);
-        it.n_split = (int32_t)stream_splits(d, it.n_ctx, it.t_q, plan.split_tiles);
+        it.n_split = (int32_t)(own <= ctx->n_cu ? stream_splits(d, it.n_ctx, it.t_q, plan.split_tiles)
+                                                : std::max<int64_t>(1, (shapes[i].key_tiles + plan.split_tiles - 1) / plan.split_tiles));
         const int64_t here = stream_units(d, shapes[i], sl.row_blocks);
         it.unit0 = (int32_t)unit0;
         unit0 += here;
@@ -685,7 +690,7 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
                                          int64_t q_pos0, void* out, const int32_t* slot_src, const float2* tile_rot,
                                          hipStream_t stream, int64_t ctx_pos0) {
     const adapshot_model_desc& d = ctx->desc;
-    if (!single_by_tiles(d, t_q, n_ctx, slot_src != nullptr)) {
+    if (!single_by_tiles(d, t_q, n_ctx, slot_src != nullptr, ctx->n_cu)) {
         StreamItem it = stream_item(k_ctx, v_ctx, n_ctx, q, k_self, v_self, t_q, q_pos0, out);
         return run_stream(ctx, &it, 1, slot_src, ctx_pos0, stream);
     }
@@ -1232,16 +1237,18 @@ extern "C" adapshot_status adapshot_query_attn_pool_batched(adapshot_ctx* ctx, i
     return st;
 }
 
-// Batches that the streaming kernel takes from the tile kernel (attn_tile_kernel): every context is read by one item --
-// items that share one find its tiles in the L2 when the tile kernel orders them by cache and split.
+// Batches that the streaming kernel takes from the tile kernel: decode steps (one 16-row block per kv head and item), as far as
+// their contexts are few bytes (stream_bytes_ok) and every one is read by one item -- items that share one find its tiles in the
+// L2 when the tile kernel orders them by cache and split.  A batch of one is priced like a single call.
 static bool streams_batch(const adapshot_ctx* ctx, const adapshot_attn_item* items, int32_t n_items) {
     const int32_t g = ctx->desc.n_q_heads / ctx->desc.n_kv_heads;
+    if (n_items == 1) return !single_by_tiles(ctx->desc, items[0].t_q, items[0].n_ctx, false, ctx->n_cu);
     std::vector<int32_t> seen;
     seen.reserve((size_t)n_items);
     int64_t tokens = 0;
     for (int32_t i = 0; i < n_items; ++i) {
         tokens += items[i].n_ctx;
-        if (attn_tile_kernel(ctx->desc, (int64_t)items[i].t_q * g, tokens, false)) return false;
+        if ((int64_t)items[i].t_q * g > 16 || !stream_bytes_ok(ctx->desc, tokens)) return false;
         if (items[i].n_ctx > 0) seen.push_back(items[i].cache_index);
     }
     std::sort(seen.begin(), seen.end());

@@ -73,22 +73,6 @@ inline int64_t plan_mfma_splits(int64_t n_cu, int64_t units, int64_t key_tiles, 
     return best;
 }
 
-// Which kernel: the 256-row tile kernel for bf16 models of head dimension 128, unless the rows of a kv head fit one 16-row
-// block (a decode step) and the launch reads at most kStreamBytes of context: the streaming kernel is one launch instead
-// of three and keeps every wavefront busy, but draws 5.3 TB/s from the memory where the tile kernel draws 6.1.  Per layer
-// of a decode step (tile kernel / streaming kernel, us): 25 MB 27.2 / 15.6, 98 MB 34.1 / 30.7, 197 MB 48.2 / 46.5 (28 queries
-// of 4k slots, 229 MB: 56.9 / 55.6), 354 MB 73.2 / 76.8, 826 MB 153 / 167.
-// A single call has no table to copy, so the tile kernel is two launches there, and with more than 8 rows the partials of
-// a context that needs splits cost the streaming kernel what the second launch costs (32/8 heads, 4 tokens = 16 rows, over
-// 244 / 900 / 2.5k / 6.8k slots: 11.3 / 12.3 / 14.5 / 16.6 us by tiles, 10.4 / 11.9 / 14.8 / 17.5 by streaming; 1 token = 4 rows:
-// 11.5 / 12.4 / 14.6 / 16.7 and 9.7 / 10.2 / 11.0 / 12.9).
-constexpr int64_t kStreamBytes = 200000000;
-inline bool attn_tile_kernel(const adapshot_model_desc& d, int64_t rows, int64_t context_tokens, bool single) {
-    if (!attn_mfma_supported(d)) return false;
-    return rows > 16 || (single && rows > 8 && context_tokens > 1024) ||
-           context_tokens * d.n_kv_heads * d.head_dim * 4 > kStreamBytes;
-}
-
 // 16-row blocks per workgroup of the streaming kernel.  Two share the loads of K and V, but leave half the workgroups: fp32
 // models want two workgroups per compute unit with one block each before that pays, bf16 models, whose products cost
 // less, half a workgroup and a context of some length (64 query tokens of 32/8 heads, one block / two: 6.4k slots
@@ -129,31 +113,44 @@ inline int64_t stream_splits(const adapshot_model_desc& d, int64_t n_ctx, int64_
     return (last + kStreamWaves - 1) / kStreamWaves > (keys / sk + kStreamWaves - 1) / kStreamWaves ? n + 1 : n;
 }
 
-// Split length (in 64-key tiles) of a launch of the streaming kernel: the longest context in n equal splits, the others in
-// splits of the same length, n the count whose price is lowest.  A tile keeps each of a compute unit's four matrix cores
-// busy for a 16-key step (bf16: half a 32-key step) of matrix instructions, softmax and load latency; a decode step is
-// bound by loads, 0.85 us per tile and workgroup, 6.2 TB/s in all.  Splitting costs the merge: 2.2 us, a little per
-// partial, and 0.8 us for every round of loads after the first (8 splits in flight per thread, a thread per 16 bytes)
-// (fp32, head_dim 128, one query over 2300 slots: 55 us in one split, 11.8 us in 36; a decode step over 16k slots: 33.6 us in
-// 8 splits, 19.5 in 32, 19.0 in 48, 21.7 in 64).
+// What a launch of the streaming kernel takes, us, by its longest split (in 64-key tiles).  A workgroup spends 4.5 us before its
+// first product and after its last one, and 0.6 us plus the loads of 82 KB/us for every round of its 8 wavefronts over its keys
+// (bf16 x 128: 2.2 us per 256 keys; bf16 x 64 and fp32 x 64: 1.4 per 256 and 128; 1.1 over an assembled cache, 2 and more where the
+// keys are gathered and rotated on the way, which is planned alike).  Splits cost their merge: 3 to 7 us where all workgroups fit
+// the chip and share it, 9 where they do not and the last one to arrive does it (fp32 x 128, 64 tokens over 6k slots: 8 splits of
+// 32 units 23.8 us, 10 splits 37.3).  So a problem gets the splits that fill the chip once, or none.  Measured / priced: 32/8 x 128,
+// 24 tokens over 830 slots, 5 splits 9.8 / 11.5 (1: 12.3 / 13.3); 64 tokens over 1.7k, 2 splits 16.7 / 18.3 (1: 19.8 / 19.9); 1 token over
+// 6.8k, 27 splits 10.4 / 11.2 (10: 13.5 / 14); 64 x bf16, 64 tokens over 2k, 4 splits 12.7 / 12.3 (1: 16.7 / 15.7); 4/2 x 64 fp32, 16 tokens over
+// 250, 1 split 6.5 / 7.3 (4: 7.8 / 8.1), over 1000, 16 splits 7.9 / 8.7 (1: 13.6 / 15.7).
+inline double stream_price(const adapshot_model_desc& d, int64_t n_cu, const StreamShape* shapes, int32_t n_shapes, int32_t row_blocks,
+                           int64_t split_tiles) {
+    const int64_t e = d.dtype == ADAPSHOT_BF16 ? 2 : 4, sk = stream_step_keys(d);
+    const double round_us = 0.6 + (double)(kStreamWaves * sk * 2 * d.head_dim * e) / 82e3;
+    int64_t units = 0, wgs = 0, read = 0, drawn = 0, longest = 0;  // tiles of a kv head: read by all workgroups, drawn from the memory
+    for (int32_t i = 0; i < n_shapes; ++i) {
+        const int64_t here = stream_units(d, shapes[i], row_blocks);
+        units += here;
+        wgs += here * std::max<int64_t>(1, (shapes[i].key_tiles + split_tiles - 1) / split_tiles);
+        read += here * shapes[i].key_tiles;
+        drawn += d.n_kv_heads * shapes[i].key_tiles;
+        longest = std::max(longest, shapes[i].key_tiles);
+    }
+    const int64_t steps = std::min(split_tiles, longest) * 64 / sk, launch_rounds = (wgs + n_cu - 1) / n_cu;
+    const double tile_mb = (double)(128 * d.head_dim * e) * 1e-6;
+    const double t = (double)launch_rounds * (4.5 + (double)((steps + kStreamWaves - 1) / kStreamWaves) * round_us);
+    const double loads = 4.5 + std::max((double)read * tile_mb / (0.045 * (double)n_cu), (double)drawn * tile_mb / 6.2);
+    // (a launch bound by the memory still wants its compute units busy: one token over 27k slots of 32/8 heads, 12 splits 35.2 us, 24
+    // 28.6, 31 26.5; and of plans that cost the same the one with more workgroups, up to the chip's)
+    return std::max(t, loads) + 0.1 * std::min(t, loads) + (split_tiles >= longest ? 0.0 : launch_rounds == 1 ? 2.8 + 4.0 * (double)units / (double)n_cu : 9.0) -
+           0.001 * (double)std::min(wgs, n_cu);
+}
+
+// Split length (in 64-key tiles) of a launch: the longest context in n equal splits, the others in splits of the same length.
 inline int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_cu, const StreamShape* shapes, int32_t n_shapes,
                                        int32_t row_blocks) {
-    int64_t unit_rows = 0;  // of the fullest unit
-    for (int32_t i = 0; i < n_shapes; ++i) unit_rows = std::max(unit_rows, std::min<int64_t>(shapes[i].rows, 16 * row_blocks));
-    int64_t longest = 0, unit_tiles = 0;
-    for (int32_t i = 0; i < n_shapes; ++i) {
-        longest = std::max(longest, shapes[i].key_tiles);
-        unit_tiles += stream_units(d, shapes[i], row_blocks) * shapes[i].key_tiles;
-    }
+    int64_t longest = 0;
+    for (int32_t i = 0; i < n_shapes; ++i) longest = std::max(longest, shapes[i].key_tiles);
     if (longest == 0) return 1;
-    const bool bf = d.dtype == ADAPSHOT_BF16;
-    const int64_t blocks = std::max(1, d.head_dim / 16);
-    const int64_t pv = bf ? 3 * blocks * 8 : 4 * 32 * blocks;
-    const int64_t qk = bf ? std::max(1, d.head_dim / 32) * 16 : d.head_dim / 4 * 32;
-    const double tile_us = bf && d.head_dim == 128 ? 0.85 : (double)(row_blocks * (pv + qk) + 250) / 2100.0;
-    const double bytes_us = bf && d.head_dim == 128 ? (double)unit_tiles * 32768.0 / 6.2e6 : 0.0;
-    const int64_t pieces = std::max<int64_t>(1, unit_rows * d.head_dim / 4);  // 16-byte pieces of a unit's rows, one per thread
-    const int64_t round_splits = 8 * std::max<int64_t>(1, 64 * kStreamWaves / pieces);
     const int64_t n_max = std::min<int64_t>(longest, kStreamMaxSplits);
     int64_t best = longest, last = 0;
     double best_t = 1e300;
@@ -161,11 +158,7 @@ inline int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_c
         const int64_t st = (longest + n - 1) / n;
         if (st == last) continue;  // no shorter splits than with one fewer
         last = st;
-        int64_t wgs = 0;
-        for (int32_t i = 0; i < n_shapes; ++i) wgs += stream_units(d, shapes[i], row_blocks) * std::max<int64_t>(1, (shapes[i].key_tiles + st - 1) / st);
-        const int64_t rounds = (wgs + n_cu - 1) / n_cu;
-        const double merge = 2.2 + 0.03 * (double)n + 0.8 * (double)((n - 1) / round_splits);
-        const double t = std::max((double)(rounds * st) * tile_us, bytes_us) + (n > 1 ? merge : 0.0);
+        const double t = stream_price(d, n_cu, shapes, n_shapes, row_blocks, st);
         if (t < best_t) {
             best_t = t;
             best = st;
@@ -199,10 +192,37 @@ inline StreamPlan plan_stream(const adapshot_model_desc& d, int64_t n_cu, int32_
     return p;
 }
 
-// The kernel of a single call: zero-copy calls of the tile kernel's shapes always run it (the streaming kernel has no gathered
-// form of head dimension 128 in bf16).
-inline bool single_by_tiles(const adapshot_model_desc& d, int32_t t_q, int64_t n_ctx, bool zero_copy) {
-    return (zero_copy && attn_mfma_supported(d)) || attn_tile_kernel(d, (int64_t)t_q * (d.n_q_heads / d.n_kv_heads), n_ctx, true);
+// Which kernel: the 256-row tile kernel for bf16 models of head dimension 128 where it is the cheaper one.  It reads a context
+// once per 256 rows and draws 6.1 TB/s, but is two launches (a batch: three), leaves wavefronts without rows idle and
+// writes a partial for every split; the streaming kernel reads it once per 16 rows, in one launch.
+// A batch goes to the streaming kernel if its items have at most 16 rows and its contexts at most kStreamBytes.  Per layer of a
+// decode step (tile kernel / streaming kernel, us): 25 MB 27.2 / 15.6, 98 MB 34.1 / 30.7, 197 MB 48.2 / 46.5 (28 queries
+// of 4k slots, 229 MB: 56.9 / 55.6), 354 MB 73.2 / 76.8, 826 MB 153 / 167.
+constexpr int64_t kStreamBytes = 200000000;
+inline bool stream_bytes_ok(const adapshot_model_desc& d, int64_t context_tokens) {
+    return context_tokens * d.n_kv_heads * d.head_dim * 4 <= kStreamBytes;
+}
+// A single call compares prices.  The tile kernel's, fitted to calls of 64 to 512 rows over 250 to 5000 slots: 13 us for
+// the two launches, 0.75 us per MB of partials, 0.65 or (more than 128 rows) 1 us per tile of a workgroup.  Us, tile /
+// streaming: 32/8 heads, 8 tokens over 250 / 1.7k / 3.4k slots 14.0 / 14.5 / 15.6 and 10.7 / 10.4 / 11.2; 24 tokens over 830 / 3.4k
+// 13.7 / 17.6 and 10.4 / 16.4; 64 tokens over 250 / 1.7k / 3.4k 14.6 / 23.5 / 24.6 and 10.1 / 17.6 / 24.5; 28/4 heads, 16 tokens over 5k
+// 18.9 and 14.8, 64 tokens over 5k 24.5 and 32.1; 64/8 heads, 16 tokens over 5k 20.1 and 22.7.
+inline bool single_by_tiles(const adapshot_model_desc& d, int32_t t_q, int64_t n_ctx, bool zero_copy, int64_t n_cu = 256) {
+    if (!attn_mfma_supported(d)) return false;
+    if (zero_copy || !stream_bytes_ok(d, n_ctx)) return true;  // (no gathered form of the streaming kernel for these models)
+    const int64_t rows = (int64_t)t_q * (d.n_q_heads / d.n_kv_heads), key_tiles = (n_ctx + 63) / 64, self_tiles = ((int64_t)t_q + 63) / 64;
+    // (from 100 MB on the partials of more than 8 rows cost more than the second launch: 32/8 heads, 4 tokens over 24k / 27k slots 27.9 /
+    // 30.5 by tiles, 26.5 / 35 by streaming)
+    if (rows > 16 * kAttnRowTile || (rows > 8 && !stream_bytes_ok(d, 2 * n_ctx))) return true;
+    const StreamShape sh{rows, key_tiles + self_tiles};  // (the query's own tokens as more context)
+    const int32_t rb = stream_row_blocks(d, n_cu, &sh, 1);
+    const double stream = stream_price(d, n_cu, &sh, 1, rb, plan_stream_split_tiles(d, n_cu, &sh, 1, rb));
+    const int64_t units = d.n_kv_heads * ((rows + kAttnRowTile - 1) / kAttnRowTile);
+    const int64_t n_split = key_tiles > 0 ? plan_mfma_splits(n_cu, units, key_tiles, self_tiles) : 0;
+    const int64_t per_wg = n_split > 0 ? (key_tiles + n_split - 1) / n_split : 0;
+    const double drawn_mb = (double)(key_tiles * d.n_kv_heads * 256 * d.head_dim) * 1e-6;
+    const double partials_mb = (double)((n_split + 1) * rows * d.n_kv_heads * d.head_dim * 2) * 1e-6;
+    return 13.0 + 0.75 * partials_mb + std::max((rows > 128 ? 1.0 : 0.65) * (double)per_wg, drawn_mb / 6.1) < stream;
 }
 
 // Split the context of one attention call so that (kv heads x row tiles x splits) fills the chip.  Keys per
@@ -214,7 +234,7 @@ inline void plan_single_attn(const adapshot_model_desc& d, int64_t n_cu, int32_t
     const int64_t key_tiles = (n_ctx + 63) / 64;
     int64_t n_split = 0, keys_per_split = 64;
     if (key_tiles > 0) {
-        if (single_by_tiles(d, t_q, n_ctx, zero_copy)) {
+        if (single_by_tiles(d, t_q, n_ctx, zero_copy, n_cu)) {
             const int64_t units = d.n_kv_heads * ((rows + kAttnRowTile - 1) / kAttnRowTile);
             n_split = force_splits > 0 ? std::min<int64_t>(force_splits, key_tiles)
                                        : plan_mfma_splits(n_cu, units, key_tiles, ((int64_t)t_q + 63) / 64);

@@ -75,12 +75,12 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     constexpr int NK = BF && D <= 128 ? 2 : 1;        // 16-key blocks of a step
     constexpr int SK = 16 * NK;                       // keys of a step
     constexpr int NV = 4 * NK;                        // V rows of a lane
-    constexpr int NP = BF ? (D == 128 ? 1 : 3) : 0;   // bf16 pieces of a softmax weight (fp32 models: as it is)
+    constexpr int NP = BF ? (D == 128 ? 2 : 3) : 0;   // bf16 pieces of a softmax weight (fp32 models: as it is)
     constexpr int STEP_REGS = NJ * KR + 4 * DG * VR;
     // The next step's K and V are loaded while this one is computed (two steps ahead is no faster and costs 16 to 32
     // registers); a step of 256 bytes per lane leaves room for its K alone, V is then loaded under the first product.
     constexpr int NB = 2;
-    constexpr int NBV = STEP_REGS > (BF ? 48 : 32) ? 1 : 2;
+    constexpr int NBV = STEP_REGS > (BF ? 48 : 32) || (BF && POOL && NR == 2) ? 1 : 2;
     constexpr int TR = 16 * NR;
     constexpr int NS = NR * DB;  // 1 KB pieces of a wavefront's output state
     static_assert(D == 8 || D % 16 == 0, "head dimensions");
@@ -123,8 +123,11 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     const char* const vctx = it.v_ctx + (int64_t)hk * D * E + (POOL ? 0 : k0 * stride);
 
     // ---- loads of step s.  Steps past the end read no rows (the zero-copy form: one row again, all lanes the same bytes).
-    // Zero-copy form: pool tokens of the rows of the next step to load, fetched one step before the rows
-    int tok_k[NK] = {}, tok_v[NV] = {};
+    // Zero-copy form: pool tokens of the rows of the next step to load, and (next) of the one after it.  These are requested ahead of
+    // the rows of the step before theirs: loads return in order, and behind those rows they would be waited for with them.
+    // (Where registers are short they are requested behind them, or, if V is loaded that late, ahead of their own.)
+    constexpr bool TOK2 = NBV > 1 && NR == 1;
+    int tok_k[NK] = {}, tok_v[NV] = {}, next_k[NK] = {}, next_v[NV] = {};
     auto pool_tok = [&](int u) __attribute__((always_inline)) -> int {
         u = u < nk ? u : nk - 1;
         u = u > 0 ? u : 0;
@@ -133,10 +136,16 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     auto fetch_tok = [&](int s) __attribute__((always_inline)) {
         if (POOL && nk > 0) {
 #pragma unroll
-            for (int b = 0; b < NK; ++b) tok_k[b] = pool_tok(SK * s + 16 * b + l16);
+            for (int b = 0; b < NK; ++b) next_k[b] = pool_tok(SK * s + 16 * b + l16);
 #pragma unroll
-            for (int r = 0; r < NV; ++r) tok_v[r] = pool_tok(SK * s + 16 * (r >> 2) + 4 * kg + (r & 3));
+            for (int r = 0; r < NV; ++r) next_v[r] = pool_tok(SK * s + 16 * (r >> 2) + 4 * kg + (r & 3));
         }
+    };
+    auto take_tok = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < NK; ++b) tok_k[b] = next_k[b];
+#pragma unroll
+        for (int r = 0; r < NV; ++r) tok_v[r] = next_v[r];
     };
     auto row_off = [&](bool on, int tok) __attribute__((always_inline)) -> uint64_t {  // the rows of a pool may span more than 4 GiB
         unsigned t = (unsigned)tok;
@@ -321,10 +330,13 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     unsigned kf[NB][NK][NJ][KR];
     unsigned vf[NBV][NV][DG][VR];
     fetch_tok(wave);
+    take_tok();
+    if (TOK2) fetch_tok(wave + W);
     load_k(wave, kf[0]);
     if (NBV > 1) {
         load_v(wave, vf[0]);
-        fetch_tok(wave + W);
+        if (!TOK2) fetch_tok(wave + W);
+        take_tok();
     }
 #pragma unroll
     for (int i = 0; i < QI; ++i) {
@@ -389,14 +401,23 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     };
     clear();
 
+    // keys that come un-rotated, turned to their positions: before the next step's rows are requested, which the tables' entries would
+    // otherwise be waited for with
+    auto turn = [&](int s, unsigned (&k)[NK][NJ][KR]) __attribute__((always_inline)) {
+        const bool self = s >= n_cs;
+#pragma unroll
+        for (int kb = 0; kb < NK; ++kb) {
+            if (self) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16);
+            else if (POOL) rotate(k[kb], p.ctx_pos0 + k0 + SK * s + 16 * kb + l16);
+        }
+    };
+
     // key_by_key: the second product without matrix instructions (for values that are not finite, see below)
     auto compute = [&](int s, unsigned (&k)[NK][NJ][KR], unsigned (&v)[NV][DG][VR], auto key_by_key) __attribute__((always_inline)) {
         const bool self = s >= n_cs;  // wavefront-uniform
         f32x4 sc[NK][NR];
 #pragma unroll
         for (int kb = 0; kb < NK; ++kb) {
-            if (self) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16);
-            else if (POOL) rotate(k[kb], p.ctx_pos0 + k0 + SK * s + 16 * kb + l16);
 #pragma unroll
             for (int nr = 0; nr < NR; ++nr) sc[kb][nr] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -497,15 +518,16 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
 #pragma unroll
                 for (int w = 0; w < 2 * NK; ++w) {
                     float x = sc[w >> 1][nr][2 * (w & 1)], y = sc[w >> 1][nr][2 * (w & 1) + 1];
-                    if (NP == 1) {
-                        pb[nr][0][w] = pack2_bf16(x, y);
-                    } else {
 #pragma unroll
-                        for (int i = 0; i < NP; ++i) {  // the upper 8 of the bits that are left, exactly
-                            pb[nr][i][w] = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
-                            x -= __uint_as_float(__float_as_uint(x) & 0xffff0000u);
-                            y -= __uint_as_float(__float_as_uint(y) & 0xffff0000u);
+                    for (int i = 0; i < NP; ++i) {
+                        if (NP == 2 && i == 1) {  // rounded: 2^-17 of the weight
+                            pb[nr][i][w] = pack2_bf16(x, y);
+                            continue;
                         }
+                        // the upper 8 of the bits that are left, exactly
+                        pb[nr][i][w] = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
+                        x -= __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+                        y -= __uint_as_float(__float_as_uint(y) & 0xffff0000u);
                     }
                 }
 #pragma unroll
@@ -553,14 +575,16 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         // second one (one step per wavefront: 7.2 -> 6.6 us of a call, 10.3 -> 9.6).
         int s = wave;
         auto step = [&](int b) __attribute__((always_inline)) {
-            if (NBV == 1) {
-                load_v(s, vf[0]);
-                fetch_tok(s + W);
-            }
+            turn(s, kf[b]);
+            if (NBV == 1) load_v(s, vf[0]);
+            if (NBV == 1) fetch_tok(s + W);
+            if (NBV == 1) take_tok();
+            if (TOK2) fetch_tok(s + 2 * W);
             load_k(s + W, kf[1 - b]);
             if (NBV > 1) {
                 load_v(s + W, vf[(1 - b) % NBV]);
-                fetch_tok(s + 2 * W);
+                if (!TOK2) fetch_tok(s + 2 * W);
+                take_tok();
             }
             compute(s, kf[b], vf[b % NBV], std::false_type{});
             s += W;
@@ -570,6 +594,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
             step(1);
         }
         if (s < n_steps) {
+            turn(s, kf[0]);
             if (NBV == 1) load_v(s, vf[0]);
             compute(s, kf[0], vf[0], std::false_type{});
         }
@@ -591,8 +616,10 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
 #pragma unroll 1
             for (int s = wave; s < n_steps; s += W) {
                 fetch_tok(s);
+                take_tok();
                 load_k(s, kf[0]);
                 load_v(s, vf[0]);
+                turn(s, kf[0]);
                 compute(s, kf[0], vf[0], std::true_type{});
             }
         }
