@@ -1,6 +1,7 @@
 // Query-over-cache attention straight from registers: the kernel for the shapes that the 256-row tile kernel
-// (attn_mfma.hip) does not cover -- fp32 models, head dimensions other than 128 -- and for its decode steps, whose
-// query rows (at most 16 per KV head) would leave seven of that kernel's eight wavefronts idle.
+// (attn_mfma.hip) does not cover -- fp32 models, head dimensions other than 128 -- and for its smaller problems: decode steps and
+// probes over contexts of up to a few thousand slots, which would leave most of that kernel's wavefronts without rows and pay
+// its second launch (attn_plan.h has the border).
 //
 // A workgroup of 8 wavefronts owns 16 * NR query rows of one KV head (rows j*g + h%g, as everywhere) and one split of
 // the context; the last split also takes the query's own tokens (causal).  The keys go to the wavefronts in steps of 16
@@ -17,8 +18,9 @@
 //                   register r of S^T as it stands.  bf16 models: v_mfma_f32_16x16x32_bf16, column c of a lane's 8 rows
 //                   picked together by byte permutes, and P in three bf16 pieces -- the upper 8 of its 24 bits, the
 //                   next 8, the last 8, exactly -- so that P is not rounded: three instructions of 16 cycles for 32 keys
-//                   where the fp32 product took eight of 32.  Head dimension 128 rounds P to one bf16, as the tile kernel
-//                   that computes the larger problems of those models does.
+//                   where the fp32 product took eight of 32.  Head dimension 128 takes two, the second one rounded: 2^-17
+//                   of a weight (against float64, 64 query tokens over 830 slots, rel. error of a bf16 result: one rounded
+//                   piece 2.8e-3, as in the tile kernel, 2.4e-3 with two, at 2 % more time).
 //
 // The wavefronts' states meet in LDS once, at the end.  With one split the workgroup writes the output rows itself:
 // rotation, attention and merge are then one launch.  With more, each workgroup leaves its merged rows (fp32) and (m, l)
@@ -33,11 +35,12 @@
 // address arithmetic) and the query rows are rotated once per workgroup and handed out through LDS.  A larger problem,
 // what a compute unit gets from beyond its L1, 45 to 48 GB/s whatever is in flight (64 or 128 KB), which is why the loads are
 // shared by two row blocks where there are rows enough, and why a single compute unit took 5 to 6 us for the 100 to 250 KB
-// of partials of a unit.  One layer, kernel time: the last to arrive merges, addresses by lane / all merge / buffers
-//   bf16, 28/4 heads x 128, decode step over 16k slots, 42 splits  18.2 / 15.1 / 13.7 us
-//   fp32, 8/2 heads x 128, 32 query tokens over 2.3k slots         18.2 / 17.2 / 13.9
-//   bf16, 32/8 heads x 64, 64 query tokens over 6.6k slots         22.4 / 22.2 / 18.9
-//   fp32, 4/2 heads x 64, 16 query tokens over 248 slots, 1 split   8.7 /  8.8 /  6.5
+// of partials of a unit.  One layer, kernel time: the last to arrive merges, addresses by lane / all merge / buffers / now
+//   bf16, 28/4 heads x 128, decode step over 16k slots             18.2 / 15.1 / 13.7 / 13.3 us
+//   fp32, 8/2 heads x 128, 32 query tokens over 2.3k slots         18.2 / 17.2 / 13.9 / 13.9
+//   bf16, 32/8 heads x 64, 64 query tokens over 6.6k slots         22.4 / 22.2 / 18.9 / 19.5
+//   fp32, 4/2 heads x 64, 16 query tokens over 248 slots, 1 split   8.7 /  8.8 /  6.5 /  6.4
+//   bf16, 32/8 heads x 128, 24 / 64 query tokens over 830 slots, tile kernel and its merge 13.0 / 16.6, here 9.8 / 12.6
 #pragma once
 #include <type_traits>
 
@@ -78,7 +81,8 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     constexpr int NP = BF ? (D == 128 ? 2 : 3) : 0;   // bf16 pieces of a softmax weight (fp32 models: as it is)
     constexpr int STEP_REGS = NJ * KR + 4 * DG * VR;
     // The next step's K and V are loaded while this one is computed (two steps ahead is no faster and costs 16 to 32
-    // registers); a step of 256 bytes per lane leaves room for its K alone, V is then loaded under the first product.
+    // registers); a step of 256 bytes per lane, or two row blocks over gathered keys, leave room for K alone, V is then loaded
+    // under the first product.
     constexpr int NB = 2;
     constexpr int NBV = STEP_REGS > (BF ? 48 : 32) || (BF && POOL && NR == 2) ? 1 : 2;
     constexpr int TR = 16 * NR;
@@ -577,8 +581,10 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         auto step = [&](int b) __attribute__((always_inline)) {
             turn(s, kf[b]);
             if (NBV == 1) load_v(s, vf[0]);
-            if (NBV == 1) fetch_tok(s + W);
-            if (NBV == 1) take_tok();
+            if (NBV == 1) {
+                fetch_tok(s + W);
+                take_tok();
+            }
             if (TOK2) fetch_tok(s + 2 * W);
             load_k(s + W, kf[1 - b]);
             if (NBV > 1) {
