@@ -329,6 +329,9 @@ struct EntropyParams {
 constexpr int kStaticEntropyPartials = 65536;
 // Device address of that array on the CURRENT device (looked up once per device, then remembered).
 hipError_t entropy_static_scratch(float** out);
+inline bool entropy_rows_aligned(const float* logits, int64_t row_stride) {  // for 16-byte loads
+    return ((uintptr_t)logits & 15u) == 0 && row_stride % 4 == 0;
+}
 hipError_t launch_entropy_chunk(const EntropyParams& p, hipStream_t stream);
 // Eq. (entropy) over a set C of answer tokens, from the same vocabulary-wide partials.
 constexpr int kMaxAnswerTokens = 16;

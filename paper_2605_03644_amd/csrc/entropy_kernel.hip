@@ -7,11 +7,10 @@
 // Partials re-base as  s' = s * exp(m - M),  t' = (t + (m - M) * s) * exp(m - M).
 #include <mutex>
 
-#include "adapshot_internal.h"
+#include "mfma_tiles.h"
 
 namespace adapshot {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Chunk partials of the entry point that allocates nothing: kStaticEntropyPartials (row, chunk) triples,
 // 768 KiB, held by every GPU the library runs on until the process ends.  Host code never uses this name as
@@ -62,16 +61,17 @@ __device__ __forceinline__ Mst mst_merge(Mst a, Mst b) {
     return r;
 }
 
+// The 64 lanes' parts merged, in every lane: the largest maximum first, each lane re-based to it once, then two plain sums (lane
+// by lane in six rounds of mst_merge, two exponentials and three exchanges through LDS each, took 1 us).
 __device__ __forceinline__ Mst mst_wave_reduce(Mst v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        Mst w;
-        w.m = __shfl_xor(v.m, o, 64);
-        w.s = __shfl_xor(v.s, o, 64);
-        w.t = __shfl_xor(v.t, o, 64);
-        v = mst_merge(v, w);
+    const float M = wave_max(v.m);  // a maximum is never NaN (fmaxf)
+    if (M != -INFINITY) {  // the same for all lanes; else all empty, or nothing but -inf: sums as they are
+        const float d = v.m - M;
+        const float w = __expf(d);
+        v.t = w > 0.f ? (v.t + d * v.s) * w : 0.f;
+        v.s *= w;
     }
-    return v;
+    return Mst{M, wave_sum(v.s), wave_sum(v.t)};
 }
 
 // a * b with 0 * anything = 0 (v_mul_legacy_f32)
@@ -252,9 +252,9 @@ __global__ __launch_bounds__(256) void entropy_chunk_kernel(EntropyParams p) {
 // The same, and the workgroup that arrives last at its row's counter merges the row's chunks (in chunk order, whatever the
 // order of arrival): one launch.  Partials go past the L2 of the workgroup's XCD and are waited for before the arrival, so
 // no cache is written back or invalidated; the counter is zero again afterwards.  What it has to avoid is counters that
-// share a line (counter_stride).  Call after call over logits that no cache holds, this / chunks and merge in two launches
-// (us): 1 row of 128256 8.8 / 11.6, 48 rows 9.6 / 11.5, 128 rows 15.5 / 15.8, 255 rows 25.3 / 25.4; 128 rows of 50257 11.0 / 11.6
-// (below 9 us the host's call is what is timed).
+// share a line (counter_stride).  Kernel time over logits that no cache holds, with chunks of 1024 to 8192 floats and a merge by
+// exchanges / with 4096 and 8192 and one re-base per lane (us): 1 row of 128256 6.8 / 4.8, 16 rows 9.7 / 5.8, 48 rows 8.9 / 7.6, 128
+// rows 15.0 / 13.6 (4.8 TB/s), 200 rows 20.6 / 19.4; 8 rows of 50257 5.7 / 4.3.  Two launches take 3 us more up to 48 rows.
 template <bool VEC, bool TOKENS>
 __global__ __launch_bounds__(256) void entropy_fused_kernel(EntropyParams p, AnswerTokens c) {
     __shared__ int last_flag;
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(1024) void entropy_row_kernel(EntropyParams p, Answ
 }
 
 hipError_t launch_entropy_rows(const EntropyParams& p, const AnswerTokens* c, hipStream_t stream) {
-    const bool vec = (((uintptr_t)p.logits & 15u) == 0) && (p.row_stride % 4 == 0);
+    const bool vec = entropy_rows_aligned(p.logits, p.row_stride);
     const dim3 grid((unsigned)p.n_rows);
     const AnswerTokens none{};
     if (c) {
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(64) void entropy_finish_kernel(EntropyParams p, Ans
 
 hipError_t launch_entropy_fused(const EntropyParams& p, const AnswerTokens* c, hipStream_t stream) {
     if ((int64_t)p.n_chunks * p.n_rows > INT32_MAX) return hipErrorInvalidValue;  // the host checks this first
-    const bool vec = (((uintptr_t)p.logits & 15u) == 0) && (p.row_stride % 4 == 0);
+    const bool vec = entropy_rows_aligned(p.logits, p.row_stride);
     const dim3 grid((unsigned)(p.n_chunks * p.n_rows)), block(256);
     const AnswerTokens none{};
     if (c) {
@@ -414,7 +414,7 @@ hipError_t launch_entropy_fused(const EntropyParams& p, const AnswerTokens* c, h
 hipError_t launch_entropy_chunk(const EntropyParams& p, hipStream_t stream) {
     if ((int64_t)p.n_chunks * p.n_rows > INT32_MAX) return hipErrorInvalidValue;  // the host checks this first
     dim3 grid((unsigned)((int64_t)p.n_chunks * p.n_rows));
-    const bool vec = (((uintptr_t)p.logits & 15u) == 0) && (p.row_stride % 4 == 0);
+    const bool vec = entropy_rows_aligned(p.logits, p.row_stride);
     if (vec)
         launch_kernel(entropy_chunk_kernel<true>, grid, dim3(256), stream, p);
     else
