@@ -1248,7 +1248,7 @@ static bool streams_batch(const adapshot_ctx* ctx, const adapshot_attn_item* ite
     int64_t tokens = 0;
     for (int32_t i = 0; i < n_items; ++i) {
         tokens += items[i].n_ctx;
-        if ((int64_t)items[i].t_q * g > 16 || !stream_bytes_ok(ctx->desc, tokens)) return false;
+        if ((int64_t)items[i].t_q * g > 16 || !stream_bytes_ok(ctx->desc, tokens / 2)) return false;
         if (items[i].n_ctx > 0) seen.push_back(items[i].cache_index);
     }
     std::sort(seen.begin(), seen.end());

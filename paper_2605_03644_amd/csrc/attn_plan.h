@@ -138,11 +138,12 @@ inline double stream_price(const adapshot_model_desc& d, int64_t n_cu, const Str
     const int64_t steps = std::min(split_tiles, longest) * 64 / sk, launch_rounds = (wgs + n_cu - 1) / n_cu;
     const double tile_mb = (double)(128 * d.head_dim * e) * 1e-6;
     const double t = (double)launch_rounds * (4.5 + (double)((steps + kStreamWaves - 1) / kStreamWaves) * round_us);
-    const double loads = 4.5 + std::max((double)read * tile_mb / (0.045 * (double)n_cu), (double)drawn * tile_mb / 6.2);
-    // (a launch bound by the memory still wants its compute units busy: one token over 27k slots of 32/8 heads, 12 splits 35.2 us, 24
-    // 28.6, 31 26.5; and of plans that cost the same the one with more workgroups, up to the chip's)
-    return std::max(t, loads) + 0.1 * std::min(t, loads) + (split_tiles >= longest ? 0.0 : launch_rounds == 1 ? 2.8 + 4.0 * (double)units / (double)n_cu : 9.0) -
-           0.001 * (double)std::min(wgs, n_cu);
+    // the memory gives more the more workgroups ask: 2.9 TB/s to 64 of them, 4.0 to 128, 5.1 to 256
+    const double busy = (double)std::min(wgs, n_cu);
+    const double loads = 4.5 + std::max((double)read * tile_mb / (0.045 * (double)n_cu), (double)drawn * tile_mb * (busy + 90.0) / (6.9 * busy));
+    // (of plans that cost the same the one with more workgroups, up to the chip's)
+    return std::max(t, loads) + (split_tiles >= longest ? 0.0 : launch_rounds == 1 ? 2.8 + 4.0 * (double)units / (double)n_cu : 9.0) -
+           0.001 * busy;
 }
 
 // Split length (in 64-key tiles) of a launch: the longest context in n equal splits, the others in splits of the same length.
@@ -195,9 +196,10 @@ inline StreamPlan plan_stream(const adapshot_model_desc& d, int64_t n_cu, int32_
 // Which kernel: the 256-row tile kernel for bf16 models of head dimension 128 where it is the cheaper one.  It reads a context
 // once per 256 rows and draws 6.1 TB/s, but is two launches (a batch: three), leaves wavefronts without rows idle and
 // writes a partial for every split; the streaming kernel reads it once per 16 rows, in one launch.
-// A batch goes to the streaming kernel if its items have at most 16 rows and its contexts at most kStreamBytes.  Per layer of a
-// decode step (tile kernel / streaming kernel, us): 25 MB 27.2 / 15.6, 98 MB 34.1 / 30.7, 197 MB 48.2 / 46.5 (28 queries
-// of 4k slots, 229 MB: 56.9 / 55.6), 354 MB 73.2 / 76.8, 826 MB 153 / 167.
+// A batch goes to the streaming kernel if its items have at most 16 rows and its contexts at most twice kStreamBytes.  Per layer of
+// a decode step (tile kernel with table copy and merge / streaming kernel, us): 28/4 heads, 6 queries of 16k slots 201 MB 50.0 / 44.6, 8
+// 267 MB 62.1 / 57.4, 28 of 5k 282 MB 71.1 / 63.9, 12 of 16k 402 MB 84.7 / 84.2, 20 669 MB 130 / 132, 32 1067 MB 196 / 206; 32/8 heads, 16
+// of 5k 323 MB 77.3 / 67.3.
 constexpr int64_t kStreamBytes = 200000000;
 inline bool stream_bytes_ok(const adapshot_model_desc& d, int64_t context_tokens) {
     return context_tokens * d.n_kv_heads * d.head_dim * 4 <= kStreamBytes;
@@ -211,9 +213,10 @@ inline bool single_by_tiles(const adapshot_model_desc& d, int32_t t_q, int64_t n
     if (!attn_mfma_supported(d)) return false;
     if (zero_copy || !stream_bytes_ok(d, n_ctx)) return true;  // (no gathered form of the streaming kernel for these models)
     const int64_t rows = (int64_t)t_q * (d.n_q_heads / d.n_kv_heads), key_tiles = (n_ctx + 63) / 64, self_tiles = ((int64_t)t_q + 63) / 64;
-    // (from 100 MB on the partials of more than 8 rows cost more than the second launch: 32/8 heads, 4 tokens over 24k / 27k slots 27.9 /
-    // 30.5 by tiles, 26.5 / 35 by streaming)
-    if (rows > 16 * kAttnRowTile || (rows > 8 && !stream_bytes_ok(d, 2 * n_ctx))) return true;
+    // 1 token over 45k slots of 32/8 heads: 41.0 by tiles, 39.5 by streaming, shorter ones further apart; but from 100 MB on the
+    // partials of more than 8 rows cost more than the second launch (4 tokens over 24k / 27k slots 27.9 / 30.5 and 26.5 / 35)
+    if (rows <= 8) return false;
+    if (rows > 16 * kAttnRowTile || !stream_bytes_ok(d, 2 * n_ctx)) return true;
     const StreamShape sh{rows, key_tiles + self_tiles};  // (the query's own tokens as more context)
     const int32_t rb = stream_row_blocks(d, n_cu, &sh, 1);
     const double stream = stream_price(d, n_cu, &sh, 1, rb, plan_stream_split_tiles(d, n_cu, &sh, 1, rb));
