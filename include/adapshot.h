@@ -23,15 +23,16 @@
  *     the GPU.  A context owns device scratch (RoPE tables, tile descriptors,
  *     split partials), so calls on ONE context must be issued in stream order on
  *     one stream at a time; use one context per concurrent stream.
- *   - Allocation and waiting.  adapshot_create allocates the RoPE tables and 16 KiB of arrival counters
+ *   - Allocation and waiting.  adapshot_create allocates the RoPE tables and 32 KiB of arrival counters
  *     (hipMalloc, blocking copies, and a wait for them).  adapshot_query_attn, adapshot_query_attn_pool, the batched attention calls, adapshot_probe_entropy,
  *     adapshot_probe_entropy_tokens and adapshot_rank_shots keep grow-only workspaces: a call that
  *     needs more than any earlier call on the context calls hipMalloc (an outgrown buffer is kept
  *     until adapshot_destroy, never freed in a call, so no call waits for the device); a call that
- *     fits the existing workspaces allocates nothing.  adapshot_assemble, adapshot_query_attn_pool, the batched
+ *     fits the existing workspaces allocates nothing.  adapshot_assemble of more than 320 shots, adapshot_query_attn_pool, the batched
  *     calls and adapshot_rank_shots write small tables into a ring of 8 pinned host buffers (hipHostMalloc
  *     when one must grow); the ninth such call in flight waits for the first one's kernels.  No
- *     call synchronises the device or the stream otherwise.  adapshot_probe_entropy_static is the
+ *     call synchronises the device or the stream otherwise.  Workgroups of a single attention call that share a merge wait
+ *     for each other for 10 to 30 us at most; where one has not arrived by then, the last one to arrive merges alone.  adapshot_probe_entropy_static is the
  *     variant of the entropy call that never allocates.
  *   - Every function validates its arguments on the host BEFORE launching
  *     anything: a call that returns an error has written nothing to device
@@ -145,8 +146,8 @@ adapshot_status adapshot_assemble(adapshot_ctx* ctx, adapshot_cache* cache, cons
  * 2e-2 (max-abs) of the exact result; keys three times as large were measured at 1.9e-2, eight times
  * as large at 6e-2.  Accumulation, maxima and sums are fp32 throughout.
  * A value of v_self that is not finite reaches only the rows that attend to its token.  Exception: bf16 models with
- * head_dim 128 in calls beyond decode steps (more than 8 query rows per kv head, or more than 200 MB of context; zero-copy
- * calls always), where it can make NaN of every row of the call.
+ * head_dim 128 in calls beyond decode steps and short probes (more than 8 query rows per kv head, or more than 200 MB of context; in
+ * a batch, more than 400 MB; zero-copy calls always), where it can make NaN of every row of the call.
  * Errors, all found before anything is launched (out is then untouched): EINVAL (null or
  * misaligned pointer, t_q < 1, layer out of range, n_ctx < 0, q_pos0 < 0, a q of 2 GiB or more, or a
  * context or query whose K/V rows span more than 4 GiB in one layer), ESTATE (n_ctx beyond
@@ -165,8 +166,9 @@ adapshot_status adapshot_query_attn(adapshot_ctx* ctx, const adapshot_cache* cac
  * first position and the rotation of the row's index inside the tile compose; Eq. rope_compensation).  Worth
  * it for a context that is attended once; a context that is attended again (further layers' probes, every
  * decode step) is cheaper assembled once.  shot_ids, order: HOST int32[m] as in adapshot_assemble; q, k_self,
- * v_self, out, q_pos0 as in adapshot_query_attn.  Two launches besides the merge of the split partials: a small
- * one that expands the plan, and the attention.  Pools registered with ADAPSHOT_KEYS_UNROTATED only (ESTATE
+ * v_self, out, q_pos0 as in adapshot_query_attn.  A small launch expands the plan, a second one attends; of more than
+ * 8 query rows per kv head the second one merges its split partials too where its workgroups fit the compute units, and
+ * a third one does elsewhere.  Pools registered with ADAPSHOT_KEYS_UNROTATED only (ESTATE
  * otherwise).  bf16 models with head_dim 128 run the matrix-core kernel described above, for which a pool layer
  * must stay below 4 GiB (ECAPACITY); other shapes run the streaming kernel, which gathers and rotates the keys in
  * registers and merges its splits itself (one launch besides the plan). */
@@ -195,7 +197,7 @@ adapshot_status adapshot_assemble_batched(adapshot_ctx* ctx, adapshot_cache* cac
  * have one common length, so
  * probes over nested prefixes of one cache read identical leading slices, and those workgroups are
  * scheduled next to each other.  Other shapes, and decode steps of such models (at most 16 query rows per kv head,
- * contexts of their own, up to 200 MB of them), run up to 32 items per launch.  The outputs of distinct items must not
+ * contexts of their own, up to 400 MB of them; a batch of one item is a single call), run up to 32 items per launch.  The outputs of distinct items must not
  * overlap; inputs may be shared between items.  A call whose arguments other than `layer` equal the previous
  * batched call's on this context (the same items, caches, pointers and lengths: the next layer of a forward pass)
  * reuses the tables the previous call left in device memory and only launches; nothing the caller does between
@@ -332,7 +334,7 @@ typedef enum {
     ADAPSHOT_KERNEL_ASSEMBLE = 0,       /* fused gather + re-encode */
     ADAPSHOT_KERNEL_ROPE_ROWS = 1,      /* rotation of the query rows (ranking); plan of a zero-copy context */
     ADAPSHOT_KERNEL_ATTN = 2,           /* split-K attention proper */
-    ADAPSHOT_KERNEL_ATTN_COMBINE = 3,   /* merge of the split partials */
+    ADAPSHOT_KERNEL_ATTN_COMBINE = 3,   /* merge of the split partials where it has a launch of its own */
     ADAPSHOT_KERNEL_ENTROPY_CHUNK = 4,  /* vocabulary pass */
     ADAPSHOT_KERNEL_ENTROPY_FINISH = 5, /* merge of the chunk partials where it has a launch of its own (more
                                          * than 1024 rows of several chunks) */
