@@ -69,12 +69,6 @@ hipError_t PinnedRing::acquire(size_t need, int* slot, void** ptr) {
     return hipSuccess;
 }
 
-hipError_t PinnedRing::mark_in_use(int slot, hipStream_t stream) {
-    hipError_t e = hipEventRecord(ev[slot], stream);
-    if (e == hipSuccess) pending[slot] = true;
-    return e;
-}
-
 void PinnedRing::release() {
     for (int s = 0; s < kSlots; ++s) {
         if (pending[s] && ev[s]) (void)hipEventSynchronize(ev[s]);
@@ -469,10 +463,10 @@ static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_
         p.n_kv_heads = ctx->desc.n_kv_heads;
         p.head_dim = ctx->desc.head_dim;
         p.dtype = ctx->desc.dtype;
-        e = timed_launch(ctx, ADAPSHOT_KERNEL_ASSEMBLE, stream, [&] { return launch_assemble(p, stream); });
+        e = timed_launch(ctx, ADAPSHOT_KERNEL_ASSEMBLE, stream, [&] {
+            return ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_assemble(p, stream); });
+        });
         if (e != hipSuccess) return fail_hip(ctx, "assemble: launch", e);
-        e = ctx->tile_ring.mark_in_use(slot, stream);
-        if (e != hipSuccess) return fail_hip(ctx, "assemble: event record", e);
         for (int32_t b = j0; b < j1; ++b) jobs[b].cache->len += jobs[b].total;
     }
     return ADAPSHOT_OK;
@@ -944,10 +938,8 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
     });
     for (size_t k = 0; k < keys.size(); ++k) haw[k] = keys[k].w;
 
-    e = launch_copy_table(ctx->batch_tab.p, host, tab_bytes, stream);
+    e = ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_copy_table(ctx->batch_tab.p, host, tab_bytes, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn_batched: table copy", e);
-    e = ctx->tile_ring.mark_in_use(slot, stream);
-    if (e != hipSuccess) return fail_hip(ctx, "query_attn_batched: event record", e);
     const AttnBatchItem* dit = (const AttnBatchItem*)ctx->batch_tab.p;
     const AttnWork* daw = (const AttnWork*)((const char*)ctx->batch_tab.p + attn_off);
     const CombineWork* dcw = (const CombineWork*)((const char*)ctx->batch_tab.p + comb_off);
@@ -1075,10 +1067,10 @@ extern "C" adapshot_status adapshot_query_attn_pool(adapshot_ctx* ctx, int32_t l
     pp.n_segs = n_segs;
     pp.n_tiles = (int32_t)n_tiles;
     pp.head_dim = d.head_dim;
-    e = timed_launch(ctx, ADAPSHOT_KERNEL_ROPE_ROWS, stream, [&] { return launch_pool_plan(pp, stream); });
+    e = timed_launch(ctx, ADAPSHOT_KERNEL_ROPE_ROWS, stream, [&] {
+        return ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_pool_plan(pp, stream); });
+    });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn_pool: plan launch", e);
-    e = ctx->tile_ring.mark_in_use(slot, stream);
-    if (e != hipSuccess) return fail_hip(ctx, "query_attn_pool: event record", e);
     adapshot_status st = run_query_attn_on(ctx, k_layer, v_layer, total, q, k_self, v_self, t_q, q_pos0, out,
                                            (const int32_t*)ctx->pool_src.p, (const float2*)ctx->pool_rot.p, stream, pos0);
     if (st == ADAPSHOT_OK) {
@@ -1220,10 +1212,10 @@ extern "C" adapshot_status adapshot_query_attn_pool_batched(adapshot_ctx* ctx, i
         pp.n_segs = ns;
         pp.n_tiles = (int32_t)n_tiles;
         pp.head_dim = d.head_dim;
-        e = timed_launch(ctx, ADAPSHOT_KERNEL_ROPE_ROWS, stream, [&] { return launch_pool_plan(pp, stream); });
+        e = timed_launch(ctx, ADAPSHOT_KERNEL_ROPE_ROWS, stream, [&] {
+            return ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_pool_plan(pp, stream); });
+        });
         if (e != hipSuccess) return fail_hip(ctx, "query_attn_pool_batched: plan launch", e);
-        e = ctx->tile_ring.mark_in_use(slot, stream);
-        if (e != hipSuccess) return fail_hip(ctx, "query_attn_pool_batched: event record", e);
         pb.slot_src = (const int32_t*)ctx->pool_src.p;
         pb.tile_rot = (const float2*)ctx->pool_rot.p;
         ctx->pool_key.swap(pkey);
@@ -1498,10 +1490,8 @@ static adapshot_status rank_prepare(adapshot_ctx* ctx, int32_t layer, hipStream_
     shot_off[n] = (int32_t)n_tok;
     shot_seg0[n] = n_seg;
     split_seg0[split + 1] = n_seg;
-    e = launch_copy_table(ctx->rank_tab.p, host, tab_bytes, stream);
+    e = ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_copy_table(ctx->rank_tab.p, host, tab_bytes, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "rank_shots: table copy", e);
-    e = ctx->tile_ring.mark_in_use(slot, stream);
-    if (e != hipSuccess) return fail_hip(ctx, "rank_shots: event record", e);
     const char* tab = (const char*)ctx->rank_tab.p;
     ctx->rank_seg_end = (const int32_t*)(tab + off_end);
     ctx->rank_seg_split = (const int32_t*)(tab + off_split);
@@ -1547,10 +1537,8 @@ static adapshot_status rank_shots_generic(adapshot_ctx* ctx, int32_t layer, cons
     e = ctx->tile_ring.acquire(off_bytes, &slot, &host);
     if (e != hipSuccess) return fail_hip(ctx, "rank_shots: pinned tables", e);
     memcpy(host, ctx->shot_offsets.data(), (size_t)(ctx->n_shots + 1) * sizeof(int64_t));
-    e = launch_copy_table(ctx->rank_tab.p, host, off_bytes, stream);
+    e = ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_copy_table(ctx->rank_tab.p, host, off_bytes, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "rank_shots: table copy", e);
-    e = ctx->tile_ring.mark_in_use(slot, stream);
-    if (e != hipSuccess) return fail_hip(ctx, "rank_shots: event record", e);
 
     RopeRowsParams rp;
     rp.q = q;
