@@ -31,8 +31,8 @@
  *     fits the existing workspaces allocates nothing.  adapshot_assemble of more than 320 shots, adapshot_query_attn_pool, the batched
  *     calls and adapshot_rank_shots write small tables into a ring of 8 pinned host buffers (hipHostMalloc
  *     when one must grow); the ninth such call in flight waits for the first one's kernels.  No
- *     call synchronises the device or the stream otherwise.  Workgroups of a single attention call that share a merge wait
- *     for each other for 10 to 30 us at most; where one has not arrived by then, the last one to arrive merges alone.  adapshot_probe_entropy_static is the
+ *     call synchronises the device or the stream otherwise.  Workgroups of a streaming attention launch that share a merge wait
+ *     for each other for 10 us at most; where one has not arrived by then, the last one to arrive merges alone.  adapshot_probe_entropy_static is the
  *     variant of the entropy call that never allocates.
  *   - Every function validates its arguments on the host BEFORE launching
  *     anything: a call that returns an error has written nothing to device
@@ -166,9 +166,8 @@ adapshot_status adapshot_query_attn(adapshot_ctx* ctx, const adapshot_cache* cac
  * first position and the rotation of the row's index inside the tile compose; Eq. rope_compensation).  Worth
  * it for a context that is attended once; a context that is attended again (further layers' probes, every
  * decode step) is cheaper assembled once.  shot_ids, order: HOST int32[m] as in adapshot_assemble; q, k_self,
- * v_self, out, q_pos0 as in adapshot_query_attn.  A small launch expands the plan, a second one attends; of more than
- * 8 query rows per kv head the second one merges its split partials too where its workgroups fit the compute units, and
- * a third one does elsewhere.  Pools registered with ADAPSHOT_KEYS_UNROTATED only (ESTATE
+ * v_self, out, q_pos0 as in adapshot_query_attn.  A small launch expands the plan, a second one attends, a third one
+ * merges the partials of the splits.  Pools registered with ADAPSHOT_KEYS_UNROTATED only (ESTATE
  * otherwise).  bf16 models with head_dim 128 run the matrix-core kernel described above, for which a pool layer
  * must stay below 4 GiB (ECAPACITY); other shapes run the streaming kernel, which gathers and rotates the keys in
  * registers and merges its splits itself (one launch besides the plan). */
@@ -334,7 +333,7 @@ typedef enum {
     ADAPSHOT_KERNEL_ASSEMBLE = 0,       /* fused gather + re-encode */
     ADAPSHOT_KERNEL_ROPE_ROWS = 1,      /* rotation of the query rows (ranking); plan of a zero-copy context */
     ADAPSHOT_KERNEL_ATTN = 2,           /* split-K attention proper */
-    ADAPSHOT_KERNEL_ATTN_COMBINE = 3,   /* merge of the split partials where it has a launch of its own */
+    ADAPSHOT_KERNEL_ATTN_COMBINE = 3,   /* merge of the split partials (matrix-core kernel) */
     ADAPSHOT_KERNEL_ENTROPY_CHUNK = 4,  /* vocabulary pass */
     ADAPSHOT_KERNEL_ENTROPY_FINISH = 5, /* merge of the chunk partials where it has a launch of its own (more
                                          * than 1024 rows of several chunks) */

@@ -711,12 +711,6 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
     af.q_pos0 = q_pos0;
     af.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
     af.pool_tokens = (int32_t)std::min<int64_t>(ctx->shot_offsets.empty() ? 0 : ctx->shot_offsets.back(), INT32_MAX);
-    // One round of workgroups merges its partials itself; with few rows the merge's launch is as short as the wait would be.
-    const int64_t units = d.n_kv_heads * ((rows + kAttnRowTile - 1) / kAttnRowTile);
-    const bool merges = rows > kMergeRows && n_split < 64 && units * (n_split + 1) <= std::min<int64_t>(ctx->n_cu, kStreamUnits);
-    af.counters = merges ? ctx->stream_counters : nullptr;
-    af.counter_stride = counter_stride(units);
-    af.wait = kTileWaitTicks;
     ap.part_o = ctx->part_o.p;
     ap.part_mlf = (float4*)ctx->part_ml.p;
     ap.out = out;
@@ -732,7 +726,6 @@ static adapshot_status run_query_attn_on(adapshot_ctx* ctx, const void* k_ctx, c
     e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN, stream,
                      [&] { return slot_src ? launch_attn_mfma_pool(ap, af, stream) : launch_attn_mfma(ap, af, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn: attention launch", e);
-    if (merges) return ADAPSHOT_OK;
     e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN_COMBINE, stream, [&] { return launch_attn_combine(ap, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn: combine launch", e);
     return ADAPSHOT_OK;

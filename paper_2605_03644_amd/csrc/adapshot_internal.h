@@ -148,11 +148,6 @@ struct AttnFold {
     // aligned and readable for 256 entries past the context's last slot (the kernel fetches it 1 KB at a time).
     const int32_t* slot_src;
     const float2* tile_rot;
-    // Single launches whose workgroups merge their unit's partials themselves (template parameter MERGE): arrival counters
-    // ([unit * counter_stride], unit = row tile * kv heads + kv head, and kStreamUnits further on again; zero between
-    // launches) and the ticks that a workgroup waits for the others.
-    unsigned* counters;
-    int32_t counter_stride, wait;
 };
 
 struct AttnParams {
@@ -218,7 +213,6 @@ struct StreamLaunch {
 hipError_t launch_attn_stream(const StreamLaunch& s, hipStream_t stream);
 hipError_t launch_attn_stream_f32(const StreamLaunch& s, hipStream_t stream);
 hipError_t launch_attn_stream_bf16(const StreamLaunch& s, hipStream_t stream);
-// f.counters given: the launch merges its partials itself (all its workgroups fit the chip), else launch_attn_combine does.
 hipError_t launch_attn_mfma(const AttnParams& p, const AttnFold& f, hipStream_t stream);
 hipError_t launch_attn_mfma_pool(const AttnParams& p, const AttnFold& f, hipStream_t stream);  // zero-copy form
 // Expands the per-shot segments of a zero-copy context into slot_src and builds tile_rot.

@@ -99,9 +99,7 @@ __device__ __forceinline__ T load_uniform(const T* ptr) {
 // The workgroup rotates its query rows (and the self split its keys) itself: at the headline size the rotation repeated
 // in every context split costs the kernel 1.4 us, and the launch it replaces cost the step 3 us.
 // NT: the K/V tile loads of the plain form carry the non-temporal bit (see load_lds_16).
-// MERGE: a single launch whose workgroups all fit the chip: those of a unit that finish together merge a share of its rows each
-// (see the end of the kernel).
-template <int WAVES, int NR, bool BATCHED, bool POOL, bool NT = false, bool MERGE = false>
+template <int WAVES, int NR, bool BATCHED, bool POOL, bool NT = false>
 __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg, AttnFold f_arg,
                                                                int n_row_tiles_arg, const AttnBatchItem* items,
                                                                const AttnWork* work) {
@@ -109,7 +107,6 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
     constexpr int PASSES = (kTileKeys * 16) / (WAVES * 64);  // 1 KB blocks of a tile per wavefront
     static_assert(PASSES * WAVES * 64 == kTileKeys * 16, "tile must divide over the threads");
     static_assert(WAVES * NR * 32 == kAttnRowTile && NR == 1, "row tile");
-    static_assert(!(MERGE && BATCHED), "a batch's partials are merged by a launch of their own");
     static_assert(!(NT && POOL), "pool tokens are shared by the lists that select them: they stay cacheable");
     // LDS: the K ring at byte 0, the V ring at 64 KB; the zero-copy form adds, after its shorter V ring, the ring of
     // slot-table pieces (8 x 1 KB), the ring of rotation rows (4 x 1 KB) and the threads' second-level table entries.
@@ -785,15 +782,8 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
     amax = max_xhalf(amax);
     const bool some = amax > 0.f && amax < INFINITY;  // all-zero row (or overflow): plain scale 1
     const float scale = some ? 1.0f / amax : 1.0f;
-    // (a launch that merges is one round of workgroups: at most 17 MB of partials)
-    const buf_rsrc part_rows = make_buffer(p.part_o, MERGE ? (unsigned)((p.n_split + 1) * p.n_kv_heads * rows) * (kD * 2u) : 0u);
-    const buf_rsrc part_stats = make_buffer(p.part_mlf, MERGE ? (unsigned)((p.n_split + 1) * p.n_kv_heads * rows) * 16u : 0u);
-    const unsigned part0 = (unsigned)((split * p.n_kv_heads + hk) * rows);  // first row of the (split, kv head)
-    if (row[0] < rows && hh == 0) {
-        const f32x4 stats = {m_run, l_tot, some ? amax : 1.0f, 0.f};
-        if (MERGE) buf_store_16<kCacheDevice>(part_stats, (part0 + (unsigned)row[0]) * 16u, __builtin_bit_cast(u32x4, stats));
-        else *(f32x4*)(p.part_mlf + ((int64_t)split * p.n_kv_heads + hk) * rows + row[0]) = stats;
-    }
+    if (row[0] < rows && hh == 0)
+        p.part_mlf[((int64_t)split * p.n_kv_heads + hk) * rows + row[0]] = make_float4(m_run, l_tot, some ? amax : 1.0f, 0.f);
     // The rows leave through 4 KB of LDS that only this wavefront touches, half a row (64 columns) at a time: a lane
     // holds 4 consecutive columns of its row per register quad, and stored from there every instruction would write
     // 8 bytes to each of 32 rows (the write-out took 3.4 of the kernel's 57 us at the headline size, 2.6 of them
@@ -825,121 +815,9 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
         for (int j = 0; j < 4; ++j) {
             const int r = 8 * j + (lane >> 3), sl = lane & 7;
             const u32x4 v = *(const u32x4*)(stage_row(r) + ((sl ^ ((r >> 1) & 7)) << 4));
-            if (MERGE) {
-                if (row0 + r < rows)
-                    buf_store_16<kCacheDevice>(part_rows, (part0 + (unsigned)(row0 + r)) * (kD * 2u) + (unsigned)(half * 128 + sl * 16), v);
-            } else if (row0 + r < rows) {
-                *(u32x4*)(obase + (int64_t)r * (kD * 2) + half * 128 + sl * 16) = v;
-            }
+            if (row0 + r < rows) *(u32x4*)(obase + (int64_t)r * (kD * 2) + half * 128 + sl * 16) = v;
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before the second half overwrites the piece
-    }
-    if (!MERGE) return;
-
-    // ---- merge, as attn_combine_rows does it: out = sum_s 2^(m_s - M) f_s O'_s / sum_s 2^(m_s - M) l_s.  The workgroups of the
-    // unit (its splits, its own tokens) arrive at a counter and those that had as much to do as the longest wait for each
-    // other and take a share of the rows each; partials go past the L2 of the XCD both ways (arrival.h, and the
-    // streaming kernel, whose merge is the same).  It saves a launch: 7 us of merge kernel and gap.
-    const AttnFold f = fold();
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // the workgroup's partials have reached memory
-    int* const role_s = (int*)lds_all;  // nobody uses the tiles any more
-    const int n = p.n_split + 1;
-    unsigned* const word = f.counters + (row_tile * p.n_kv_heads + hk) * f.counter_stride;
-    if (tid == 0) {
-        const int self_tiles = (p.t_q + kTileKeys - 1) / kTileKeys, ctx_tiles = (int)(p.keys_per_split / kTileKeys);
-        const bool stays = n_tiles + 4 >= (self_tiles > ctx_tiles ? self_tiles : ctx_tiles);
-        const unsigned mine = stays ? 1u : 1u + kArrivalPassed;
-        const unsigned before = __hip_atomic_fetch_add(word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        unsigned seen = before + mine;
-        const bool last = arrived_all(seen, n);
-        if (stays) seen = wait_for_arrivals(word, seen, n, f.wait);
-        // the counter is not looked at again: the last workgroup to say so puts both words back to zero
-        if (__hip_atomic_fetch_add(word + kStreamUnits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (unsigned)n) {
-            __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(word + kStreamUnits, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        const int n_rows = rows - row_tile * kAttnRowTile < kAttnRowTile ? rows - row_tile * kAttnRowTile : kAttnRowTile;
-        const MergeRole role = merge_role(seen, n, last, stays);
-        const int shares = arrival_stayers(seen, n), rank = arrival_rank(before);
-        role_s[0] = role == kMergeShare ? n_rows * rank / shares : 0;
-        role_s[1] = role == kMergeShare ? n_rows * (rank + 1) / shares : role == kMergeAll ? n_rows : 0;
-        role_s[2] = shares > 0 ? (n_rows + shares - 1) / shares : n_rows;
-    }
-    __syncthreads();
-    const int r_lo = role_s[0], r_hi = role_s[1];
-    if (r_lo >= r_hi) return;
-    typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-    typedef float f32x8 __attribute__((ext_vector_type(8)));
-    constexpr int SB = 8;  // partial rows in flight per thread
-    constexpr int RP = WAVES * 4;  // rows that the workgroup's threads cover, 16 lanes of 16 bytes each
-    // A share has fewer rows than that: ng groups of threads take the splits of a row between them (by the sizes alone, so that
-    // whoever merges adds the same sums).
-    int ng = RP / role_s[2];
-    const int ng_max = (n + SB - 1) / SB;
-    ng = ng < 1 ? 1 : ng > ng_max ? ng_max : ng;
-    const int rp = RP / ng;  // rows of a pass
-    const int c = tid & 15, slot = tid >> 4, grp = slot / rp, rs = slot - grp * rp;
-    const unsigned split_rows = (unsigned)(p.n_kv_heads * rows);
-    const unsigned unit0 = (unsigned)(hk * rows + row_tile * kAttnRowTile);  // first row of the unit in a split
-    float* const w_s = (float*)(lds_all + 1024);                             // [split][row of the share], 64 x 256
-    f32x8* const red_s = (f32x8*)(lds_all + 1024 + 65536);                   // [slot][c]
-    f16x8 x[SB];
-    auto load_rows = [&](int r, int s0) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < SB; ++u) {
-            const int s = s0 + u * ng;
-            if (s < n && r < r_hi)
-                x[u] = __builtin_bit_cast(f16x8, buf_load_16<kCacheDevice>(part_rows, ((unsigned)s * split_rows + unit0 + (unsigned)r) * (kD * 2u) + 16u * (unsigned)c));
-        }
-    };
-    // the weights 2^(m_s - M) f_s / sum: a wavefront per row, a lane per split (at most 64); the first rows are requested behind them
-    f32x4 st = {-INFINITY, 0.f, 0.f, 0.f};
-    auto load_stats = [&](int r) __attribute__((always_inline)) {
-        if (lane < n) st = __builtin_bit_cast(f32x4, buf_load_16<kCacheDevice>(part_stats, ((unsigned)lane * split_rows + unit0 + (unsigned)r) * 16u));
-    };
-    if (r_lo + wave < r_hi) load_stats(r_lo + wave);
-    if (grp < ng) load_rows(r_lo + rs, grp);
-    for (int r = r_lo + wave; r < r_hi; r += WAVES) {
-        if (r != r_lo + wave) load_stats(r);
-        const float M = wave_max(st[0]);
-        const float w = st[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st[0] - M);
-        const float L = wave_sum(w == 0.f ? 0.f : w * st[1]);
-        if (lane < n) w_s[lane * kAttnRowTile + (r - r_lo)] = w == 0.f ? 0.f : w * st[2] / L;
-    }
-    __syncthreads();
-    for (int r0 = r_lo; r0 < r_hi; r0 += rp) {
-        const int r = r0 + rs;
-        f32x8 acc;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-        if (grp < ng && r < r_hi) {
-            for (int s0 = grp; s0 < n; s0 += SB * ng) {
-                if (r0 != r_lo || s0 != grp) load_rows(r, s0);
-#pragma unroll
-                for (int u = 0; u < SB; ++u) {
-                    const int s = s0 + u * ng;
-                    if (s >= n) continue;
-                    const float w = w_s[s * kAttnRowTile + (r - r_lo)];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) acc[i] += w * (float)x[u][i];
-                }
-            }
-            if (ng > 1) red_s[slot * 16 + c] = acc;
-        }
-        if (ng > 1) __syncthreads();
-        if (grp == 0 && r < r_hi) {
-            for (int k = 1; k < ng; ++k) {
-                const f32x8 y = red_s[(slot + k * rp) * 16 + c];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc[i] += y[i];
-            }
-            u32x4 y;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) y[i] = pack2_bf16(acc[2 * i], acc[2 * i + 1]);
-            const int mrow = row_tile * kAttnRowTile + r, j = mrow / g;
-            *(u32x4*)((char*)p.out + (((int64_t)j * p.n_q_heads + hk * g + (mrow - j * g)) * kD + 8 * c) * 2) = y;
-        }
-        if (ng > 1) __syncthreads();
     }
 }
 
@@ -949,15 +827,7 @@ hipError_t launch_attn_mfma(const AttnParams& p, const AttnFold& f, hipStream_t 
     const int n_row_tiles = (rows + kAttnRowTile - 1) / kAttnRowTile;
     const unsigned blocks = (unsigned)(p.n_kv_heads * n_row_tiles * (p.n_split + 1));
     if (blocks == 0) return hipSuccess;
-    constexpr int NR = kAttnRowTile / (32 * kAttnWaves);
-    if (f.counters && blocks > (unsigned)kStreamUnits) return hipErrorInvalidValue;  // (far beyond one round)
-    if (f.counters && rows <= kAttnStreamRows)
-        launch_kernel((attn_mfma_kernel<kAttnWaves, NR, false, false, true, true>), dim3(blocks), dim3(kAttnWaves * 64), stream, p, f,
-                      n_row_tiles, (const AttnBatchItem*)nullptr, (const AttnWork*)nullptr);
-    else if (f.counters)
-        launch_kernel((attn_mfma_kernel<kAttnWaves, NR, false, false, false, true>), dim3(blocks), dim3(kAttnWaves * 64), stream, p, f,
-                      n_row_tiles, (const AttnBatchItem*)nullptr, (const AttnWork*)nullptr);
-    else if (rows <= kAttnStreamRows)  // every tile is read by one workgroup per kv head, which has few rows to feed
+    if (rows <= kAttnStreamRows)  // every tile is read by one workgroup per kv head, which has few rows to feed
         launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, false, true>),
                       dim3(blocks), dim3(kAttnWaves * 64), stream, p, f, n_row_tiles, (const AttnBatchItem*)nullptr,
                       (const AttnWork*)nullptr);
@@ -976,14 +846,8 @@ hipError_t launch_attn_mfma_pool(const AttnParams& p, const AttnFold& f, hipStre
     if (blocks == 0) return hipSuccess;
     if (!f.slot_src || !f.tile_rot || p.keys_per_split % kTileKeys != 0)
         return hipErrorInvalidValue;
-    if (f.counters && blocks > (unsigned)kStreamUnits) return hipErrorInvalidValue;
-    constexpr int NR = kAttnRowTile / (32 * kAttnWaves);
-    if (f.counters)
-        launch_kernel((attn_mfma_kernel<kAttnWaves, NR, false, true, false, true>), dim3(blocks), dim3(kAttnWaves * 64), stream, p, f,
-                      n_row_tiles, (const AttnBatchItem*)nullptr, (const AttnWork*)nullptr);
-    else
-        launch_kernel((attn_mfma_kernel<kAttnWaves, NR, false, true>), dim3(blocks), dim3(kAttnWaves * 64), stream, p, f, n_row_tiles,
-                      (const AttnBatchItem*)nullptr, (const AttnWork*)nullptr);
+    launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, true>), dim3(blocks),
+                  dim3(kAttnWaves * 64), stream, p, f, n_row_tiles, (const AttnBatchItem*)nullptr, (const AttnWork*)nullptr);
     return hipGetLastError();
 }
 

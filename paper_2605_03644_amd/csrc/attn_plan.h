@@ -26,14 +26,6 @@ constexpr int kStreamUnits = 4096;    // (problem, row tile, kv head) units of a
 // How long a workgroup waits for the others of its unit before it leaves the merge to the last one, in ticks of 10 ns.  Those
 // of a launch that has the chip to itself arrive within 1 to 3 us of each other.
 constexpr int32_t kStreamWaitTicks = 1000;
-// The same for the tile kernel's workgroups, which run for longer and finish less evenly; only those with as many tiles as the
-// longest wait at all.
-constexpr int32_t kTileWaitTicks = 3000;
-// A single call of the tile kernel whose workgroups fit the chip in one round merges its partials in the same launch from this many
-// rows per kv head on (exclusive).  Call after call, merge kernel / merged in the launch, us: zero-copy 32/8 heads, 4 tokens over 1k
-// slots 14.5 / 13.1, 16 over 3.6k 18.2 / 15.9, 64 over 3.6k 25.1 / 21.6, 28/4 heads, 32 over 5.7k 25.6 / 20.8, 32/8 heads, 128 over 26k 76.4 /
-// 74.0; over a cache 28/4 heads, 64 over 5k 24.3 / 21.1, 32/8 heads, 32 over 6.8k 21.3 / 19.5, 16 over 20k 26.4 / 26.0, 128 over 26.6k 63.7 / 63.3.
-constexpr int64_t kMergeRows = 8;
 // Distance of the arrival counters of n units (of an entropy call: rows), in counters: up to a 128-byte line each.  Atomics
 // on one line follow each other at about 14 ns whatever counter they name (16 rows x 126 arrivals in one line: 29 us, a line
 // for every row: 10 us).
@@ -212,9 +204,8 @@ constexpr int64_t kStreamBytes = 200000000;
 inline bool stream_bytes_ok(const adapshot_model_desc& d, int64_t context_tokens) {
     return context_tokens * d.n_kv_heads * d.head_dim * 4 <= kStreamBytes;
 }
-// A single call compares prices.  The tile kernel's, fitted to calls of 64 to 512 rows over 250 to 5000 slots: 11.5 us (13
-// where the merge is a launch of its own), 0.75 us per MB of partials, 0.65 or (more than 128 rows) 1 us per tile of a
-// workgroup.  Us, tile kernel with a merge of its own /
+// A single call compares prices.  The tile kernel's, fitted to calls of 64 to 512 rows over 250 to 5000 slots: 13 us for
+// the two launches, 0.75 us per MB of partials, 0.65 or (more than 128 rows) 1 us per tile of a workgroup.  Us, tile /
 // streaming: 32/8 heads, 8 tokens over 250 / 1.7k / 3.4k slots 14.0 / 14.5 / 15.6 and 10.7 / 10.4 / 11.2; 24 tokens over 830 / 3.4k
 // 13.7 / 17.6 and 10.4 / 16.4; 64 tokens over 250 / 1.7k / 3.4k 14.6 / 23.5 / 24.6 and 10.1 / 17.6 / 24.5; 28/4 heads, 16 tokens over 5k
 // 18.9 and 14.8, 64 tokens over 5k 24.5 and 32.1; 64/8 heads, 16 tokens over 5k 20.1 and 22.7.
@@ -234,7 +225,7 @@ inline bool single_by_tiles(const adapshot_model_desc& d, int32_t t_q, int64_t n
     const int64_t per_wg = n_split > 0 ? (key_tiles + n_split - 1) / n_split : 0;
     const double drawn_mb = (double)(key_tiles * d.n_kv_heads * 256 * d.head_dim) * 1e-6;
     const double partials_mb = (double)((n_split + 1) * rows * d.n_kv_heads * d.head_dim * 2) * 1e-6;
-    return 11.5 + 0.75 * partials_mb + std::max((rows > 128 ? 1.0 : 0.65) * (double)per_wg, drawn_mb / 6.1) < stream;
+    return 13.0 + 0.75 * partials_mb + std::max((rows > 128 ? 1.0 : 0.65) * (double)per_wg, drawn_mb / 6.1) < stream;
 }
 
 // Split the context of one attention call so that (kv heads x row tiles x splits) fills the chip.  Keys per

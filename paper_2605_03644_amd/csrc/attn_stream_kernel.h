@@ -44,6 +44,7 @@
 #pragma once
 #include <type_traits>
 
+#include "arrival.h"
 #include "mfma_tiles.h"
 
 namespace adapshot {
@@ -723,11 +724,19 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     unsigned* const exits = word + kStreamUnits;
     unsigned n_exits = 0;
     if (tid == 0) {
-        const unsigned mine = p.wait > 0 ? 1u : 1u + kArrivalPassed;  // (where nobody waits, nobody stays)
-        unsigned seen = __hip_atomic_fetch_add(word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
+        unsigned seen = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
         const bool last = arrived_all(seen, n_split);
         if (p.wait > 0) {
-            seen = wait_for_arrivals(word, seen, n_split, p.wait);
+            const u64 t0 = __builtin_amdgcn_s_memrealtime();
+            while (!arrived_all(seen, n_split)) {
+                if (__builtin_amdgcn_s_memrealtime() - t0 < (u64)p.wait) {
+                    __builtin_amdgcn_s_sleep(2);
+                    seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else if (__hip_atomic_compare_exchange_strong(word, &seen, seen + kArrivalLeft, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT)) {
+                    break;  // (a failed exchange has read the word again; it changes at most twice per workgroup)
+                }
+            }
             // the counter is not looked at again: the last workgroup to say so puts both words back to zero
             n_exits = __hip_atomic_fetch_add(exits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
         } else if (last) {

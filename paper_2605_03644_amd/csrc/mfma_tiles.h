@@ -1,7 +1,6 @@
 // Device helpers shared by the matrix-core kernels (attention, streaming attention, ranking).
 #pragma once
 #include "adapshot_internal.h"
-#include "arrival.h"
 
 namespace adapshot {
 
@@ -71,22 +70,6 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
     float r;
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
-}
-
-// One thread of a workgroup that has arrived and stays: looks at the counter until all n have arrived, or for `ticks` of 10 ns and
-// then leaves.  Returns the counter as last seen.
-__device__ __forceinline__ unsigned wait_for_arrivals(unsigned* word, unsigned seen, int n, int ticks) {
-    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-    while (!arrived_all(seen, n)) {
-        if (__builtin_amdgcn_s_memrealtime() - t0 < (unsigned long long)ticks) {
-            __builtin_amdgcn_s_sleep(2);
-            seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else if (__hip_atomic_compare_exchange_strong(word, &seen, seen + kArrivalLeft, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT)) {
-            break;  // (a failed exchange has read the word again; it changes at most twice per workgroup)
-        }
-    }
-    return seen;
 }
 
 // ---- buffer accesses: a base and a size in scalar registers, a 32-bit byte offset per lane.  Reads past the size return zero.
