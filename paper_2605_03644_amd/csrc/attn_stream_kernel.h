@@ -85,6 +85,9 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     // under the first product.
     constexpr int NB = 2;
     constexpr int NBV = STEP_REGS > (BF ? 48 : 32) || (BF && POOL && NR == 2) ? 1 : 2;
+    // Gathered keys are turned to their positions before the next step's rows are requested, unless V is loaded late, for want of registers:
+    // then behind them (bf16 x 256, 64 tokens over 25k slots: before 381 us and 106 registers in memory, behind 206 and 11).
+    constexpr bool LATE = POOL && NBV == 1;
     constexpr int TR = 16 * NR;
     constexpr int NS = NR * DB;  // 1 KB pieces of a wavefront's output state
     static_assert(D == 8 || D % 16 == 0, "head dimensions");
@@ -151,10 +154,13 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
 #pragma unroll
         for (int r = 0; r < NV; ++r) tok_v[r] = next_v[r];
     };
-    auto row_off = [&](bool on, int tok) __attribute__((always_inline)) -> uint64_t {  // the rows of a pool may span more than 4 GiB
-        unsigned t = (unsigned)tok;
-        t = t < (unsigned)p.pool_tokens ? t : (unsigned)p.pool_tokens - 1u;  // never outside the pool
-        return on ? (uint64_t)t * (uint64_t)stride : 0;
+    // Zero-copy form: row u of the query's own tokens, or the pool's row tok; the rows of a pool may span more than 4 GiB.  One path for
+    // both: a branch around the loads costs registers and waits at its end (32/8 heads x 64 fp32, 64 tokens over 25k slots 281 / 250 us,
+    // 8/2 x 128 fp32 141 / 131; bf16 x 256, 64 tokens over 9.8k slots 218 / 96: 255 registers in memory, 11 without it).
+    auto row_off = [&](bool self, bool on, int u, int tok) __attribute__((always_inline)) -> uint64_t {
+        unsigned r = (unsigned)(u < n_self ? u : n_self - 1);
+        if (!self) r = (unsigned)tok < (unsigned)p.pool_tokens ? (unsigned)tok : (unsigned)p.pool_tokens - 1u;  // never outside the pool
+        return on ? (uint64_t)r * (uint64_t)stride : 0;
     };
     // An assembled context, and the query's own tokens, are read through buffers of exactly the split's rows: a lane's offset is its
     // place in the step plus the step's (a scalar), rows past the end read as zero without a trip to memory, and nothing is
@@ -169,10 +175,10 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     const unsigned v_lane = (unsigned)(4 * kg * stride) + (unsigned)(VW * l16 * E);
     auto load_k = [&](int s, unsigned (&dst)[NK][NJ][KR]) __attribute__((always_inline)) {
         const bool on = s < n_steps, self = s >= n_cs;
-        if (POOL && !self) {
+        if (POOL) {
 #pragma unroll
             for (int b = 0; b < NK; ++b) {
-                const char* src = kctx + row_off(on, tok_k[b]);
+                const char* src = (self ? kself : kctx) + row_off(self, on, SK * (s - n_cs) + 16 * b + l16, tok_k[b]);
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     if (KR == 4) {
@@ -209,10 +215,10 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     };
     auto load_v = [&](int s, unsigned (&dst)[NV][DG][VR]) __attribute__((always_inline)) {
         const bool on = s < n_steps, self = s >= n_cs;
-        if (POOL && !self) {
+        if (POOL) {
 #pragma unroll
             for (int r = 0; r < NV; ++r) {
-                const char* src = vctx + row_off(on, tok_v[r]);
+                const char* src = (self ? vself : vctx) + row_off(self, on, SK * (s - n_cs) + 16 * (r >> 2) + 4 * kg + (r & 3), tok_v[r]);
 #pragma unroll
                 for (int dg = 0; dg < DG; ++dg) {
                     const char* q = src + (16 * VW * dg + VW * l16) * E;
@@ -405,8 +411,8 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     };
     clear();
 
-    // keys that come un-rotated, turned to their positions: before the next step's rows are requested, which the tables' entries would
-    // otherwise be waited for with
+    // keys that come un-rotated, turned to their positions; loads return in order, and behind the next step's rows the tables' entries
+    // are waited for with them
     auto turn = [&](int s, unsigned (&k)[NK][NJ][KR]) __attribute__((always_inline)) {
         const bool self = s >= n_cs;
 #pragma unroll
@@ -579,9 +585,9 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         // second one (one step per wavefront: 7.2 -> 6.6 us of a call, 10.3 -> 9.6).
         int s = wave;
         auto step = [&](int b) __attribute__((always_inline)) {
-            turn(s, kf[b]);
-            if (NBV == 1) load_v(s, vf[0]);
+            if (!LATE) turn(s, kf[b]);
             if (NBV == 1) {
+                load_v(s, vf[0]);
                 fetch_tok(s + W);
                 take_tok();
             }
@@ -592,6 +598,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
                 if (!TOK2) fetch_tok(s + 2 * W);
                 take_tok();
             }
+            if (LATE) turn(s, kf[b]);
             compute(s, kf[b], vf[b % NBV], std::false_type{});
             s += W;
         };
