@@ -23,7 +23,7 @@
  *     the GPU.  A context owns device scratch (RoPE tables, tile descriptors,
  *     split partials), so calls on ONE context must be issued in stream order on
  *     one stream at a time; use one context per concurrent stream.
- *   - Allocation and waiting.  adapshot_create allocates the RoPE tables and 32 KiB of arrival counters
+ *   - Allocation and waiting.  adapshot_create allocates the RoPE tables and 16 KiB of arrival counters
  *     (hipMalloc, blocking copies, and a wait for them).  adapshot_query_attn, adapshot_query_attn_pool, the batched attention calls, adapshot_probe_entropy,
  *     adapshot_probe_entropy_tokens and adapshot_rank_shots keep grow-only workspaces: a call that
  *     needs more than any earlier call on the context calls hipMalloc (an outgrown buffer is kept
@@ -31,8 +31,7 @@
  *     fits the existing workspaces allocates nothing.  adapshot_assemble of more than 320 shots, adapshot_query_attn_pool, the batched
  *     calls and adapshot_rank_shots write small tables into a ring of 8 pinned host buffers (hipHostMalloc
  *     when one must grow); the ninth such call in flight waits for the first one's kernels.  No
- *     call synchronises the device or the stream otherwise.  Workgroups of a streaming attention launch that share a merge wait
- *     for each other for 10 us at most; where one has not arrived by then, the last one to arrive merges alone.  adapshot_probe_entropy_static is the
+ *     call synchronises the device or the stream otherwise.  adapshot_probe_entropy_static is the
  *     variant of the entropy call that never allocates.
  *   - Every function validates its arguments on the host BEFORE launching
  *     anything: a call that returns an error has written nothing to device

@@ -231,8 +231,8 @@ extern "C" adapshot_status adapshot_create(const adapshot_model_desc* desc, adap
     if (e == hipSuccess) e = hipMalloc((void**)&ctx->tab_hi, hi.size() * sizeof(float2));
     if (e == hipSuccess) e = hipMemcpy(ctx->tab_lo, lo.data(), lo.size() * sizeof(float2), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(ctx->tab_hi, hi.data(), hi.size() * sizeof(float2), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&ctx->stream_counters, 2 * kStreamUnits * sizeof(unsigned));
-    const std::vector<unsigned> zeros(2 * kStreamUnits, 0u);
+    if (e == hipSuccess) e = hipMalloc((void**)&ctx->stream_counters, kStreamUnits * sizeof(unsigned));
+    const std::vector<unsigned> zeros(kStreamUnits, 0u);
     if (e == hipSuccess) e = hipMemcpy(ctx->stream_counters, zeros.data(), zeros.size() * sizeof(unsigned), hipMemcpyHostToDevice);
     // The caller's streams need not be ordered behind the null stream, and a counter that is not zero when a first launch
     // counts on it would never be again: everything above has landed before the context is handed out.
@@ -615,7 +615,7 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
     const int64_t units = plan.units, tr = 16 * plan.row_blocks;
     StreamLaunch sl;
     sl.row_blocks = plan.row_blocks;
-    int64_t unit0 = 0, grid_x = 0, n_split = 1, wgs = 0;
+    int64_t unit0 = 0, grid_x = 0, n_split = 1;
     // own tokens in splits of their own as long as the workgroups fit the chip
     int64_t own = 0;
     for (int32_t i = 0; i < n_items; ++i)
@@ -630,9 +630,7 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
         unit0 += here;
         grid_x = std::max(grid_x, here * it.n_split);
         n_split = std::max<int64_t>(n_split, it.n_split);
-        wgs += here * it.n_split;
     }
-    sl.wait = wgs <= ctx->n_cu ? kStreamWaitTicks : 0;
     if (grid_x > INT32_MAX || unit0 > INT32_MAX) return fail(ctx, ADAPSHOT_EINVAL, "query_attn: too many workgroups");
     sl.part_o = nullptr;
     sl.part_ml = nullptr;

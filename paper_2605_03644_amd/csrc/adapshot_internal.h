@@ -187,11 +187,10 @@ struct StreamArgs {
     const float2* tab_hi;
     float* part_o;       // [unit][max_split][16 NR rows][d] fp32, unnormalised (launches with splits)
     float* part_ml;      // [unit][max_split][16 NR rows] (m, l)
-    unsigned* counters;  // [unit * counter_stride], and kStreamUnits further on again; zero between launches
+    unsigned* counters;  // [unit * counter_stride], zero between launches
     const int32_t* slot_src;  // zero-copy form: context slot -> pool token (null: the context is an assembled cache)
     int64_t ctx_pos0;         // zero-copy form: position of context slot 0
     int32_t n_q_heads, n_kv_heads, g, max_split, pool_tokens, counter_stride;
-    int32_t wait;  // ticks (10 ns) that a workgroup waits for the others of its unit; 0: the last to arrive merges alone
     float q_scale;
     StreamItem it[NI];
 };
@@ -203,7 +202,7 @@ struct StreamLaunch {
     unsigned* counters;
     const int32_t* slot_src;
     int64_t ctx_pos0;
-    int32_t n_q_heads, n_kv_heads, head_dim, dtype, max_split, pool_tokens, counter_stride, wait;
+    int32_t n_q_heads, n_kv_heads, head_dim, dtype, max_split, pool_tokens, counter_stride;
     int32_t row_blocks;  // 16-row blocks per workgroup: 1 or 2
     int32_t grid_x;      // workgroups of the largest problem
     int32_t n_items;

@@ -23,9 +23,6 @@ constexpr int kStreamWaves = 8;       // wavefronts per workgroup, each with key
 constexpr int kStreamItems = 32;      // attention problems per launch (their descriptions travel in the kernel arguments)
 constexpr int kStreamMaxSplits = 64;  // context splits per problem
 constexpr int kStreamUnits = 4096;    // (problem, row tile, kv head) units of a launch that is split: one arrival counter each
-// How long a workgroup waits for the others of its unit before it leaves the merge to the last one, in ticks of 10 ns.  Those
-// of a launch that has the chip to itself arrive within 1 to 3 us of each other.
-constexpr int32_t kStreamWaitTicks = 1000;
 // Distance of the arrival counters of n units (of an entropy call: rows), in counters: up to a 128-byte line each.  Atomics
 // on one line follow each other at about 14 ns whatever counter they name (16 rows x 126 arrivals in one line: 29 us, a line
 // for every row: 10 us).

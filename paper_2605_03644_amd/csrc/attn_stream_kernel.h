@@ -24,8 +24,7 @@
 //
 // The wavefronts' states meet in LDS once, at the end.  With one split the workgroup writes the output rows itself:
 // rotation, attention and merge are then one launch.  With more, each workgroup leaves its merged rows (fp32) and (m, l)
-// in a workspace and arrives at the unit's counter; where the whole launch fits the chip all workgroups of the unit then
-// merge a share of its rows each, elsewhere the one that arrived last merges them all.  Partials are written and read
+// in a workspace, and the workgroup that arrives last at the unit's counter merges them: partials are written and read
 // with device-scope accesses that bypass the L2 of the workgroup's XCD, so no cache has to be written back or invalidated,
 // and the counter is back at zero afterwards.  The merge runs in split order whatever the order of arrival: the same
 // inputs give the same bits.
@@ -44,7 +43,6 @@
 #pragma once
 #include <type_traits>
 
-#include "arrival.h"
 #include "mfma_tiles.h"
 
 namespace adapshot {
@@ -96,7 +94,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     __shared__ float2 wml[W][TR];
     __shared__ __attribute__((aligned(16))) char qs[TR * D * E];
     __shared__ float sw[kStreamMaxSplits][TR];
-    __shared__ int role;
+    __shared__ int last_flag;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -713,13 +711,10 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     }
     if (n_split == 1) return;
 
-    // ---- merge over the splits.  A workgroup that has left its partial arrives at the unit's counter.  Where all workgroups
-    // of the launch fit the chip at once (p.wait > 0) it then waits for the others, and every one of them merges its share of
-    // the unit's rows: the partials of a unit are 100 to 250 KB, which a single compute unit draws in 4 to 6 us.  The wait
-    // is bounded, because other launches may hold the compute units that a late workgroup needs: a workgroup that has
-    // waited p.wait ticks leaves, and says so in the counter; if anybody left before the last one arrived, that one merges
-    // everything, as it does where nobody waits.  Once all have arrived the counter does not change any more, so all see
-    // the same.  Whoever merges adds the splits in the same order: the same inputs give the same bits.
+    // ---- merge over the splits, by the workgroup that arrives last at the unit's counter.  Nobody waits: a workgroup that
+    // waited for the others, to merge a share of the rows, would hold its compute unit while workgroups of other streams' launches
+    // -- or of its own -- need it.  (Waits of up to 10 us, nobody / all wait: one token over 16k slots of 28/4 heads 15.6 / 13.8 us
+    // alone, but 13.1 / 13.8, 10.0 / 21.1 and 9.0 / 21.1 us a call on 2, 3 and 4 streams.)
     float* const pml = p.part_ml + unit * p.max_split * (TR * 2);
     if (wave == 0 && kg == 0) {
 #pragma unroll
@@ -727,67 +722,38 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's partials have reached memory
     __syncthreads();
-    unsigned* const word = p.counters + unit * p.counter_stride;
-    unsigned* const exits = word + kStreamUnits;
-    unsigned n_exits = 0;
     if (tid == 0) {
-        unsigned seen = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-        const bool last = arrived_all(seen, n_split);
-        if (p.wait > 0) {
-            const u64 t0 = __builtin_amdgcn_s_memrealtime();
-            while (!arrived_all(seen, n_split)) {
-                if (__builtin_amdgcn_s_memrealtime() - t0 < (u64)p.wait) {
-                    __builtin_amdgcn_s_sleep(2);
-                    seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                } else if (__hip_atomic_compare_exchange_strong(word, &seen, seen + kArrivalLeft, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                                __HIP_MEMORY_SCOPE_AGENT)) {
-                    break;  // (a failed exchange has read the word again; it changes at most twice per workgroup)
-                }
-            }
-            // the counter is not looked at again: the last workgroup to say so puts both words back to zero
-            n_exits = __hip_atomic_fetch_add(exits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-        } else if (last) {
-            __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        role = merge_role(seen, n_split, last, p.wait > 0);
+        unsigned* const word = p.counters + unit * p.counter_stride;
+        const unsigned before = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last_flag = before == (unsigned)n_split - 1u ? 1 : 0;
+        if (last_flag) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    const int what = role;
-    if (tid == 0 && n_exits == (unsigned)n_split) {
-        __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(exits, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (what == kMergeNothing) return;
+    if (!last_flag) return;
 
     const int n_rows = rows - row0 < TR ? rows - row0 : TR;
     const int e4 = n_rows * (D / 4);  // 16-byte pieces of the output rows
-    const int e_lo = what == kMergeShare ? e4 * split / n_split : 0;
-    const int e_hi = what == kMergeShare ? e4 * (split + 1) / n_split : e4;
-    if (e_lo >= e_hi) return;
     constexpr int PB = 8;  // splits in flight per thread
-    // The pieces are few, so ng groups of threads take the splits of a piece between them, up to 8 splits each; their number
-    // depends on the sizes only, not on who merges.
-    int ng = T / (p.wait > 0 ? (e4 + n_split - 1) / n_split : e4);
+    int ng = T / e4;  // groups of threads that take the splits of a piece between them, where the pieces are few
     const int ng_max = (n_split + PB - 1) / PB;
     ng = ng < 1 ? 1 : ng > ng_max ? ng_max : ng;
-    const int pe = T / ng < e_hi - e_lo ? T / ng : e_hi - e_lo;  // pieces of a pass
+    const int pe = T / ng < e4 ? T / ng : e4;  // pieces of a pass
     const int grp = tid / pe, ei = tid - grp * pe;
     auto piece = [&](int e, int sp, f32x4& x) __attribute__((always_inline)) {
         x = __builtin_bit_cast(f32x4, buf_load_16<kCacheDevice>(parts, (unsigned)(sp * (TR * D) + 4 * e) * 4u));
     };
     // weights of the splits, a wavefront per row and a lane per split: sw[s][row] = 2^(m_s - M) / L
-    const int r_lo = e_lo / (D / 4), r_hi = (e_hi - 1) / (D / 4);
     f32x2 ml = {-INFINITY, 0.f};
-    if (r_lo + wave <= r_hi && lane < n_split) ml = stream_load2(pml + (lane * TR + r_lo + wave) * 2);
+    if (wave < n_rows && lane < n_split) ml = stream_load2(pml + (lane * TR + wave) * 2);
     f32x4 x[PB];
 #pragma unroll
     for (int b = 0; b < PB; ++b) {  // the first pieces are requested with the first (m, l)
         const int sp = grp + b * ng;
         x[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (grp < ng && e_lo + ei < e_hi && sp < n_split) piece(e_lo + ei, sp, x[b]);
+        if (grp < ng && ei < e4 && sp < n_split) piece(ei, sp, x[b]);
     }
-    for (int row = r_lo + wave; row <= r_hi; row += W) {
-        if (row != r_lo + wave) ml = lane < n_split ? stream_load2(pml + (lane * TR + row) * 2) : f32x2{-INFINITY, 0.f};
+    for (int row = wave; row < n_rows; row += W) {
+        if (row != wave) ml = lane < n_split ? stream_load2(pml + (lane * TR + row) * 2) : f32x2{-INFINITY, 0.f};
         const float M = wave_max(ml[0]);
         const float w = ml[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[0] - M);
         const float L = wave_sum(w == 0.f ? 0.f : w * ml[1]);
@@ -795,13 +761,13 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     }
     __syncthreads();
     f32x4* const red = &os[0][0][0];  // [ng][pe], at most one piece per thread
-    for (int e0 = e_lo; e0 < e_hi; e0 += pe) {
+    for (int e0 = 0; e0 < e4; e0 += pe) {
         const int e = e0 + ei;
         const int row = e / (D / 4);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        if (grp < ng && e < e_hi) {
+        if (grp < ng && e < e4) {
             for (int s0 = grp; s0 < n_split; s0 += PB * ng) {
-                if (e0 != e_lo || s0 != grp) {
+                if (e0 != 0 || s0 != grp) {
 #pragma unroll
                     for (int b = 0; b < PB; ++b) {
                         const int sp = s0 + b * ng;
@@ -823,7 +789,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         }
         if (ng == 1) continue;  // the same for every thread
         __syncthreads();
-        if (tid < pe && e < e_hi) {
+        if (tid < pe && e < e4) {
             acc = red[tid];
             for (int gidx = 1; gidx < ng; ++gidx) {
                 const f32x4 y = red[gidx * pe + tid];
@@ -851,7 +817,6 @@ static hipError_t launch_stream_form(const StreamLaunch& s, hipStream_t stream) 
         a.g = s.n_q_heads / s.n_kv_heads;
         a.max_split = s.max_split;
         a.counter_stride = s.counter_stride;
-        a.wait = s.wait;
         a.pool_tokens = s.pool_tokens;
         a.q_scale = s.q_scale;
         for (int i = 0; i < s.n_items; ++i) a.it[i] = s.items[i];
