@@ -615,7 +615,7 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
     const int64_t units = plan.units, tr = 16 * plan.row_blocks;
     StreamLaunch sl;
     sl.row_blocks = plan.row_blocks;
-    int64_t unit0 = 0, grid_x = 0, n_split = 1;
+    int64_t unit0 = 0, block0 = 0, n_split = 1;
     // own tokens in splits of their own as long as the workgroups fit the chip
     int64_t own = 0;
     for (int32_t i = 0; i < n_items; ++i)
@@ -628,10 +628,11 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
         const int64_t here = stream_units(d, shapes[i], sl.row_blocks);
         it.unit0 = (int32_t)unit0;
         unit0 += here;
-        grid_x = std::max(grid_x, here * it.n_split);
+        it.block0 = (int32_t)block0;
+        block0 += here * it.n_split;
         n_split = std::max<int64_t>(n_split, it.n_split);
     }
-    if (grid_x > INT32_MAX || unit0 > INT32_MAX) return fail(ctx, ADAPSHOT_EINVAL, "query_attn: too many workgroups");
+    if (block0 > INT32_MAX || unit0 > INT32_MAX) return fail(ctx, ADAPSHOT_EINVAL, "query_attn: too many workgroups");
     sl.part_o = nullptr;
     sl.part_ml = nullptr;
     if (n_split > 1) {
@@ -653,7 +654,7 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
     sl.dtype = d.dtype;
     sl.max_split = (int32_t)n_split;
     sl.pool_tokens = (int32_t)std::min<int64_t>(ctx->shot_offsets.empty() ? 0 : ctx->shot_offsets.back(), INT32_MAX);
-    sl.grid_x = (int32_t)grid_x;
+    sl.n_wgs = (int32_t)block0;
     sl.n_items = n_items;
     sl.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
     sl.items = items;

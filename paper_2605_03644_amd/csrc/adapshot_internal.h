@@ -180,6 +180,7 @@ struct StreamItem {
     int32_t n_ctx, t_q, q_pos0;
     int32_t keys_per_split, n_split;  // the last split also takes the query's own tokens
     int32_t unit0;      // first unit of the problem in the workspaces
+    int32_t block0;     // its first workgroup in the launch
 };
 template <int NI>
 struct StreamArgs {
@@ -204,7 +205,7 @@ struct StreamLaunch {
     int64_t ctx_pos0;
     int32_t n_q_heads, n_kv_heads, head_dim, dtype, max_split, pool_tokens, counter_stride;
     int32_t row_blocks;  // 16-row blocks per workgroup: 1 or 2
-    int32_t grid_x;      // workgroups of the largest problem
+    int32_t n_wgs;       // workgroups of all problems
     int32_t n_items;
     float q_scale;
     const StreamItem* items;

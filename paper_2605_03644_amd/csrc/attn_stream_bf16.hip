@@ -16,7 +16,7 @@ hipError_t launch_attn_stream_bf16(const StreamLaunch& s, hipStream_t stream) {
 }
 
 hipError_t launch_attn_stream(const StreamLaunch& s, hipStream_t stream) {
-    if (s.n_items < 1 || s.n_items > kStreamItems || s.grid_x < 1) return hipErrorInvalidValue;
+    if (s.n_items < 1 || s.n_items > kStreamItems || s.n_wgs < 1) return hipErrorInvalidValue;
     return s.dtype == ADAPSHOT_BF16 ? launch_attn_stream_bf16(s, stream) : launch_attn_stream_f32(s, stream);
 }
 
