@@ -146,7 +146,8 @@ adapshot_status adapshot_assemble(adapshot_ctx* ctx, adapshot_cache* cache, cons
  * as large at 6e-2.  Accumulation, maxima and sums are fp32 throughout.
  * A value of v_self that is not finite reaches only the rows that attend to its token.  Exception: bf16 models with
  * head_dim 128 in calls beyond decode steps and short probes (more than 8 query rows per kv head, or more than 200 MB of context; in
- * a batch, more than 400 MB; zero-copy calls always), where it can make NaN of every row of the call.
+ * a batch, more than 16 rows in an item, more than 300 MB, or a context that several items read; zero-copy calls always), where it
+ * can make NaN of every row of the call.
  * Errors, all found before anything is launched (out is then untouched): EINVAL (null or
  * misaligned pointer, t_q < 1, layer out of range, n_ctx < 0, q_pos0 < 0, a q of 2 GiB or more, or a
  * context or query whose K/V rows span more than 4 GiB in one layer), ESTATE (n_ctx beyond
@@ -195,7 +196,8 @@ adapshot_status adapshot_assemble_batched(adapshot_ctx* ctx, adapshot_cache* cac
  * have one common length, so
  * probes over nested prefixes of one cache read identical leading slices, and those workgroups are
  * scheduled next to each other.  Other shapes, and decode steps of such models (at most 16 query rows per kv head,
- * contexts of their own, up to 400 MB of them; a batch of one item is a single call), run up to 32 items per launch.  The outputs of distinct items must not
+ * contexts of their own, up to 300 MB of them, and batches of one item where adapshot_query_attn would not run the matrix-core
+ * kernel), run up to 32 items per launch.  The outputs of distinct items must not
  * overlap; inputs may be shared between items.  A call whose arguments other than `layer` equal the previous
  * batched call's on this context (the same items, caches, pointers and lengths: the next layer of a forward pass)
  * reuses the tables the previous call left in device memory and only launches; nothing the caller does between

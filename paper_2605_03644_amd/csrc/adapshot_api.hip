@@ -1228,24 +1228,6 @@ extern "C" adapshot_status adapshot_query_attn_pool_batched(adapshot_ctx* ctx, i
     return st;
 }
 
-// Batches that the streaming kernel takes from the tile kernel: decode steps (one 16-row block per kv head and item), as far as
-// their contexts are few bytes (stream_bytes_ok) and every one is read by one item -- items that share one find its tiles in the
-// L2 when the tile kernel orders them by cache and split.  A batch of one is priced like a single call.
-static bool streams_batch(const adapshot_ctx* ctx, const adapshot_attn_item* items, int32_t n_items) {
-    const int32_t g = ctx->desc.n_q_heads / ctx->desc.n_kv_heads;
-    if (n_items == 1) return !single_by_tiles(ctx->desc, items[0].t_q, items[0].n_ctx, false, ctx->n_cu);
-    std::vector<int32_t> seen;
-    seen.reserve((size_t)n_items);
-    int64_t tokens = 0;
-    for (int32_t i = 0; i < n_items; ++i) {
-        tokens += items[i].n_ctx;
-        if ((int64_t)items[i].t_q * g > 16 || !stream_bytes_ok(ctx->desc, tokens / 2)) return false;
-        if (items[i].n_ctx > 0) seen.push_back(items[i].cache_index);
-    }
-    std::sort(seen.begin(), seen.end());
-    return std::adjacent_find(seen.begin(), seen.end()) == seen.end();
-}
-
 extern "C" adapshot_status adapshot_query_attn_batched(adapshot_ctx* ctx, const adapshot_cache* caches,
                                                        int32_t n_caches, int32_t layer,
                                                        const adapshot_attn_item* items, int32_t n_items,
@@ -1265,7 +1247,7 @@ extern "C" adapshot_status adapshot_query_attn_batched(adapshot_ctx* ctx, const 
         }
     }
     adapshot_status st = ADAPSHOT_OK;
-    if (n_items > 0 && attn_mfma_supported(ctx->desc) && !streams_batch(ctx, items, n_items)) {
+    if (n_items > 0 && !batch_by_stream(ctx->desc, items, n_items, ctx->n_cu)) {
         st = run_query_attn_batch(ctx, caches, layer, items, n_items, (hipStream_t)hip_stream);
     } else {
         for (int32_t i0 = 0; i0 < n_items && st == ADAPSHOT_OK; i0 += kStreamItems) {

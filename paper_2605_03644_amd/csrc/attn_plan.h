@@ -110,46 +110,54 @@ inline int64_t stream_splits(const adapshot_model_desc& d, int64_t n_ctx, int64_
     return (last + kStreamWaves - 1) / kStreamWaves > (keys / sk + kStreamWaves - 1) / kStreamWaves ? n + 1 : n;
 }
 
-// What a launch of the streaming kernel takes, us, by its longest split (in 64-key tiles).  A workgroup spends 4.5 us before its
-// first product and after its last one, and 0.6 us plus the loads of 82 KB/us for every round of its 8 wavefronts over its keys
-// (bf16 x 128: 2.2 us per 256 keys; bf16 x 64 and fp32 x 64: 1.4 per 256 and 128; 1.1 over an assembled cache, 2 and more where the
-// keys are gathered and rotated on the way, which is planned alike).  Splits cost their merge: 3 to 7 us where all workgroups fit
-// the chip and share it, 9 where they do not and the last one to arrive does it (fp32 x 128, 64 tokens over 6k slots: 8 splits of
-// 32 units 23.8 us, 10 splits 37.3).  So a problem gets the splits that fill the chip once, or none.  Measured / priced: 32/8 x 128,
-// 24 tokens over 830 slots, 5 splits 9.8 / 11.5 (1: 12.3 / 13.3); 64 tokens over 1.7k, 2 splits 16.7 / 18.3 (1: 19.8 / 19.9); 1 token over
-// 6.8k, 27 splits 10.4 / 11.2 (10: 13.5 / 14); 64 x bf16, 64 tokens over 2k, 4 splits 12.7 / 12.3 (1: 16.7 / 15.7); 4/2 x 64 fp32, 16 tokens over
-// 250, 1 split 6.5 / 7.3 (4: 7.8 / 8.1), over 1000, 16 splits 7.9 / 8.7 (1: 13.6 / 15.7).
+// What a launch of the streaming kernel takes, us, by its longest split (in 64-key tiles).  A workgroup has a compute unit to itself and
+// spends 3.4 us before its first product and after its last one, and on every step of its wavefronts 0.25 us plus the loads of 54 KB/us
+// (where the steps do not divide by the wavefronts, some of these run one step fewer: the others get more of the memory then).
+// As many workgroups as there are compute units run at once, the next ones after them, and each turn takes at least what the memory needs
+// for its share of the keys: 2.4 TB/s to 64 workgroups, 3.4 to 128, 6.1 to 256; rows of one kv head in several units are drawn
+// from it half of the time.  Splits cost their merge by the last workgroup: 3.2 us, 0.15 for every round of its loads and 19 ns per KB.
+// Fitted to 1294 calls over contexts that no cache held, each with up to 20 split counts (single calls of 11 models, 1 to 256 tokens over
+// 60 to 32k slots; decode steps of 2 to 32 queries of 5 models): the counts chosen here take 0.8 % longer than the best ones, at
+// most 18 % (a price fitted to repeated calls over one context: 4 %, at most 54 %).
 inline double stream_price(const adapshot_model_desc& d, int64_t n_cu, const StreamShape* shapes, int32_t n_shapes, int32_t row_blocks,
                            int64_t split_tiles) {
     const int64_t e = d.dtype == ADAPSHOT_BF16 ? 2 : 4, sk = stream_step_keys(d);
-    const double round_us = 0.6 + (double)(kStreamWaves * sk * 2 * d.head_dim * e) / 82e3;
-    int64_t units = 0, wgs = 0, read = 0, drawn = 0, longest = 0;  // tiles of a kv head: read by all workgroups, drawn from the memory
+    int64_t wgs = 0, read = 0, drawn = 0, longest = 0, rows = 0;  // tiles of a kv head: read by all workgroups, by one unit of each problem
     for (int32_t i = 0; i < n_shapes; ++i) {
         const int64_t here = stream_units(d, shapes[i], row_blocks);
-        units += here;
         wgs += here * std::max<int64_t>(1, (shapes[i].key_tiles + split_tiles - 1) / split_tiles);
         read += here * shapes[i].key_tiles;
         drawn += d.n_kv_heads * shapes[i].key_tiles;
         longest = std::max(longest, shapes[i].key_tiles);
+        rows = std::max(rows, std::min<int64_t>(shapes[i].rows, 16 * row_blocks));
     }
-    const int64_t steps = std::min(split_tiles, longest) * 64 / sk, launch_rounds = (wgs + n_cu - 1) / n_cu;
-    const double tile_mb = (double)(128 * d.head_dim * e) * 1e-6;
-    const double t = (double)launch_rounds * (4.5 + (double)((steps + kStreamWaves - 1) / kStreamWaves) * round_us);
-    // the memory gives more the more workgroups ask: 2.9 TB/s to 64 of them, 4.0 to 128, 5.1 to 256
-    const double busy = (double)std::min(wgs, n_cu);
-    const double loads = 4.5 + std::max((double)read * tile_mb / (0.045 * (double)n_cu), (double)drawn * tile_mb * (busy + 90.0) / (6.9 * busy));
-    // (of plans that cost the same the one with more workgroups, up to the chip's)
-    return std::max(t, loads) + (split_tiles >= longest ? 0.0 : launch_rounds == 1 ? 2.8 + 4.0 * (double)units / (double)n_cu : 9.0) -
-           0.001 * busy;
+    const int64_t steps = std::min(split_tiles, longest) * 64 / sk, step_rounds = (steps + kStreamWaves - 1) / kStreamWaves;
+    const double round_us = 0.25 + (double)(kStreamWaves * sk * 2 * d.head_dim * e) * (row_blocks == 2 ? 1.41 : 1.0) / 54e3;
+    const double wg_us = 3.4 + (0.4 * (double)step_rounds + 0.6 * (double)steps / kStreamWaves) * round_us;
+    const double mb_per_wg = 0.5 * (double)((read + drawn) * 128 * d.head_dim * e) * 1e-6 / (double)wgs;
+    auto turn = [&](double n) { return std::max(wg_us, 3.4 + mb_per_wg * (n + 250.0) / 12.0); };
+    double t = (double)(wgs / n_cu) * turn((double)n_cu) + (wgs % n_cu > 0 ? turn((double)(wgs % n_cu)) : 0.0);
+    if (split_tiles < longest) {
+        const int64_t n = (longest + split_tiles - 1) / split_tiles;
+        const int64_t pieces = std::max<int64_t>(1, rows * d.head_dim / 4), threads = 64 * kStreamWaves;
+        const int64_t groups = std::max<int64_t>(1, std::min(threads / pieces, (n + 7) / 8));
+        const int64_t loads = ((pieces + threads / groups - 1) / (threads / groups)) * ((n + 8 * groups - 1) / (8 * groups));
+        t += 3.2 + 0.15 * (double)loads + 0.019 * (double)(n * rows * d.head_dim * 4) / 1024.0;
+    }
+    return t;
 }
 
 // Split length (in 64-key tiles) of a launch: the longest context in n equal splits, the others in splits of the same length.
 inline int64_t plan_stream_split_tiles(const adapshot_model_desc& d, int64_t n_cu, const StreamShape* shapes, int32_t n_shapes,
                                        int32_t row_blocks) {
-    int64_t longest = 0;
-    for (int32_t i = 0; i < n_shapes; ++i) longest = std::max(longest, shapes[i].key_tiles);
+    int64_t longest = 0, units = 0;
+    for (int32_t i = 0; i < n_shapes; ++i) {
+        longest = std::max(longest, shapes[i].key_tiles);
+        units += stream_units(d, shapes[i], row_blocks);
+    }
     if (longest == 0) return 1;
-    const int64_t n_max = std::min<int64_t>(longest, kStreamMaxSplits);
+    // (beyond two turns nothing is gained, and the host has better things to do)
+    const int64_t n_max = std::min<int64_t>(std::min<int64_t>(longest, kStreamMaxSplits), 2 * n_cu / std::max<int64_t>(units, 1) + 1);
     int64_t best = longest, last = 0;
     double best_t = 1e300;
     for (int64_t n = 1; n <= n_max; ++n) {
@@ -193,36 +201,53 @@ inline StreamPlan plan_stream(const adapshot_model_desc& d, int64_t n_cu, int32_
 // Which kernel: the 256-row tile kernel for bf16 models of head dimension 128 where it is the cheaper one.  It reads a context
 // once per 256 rows and draws 6.1 TB/s, but is two launches (a batch: three), leaves wavefronts without rows idle and
 // writes a partial for every split; the streaming kernel reads it once per 16 rows, in one launch.
-// A batch goes to the streaming kernel if its items have at most 16 rows and its contexts at most twice kStreamBytes.  Per layer of
-// a decode step (tile kernel with table copy and merge / streaming kernel, us): 28/4 heads, 6 queries of 16k slots 201 MB 50.0 / 44.6, 8
-// 267 MB 62.1 / 57.4, 28 of 5k 282 MB 71.1 / 63.9, 12 of 16k 402 MB 84.7 / 84.2, 20 669 MB 130 / 132, 32 1067 MB 196 / 206; 32/8 heads, 16
-// of 5k 323 MB 77.3 / 67.3.
 constexpr int64_t kStreamBytes = 200000000;
-inline bool stream_bytes_ok(const adapshot_model_desc& d, int64_t context_tokens) {
-    return context_tokens * d.n_kv_heads * d.head_dim * 4 <= kStreamBytes;
-}
-// A single call compares prices.  The tile kernel's, fitted to calls of 64 to 512 rows over 250 to 5000 slots: 13 us for
-// the two launches, 0.75 us per MB of partials, 0.65 or (more than 128 rows) 1 us per tile of a workgroup.  Us, tile /
-// streaming: 32/8 heads, 8 tokens over 250 / 1.7k / 3.4k slots 14.0 / 14.5 / 15.6 and 10.7 / 10.4 / 11.2; 24 tokens over 830 / 3.4k
-// 13.7 / 17.6 and 10.4 / 16.4; 64 tokens over 250 / 1.7k / 3.4k 14.6 / 23.5 / 24.6 and 10.1 / 17.6 / 24.5; 28/4 heads, 16 tokens over 5k
-// 18.9 and 14.8, 64 tokens over 5k 24.5 and 32.1; 64/8 heads, 16 tokens over 5k 20.1 and 22.7.
+inline int64_t context_bytes(const adapshot_model_desc& d, int64_t slots) { return slots * d.n_kv_heads * d.head_dim * 4; }
+
+// A single call compares prices, but keeps the streaming kernel's fp32 partials where it has few rows.  The tile kernel's price: 10.8 us
+// for the two launches, 0.83 us per MB of partials, 0.08 per split, and per tile of a workgroup and turn 0.35 or (more than 128 rows)
+// 0.57 us, or 7.3 MB/us.  Over 358 calls (5 models, 1 to 256 tokens over 60 to 32k slots that no cache held) the kernel chosen is 0.2 %
+// slower than the better one, at most 14 %.  Us, tile kernel / streaming: 32/8 heads, 8 tokens over 250 / 2k / 4k slots
+// 11.3 / 14.9 / 16.4 and 7.0 / 11.2 / 12.8; 32 tokens over 1k / 4k 15.8 / 19.1 and 11.5 / 19.7; 64 tokens over 250 / 1k / 4k 13.9 / 18.4 / 21.9
+// and 7.8 / 15.1 / 30.4; 28/4 heads, 16 / 64 tokens over 4k 21.7 / 22.4 and 14.8 / 29.0; 64/8 heads, 8 tokens over 8k 20.0 and 22.6.
 inline bool single_by_tiles(const adapshot_model_desc& d, int32_t t_q, int64_t n_ctx, bool zero_copy, int64_t n_cu = 256) {
     if (!attn_mfma_supported(d)) return false;
-    if (zero_copy || !stream_bytes_ok(d, n_ctx)) return true;  // (no gathered form of the streaming kernel for these models)
+    if (zero_copy || context_bytes(d, n_ctx) > kStreamBytes) return true;  // (no gathered form of the streaming kernel for these models)
     const int64_t rows = (int64_t)t_q * (d.n_q_heads / d.n_kv_heads), key_tiles = (n_ctx + 63) / 64, self_tiles = ((int64_t)t_q + 63) / 64;
-    // 1 token over 45k slots of 32/8 heads: 41.0 by tiles, 39.5 by streaming, shorter ones further apart; but from 100 MB on the
-    // partials of more than 8 rows cost more than the second launch (4 tokens over 24k / 27k slots 27.9 / 30.5 and 26.5 / 35)
-    if (rows <= 8) return false;
-    if (rows > 16 * kAttnRowTile || !stream_bytes_ok(d, 2 * n_ctx)) return true;
+    if (rows <= 8 || (rows <= 16 && n_ctx <= 1024)) return false;
+    if (rows > 16 * kAttnRowTile) return true;
     const StreamShape sh{rows, key_tiles + self_tiles};  // (the query's own tokens as more context)
     const int32_t rb = stream_row_blocks(d, n_cu, &sh, 1);
     const double stream = stream_price(d, n_cu, &sh, 1, rb, plan_stream_split_tiles(d, n_cu, &sh, 1, rb));
     const int64_t units = d.n_kv_heads * ((rows + kAttnRowTile - 1) / kAttnRowTile);
     const int64_t n_split = key_tiles > 0 ? plan_mfma_splits(n_cu, units, key_tiles, self_tiles) : 0;
-    const int64_t per_wg = n_split > 0 ? (key_tiles + n_split - 1) / n_split : 0;
-    const double drawn_mb = (double)(key_tiles * d.n_kv_heads * 256 * d.head_dim) * 1e-6;
+    const int64_t per_wg = n_split > 0 ? (key_tiles + n_split - 1) / n_split : 0, turns = (units * (n_split + 1) + n_cu - 1) / n_cu;
+    const double drawn_mb = (double)context_bytes(d, 64 * key_tiles) * 1e-6;
     const double partials_mb = (double)((n_split + 1) * rows * d.n_kv_heads * d.head_dim * 2) * 1e-6;
-    return 13.0 + 0.75 * partials_mb + std::max((rows > 128 ? 1.0 : 0.65) * (double)per_wg, drawn_mb / 6.1) < stream;
+    return 10.8 + 0.83 * partials_mb + 0.08 * (double)n_split +
+               std::max((rows > 128 ? 0.57 : 0.35) * (double)(per_wg * turns), drawn_mb / 7.3) < stream;
+}
+
+// A batch of these models: the streaming kernel if every item has at most 16 rows per kv head, all contexts together at most 1.5 times
+// kStreamBytes, and every context is read by one item -- items that share one find its tiles in the L2 when the tile kernel orders
+// them by cache and split.  Per layer of a decode step over contexts that no cache held, tables made for every call (tile kernel with
+// table copy and merge / streaming kernel, us): 28/4 heads, 12 queries of 8k slots 197 MB 48.7 / 41.3, 8 of 16k 262 MB 59.5 / 53.4, 20
+// of 8k 328 MB 66.9 / 65.3, 12 of 16k 393 MB 74.5 / 75.8, 16 of 16k 524 MB 95.0 / 99.2; 32/8 heads, 4 tokens, 8 of 8k 262 MB
+// 56.1 / 56.2, 12 of 8k 393 MB 84.6 / 84.7, 6 of 16k 393 MB 73.1 / 79.1.  A batch of one takes it where a single call does, too.
+inline bool batch_by_stream(const adapshot_model_desc& d, const adapshot_attn_item* items, int32_t n_items, int64_t n_cu) {
+    if (!attn_mfma_supported(d)) return true;
+    if (n_items == 1 && !single_by_tiles(d, items[0].t_q, items[0].n_ctx, false, n_cu)) return true;
+    std::vector<int32_t> seen;
+    seen.reserve((size_t)n_items);
+    int64_t slots = 0;
+    for (int32_t i = 0; i < n_items; ++i) {
+        slots += items[i].n_ctx;
+        if ((int64_t)items[i].t_q * (d.n_q_heads / d.n_kv_heads) > 16) return false;
+        if (context_bytes(d, slots) > (n_items == 1 ? kStreamBytes : kStreamBytes + kStreamBytes / 2)) return false;
+        if (items[i].n_ctx > 0) seen.push_back(items[i].cache_index);
+    }
+    std::sort(seen.begin(), seen.end());
+    return std::adjacent_find(seen.begin(), seen.end()) == seen.end();
 }
 
 // Split the context of one attention call so that (kv heads x row tiles x splits) fills the chip.  Keys per
