@@ -320,7 +320,8 @@ adapshot_status adapshot_set_attn_splits(adapshot_ctx* ctx, int32_t n_split);
 /* The split plan adapshot_query_attn uses for t_q query tokens over n_ctx context slots on a GPU with
  * n_compute_units compute units (host logic, nothing is launched, no GPU needed): the context is cut into
  * *n_split pieces of *keys_per_split slots (a multiple of 64; the last piece may be shorter; an empty context
- * has no piece), and the query's own tokens form one more (bf16, head_dim 128) or go with the last piece (other shapes).  EINVAL on a bad description or argument. */
+ * has no piece), and the query's own tokens form one more (calls of the matrix-core kernel) or go with the last piece (calls of the
+ * streaming kernel).  EINVAL on a bad description or argument. */
 adapshot_status adapshot_attn_split_plan(const adapshot_model_desc* desc, int32_t n_compute_units, int32_t t_q,
                                          int64_t n_ctx, int32_t* n_split, int64_t* keys_per_split);
 

@@ -612,25 +612,19 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
     StreamShape shapes[kStreamItems];
     for (int32_t i = 0; i < n_items; ++i) shapes[i] = StreamShape{(int64_t)items[i].t_q * g, ((int64_t)items[i].n_ctx + 63) / 64};
     const StreamPlan plan = plan_stream(d, ctx->n_cu, ctx->force_splits, shapes, n_items);
-    const int64_t units = plan.units, tr = 16 * plan.row_blocks;
+    const int64_t units = plan.units, n_split = plan.n_split, tr = 16 * plan.row_blocks;
     StreamLaunch sl;
     sl.row_blocks = plan.row_blocks;
-    int64_t unit0 = 0, block0 = 0, n_split = 1;
-    // own tokens in splits of their own as long as the workgroups fit the chip
-    int64_t own = 0;
-    for (int32_t i = 0; i < n_items; ++i)
-        own += stream_units(d, shapes[i], sl.row_blocks) * stream_splits(d, items[i].n_ctx, items[i].t_q, plan.split_tiles);
+    int64_t unit0 = 0, block0 = 0;
     for (int32_t i = 0; i < n_items; ++i) {
         StreamItem& it = items[i];
         it.keys_per_split = (int32_t)(plan.split_tiles * 64);
-        it.n_split = (int32_t)(own <= ctx->n_cu ? stream_splits(d, it.n_ctx, it.t_q, plan.split_tiles)
-                                                : std::max<int64_t>(1, (shapes[i].key_tiles + plan.split_tiles - 1) / plan.split_tiles));
+        it.n_split = (int32_t)stream_splits(shapes[i], plan.split_tiles);
         const int64_t here = stream_units(d, shapes[i], sl.row_blocks);
         it.unit0 = (int32_t)unit0;
         unit0 += here;
         it.block0 = (int32_t)block0;
         block0 += here * it.n_split;
-        n_split = std::max<int64_t>(n_split, it.n_split);
     }
     if (block0 > INT32_MAX || unit0 > INT32_MAX) return fail(ctx, ADAPSHOT_EINVAL, "query_attn: too many workgroups");
     sl.part_o = nullptr;

@@ -18,7 +18,7 @@ extern "C" int64_t workgroups(const adapshot_model_desc* d, const int64_t* rows,
     for (int32_t i = 0; i < n; ++i) s.push_back(StreamShape{rows[i], tiles[i]});
     const StreamPlan p = plan_stream(*d, 256, 0, s.data(), n);
     int64_t wgs = 0;
-    for (const StreamShape& x : s) wgs += stream_units(*d, x, p.row_blocks) * std::max<int64_t>(1, (x.key_tiles + p.split_tiles - 1) / p.split_tiles);
+    for (const StreamShape& x : s) wgs += stream_units(*d, x, p.row_blocks) * stream_splits(x, p.split_tiles);
     return wgs;
 }
 """
@@ -98,3 +98,19 @@ def test_a_few_decode_steps_fill_the_chip_at_most_once(plan, hq, hkv, nq, n):
     arr = lambda x: (ctypes.c_int64 * len(x))(*x)  # noqa: E731
     wgs = plan.workgroups(ctypes.byref(_desc(hq, hkv)), arr([hq // hkv] * nq), arr([-(-x // 64) for x in lens]), ctypes.c_int32(nq))
     assert min(28, hkv * nq * (n // 64)) <= wgs <= 256
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(8, 2, 128, ad.F32), (4, 2, 64, ad.F32), (32, 8, 64, ad.BF16), (28, 4, 128, ad.BF16), (8, 4, 256, ad.BF16)])
+def test_a_launch_makes_the_splits_of_the_public_plan(plan, hq, hkv, d, dtype):
+    """Also where the query's own tokens would give the last split another step (they were a split of their own there, which the public
+    plan did not name)."""
+    desc, g = ad.ModelDesc(1, hq, hkv, d, 5.0e5, dtype, ad.KEYS_UNROTATED, 1 << 20), hq // hkv
+    arr = lambda x: (ctypes.c_int64 * 1)(x)  # noqa: E731
+    for t_q in (1, 2, 16, 64):
+        for n in (1, 63, 64, 256, 2300, 3315, 8100, 30000):
+            if dtype == ad.BF16 and d == 128 and t_q * g > 8:
+                continue
+            n_split, _ = ad.attn_split_plan(hq, hkv, d, dtype, 256, t_q, n)
+            wgs = plan.workgroups(ctypes.byref(desc), arr(t_q * g), arr(-(-n // 64)), ctypes.c_int32(1))
+            units = hkv * -(-t_q * g // 16)
+            assert wgs in (n_split * units, n_split * hkv * -(-t_q * g // 32))   # one or two row blocks a workgroup
