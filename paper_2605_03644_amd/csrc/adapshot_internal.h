@@ -397,7 +397,7 @@ inline void launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipSt
 
 // The event is the dispatch's own completion where that is possible: recorded behind the kernel it is a packet of its own, which
 // the next kernel waits for.  Recorded / attached, us: sweeps of 7 queries over one layer 152.2 / 146.0, of one query over two
-// layers 129.3 / 121.5, 32 decode queries of 16k slots, 8 layers 1473 / 1463.  Not in a capture, where it stays a node, nor in a
+// layers 129.3 / 121.5; 32 decode queries of 16k slots the same (a table copy in 185 us).  Not in a capture, where it stays a node, nor in a
 // launch that carries timing events already.
 template <typename F>
 hipError_t PinnedRing::launch_reader(int slot, hipStream_t stream, F&& launch) {

@@ -32,14 +32,15 @@
 // What bounds it: a small problem, the launch, two or three round trips to memory (keys and query rows, arrival, partials)
 // and the instructions between them, 4 cycles each and two wavefronts per SIMD: loads therefore go through buffers (no
 // address arithmetic) and the query rows are rotated once per workgroup and handed out through LDS.  A larger problem,
-// what a compute unit gets from beyond its L1, 45 to 48 GB/s whatever is in flight (64 or 128 KB), which is why the loads are
-// shared by two row blocks where there are rows enough, and why a single compute unit took 5 to 6 us for the 100 to 250 KB
-// of partials of a unit.  One layer, kernel time: the last to arrive merges, addresses by lane / all merge / buffers / now
-//   bf16, 28/4 heads x 128, decode step over 16k slots             18.2 / 15.1 / 13.7 / 13.3 us
-//   fp32, 8/2 heads x 128, 32 query tokens over 2.3k slots         18.2 / 17.2 / 13.9 / 13.9
-//   bf16, 32/8 heads x 64, 64 query tokens over 6.6k slots         22.4 / 22.2 / 18.9 / 19.5
-//   fp32, 4/2 heads x 64, 16 query tokens over 248 slots, 1 split   8.7 /  8.8 /  6.5 /  6.4
-//   bf16, 32/8 heads x 128, 24 / 64 query tokens over 830 slots, tile kernel and its merge 13.0 / 16.6, here 9.8 / 12.6
+// what a compute unit gets from beyond its L1 -- 54 KB/us where few of them ask, 45 in launches that fill the chip, whatever is in flight
+// (64 or 128 KB) -- which is why the loads are shared by two row blocks where there are rows enough.  Splits beyond a few dozen
+// are bound by their merge, which one compute unit does: 3 us and 19 ns per KB of partials.  One layer, call after call over contexts
+// that no cache holds, addresses by lane and splits priced with a warm cache / now
+//   bf16, 28/4 heads x 128, one token over 16k slots               19.9 / 15.3 us
+//   bf16, 32/8 heads x 128, one token over 4k slots                14.3 / 10.5
+//   bf16, 28/4 heads x 128, 4 queries of 8k slots, one token each  23.0 / 19.7
+//   fp32, 8/2 heads x 128, 32 query tokens over 2k slots           18.7 / 13.7
+//   bf16, 32/8 heads x 128, 24 query tokens over 830 slots, tile kernel and its merge 15.5, here 12.1
 #pragma once
 #include <type_traits>
 
@@ -681,7 +682,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         l_wg[nr] = L;
     }
     const int64_t unit = it.unit0 + (int64_t)rt * hkv + hk;
-    // partials of the unit, [split][row][column]: at most 64 splits of 64 rows of 256 columns
+    // partials of the unit, [split][row][column]: at most 64 splits of 32 rows of 256 columns
     const buf_rsrc parts = make_buffer(p.part_o + unit * p.max_split * (TR * D), (unsigned)(n_split * (TR * D) * 4));
     auto store_out = [&](int row, int d0, f32x4 y) __attribute__((always_inline)) {
         const int j = row / g;
