@@ -5,9 +5,10 @@
 //
 // A workgroup of 8 wavefronts owns 16 * NR query rows of one KV head (rows j*g + h%g, as everywhere) and one split of
 // the context; the last split also takes the query's own tokens (causal).  The keys go to the wavefronts in steps of 16
-// (bf16 models: 32), round robin, and every wavefront runs a flash-attention state of its own over its keys: no LDS, no
-// barrier and no other wavefront in the key loop.  K and V rows are loaded from global memory in exactly the lanes where
-// the matrix instructions want them, so the loop is loads, matrix instructions and a softmax of 4 or 8 values:
+// (bf16 models: 32), round robin, and every wavefront runs a flash-attention state of its own over its keys: no
+// barrier and no other wavefront in the key loop.  V rows are loaded from global memory in exactly the lanes where
+// the matrix instructions want them, K rows whole into LDS and from there into the lanes (or, where that is no gain, straight into them),
+// so the loop is loads, matrix instructions and a softmax of 4 or 8 values:
 //
 //   S^T = K . Q^T   A = K: lane (key l%16, group l/16) holds KW consecutive columns 4*KW*j + KW*(l/16) of its key for
 //                   every j (16 bytes), B = Q in the same lanes and columns: bf16 models v_mfma_f32_16x16x32_bf16 on the
@@ -90,8 +91,22 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     constexpr int TR = 16 * NR;
     constexpr int NS = NR * DB;  // 1 KB pieces of a wavefront's output state
     static_assert(D == 8 || D % 16 == 0, "head dimensions");
+    // Keys of an assembled context come through LDS (dma_k), two steps per wavefront, where these and the states fit and the loads are
+    // what the loop waits for.  Calls over contexts that no cache held, straight into the lanes / through LDS, us: bf16 x 64, 64 tokens over
+    // 6.6k slots 22.3 / 19.5, 32/8 heads x 128, 24 tokens over 830 10.3 / 9.7, fp32 x 64, 16 tokens over 1k 8.3 / 8.1; not fp32 x 128, whose
+    // matrix instructions take longer than its loads (32 tokens over 2k 13.5 / 13.7), nor two row blocks of fp32 x 64 (200 over 2k 44.3 / 46.7).
+    constexpr int RB = D * E;                                        // bytes of a row
+    constexpr int KS_BYTES = SK * RB;                                // keys of a step
+    constexpr int OS_BYTES = NS * 1024 > KS_BYTES ? NS * 1024 : KS_BYTES;
+    constexpr bool KL = !POOL && RB >= 128 && W * (OS_BYTES + KS_BYTES) <= 128 * 1024 && (BF || (D == 64 && NR == 1));
+    constexpr int RI = KL ? 1024 / RB : 1;                           // rows of one load instruction
+    constexpr int CR = RB >= 16 ? RB / 16 : 1;                       // 16-byte chunks of a row
+    constexpr int RG = RB < 256 ? 256 / RB : 1, CM = CR < 16 ? CR - 1 : 15;  // row r keeps chunk c at place c ^ (r / RG & CM)
 
-    __shared__ f32x4 os[W][NS][64];
+    // (the states take the place of the even steps' keys)
+    __shared__ __attribute__((aligned(1024))) char ks0[W * (KL ? OS_BYTES : NS * 1024)];
+    __shared__ __attribute__((aligned(1024))) char ks1[KL ? W * KS_BYTES : 16];
+    f32x4 (*const os)[NS][64] = (f32x4 (*)[NS][64])ks0;
     __shared__ float2 wml[W][TR];
     __shared__ __attribute__((aligned(16))) char qs[TR * D * E];
     __shared__ float sw[kStreamMaxSplits][TR];
@@ -220,6 +235,38 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
             }
         }
     };
+    // The same through LDS (KL): straight from memory a quarter of a wavefront asks for 16 bytes of 16 rows each, 64 look-ups of
+    // cache lines an instruction; row by row it asks for whole lines, 8 of them, and the lanes of the matrix instruction take their chunks
+    // from LDS.  A wavefront's keys are its own: no barrier.  (128 KB of K and V rows into every workgroup, 64 / 256 workgroups,
+    // out of the last-level cache: 2.8 / 5.0 us with K in the instruction's lanes, 1.65 / 3.9 by rows; out of HBM 3.1 / 6.9 and 2.1 / 7.0.)
+    constexpr int KD = KL ? (CM + 1) * RG / RI : 1;  // instructions after which the chunks' places repeat
+    unsigned kd_lane[KD];
+    if (KL) {
+#pragma unroll
+        for (int i = 0; i < KD; ++i) {
+            const int r = i * RI + lane / CR;
+            kd_lane[i] = (unsigned)((lane / CR) * stride) + 16u * (unsigned)((lane % CR) ^ ((r / RG) & CM));
+        }
+    }
+    auto dma_k = [&](int s, char* buf) __attribute__((always_inline)) {
+        const bool on = s < n_steps, self = s >= n_cs;
+        const buf_rsrc rows_k = make_buffer(self ? kself : kctx, on ? (self ? self_bytes : ctx_bytes) : 0u);
+        const unsigned step = (unsigned)(SK * (self ? s - n_cs : s)) * (unsigned)stride;
+#pragma unroll
+        for (int i = 0; i < (KL ? KS_BYTES / 1024 : 0); ++i)
+            buf_load_lds_16(rows_k, buf + i * 1024, kd_lane[i % KD] + step + (unsigned)(i * RI) * (unsigned)stride);
+    };
+    auto take_k = [&](const char* buf, unsigned (&dst)[NK][NJ][KR]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < NK; ++b)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int r = 16 * b + l16;
+                const u32x4 x = *(const u32x4*)(buf + r * RB + (((4 * j + kg) ^ ((r / RG) & CM)) << 4));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dst[b][j][i % KR] = x[i];
+            }
+    };
     auto load_v = [&](int s, unsigned (&dst)[NV][DG][VR]) __attribute__((always_inline)) {
         const bool on = s < n_steps, self = s >= n_cs;
         if (POOL) {
@@ -344,13 +391,24 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
             tl[i][e] = l4[e];
         }
     }
-    unsigned kf[NB][NK][NJ][KR];
+    unsigned kf[KL ? 1 : NB][NK][NJ][KR];
+    char* const kw0 = ks0 + (KL ? wave * OS_BYTES : 0);
+    char* const kw1 = ks1 + (KL ? wave * KS_BYTES : 0);
+    // keys of step s into buffer b; LDS: every read of what the buffer held has returned
+    auto get_k = [&](int s, int b) __attribute__((always_inline)) {
+        if (!KL) {
+            load_k(s, kf[b % (KL ? 1 : NB)]);
+            return;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        dma_k(s, b == 0 ? kw0 : kw1);
+    };
     unsigned vf[NBV][NV][DG][VR];
     fetch_tok(wave);
     take_tok();
     if (TOK2) fetch_tok(wave + W);
-    load_k(wave, kf[0]);
-    if (NBV > 1) {
+    get_k(wave, 0);
+    if (NBV > 1 && !KL) {
         load_v(wave, vf[0]);
         if (!TOK2) fetch_tok(wave + W);
         take_tok();
@@ -385,6 +443,9 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     }
     // (a barrier that leaves the loads of keys and values in flight)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    // (V behind the barrier: the wavefronts that take the query rows stand in line with the others' requests, and 64 KB of keys are
+    // enough to be in flight until then: 1357 calls, V before the barrier 2 % faster than without LDS, behind it 4 %)
+    if (NBV > 1 && KL) load_v(wave, vf[0]);
     unsigned qf[NR][NJ][KR];
     int jrow[NR];
 #pragma unroll
@@ -592,21 +653,26 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         // second one (one step per wavefront: 7.2 -> 6.6 us of a call, 10.3 -> 9.6).
         int s = wave;
         auto step = [&](int b) __attribute__((always_inline)) {
-            if (!LATE) turn(s, kf[b]);
+            const int kb = KL ? 0 : b;
+            if (!LATE && !KL) turn(s, kf[kb]);
             if (NBV == 1) {
                 load_v(s, vf[0]);
                 fetch_tok(s + W);
                 take_tok();
             }
             if (TOK2) fetch_tok(s + 2 * W);
-            load_k(s + W, kf[1 - b]);
+            get_k(s + W, 1 - b);
             if (NBV > 1) {
                 load_v(s + W, vf[(1 - b) % NBV]);
                 if (!TOK2) fetch_tok(s + 2 * W);
                 take_tok();
             }
-            if (LATE) turn(s, kf[b]);
-            compute(s, kf[b], vf[b % NBV], std::false_type{});
+            if (KL) {
+                __builtin_amdgcn_sched_barrier(0);  // the next step's loads first
+                take_k(b == 0 ? kw0 : kw1, kf[0]);
+            }
+            if (LATE || KL) turn(s, kf[kb]);
+            compute(s, kf[kb], vf[b % NBV], std::false_type{});
             s += W;
         };
         while (s + W < n_steps) {
@@ -614,6 +680,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
             step(1);
         }
         if (s < n_steps) {
+            if (KL) take_k(kw0, kf[0]);
             turn(s, kf[0]);
             if (NBV == 1) load_v(s, vf[0]);
             compute(s, kf[0], vf[0], std::false_type{});
@@ -637,8 +704,9 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
             for (int s = wave; s < n_steps; s += W) {
                 fetch_tok(s);
                 take_tok();
-                load_k(s, kf[0]);
+                get_k(s, 0);
                 load_v(s, vf[0]);
+                if (KL) take_k(kw0, kf[0]);
                 turn(s, kf[0]);
                 compute(s, kf[0], vf[0], std::true_type{});
             }

@@ -87,6 +87,11 @@ __device__ __forceinline__ u32x2 buf_load_8(buf_rsrc r, unsigned off) {
 }
 __device__ __forceinline__ unsigned buf_load_4(buf_rsrc r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0); }
 __device__ __forceinline__ unsigned short buf_load_2(buf_rsrc r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0); }
+// 16 bytes per lane straight into LDS: lane l's land at dst + 16*l (dst is wave-uniform).  The compiler knows these loads: it waits for
+// those into an array before it reads from that array, and for no others.
+__device__ __forceinline__ void buf_load_lds_16(buf_rsrc r, char* dst, unsigned off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)off, 0, 0, 0);
+}
 template <int CACHE = 0>
 __device__ __forceinline__ void buf_store_16(buf_rsrc r, unsigned off, u32x4 v) {
     __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, CACHE);
