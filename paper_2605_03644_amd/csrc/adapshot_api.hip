@@ -620,6 +620,7 @@ static adapshot_status run_stream(adapshot_ctx* ctx, StreamItem* items, int32_t 
         StreamItem& it = items[i];
         it.keys_per_split = (int32_t)(plan.split_tiles * 64);
         it.n_split = (int32_t)stream_splits(shapes[i], plan.split_tiles);
+        it.div_split = fast_div(it.n_split);
         const int64_t here = stream_units(d, shapes[i], sl.row_blocks);
         it.unit0 = (int32_t)unit0;
         unit0 += here;

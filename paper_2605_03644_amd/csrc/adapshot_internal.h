@@ -169,6 +169,18 @@ struct AttnParams {
     // layer, so that the tables of a batch serve every layer of a model (0 for single calls).
     int64_t layer_stride_bytes;
 };
+// Division of n in [0, 2^31) by a fixed d >= 1: with s = ceil(log2 d), n / d = n * ceil(2^(31 + s) / d) >> (31 + s), exactly, as the
+// rounded-up factor is off by less than 2^-31 of itself per unit of n.  (A division by a kernel argument is 30 dependent instructions.)
+struct FastDiv {
+    uint32_t mul;
+    int32_t shift;
+    __device__ __forceinline__ int of(int n) const { return (int)(__umulhi((unsigned)n << 1, mul) >> shift); }
+};
+inline FastDiv fast_div(int32_t d) {
+    int32_t s = 0;
+    while (((int64_t)1 << s) < d) ++s;
+    return FastDiv{(uint32_t)((((uint64_t)1 << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d), s};
+}
 // ---- streaming attention (attn_stream_kernel.h): every shape the 256-row tile kernel does not cover -------------
 struct StreamItem {
     const char* q;
@@ -181,6 +193,7 @@ struct StreamItem {
     int32_t keys_per_split, n_split;  // the last split also takes the query's own tokens
     int32_t unit0;      // first unit of the problem in the workspaces
     int32_t block0;     // its first workgroup in the launch
+    FastDiv div_split;  // by n_split
 };
 template <int NI>
 struct StreamArgs {
@@ -192,6 +205,7 @@ struct StreamArgs {
     const int32_t* slot_src;  // zero-copy form: context slot -> pool token (null: the context is an assembled cache)
     int64_t ctx_pos0;         // zero-copy form: position of context slot 0
     int32_t n_q_heads, n_kv_heads, g, max_split, pool_tokens, counter_stride;
+    FastDiv div_hkv, div_g;
     float q_scale;
     StreamItem it[NI];
 };

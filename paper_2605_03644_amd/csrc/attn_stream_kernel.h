@@ -35,13 +35,12 @@
 // address arithmetic) and the query rows are rotated once per workgroup and handed out through LDS.  A larger problem,
 // what a compute unit gets from beyond its L1 -- 54 KB/us where few of them ask, 45 in launches that fill the chip, whatever is in flight
 // (64 or 128 KB) -- which is why the loads are shared by two row blocks where there are rows enough.  Splits beyond a few dozen
-// are bound by their merge, which one compute unit does: 3 us and 19 ns per KB of partials.  One layer, call after call over contexts
+// are bound by their merge, which one compute unit does.  One layer, call after call over contexts
 // that no cache holds, addresses by lane and splits priced with a warm cache / now
-//   bf16, 28/4 heads x 128, one token over 16k slots               19.9 / 15.3 us
-//   bf16, 32/8 heads x 128, one token over 4k slots                14.3 / 10.5
-//   bf16, 28/4 heads x 128, 4 queries of 8k slots, one token each  23.0 / 19.7
-//   fp32, 8/2 heads x 128, 32 query tokens over 2k slots           18.7 / 13.7
-//   bf16, 32/8 heads x 128, 24 query tokens over 830 slots, tile kernel and its merge 15.5, here 12.1
+//   bf16, 28/4 heads x 128, one token over 16k slots               19.9 / 13.4 us
+//   bf16, 32/8 heads x 128, one token over 4k slots                14.3 / 8.8
+//   fp32, 8/2 heads x 128, 32 query tokens over 2k slots           18.7 / 11.7
+//   bf16, 32/8 heads x 128, 24 query tokens over 830 slots, tile kernel and its merge 15.5, here 8.5
 #pragma once
 #include <type_traits>
 
@@ -129,9 +128,8 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     const int n_split = it.n_split;
     const int hkv = p.n_kv_heads, g = p.g;
     const int rows = it.t_q * g;
-    const int hk = block % hkv;
-    const int rest = block / hkv;
-    const int split = rest % n_split, rt = rest / n_split;
+    const int rest = p.div_hkv.of(block), hk = block - rest * hkv;
+    const int rt = it.div_split.of(rest), split = rest - rt * n_split;
     const int row0 = rt * TR;
     if (row0 >= rows) return;
     const bool last_split = split == n_split - 1;
@@ -141,7 +139,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     int nk = it.n_ctx - k0;  // context keys of this split
     if (nk > it.keys_per_split) nk = it.keys_per_split;
     if (nk < 0) nk = 0;
-    const int j_last = ((row0 + TR < rows ? row0 + TR : rows) - 1) / g;
+    const int j_last = p.div_g.of((row0 + TR < rows ? row0 + TR : rows) - 1);
     const int n_self = last_split ? j_last + 1 : 0;  // own tokens that any row of the tile sees
     const int n_cs = (nk + SK - 1) / SK;
     const int n_steps = n_cs + (n_self + SK - 1) / SK;
@@ -378,7 +376,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         if (wave * 64 + i * T >= TR * CH) break;
         const int r = (tid + i * T) / CH < TR ? (tid + i * T) / CH : TR - 1, c = tid % CH;
         const int rc = row0 + r < rows ? row0 + r : rows - 1;
-        const int j = rc / g;
+        const int j = p.div_g.of(rc);
         const char* src = it.q + (((int64_t)j * p.n_q_heads + hk * g + (rc - j * g)) * D) * E + 16 * c;
         qa[i] = *(const u32x4*)src;
         qb[i] = *(const u32x4*)(src + 16 * CH);
@@ -451,7 +449,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
 #pragma unroll
     for (int nr = 0; nr < NR; ++nr) {
         const int row = row0 + 16 * nr + l16;
-        jrow[nr] = (row < rows ? row : rows - 1) / g;
+        jrow[nr] = p.div_g.of(row < rows ? row : rows - 1);
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
             if (KR == 4) {
@@ -485,8 +483,12 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         const bool self = s >= n_cs;
 #pragma unroll
         for (int kb = 0; kb < NK; ++kb) {
-            if (self) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16);
-            else if (POOL) rotate(k[kb], p.ctx_pos0 + k0 + SK * s + 16 * kb + l16);
+            // (blocks past the own tokens are masked, whatever they hold)
+            if (self) {
+                if (SK * (s - n_cs) + 16 * kb < n_self) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16);
+            } else if (POOL) {
+                rotate(k[kb], p.ctx_pos0 + k0 + SK * s + 16 * kb + l16);
+            }
         }
     };
 
@@ -753,7 +755,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     // partials of the unit, [split][row][column]: at most 64 splits of 32 rows of 256 columns
     const buf_rsrc parts = make_buffer(p.part_o + unit * p.max_split * (TR * D), (unsigned)(n_split * (TR * D) * 4));
     auto store_out = [&](int row, int d0, f32x4 y) __attribute__((always_inline)) {
-        const int j = row / g;
+        const int j = p.div_g.of(row);
         const int64_t e = ((int64_t)j * p.n_q_heads + hk * g + (row - j * g)) * D + d0;
         if (BF) *(uint2*)(it.out + e * 2) = make_uint2(pack2_bf16(y[0], y[1]), pack2_bf16(y[2], y[3]));
         else *(f32x4*)(it.out + e * 4) = y;
@@ -808,74 +810,70 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     __syncthreads();
     if (!last_flag) return;
 
+    // Without branches over absent splits: a taken branch to code that no wavefront of the compute unit has run yet is 70 ns, loads past
+    // the end of a buffer and weights of 0 are none.  Calls over cold contexts, with such branches / without, us: 28/4 heads, one token over 16k
+    // slots 15.1 / 13.4, 32/8 heads over 4k 9.8 / 8.8, 24 tokens over 830 9.7 / 8.5, fp32 x 128, 32 tokens over 2k 13.8 / 11.7.  (More splits in
+    // flight made it longer, not shorter: 16 or 24 of them, with branches, 1.5 and 12 % of such calls.)
     const int n_rows = rows - row0 < TR ? rows - row0 : TR;
     const int e4 = n_rows * (D / 4);  // 16-byte pieces of the output rows
-    constexpr int PB = 8;  // splits in flight per thread
-    int ng = T / e4;  // groups of threads that take the splits of a piece between them, where the pieces are few
-    const int ng_max = (n_split + PB - 1) / PB;
-    ng = ng < 1 ? 1 : ng > ng_max ? ng_max : ng;
-    const int pe = T / ng < e4 ? T / ng : e4;  // pieces of a pass
-    const int grp = tid / pe, ei = tid - grp * pe;
-    auto piece = [&](int e, int sp, f32x4& x) __attribute__((always_inline)) {
-        x = __builtin_bit_cast(f32x4, buf_load_16<kCacheDevice>(parts, (unsigned)(sp * (TR * D) + 4 * e) * 4u));
-    };
-    // weights of the splits, a wavefront per row and a lane per split: sw[s][row] = 2^(m_s - M) / L
-    f32x2 ml = {-INFINITY, 0.f};
-    if (wave < n_rows && lane < n_split) ml = stream_load2(pml + (lane * TR + wave) * 2);
-    f32x4 x[PB];
+    constexpr int PB = 8;             // splits in flight per thread, twice
+    // Threads in groups of a power of two, one for every piece of a pass; the groups take the splits between them.
+    const int lg_t = 31 - __builtin_clz(T), lg_e = e4 > 1 ? 32 - __builtin_clz(e4 - 1) : 0;
+    const int lg_pe = lg_e < lg_t - 3 ? lg_t - 3 : lg_e < lg_t ? lg_e : lg_t;
+    const int pe = 1 << lg_pe, ng = T >> lg_pe;  // pieces of a pass; at most 8 groups
+    const int grp = tid >> lg_pe, ei = tid & (pe - 1);
+    const unsigned split_bytes = TR * D * 4;
+    auto pieces = [&](int e, int s0, f32x4 (&x)[PB]) __attribute__((always_inline)) {
+        const unsigned at = e < e4 ? (unsigned)(s0 + grp) * split_bytes + 16u * (unsigned)e : 0xf0000000u;
 #pragma unroll
-    for (int b = 0; b < PB; ++b) {  // the first pieces are requested with the first (m, l)
-        const int sp = grp + b * ng;
-        x[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (grp < ng && ei < e4 && sp < n_split) piece(ei, sp, x[b]);
-    }
-    for (int row = wave; row < n_rows; row += W) {
-        if (row != wave) ml = lane < n_split ? stream_load2(pml + (lane * TR + row) * 2) : f32x2{-INFINITY, 0.f};
-        const float M = wave_max(ml[0]);
-        const float w = ml[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[0] - M);
-        const float L = wave_sum(w == 0.f ? 0.f : w * ml[1]);
-        if (lane < n_split) sw[lane][row] = w == 0.f ? 0.f : w * (1.0f / L);
+        for (int b = 0; b < PB; ++b) x[b] = __builtin_bit_cast(f32x4, buf_load_16<kCacheDevice>(parts, at + (unsigned)(b * ng) * split_bytes));
+    };
+    // weights of the splits, a wavefront per row and a lane per split: sw[s][row] = 2^(m_s - M) / L, 0 for absent splits
+    const buf_rsrc mls = make_buffer(pml, (unsigned)(n_split * (TR * 8)));
+    constexpr int WR = (TR + W - 1) / W;  // rows of a wavefront
+    u32x2 ml[WR];
+#pragma unroll
+    for (int i = 0; i < WR; ++i) ml[i] = buf_load_8<kCacheDevice>(mls, (unsigned)((lane * TR + wave + i * W) * 8));
+    f32x4 x[PB];
+    pieces(ei, 0, x);  // requested with the (m, l)
+#pragma unroll
+    for (int i = 0; i < WR; ++i) {
+        const float m = lane < n_split ? __uint_as_float(ml[i][0]) : -INFINITY;
+        const float M = wave_max(m);
+        const float w = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+        const float L = wave_sum(w == 0.f ? 0.f : w * __uint_as_float(ml[i][1]));
+        sw[lane][wave + i * W] = w == 0.f ? 0.f : w * (1.0f / L);
     }
     __syncthreads();
-    f32x4* const red = &os[0][0][0];  // [ng][pe], at most one piece per thread
+    f32x4* const red = (f32x4*)ks0;  // a piece per thread
     for (int e0 = 0; e0 < e4; e0 += pe) {
         const int e = e0 + ei;
         const int row = e / (D / 4);
+        if (e0 != 0) pieces(e, 0, x);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        if (grp < ng && e < e4) {
-            for (int s0 = grp; s0 < n_split; s0 += PB * ng) {
-                if (e0 != 0 || s0 != grp) {
+        for (int s0 = 0; s0 < n_split; s0 += PB * ng) {  // (s0 + grp + b * ng < 64: PB * ng divides it)
+            f32x4 y[PB];
+            pieces(e, s0 + PB * ng, y);
+            const float* wr = &sw[s0 + grp][row < TR ? row : 0];
 #pragma unroll
-                    for (int b = 0; b < PB; ++b) {
-                        const int sp = s0 + b * ng;
-                        if (sp < n_split) piece(e, sp, x[b]);
-                    }
-                }
+            for (int b = 0; b < PB; ++b) {
+                const float w = wr[b * ng * TR];
 #pragma unroll
-                for (int b = 0; b < PB; ++b) {
-                    const int sp = s0 + b * ng;
-                    if (sp < n_split) {
-                        const float w = sw[sp][row];
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) acc[i] += w * x[b][i];
-                    }
-                }
+                for (int i = 0; i < 4; ++i) acc[i] += w * x[b][i];
+                x[b] = y[b];
             }
-            if (ng == 1) store_out(row0 + row, 4 * (e - row * (D / 4)), acc);
-            else red[grp * pe + ei] = acc;
         }
-        if (ng == 1) continue;  // the same for every thread
-        __syncthreads();
-        if (tid < pe && e < e4) {
-            acc = red[tid];
-            for (int gidx = 1; gidx < ng; ++gidx) {
-                const f32x4 y = red[gidx * pe + tid];
+        if (ng > 1) {  // (then this is the only pass)
+            red[tid] = acc;
+            __syncthreads();
+            if (grp != 0) continue;
+            for (int k = 1; k < ng; ++k) {
+                const f32x4 z = red[tid + (k << lg_pe)];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] += y[i];
+                for (int i = 0; i < 4; ++i) acc[i] += z[i];
             }
-            store_out(row0 + row, 4 * (e - row * (D / 4)), acc);
         }
-        __syncthreads();
+        if (e < e4) store_out(row0 + row, 4 * (e - row * (D / 4)), acc);
     }
 }
 
@@ -892,6 +890,8 @@ static hipError_t launch_stream_form(const StreamLaunch& s, hipStream_t stream) 
         a.n_q_heads = s.n_q_heads;
         a.n_kv_heads = s.n_kv_heads;
         a.g = s.n_q_heads / s.n_kv_heads;
+        a.div_hkv = fast_div(s.n_kv_heads);
+        a.div_g = fast_div(a.g);
         a.max_split = s.max_split;
         a.counter_stride = s.counter_stride;
         a.pool_tokens = s.pool_tokens;

@@ -82,8 +82,9 @@ template <int CACHE = 0>
 __device__ __forceinline__ u32x4 buf_load_16(buf_rsrc r, unsigned off) {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, CACHE));
 }
+template <int CACHE = 0>
 __device__ __forceinline__ u32x2 buf_load_8(buf_rsrc r, unsigned off) {
-    return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, CACHE));
 }
 __device__ __forceinline__ unsigned buf_load_4(buf_rsrc r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0); }
 __device__ __forceinline__ unsigned short buf_load_2(buf_rsrc r, unsigned off) { return __builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0); }
