@@ -779,7 +779,25 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
             stream_tiles = std::adjacent_find(seen.begin(), seen.end()) == seen.end();
         }
     }
+    // A batch in the kernel arguments: the launches for a layer.
+    auto launch_args = [&]() -> adapshot_status {
+        BatchArgs& a = ctx->batch_args;
+        for (int32_t i = 0; i < n_items; ++i) {
+            a.it[i].k_ctx = ctx->batch_ctx[i].k0 + (int64_t)layer * ctx->batch_ctx[i].layer_stride_bytes;
+            a.it[i].v_ctx = ctx->batch_ctx[i].v0 + (int64_t)layer * ctx->batch_ctx[i].layer_stride_bytes;
+        }
+        hipError_t e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN, stream, [&] {
+            return launch_attn_mfma_batch_args(a, (int)ctx->batch_n_attn, pool != nullptr, stream_tiles, stream);
+        });
+        if (e != hipSuccess) return fail_hip(ctx, "query_attn_batched: attention launch", e);
+        e = timed_launch(ctx, ADAPSHOT_KERNEL_ATTN_COMBINE, stream, [&] {
+            return launch_attn_combine_batch_args(ctx->batch_comb, (int)ctx->batch_n_comb, ctx->batch_max_partials, stream);
+        });
+        if (e != hipSuccess) return fail_hip(ctx, "query_attn_batched: combine launch", e);
+        return ADAPSHOT_OK;
+    };
     if (!ctx->batch_key.empty() && key == ctx->batch_key) {
+        if (ctx->batch_by_args) return launch_args();
         const AttnBatchItem* dit = (const AttnBatchItem*)ctx->batch_tab.p;
         const AttnWork* daw = (const AttnWork*)((const char*)ctx->batch_tab.p + ctx->batch_attn_off);
         const CombineWork* dcw = (const CombineWork*)((const char*)ctx->batch_tab.p + ctx->batch_comb_off);
@@ -807,12 +825,12 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
                                            : plan_balanced_split_tiles(ctx->n_cu, shapes);
 
     struct Plan {
-        int64_t rows, n_row_tiles, n_split, keys_per_split;
+        int64_t rows, n_row_tiles, n_split, keys_per_split, part_row0;
         size_t po_off, pml_off;
     };
     std::vector<Plan> plan((size_t)n_items);
     size_t po_bytes = 0, pml_bytes = 0;
-    int64_t n_attn = 0, n_comb = 0;
+    int64_t n_attn = 0, n_comb = 0, part_rows = 0, max_row_tiles = 0;
     int32_t max_partials = 1;
     for (int32_t i = 0; i < n_items; ++i) {
         const adapshot_attn_item& it = items[i];
@@ -829,6 +847,9 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
             pl.n_split = (it.n_ctx + pl.keys_per_split - 1) / pl.keys_per_split;
         }
         auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
+        pl.part_row0 = part_rows;
+        part_rows += (pl.n_split + 1) * d.n_kv_heads * pl.rows;
+        max_row_tiles = std::max(max_row_tiles, pl.n_row_tiles);
         pl.po_off = po_bytes;
         po_bytes += up((size_t)(pl.n_split + 1) * d.n_kv_heads * pl.rows * d.head_dim * 2);  // fp16 rows
         pl.pml_off = pml_bytes;
@@ -843,6 +864,85 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
     // ---- workspace and tables
     hipError_t e = ctx->part_o.reserve(po_bytes, ctx->retired);
     if (e == hipSuccess) e = ctx->part_ml.reserve(pml_bytes, ctx->retired);
+    const bool by_args = n_items <= kBatchArgItems && n_attn / d.n_kv_heads <= kBatchArgWork && part_rows <= INT32_MAX &&
+                         max_row_tiles <= kBatchArgRowTiles;
+    if (by_args && e != hipSuccess) return fail_hip(ctx, "query_attn_batched: workspace", e);
+    // A workgroup's place in the dispatch order, for the n_kv_heads workgroups that differ in the kv head only: longest first.
+    // Among equal lengths, the workgroups that read the same slice of the same
+    // cache (probes over nested prefixes of one ordering share their leading splits, because the split
+    // length is common) are adjacent, kv head fastest: they start together on the XCD that serves that head
+    // and the later ones find the slice in its L2 -- the shared prefix of a probe tree is fetched once.
+    struct Key {
+        int64_t tiles;
+        int32_t cache, item, split, row_tile;
+    };
+    std::vector<Key> keys;
+    keys.reserve((size_t)(n_attn / d.n_kv_heads));
+    for (int32_t i = 0; i < n_items; ++i) {
+        const adapshot_attn_item& it = items[i];
+        const Plan& pl = plan[(size_t)i];
+        for (int64_t sp = 0; sp <= pl.n_split; ++sp) {
+            int64_t tiles;
+            if (sp == pl.n_split) tiles = (it.t_q + 63) / 64;
+            else tiles = (std::min<int64_t>(it.n_ctx, (sp + 1) * pl.keys_per_split) - sp * pl.keys_per_split + 63) / 64;
+            for (int64_t rt = 0; rt < pl.n_row_tiles; ++rt)
+                keys.push_back(Key{tiles, sp == pl.n_split ? -1 : it.cache_index, i, (int32_t)sp, (int32_t)rt});
+        }
+    }
+    std::stable_sort(keys.begin(), keys.end(), [](const Key& a, const Key& b) {
+        if (a.tiles != b.tiles) return a.tiles > b.tiles;
+        if (a.cache != b.cache) return a.cache < b.cache;
+        if (a.cache >= 0 && a.split != b.split) return a.split < b.split;
+        return false;
+    });
+    if (by_args) {
+        BatchArgs& a = ctx->batch_args;
+        CombineArgs& cb = ctx->batch_comb;
+        a.part_o = ctx->part_o.p;
+        a.part_mlf = (float4*)ctx->part_ml.p;
+        a.tab_lo = ctx->tab_lo;
+        a.tab_hi = ctx->tab_hi;
+        a.tile_rot = pool ? pool->tile_rot : nullptr;
+        a.n_q_heads = d.n_q_heads;
+        a.n_kv_heads = d.n_kv_heads;
+        a.pool_tokens = (int32_t)std::min<int64_t>(ctx->shot_offsets.empty() ? 0 : ctx->shot_offsets.back(), INT32_MAX);
+        a.q_scale = (float)(1.4426950408889634 / sqrt((double)d.head_dim));
+        a.div_hkv = fast_div(d.n_kv_heads);
+        cb.part_o = a.part_o;
+        cb.part_mlf = a.part_mlf;
+        cb.n_q_heads = d.n_q_heads;
+        cb.n_kv_heads = d.n_kv_heads;
+        int64_t block0 = 0;
+        for (int32_t i = 0; i < kBatchArgItems; ++i) {
+            if (i >= n_items) {  // (nobody's)
+                a.it[i] = BatchArgItem{};
+                cb.it[i] = {nullptr, 0, 0, 0, INT32_MAX};
+                continue;
+            }
+            const adapshot_attn_item& it = items[i];
+            const Plan& pl = plan[(size_t)i];
+            if (pool) {
+                ctx->batch_ctx[i] = {(const char*)ctx->k_pool, (const char*)ctx->v_pool, ctx->pool_layer_stride_tokens * ctx->row_bytes};
+            } else {
+                const adapshot_cache& c = caches[it.cache_index];
+                ctx->batch_ctx[i] = {(const char*)c.k, (const char*)c.v, c.capacity * ctx->row_bytes};
+            }
+            a.it[i] = BatchArgItem{it.q, it.k_self, it.v_self, nullptr, nullptr,  // (the layer's rows: at the launch)
+                                   pool ? pool->slot_src + pool->list_base[it.cache_index] : nullptr,
+                                   (int32_t)it.n_ctx, (int32_t)it.q_pos0, it.t_q, (int32_t)pl.keys_per_split, (int32_t)pl.n_split,
+                                   (int32_t)pl.part_row0};
+            cb.it[i] = {it.out, (int32_t)pl.part_row0, it.t_q, (int32_t)pl.n_split, (int32_t)block0};
+            block0 += (d.n_kv_heads * pl.rows + 15) / 16;
+        }
+        for (size_t k = 0; k < keys.size(); ++k) a.work[k] = batch_work(keys[k].item, keys[k].split, keys[k].row_tile);
+        ctx->batch_by_args = true;
+        ctx->batch_n_attn = n_attn;
+        ctx->batch_n_comb = n_comb;
+        ctx->batch_max_partials = max_partials;
+        const adapshot_status st = launch_args();
+        if (st == ADAPSHOT_OK) ctx->batch_key.swap(key);
+        return st;
+    }
     const size_t items_bytes = (size_t)n_items * sizeof(AttnBatchItem);
     const size_t attn_off = (items_bytes + 255) & ~(size_t)255;
     const size_t comb_off = (attn_off + (size_t)n_attn * sizeof(AttnWork) + 255) & ~(size_t)255;
@@ -857,13 +957,6 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
     AttnBatchItem* hit = (AttnBatchItem*)host;
     AttnWork* haw = (AttnWork*)((char*)host + attn_off);
     CombineWork* hcw = (CombineWork*)((char*)host + comb_off);
-    struct Key {
-        int64_t tiles;
-        int32_t cache;
-        AttnWork w;
-    };
-    std::vector<Key> keys;
-    keys.reserve((size_t)n_attn);
     int64_t ic = 0;
     for (int32_t i = 0; i < n_items; ++i) {
         const adapshot_attn_item& it = items[i];
@@ -902,28 +995,12 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
         b.attn.n_kv_heads = d.n_kv_heads;
         b.attn.head_dim = d.head_dim;
         b.attn.dtype = d.dtype;
-        for (int64_t sp = 0; sp <= pl.n_split; ++sp) {
-            int64_t tiles;
-            if (sp == pl.n_split) tiles = (it.t_q + 63) / 64;
-            else tiles = (std::min<int64_t>(it.n_ctx, (sp + 1) * pl.keys_per_split) - sp * pl.keys_per_split + 63) / 64;
-            for (int64_t rt = 0; rt < pl.n_row_tiles; ++rt)
-                for (int32_t hk = 0; hk < d.n_kv_heads; ++hk)
-                    keys.push_back(Key{tiles, sp == pl.n_split ? -1 : it.cache_index, AttnWork{i, hk, (int32_t)rt, (int32_t)sp}});
-        }
         const int64_t pairs = d.n_kv_heads * pl.rows;
         for (int64_t p0 = 0; p0 < pairs; p0 += 16) hcw[ic++] = CombineWork{i, (int32_t)p0};
     }
-    // Longest workgroups first.  Among equal lengths, the workgroups that read the same slice of the same
-    // cache (probes over nested prefixes of one ordering share their leading splits, because the split
-    // length is common) are adjacent, kv head fastest: they start together on the XCD that serves that head
-    // and the later ones find the slice in its L2 -- the shared prefix of a probe tree is fetched once.
-    std::stable_sort(keys.begin(), keys.end(), [](const Key& a, const Key& b) {
-        if (a.tiles != b.tiles) return a.tiles > b.tiles;
-        if (a.cache != b.cache) return a.cache < b.cache;
-        if (a.cache >= 0 && a.w.split != b.w.split) return a.w.split < b.w.split;
-        return false;
-    });
-    for (size_t k = 0; k < keys.size(); ++k) haw[k] = keys[k].w;
+    size_t at = 0;
+    for (const Key& k : keys)
+        for (int32_t hk = 0; hk < d.n_kv_heads; ++hk) haw[at++] = AttnWork{k.item, hk, k.row_tile, k.split};
 
     e = ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_copy_table(ctx->batch_tab.p, host, tab_bytes, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn_batched: table copy", e);
@@ -937,6 +1014,7 @@ static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_ca
                      [&] { return launch_attn_combine_batched(dit, dcw, (int)n_comb, max_partials, stream); });
     if (e != hipSuccess) return fail_hip(ctx, "query_attn_batched: combine launch", e);
     ctx->batch_key.swap(key);
+    ctx->batch_by_args = false;
     ctx->batch_n_attn = n_attn;
     ctx->batch_max_partials = max_partials;
     ctx->batch_n_comb = n_comb;

@@ -20,6 +20,19 @@ namespace adapshot {
 constexpr int kRopeLoBits = 6;
 constexpr int kRopeLo = 1 << kRopeLoBits;
 
+// Division of n in [0, 2^31) by a fixed d >= 1: with s = ceil(log2 d), n / d = n * ceil(2^(31 + s) / d) >> (31 + s), exactly, as the
+// rounded-up factor is off by less than 2^-31 of itself per unit of n.  (A division by a kernel argument is 30 dependent instructions.)
+struct FastDiv {
+    uint32_t mul;
+    int32_t shift;
+    __device__ __forceinline__ int of(int n) const { return (int)(__umulhi((unsigned)n << 1, mul) >> shift); }
+};
+inline FastDiv fast_div(int32_t d) {
+    int32_t s = 0;
+    while (((int64_t)1 << s) < d) ++s;
+    return FastDiv{(uint32_t)((((uint64_t)1 << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d), s};
+}
+
 // ---- assemble tiles -------------------------------------------------------------
 // One tile = up to kTileTok consecutive tokens of ONE shot: contiguous in the pool
 // and contiguous in the cache.  Angle of token tau in the tile: angle0 + tau*angle_step.
@@ -169,18 +182,6 @@ struct AttnParams {
     // layer, so that the tables of a batch serve every layer of a model (0 for single calls).
     int64_t layer_stride_bytes;
 };
-// Division of n in [0, 2^31) by a fixed d >= 1: with s = ceil(log2 d), n / d = n * ceil(2^(31 + s) / d) >> (31 + s), exactly, as the
-// rounded-up factor is off by less than 2^-31 of itself per unit of n.  (A division by a kernel argument is 30 dependent instructions.)
-struct FastDiv {
-    uint32_t mul;
-    int32_t shift;
-    __device__ __forceinline__ int of(int n) const { return (int)(__umulhi((unsigned)n << 1, mul) >> shift); }
-};
-inline FastDiv fast_div(int32_t d) {
-    int32_t s = 0;
-    while (((int64_t)1 << s) < d) ++s;
-    return FastDiv{(uint32_t)((((uint64_t)1 << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d), s};
-}
 // ---- streaming attention (attn_stream_kernel.h): every shape the 256-row tile kernel does not cover -------------
 struct StreamItem {
     const char* q;
@@ -259,6 +260,48 @@ struct AttnWork {  // one workgroup of the batched MFMA kernel
 struct CombineWork {  // one workgroup of the batched combine kernel: 16 (kv head, row) pairs from pair0 on (fp16 partials)
     int32_t item, pair0;
 };
+// A smaller batch travels in the kernel arguments, which costs neither the table copy (4.2 us) nor the wait of the kernel behind it for its
+// completion event (4.5 us): a decode step of 32 queries of 16k slots 185 -> 180 us a layer, passes of probe sweeps over one to
+// three layers 235 -> 203 and 170 -> 145.  An entry of work is an (item, split, row tile), served by n_kv_heads workgroups, the
+// kv head fastest as in the tables.  Kernel arguments end at 4 KB.
+constexpr int kBatchArgItems = 32, kBatchArgWork = 352;
+struct BatchArgItem {
+    const void* q;
+    const void* k_self;
+    const void* v_self;
+    const void* k_ctx;  // one layer of the context; zero-copy form: of the pool
+    const void* v_ctx;
+    const int32_t* slot_src;  // zero-copy form
+    int32_t n_ctx, q_pos0, t_q, keys_per_split, n_split;
+    int32_t part_row0;  // first row of the item's partials
+};
+struct BatchArgs {
+    void* part_o;      // rows of fp16 values, [item][n_split + 1][h_kv][rows]
+    float4* part_mlf;
+    const float2* tab_lo;
+    const float2* tab_hi;
+    const float2* tile_rot;
+    int32_t n_q_heads, n_kv_heads, pool_tokens;
+    float q_scale;
+    FastDiv div_hkv;
+    BatchArgItem it[kBatchArgItems];
+    uint32_t work[kBatchArgWork];
+};
+inline uint32_t batch_work(int32_t item, int32_t split, int32_t row_tile) { return (uint32_t)(item | split << 5 | row_tile << 12); }
+constexpr int32_t kBatchArgRowTiles = 1 << 20;
+static_assert(kBatchArgItems <= 32 && sizeof(BatchArgs) <= 4096, "work entries, kernel arguments");
+struct CombineArgs {
+    const void* part_o;
+    const float4* part_mlf;
+    int32_t n_q_heads, n_kv_heads;
+    struct {
+        void* out;
+        int32_t part_row0, t_q, n_split;
+        int32_t block0;  // the item's first workgroup
+    } it[kBatchArgItems];
+};
+hipError_t launch_attn_mfma_batch_args(const BatchArgs& a, int n_wgs, bool pool, bool stream_tiles, hipStream_t stream);
+hipError_t launch_attn_combine_batch_args(const CombineArgs& a, int n_wgs, int max_partials, hipStream_t stream);
 // Tables written by the host into pinned memory are brought to device memory by a kernel (a DMA copy
 // between two kernels of a stream costs more than the copy itself).  bytes is a multiple of 16.
 hipError_t launch_copy_table(void* dst, const void* src_pinned, size_t bytes, hipStream_t stream);
@@ -468,6 +511,14 @@ struct adapshot_ctx {
     // (pool_src, pool_rot) were built from: a call with the same inputs -- the next layer of the same batch --
     // reuses them instead of planning and uploading again.  Empty = nothing to reuse.
     std::vector<unsigned char> batch_key, pool_key;
+    // (a batch in the kernel arguments keeps those: the contexts' layer 0 and strides are beside them)
+    bool batch_by_args = false;
+    adapshot::BatchArgs batch_args;
+    adapshot::CombineArgs batch_comb;
+    struct {
+        const char *k0, *v0;
+        int64_t layer_stride_bytes;
+    } batch_ctx[adapshot::kBatchArgItems];
     int64_t batch_n_attn = 0, batch_n_comb = 0;
     int32_t batch_max_partials = 0;
     size_t batch_attn_off = 0, batch_comb_off = 0;

@@ -144,19 +144,18 @@ __device__ __forceinline__ void attn_combine_rows(const AttnParams& p, int64_t p
     typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
     constexpr int d = 128;
     const int g = p.n_q_heads / p.n_kv_heads;
-    const int64_t rows = (int64_t)p.t_q * g;
-    const int64_t n_pairs = rows * p.n_kv_heads;
-    const int64_t pair = pair0 + (threadIdx.x / 16);
+    const int rows = p.t_q * g, n_pairs = rows * p.n_kv_heads;  // (query rows span less than 2 GiB)
+    const int pair = (int)pair0 + (int)(threadIdx.x / 16);
     if (pair >= n_pairs) return;
     const int c = threadIdx.x % 16;
-    const int hk = (int)(pair / rows);
-    const int64_t row = pair - (int64_t)hk * rows;
-    const int j = (int)(row / g);
-    const int h = hk * g + (int)(row - (int64_t)j * g);
+    const int hk = (int)((unsigned)pair / (unsigned)rows);
+    const int row = pair - hk * rows;
+    const int j = (int)((unsigned)row / (unsigned)g);
+    const int h = hk * g + (row - j * g);
     const int ns = p.n_split + 1;
-    const int64_t split_stride = (int64_t)p.n_kv_heads * rows;  // pairs per split
+    const int64_t split_stride = n_pairs;
     const float4* mlf = p.part_mlf + pair;
-    const char* po = (const char*)p.part_o + (pair * d + 8 * c) * 2;
+    const char* po = (const char*)p.part_o + ((int64_t)pair * d + 8 * c) * 2;
 
     // One round of loads per SB splits: their (m, l, f) and their rows are requested together; the running
     // maximum M is raised afterwards and what has been accumulated is rescaled (nothing yet: factor 0).
@@ -213,6 +212,30 @@ template <int SB>
 __global__ __launch_bounds__(256) void attn_combine_batched_kernel(const AttnBatchItem* items, const CombineWork* work) {
     const CombineWork w = work[blockIdx.x];
     attn_combine_rows<SB>(items[w.item].attn, w.pair0);
+}
+
+template <int SB>
+__global__ __launch_bounds__(256) void attn_combine_args_kernel(CombineArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int start = lane < kBatchArgItems ? a.it[lane % kBatchArgItems].block0 : INT32_MAX;
+    const int item = __builtin_amdgcn_readfirstlane((int)__popcll(__builtin_amdgcn_ballot_w64(start <= (int)blockIdx.x)) - 1);
+    const auto& it = a.it[item];
+    AttnParams p;
+    p.part_o = (char*)a.part_o + (int64_t)it.part_row0 * 256;
+    p.part_mlf = const_cast<float4*>(a.part_mlf) + it.part_row0;
+    p.out = it.out;
+    p.n_split = it.n_split;
+    p.t_q = it.t_q;
+    p.n_q_heads = a.n_q_heads;
+    p.n_kv_heads = a.n_kv_heads;
+    attn_combine_rows<SB>(p, (int64_t)((int)blockIdx.x - it.block0) * 16);
+}
+
+hipError_t launch_attn_combine_batch_args(const CombineArgs& a, int n_wgs, int max_partials, hipStream_t stream) {
+    if (n_wgs <= 0) return hipSuccess;
+    if (max_partials > 8) launch_kernel(attn_combine_args_kernel<16>, dim3((unsigned)n_wgs), dim3(256), stream, a);
+    else launch_kernel(attn_combine_args_kernel<8>, dim3((unsigned)n_wgs), dim3(256), stream, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_attn_combine(const AttnParams& p, hipStream_t stream) {

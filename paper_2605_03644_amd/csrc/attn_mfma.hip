@@ -82,8 +82,28 @@ __device__ __forceinline__ T load_uniform(const T* ptr) {
     return out;
 }
 
-// WAVES wavefronts, each owning NR blocks of 32 rows for the whole key loop.  BATCHED: the workgroup takes
-// its problem and its (kv head, row tile, split) from the work list instead of the launch arguments.
+// Where a workgroup has its problem and its (kv head, row tile, split) from.
+enum AttnForm { kAttnSingle, kAttnTables, kAttnArgs };
+template <int FORM>
+struct AttnFormArgs;
+template <>
+struct AttnFormArgs<kAttnSingle> {
+    AttnParams p;
+    AttnFold f;
+    int n_row_tiles;  // per kv head
+};
+template <>
+struct AttnFormArgs<kAttnTables> {  // a batch, tables in device memory
+    const AttnBatchItem* items;
+    const AttnWork* work;
+    int layer;
+};
+template <>
+struct AttnFormArgs<kAttnArgs> {  // a batch, tables in the kernel arguments
+    BatchArgs b;
+};
+
+// WAVES wavefronts, each owning NR blocks of 32 rows for the whole key loop.
 // POOL: the zero-copy form.  The context is not an assembled cache but the pool itself, read through the
 // table slot_src (context slot -> pool token): every 64-slot tile is gathered row by row into LDS, and its
 // keys are rotated there, in place, to the positions pos0 + slot before the first product reads them
@@ -99,11 +119,8 @@ __device__ __forceinline__ T load_uniform(const T* ptr) {
 // The workgroup rotates its query rows (and the self split its keys) itself: at the headline size the rotation repeated
 // in every context split costs the kernel 1.4 us, and the launch it replaces cost the step 3 us.
 // NT: the K/V tile loads of the plain form carry the non-temporal bit (see load_lds_16).
-template <int WAVES, int NR, bool BATCHED, bool POOL, bool NT = false>
-__global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg, AttnFold f_arg,
-                                                               int n_row_tiles_arg, const AttnBatchItem* items,
-                                                               const AttnWork* work) {
-    // n_row_tiles_arg: row tiles per kv head of the single problem; for a batch, the layer to attend in
+template <int WAVES, int NR, int FORM, bool POOL, bool NT = false>
+__global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM> a) {
     constexpr int PASSES = (kTileKeys * 16) / (WAVES * 64);  // 1 KB blocks of a tile per wavefront
     static_assert(PASSES * WAVES * 64 == kTileKeys * 16, "tile must divide over the threads");
     static_assert(WAVES * NR * 32 == kAttnRowTile && NR == 1, "row tile");
@@ -134,23 +151,42 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
     AttnParams p;
     int hk, row_tile, split;
     int item = 0;
-    if (BATCHED) {
-        const AttnWork w = load_uniform(work + blockIdx.x);
+    if constexpr (FORM == kAttnTables) {
+        const AttnWork w = load_uniform(a.work + blockIdx.x);
         item = w.item;
-        p = load_uniform(&items[w.item].attn);
-        p.k_cache = (const char*)p.k_cache + (int64_t)n_row_tiles_arg * p.layer_stride_bytes;
-        p.v_cache = (const char*)p.v_cache + (int64_t)n_row_tiles_arg * p.layer_stride_bytes;
+        p = load_uniform(&a.items[w.item].attn);
+        p.k_cache = (const char*)p.k_cache + (int64_t)a.layer * p.layer_stride_bytes;
+        p.v_cache = (const char*)p.v_cache + (int64_t)a.layer * p.layer_stride_bytes;
         hk = w.hk;
         row_tile = w.row_tile;
         split = w.split;
+    } else if constexpr (FORM == kAttnArgs) {
+        const int e = a.b.div_hkv.of((int)blockIdx.x);
+        const uint32_t w = a.b.work[e];
+        hk = (int)blockIdx.x - e * a.b.n_kv_heads;
+        item = (int)(w & 31u);
+        split = (int)(w >> 5 & 127u);
+        row_tile = (int)(w >> 12);
+        const BatchArgItem& it = a.b.it[item];
+        p.k_cache = it.k_ctx;
+        p.v_cache = it.v_ctx;
+        p.v_self = it.v_self;
+        p.part_o = (char*)a.b.part_o + (int64_t)it.part_row0 * kRowBytes;
+        p.part_mlf = a.b.part_mlf + it.part_row0;
+        p.n_ctx = it.n_ctx;
+        p.keys_per_split = it.keys_per_split;
+        p.n_split = it.n_split;
+        p.t_q = it.t_q;
+        p.n_q_heads = a.b.n_q_heads;
+        p.n_kv_heads = a.b.n_kv_heads;
     } else {
         // blockIdx.x -> (kv head fastest: workgroups round-robin over the 8 XCDs, so with 8 kv heads every
         // XCD's L2 sees the K/V of one head only), row tile, split
-        p = p_arg;
+        p = a.p;
         hk = blockIdx.x % p.n_kv_heads;
         const int rest = blockIdx.x / p.n_kv_heads;
-        row_tile = rest % n_row_tiles_arg;
-        split = rest / n_row_tiles_arg;
+        row_tile = rest % a.n_row_tiles;
+        split = rest / a.n_row_tiles;
         // the self split is dispatched first: its workgroups are short, and what the grid has beyond one
         // workgroup per compute unit then starts as soon as they are done
         split = split == 0 ? p.n_split : split - 1;
@@ -158,8 +194,21 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
     const bool self = split == p.n_split;
     // the prologue-only arguments are fetched where they are used, not held through the key loop
     auto fold = [&]() __attribute__((always_inline)) -> AttnFold {
-        if (BATCHED) return load_uniform(&items[item].fold);
-        return f_arg;
+        if constexpr (FORM == kAttnTables) return load_uniform(&a.items[item].fold);
+        else if constexpr (FORM == kAttnArgs) {
+            const BatchArgItem& it = a.b.it[item];
+            AttnFold f;
+            f.q_raw = it.q;
+            f.k_self_raw = it.k_self;
+            f.tab_lo = a.b.tab_lo;
+            f.tab_hi = a.b.tab_hi;
+            f.q_pos0 = it.q_pos0;
+            f.q_scale = a.b.q_scale;
+            f.pool_tokens = a.b.pool_tokens;
+            f.slot_src = it.slot_src;
+            f.tile_rot = a.b.tile_rot;
+            return f;
+        } else return a.f;
     };
 
     const int g = p.n_q_heads / p.n_kv_heads;
@@ -821,20 +870,19 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnParams p_arg,
     }
 }
 
+constexpr int kRowBlocks = kAttnRowTile / (32 * kAttnWaves);
+
 hipError_t launch_attn_mfma(const AttnParams& p, const AttnFold& f, hipStream_t stream) {
     const int g = p.n_q_heads / p.n_kv_heads;
     const int rows = p.t_q * g;
     const int n_row_tiles = (rows + kAttnRowTile - 1) / kAttnRowTile;
     const unsigned blocks = (unsigned)(p.n_kv_heads * n_row_tiles * (p.n_split + 1));
     if (blocks == 0) return hipSuccess;
+    const AttnFormArgs<kAttnSingle> a{p, f, n_row_tiles};
     if (rows <= kAttnStreamRows)  // every tile is read by one workgroup per kv head, which has few rows to feed
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, false, true>),
-                      dim3(blocks), dim3(kAttnWaves * 64), stream, p, f, n_row_tiles, (const AttnBatchItem*)nullptr,
-                      (const AttnWork*)nullptr);
+        launch_kernel((attn_mfma_kernel<kAttnWaves, kRowBlocks, kAttnSingle, false, true>), dim3(blocks), dim3(kAttnWaves * 64), stream, a);
     else
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, false>), dim3(blocks),
-                      dim3(kAttnWaves * 64), stream, p, f, n_row_tiles, (const AttnBatchItem*)nullptr,
-                      (const AttnWork*)nullptr);
+        launch_kernel((attn_mfma_kernel<kAttnWaves, kRowBlocks, kAttnSingle, false>), dim3(blocks), dim3(kAttnWaves * 64), stream, a);
     return hipGetLastError();
 }
 
@@ -846,24 +894,28 @@ hipError_t launch_attn_mfma_pool(const AttnParams& p, const AttnFold& f, hipStre
     if (blocks == 0) return hipSuccess;
     if (!f.slot_src || !f.tile_rot || p.keys_per_split % kTileKeys != 0)
         return hipErrorInvalidValue;
-    launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), false, true>), dim3(blocks),
-                  dim3(kAttnWaves * 64), stream, p, f, n_row_tiles, (const AttnBatchItem*)nullptr, (const AttnWork*)nullptr);
+    launch_kernel((attn_mfma_kernel<kAttnWaves, kRowBlocks, kAttnSingle, true>), dim3(blocks), dim3(kAttnWaves * 64), stream,
+                  AttnFormArgs<kAttnSingle>{p, f, n_row_tiles});
+    return hipGetLastError();
+}
+
+template <int FORM>
+static hipError_t launch_batched(const AttnFormArgs<FORM>& a, int n_wgs, bool pool, bool stream_tiles, hipStream_t stream) {
+    if (n_wgs <= 0) return hipSuccess;
+    const dim3 grid((unsigned)n_wgs), block(kAttnWaves * 64);
+    if (pool) launch_kernel((attn_mfma_kernel<kAttnWaves, kRowBlocks, FORM, true>), grid, block, stream, a);
+    else if (stream_tiles) launch_kernel((attn_mfma_kernel<kAttnWaves, kRowBlocks, FORM, false, true>), grid, block, stream, a);
+    else launch_kernel((attn_mfma_kernel<kAttnWaves, kRowBlocks, FORM, false>), grid, block, stream, a);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_mfma_batched(const AttnBatchItem* items, const AttnWork* work, int n_work, bool pool,
                                     bool stream_tiles, int layer, hipStream_t stream) {
-    if (n_work <= 0) return hipSuccess;
-    if (pool)
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), true, true>), dim3((unsigned)n_work),
-                      dim3(kAttnWaves * 64), stream, AttnParams{}, AttnFold{}, layer, items, work);
-    else if (stream_tiles)
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), true, false, true>),
-                      dim3((unsigned)n_work), dim3(kAttnWaves * 64), stream, AttnParams{}, AttnFold{}, layer, items, work);
-    else
-        launch_kernel((attn_mfma_kernel<kAttnWaves, kAttnRowTile / (32 * kAttnWaves), true, false>), dim3((unsigned)n_work),
-                      dim3(kAttnWaves * 64), stream, AttnParams{}, AttnFold{}, layer, items, work);
-    return hipGetLastError();
+    return launch_batched(AttnFormArgs<kAttnTables>{items, work, layer}, n_work, pool, stream_tiles, stream);
+}
+
+hipError_t launch_attn_mfma_batch_args(const BatchArgs& b, int n_wgs, bool pool, bool stream_tiles, hipStream_t stream) {
+    return launch_batched(AttnFormArgs<kAttnArgs>{b}, n_wgs, pool, stream_tiles, stream);
 }
 
 }  // namespace adapshot
