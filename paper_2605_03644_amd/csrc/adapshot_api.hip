@@ -214,12 +214,12 @@ extern "C" adapshot_status adapshot_create(const adapshot_model_desc* desc, adap
     // RoPE tables in fp64, rounded once to fp32.
     const int half = desc->head_dim / 2;
     const int64_t n_hi = (ctx->max_position + kRopeLo - 1) / kRopeLo + 1;
-    std::vector<float2> lo((size_t)kRopeLo * half), hi((size_t)n_hi * half);
+    std::vector<float2> lo((size_t)(2 * kRopeLo) * half), hi((size_t)n_hi * half);
     std::vector<double> theta(half);
     for (int i = 0; i < half; ++i) theta[i] = pow(desc->rope_theta, -2.0 * (double)i / (double)desc->head_dim);
-    for (int r = 0; r < kRopeLo; ++r)
+    for (int r = 0; r < 2 * kRopeLo; ++r)
         for (int i = 0; i < half; ++i) {
-            double a = (double)r * theta[i];
+            double a = (r < kRopeLo ? (double)r : (double)(r - kRopeLo) + 0.5) * theta[i];
             lo[(size_t)r * half + i] = make_float2((float)cos(a), (float)sin(a));
         }
     for (int64_t r = 0; r < n_hi; ++r)

@@ -16,7 +16,8 @@ namespace adapshot {
 // Angle multiplier a (a position or a position offset) is split as a = 64*hi + lo.
 // tab_hi[hi][i] = (cos, sin)(64*hi*theta_i), tab_lo[lo][i] = (cos, sin)(lo*theta_i),
 // both evaluated in fp64 and rounded once to fp32.  cos/sin(a*theta_i) follows by one
-// angle addition in fp32 (error ~3e-7 absolute), see Eq. (rope_compensation).
+// angle addition in fp32 (error ~3e-7 absolute), see Eq. (rope_compensation).  The rows of tab_lo from kRopeLo on are those
+// of lo + 1/2, which the zero-copy attention uses: a tile of 64 keys lies symmetrically around its centre.
 constexpr int kRopeLoBits = 6;
 constexpr int kRopeLo = 1 << kRopeLoBits;
 
@@ -157,7 +158,8 @@ struct AttnFold {
     int32_t pool_tokens;  // zero-copy form: tokens in a pool layer (gathered rows are clamped to it)
     // Zero-copy form (template parameter POOL): k_cache / v_cache are the POOL's layer, context slot u holds pool
     // token slot_src[u], and its key is rotated to position pos0 + u inside the key loop;
-    // tile_rot[i][f] = (cos, sin)((pos0 + 64 i) theta_f) for every 64-slot tile of the context.  slot_src is 16-byte
+    // row i of tile_rot, 64 entries, holds (cos, sin)((pos0 + 64 i + 31.5) theta_f), the centre of 64-slot tile i, in the order
+    // of tile_rot_place().  slot_src is 16-byte
     // aligned and readable for 256 entries past the context's last slot (the kernel fetches it 1 KB at a time).
     const int32_t* slot_src;
     const float2* tile_rot;
@@ -230,7 +232,9 @@ hipError_t launch_attn_stream_f32(const StreamLaunch& s, hipStream_t stream);
 hipError_t launch_attn_stream_bf16(const StreamLaunch& s, hipStream_t stream);
 hipError_t launch_attn_mfma(const AttnParams& p, const AttnFold& f, hipStream_t stream);
 hipError_t launch_attn_mfma_pool(const AttnParams& p, const AttnFold& f, hipStream_t stream);  // zero-copy form
-// Expands the per-shot segments of a zero-copy context into slot_src and builds tile_rot.
+// Place of frequency f in a row of tile_rot: those of a lane's four, 4 c .. 4 c + 3, are 16 bytes of either half of the row.
+__device__ __forceinline__ int tile_rot_place(int f) { return ((f >> 1) & 1) * 32 + (f >> 2) * 2 + (f & 1); }
+// Expands the per-shot segments of a zero-copy context into slot_src and builds tile_rot (head_dim 128).
 struct PoolSeg {
     int32_t slot0, src_tok0, len, pad;
 };

@@ -107,8 +107,8 @@ struct AttnFormArgs<kAttnArgs> {  // a batch, tables in the kernel arguments
 // POOL: the zero-copy form.  The context is not an assembled cache but the pool itself, read through the
 // table slot_src (context slot -> pool token): every 64-slot tile is gathered row by row into LDS, and its
 // keys are rotated there, in place, to the positions pos0 + slot before the first product reads them
-// (R(a)R(b) = R(a+b): tile_rot holds (cos, sin) of the tile's first position, every thread keeps the entries of
-// the 64-row second-level table that its share of a tile needs).  The key loop is the plain form's -- four K
+// (R(a)R(b) = R(a+b): tile_rot holds (cos, sin) of the tile's centre, every thread keeps the entries of
+// the second-level table, half positions from the centre, that its share of a tile needs).  The key loop is the plain form's -- four K
 // tiles in LDS, one workgroup barrier per tile, the two wavefronts of a SIMD in rotated phase order -- with
 // three additions: K(t+1), which the pipeline has landed a tile early anyway, is rotated by all 512 threads
 // during tile t; the slot table entries and the rotation row of a tile arrive through the same direct-to-LDS
@@ -129,10 +129,10 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
     // slot-table pieces (8 x 1 KB), the ring of rotation rows (4 x 1 KB) and the threads' second-level table entries.
     constexpr int kVBuf = POOL ? 3 : kNBuf;
     constexpr int kIdxSlots = 8, kRotSlots = 4;
-    constexpr int kLoBytes = WAVES * 64 * 64;
+    constexpr int kLoBytes = WAVES * 64 * 32;
     constexpr int kPoolBytes = POOL ? (kIdxSlots + kRotSlots) * 1024 + kLoBytes : 0;
-    // The plain form adds 4 KB per wavefront through which the partial rows leave (the zero-copy form reuses its
-    // threads' table entries for that).
+    // The plain form adds 4 KB per wavefront through which the partial rows leave (the zero-copy form reuses its K ring
+    // for that).
     constexpr int kStageBytes = POOL ? 0 : WAVES * 4096;
     __shared__ __attribute__((aligned(65536))) char lds_all[(kNBuf + kVBuf) * kTileBytes + kPoolBytes + kStageBytes];
     static_assert(sizeof(lds_all) <= 160 * 1024, "LDS of a compute unit");
@@ -357,36 +357,53 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
         load_lds_16((const char*)pf.tile_rot, (unsigned)(gt * 512 + (lane & 31) * 16),
                     __builtin_amdgcn_readfirstlane(lds_addr(rot_s + (T & (kRotSlots - 1)) * 1024)));
     };
-    // rotate the keys of tile T, landed in K buffer `buf` (= T % 4), in place: thread = (row r, chunk pair cp), the
-    // same pairing as the assemble kernel; position of row r = (tile's first position) + r
+    // Rotate the keys of tile T, landed in K buffer `buf` (= T % 4), in place.  A thread has four frequencies, 4 rf .. 4 rf + 3
+    // (8 bytes of either half of a row), of two rows at the same distance b + 1/2 from the tile's centre, 31 - b and 32 + b: the
+    // cosines and sines of the sum and of the difference of two angles share their products (6 instead of 8 instructions), and two rows
+    // share the reads of both angles' entries.  With one row and eight frequencies a thread, tile angle and row angle
+    // were 128 of the 192 bytes that it moved through LDS, which the fragment reads of both products keep two thirds busy.
+    const int rf = lane & 15, rb_row = wave + 8 * (lane >> 4);
+    const unsigned rot_at = (unsigned)((31 - rb_row) * kRowBytes + (((rf >> 1) ^ ((31 - rb_row) & 15)) << 4) + ((rf & 1) << 3));
     auto pool_rotate = [&](int T, int buf) __attribute__((always_inline)) {
-        static_assert(!POOL || WAVES * 64 == kTileKeys * 8, "one (row, chunk pair) per thread");
+        static_assert(!POOL || (WAVES == 8 && kTileKeys == 64), "two rows of four frequency pairs per thread");
         if (T >= n_tiles) return;
         __builtin_amdgcn_s_setprio(0);
-        const int r = tid >> 3, cp = tid & 7;
-        const f32x4* hi = (const f32x4*)(rot_s + buf * 1024 + cp * 64);
-        u32x4* a1 = (u32x4*)(k_s[buf] + r * kRowBytes + ((cp ^ (r & 15)) << 4));
-        u32x4* a2 = (u32x4*)(k_s[buf] + r * kRowBytes + (((cp + 8) ^ (r & 15)) << 4));
-        u32x4 x1 = *a1, x2 = *a2;
+        // row 63 - r has its places 15 - (r & 15) as row r has them by r & 15, and the second half of a row is 8 chunks on
+        u32x2* const am1 = (u32x2*)(k_s[buf] + rot_at);
+        u32x2* const am2 = (u32x2*)(k_s[buf] + (rot_at ^ 128u));
+        u32x2* const ap1 = (u32x2*)(k_s[buf] + (rot_at ^ (63u * kRowBytes + 240u)));
+        u32x2* const ap2 = (u32x2*)(k_s[buf] + (rot_at ^ (63u * kRowBytes + 112u)));
+        u32x2 xm1 = *am1, xm2 = *am2, xp1 = *ap1, xp2 = *ap2;
+        auto turn = [&](unsigned& x1, unsigned& x2, float c0, float s0, float c1, float s1) __attribute__((always_inline)) {
+            const float a1l = __uint_as_float(x1 << 16), a1h = __uint_as_float(x1 & 0xffff0000u);
+            const float a2l = __uint_as_float(x2 << 16), a2h = __uint_as_float(x2 & 0xffff0000u);
+            x1 = pack2_bf16(a1l * c0 - a2l * s0, a1h * c1 - a2h * s1);
+            x2 = pack2_bf16(a2l * c0 + a1l * s0, a2h * c1 + a1h * s1);
+        };
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {  // word w holds elements 2w, 2w+1 of the chunk: frequencies 8 cp + 2w, + 2w + 1
-            const f32x4 h = hi[w], l = *(const f32x4*)(lo_s + w * (WAVES * 64 * 16) + tid * 16);
-            const float c0 = h[0] * l[0] - h[1] * l[1], s0 = h[1] * l[0] + h[0] * l[1];
-            const float c1 = h[2] * l[2] - h[3] * l[3], s1 = h[3] * l[2] + h[2] * l[3];
-            const float a1l = __uint_as_float(x1[w] << 16), a1h = __uint_as_float(x1[w] & 0xffff0000u);
-            const float a2l = __uint_as_float(x2[w] << 16), a2h = __uint_as_float(x2[w] & 0xffff0000u);
-            x1[w] = pack2_bf16(a1l * c0 - a2l * s0, a1h * c1 - a2h * s1);
-            x2[w] = pack2_bf16(a2l * c0 + a1l * s0, a2h * c1 + a1h * s1);
+        for (int w = 0; w < 2; ++w) {  // word w holds frequencies 4 rf + 2 w, + 1
+            const f32x4 h = *(const f32x4*)(rot_s + buf * 1024 + w * 256 + rf * 16);
+            const f32x4 l = *(const f32x4*)(lo_s + w * (WAVES * 64 * 16) + tid * 16);
+            const float p0 = h[0] * l[0], q0 = h[1] * l[0], p1 = h[2] * l[2], q1 = h[3] * l[2];
+            unsigned y1 = xm1[w], y2 = xm2[w], z1 = xp1[w], z2 = xp2[w];
+            turn(y1, y2, p0 + h[1] * l[1], q0 - h[0] * l[1], p1 + h[3] * l[3], q1 - h[2] * l[3]);
+            turn(z1, z2, p0 - h[1] * l[1], q0 + h[0] * l[1], p1 - h[3] * l[3], q1 + h[2] * l[3]);
+            xm1[w] = y1;
+            xm2[w] = y2;
+            xp1[w] = z1;
+            xp2[w] = z2;
         }
-        *a1 = x1;
-        *a2 = x2;
+        *am1 = xm1;
+        *am2 = xm2;
+        *ap1 = xp1;
+        *ap2 = xp2;
     };
     if (!self) {
         if (POOL) {
-            // this thread's entries of the second-level table: (cos, sin)(r theta_f), f = 8 cp .. 8 cp + 7
-            const f32x4* tl = (const f32x4*)(pf.tab_lo + (tid >> 3) * (kD / 2) + 8 * (tid & 7));
+            // this thread's entries of the second-level table: (cos, sin)((b + 1/2) theta_f), f = 4 rf .. 4 rf + 3
+            const f32x4* tl = (const f32x4*)(pf.tab_lo + (kRopeLo + rb_row) * (kD / 2) + 4 * rf);
 #pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) *(f32x4*)(lo_s + e2 * (WAVES * 64 * 16) + tid * 16) = tl[e2];
+            for (int e2 = 0; e2 < 2; ++e2) *(f32x4*)(lo_s + e2 * (WAVES * 64 * 16) + tid * 16) = tl[e2];
             // K(0), V(0), K(1); the slot-table pieces of tiles 1-4 and the rotation rows of tiles 0-2
             unsigned off[PASSES];
             pool_rows_direct(0, off);
@@ -838,11 +855,11 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
     // 8 bytes to each of 32 rows (the write-out took 3.4 of the kernel's 57 us at the headline size, 2.6 of them
     // for that); read back row-wise, an instruction writes 128 contiguous bytes of each of eight rows.  Row r of
     // the piece is 128 bytes whose 16-byte slots are permuted by (r / 2) % 8, which spreads both directions over
-    // the banks.  The plain form has the space to spare; the zero-copy form reuses the wavefront's share of the
-    // second-level table entries (four 1 KB pieces, one per plane), which the key loop is done with.
+    // the banks.  The plain form has the space to spare; the zero-copy form takes one of the 1 KB blocks of every
+    // K buffer that this wavefront alone loads: nobody reads K behind the last barrier.
     typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
     auto stage_row = [&](int r) __attribute__((always_inline)) -> char* {
-        if (POOL) return lo_s + (r >> 3) * (WAVES * 64 * 16) + wave * 1024 + (r & 7) * 128;
+        if (POOL) return k_s[r >> 3] + wave * 1024 + (r & 7) * 128;
         return lds_all + (kNBuf + kVBuf) * kTileBytes + kPoolBytes + wave * 4096 + r * 128;
     };
     const int row0 = row_tile * kAttnRowTile + wave * NR * 32;  // first row of this wavefront
