@@ -110,11 +110,10 @@ struct AttnFormArgs<kAttnArgs> {  // a batch, tables in the kernel arguments
 // (R(a)R(b) = R(a+b): tile_rot holds (cos, sin) of the tile's centre, every thread keeps the entries of
 // the second-level table, half positions from the centre, that its share of a tile needs).  The key loop is the plain form's -- four K
 // tiles in LDS, one workgroup barrier per tile, the two wavefronts of a SIMD in rotated phase order -- with
-// three additions: K(t+1), which the pipeline has landed a tile early anyway, is rotated by all 512 threads
-// during tile t; the slot table entries and the rotation row of a tile arrive through the same direct-to-LDS
+// two additions: K(t+1), which the pipeline has landed a tile early anyway, is rotated by all 512 threads
+// during tile t; and the slot table entries and the rotation row of a tile arrive through the same direct-to-LDS
 // path as the tiles (one more load per tile for wavefronts 0 and 1, which changes their wait counts, nothing
-// else); and V keeps three tiles in LDS instead of four, which pays for the tables (V(t+1) has one tile of
-// time to land instead of two).  What a context split computes is what the plain form computes over the
+// else).  What a context split computes is what the plain form computes over the
 // assembled cache.
 // The workgroup rotates its query rows (and the self split its keys) itself: at the headline size the rotation repeated
 // in every context split costs the kernel 1.4 us, and the launch it replaces cost the step 3 us.
@@ -125,20 +124,19 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
     static_assert(PASSES * WAVES * 64 == kTileKeys * 16, "tile must divide over the threads");
     static_assert(WAVES * NR * 32 == kAttnRowTile && NR == 1, "row tile");
     static_assert(!(NT && POOL), "pool tokens are shared by the lists that select them: they stay cacheable");
-    // LDS: the K ring at byte 0, the V ring at 64 KB; the zero-copy form adds, after its shorter V ring, the ring of
+    // LDS: the K ring at byte 0, the V ring at 64 KB; the zero-copy form adds, after its V ring, the ring of
     // slot-table pieces (8 x 1 KB), the ring of rotation rows (4 x 1 KB) and the threads' second-level table entries.
-    constexpr int kVBuf = POOL ? 3 : kNBuf;
     constexpr int kIdxSlots = 8, kRotSlots = 4;
     constexpr int kLoBytes = WAVES * 64 * 32;
     constexpr int kPoolBytes = POOL ? (kIdxSlots + kRotSlots) * 1024 + kLoBytes : 0;
     // The plain form adds 4 KB per wavefront through which the partial rows leave (the zero-copy form reuses its K ring
     // for that).
     constexpr int kStageBytes = POOL ? 0 : WAVES * 4096;
-    __shared__ __attribute__((aligned(65536))) char lds_all[(kNBuf + kVBuf) * kTileBytes + kPoolBytes + kStageBytes];
+    __shared__ __attribute__((aligned(65536))) char lds_all[2 * kNBuf * kTileBytes + kPoolBytes + kStageBytes];
     static_assert(sizeof(lds_all) <= 160 * 1024, "LDS of a compute unit");
     char (*const k_s)[kTileBytes] = (char (*)[kTileBytes])lds_all;
     char (*const v_s)[kTileBytes] = (char (*)[kTileBytes])(lds_all + kNBuf * kTileBytes);
-    char* const idx_s = lds_all + (kNBuf + kVBuf) * kTileBytes;
+    char* const idx_s = lds_all + 2 * kNBuf * kTileBytes;
     char* const rot_s = idx_s + kIdxSlots * 1024;
     char* const lo_s = rot_s + kRotSlots * 1024;
 
@@ -477,7 +475,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
         const int r_last = rows - 1, j_last = r_last / g;
         const int jc = valid ? j : j_last, gc = valid ? row[0] - j * g : r_last - j_last * g;
         const unsigned qoff = (unsigned)(((jc * p.n_q_heads + hk * g + gc) * kD) * 2);  // the host keeps Q below 2 GiB
-        char* const qst = wave < WAVES / 2 ? k_s[2] + wave * 8192 : v_s[kVBuf - 2] + (wave - WAVES / 2) * 8192;
+        char* const qst = wave < WAVES / 2 ? k_s[2] + wave * 8192 : v_s[2] + (wave - WAVES / 2) * 8192;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int rl = 4 * i + (lane >> 4);  // row of the wavefront that this lane fetches a piece of
@@ -533,8 +531,8 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
         const u32x4 w = *(const __attribute__((address_space(3))) u32x4*)(kp[kk] + buf * kTileBytes + kb * (32 * kRowBytes));
         return __builtin_bit_cast(bf16x8, w);
     };
-    auto v_frag = [&](int buf, int ks, int db, unsigned voff) __attribute__((always_inline)) -> bf16x8 {
-        lds_char* a = vp[db] + voff + buf * kTileBytes + ks * (16 * kRowBytes);
+    auto v_frag = [&](int buf, int ks, int db) __attribute__((always_inline)) -> bf16x8 {
+        lds_char* a = vp[db] + buf * kTileBytes + ks * (16 * kRowBytes);
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)a);
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(a + 8 * kRowBytes));
         const s16x8 av = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -576,17 +574,16 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
             if (i + kFD < 16) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
     };
-    // O^T += V^T . P^T from V buffer `buf` (plus voff bytes, the zero-copy form's run-time ring position):
-    // 16 MFMAs, 2 transposing reads per fragment
-    auto pv_phase = [&](int buf, unsigned voff = 0u) __attribute__((always_inline)) {
+    // O^T += V^T . P^T from V buffer `buf`: 16 MFMAs, 2 transposing reads per fragment
+    auto pv_phase = [&](int buf) __attribute__((always_inline)) {
         __builtin_amdgcn_s_setprio(1);
         bf16x8 fr[kFD];
 #pragma unroll
-        for (int i = 0; i < kFD; ++i) fr[i] = v_frag(buf, i / 4, i % 4, voff);
+        for (int i = 0; i < kFD; ++i) fr[i] = v_frag(buf, i / 4, i % 4);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {  // ks = i / 4, db = i % 4
             const bf16x8 a = fr[i % kFD];
-            if (i + kFD < 16) fr[i % kFD] = v_frag(buf, (i + kFD) / 4, (i + kFD) % 4, voff);
+            if (i + kFD < 16) fr[i % kFD] = v_frag(buf, (i + kFD) / 4, (i + kFD) % 4);
             o[i % 4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, pb[i / 4]), o[i % 4], 0, 0, 0);
         }
         __builtin_amdgcn_sched_group_barrier(0x100, 2 * kFD, 0);
@@ -710,38 +707,30 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
     } else if (POOL) {
         // ---- zero-copy key loop.  K(0), K(1), V(0), the table pieces and rotation rows requested so far have
         // landed (wait and barrier above).  K(0) is rotated now; the rest of the pipeline starts in the order the
-        // waits below assume: K(2), then the group V(1), K(3) and the extra load of wavefronts 0 and 1.
+        // waits below assume: V(1), K(2), then the group V(2), K(3) and the extra load of wavefronts 0 and 1.
         pool_rotate(0, 0);
-        {
-            unsigned off[PASSES];
-            pool_rows(2, off);
-            pool_gather_k(off, lds_addr(k_s[2]));
-            pool_rows(1, off);
-            pool_gather_v(off, lds_addr(v_s[1]));
-            pool_rows(3, off);
-            pool_gather_k(off, lds_addr(k_s[3]));
-            if (wave == 0) issue_idx(5);
-            if (wave == 1) issue_rot(3);
-        }
+        unsigned off[PASSES];  // of the last K tile requested: the next V tile's
+        pool_rows(1, off);
+        pool_gather_v(off, lds_addr(v_s[1]));
+        pool_rows(2, off);
+        pool_gather_k(off, lds_addr(k_s[2]));
+        pool_gather_v(off, lds_addr(v_s[2]));
+        pool_rows(3, off);
+        pool_gather_k(off, lds_addr(k_s[3]));
+        if (wave == 0) issue_idx(5);
+        if (wave == 1) issue_rot(3);
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // the rotated K(0) is visible
-        // V ring positions (bytes from V buffer 0) of V(t) and V(t-1); the third buffer holds V(t+1)
-        unsigned vo_cur = 0u, vo_prev = 2u * kTileBytes;
-        // End of tile t (b = t % 4).  Every load but the last K tile's (and the extra one behind it) has landed:
-        // V(t+1), K(t+2) with its rotation row, the table pieces up to tile t+5.  The buffers of V(t-1) and K(t)
-        // are refilled with V(t+2) and K(t+4); piece (t+6) % 8 and rotation slot (t+4) % 4 were last read tiles ago.
+        // End of tile t (b = t % 4).  Every load but the last group's -- V(t+2), K(t+3) and the extra one -- has landed:
+        // V(t+1), K(t+2) with its rotation row, the table pieces up to tile t+4.  The buffers of V(t-1) and K(t)
+        // are refilled with V(t+3) and K(t+4); piece (t+6) % 8 and rotation slot (t+4) % 4 were last read tiles ago.
         auto end_of_tile_z = [&](int t, int b) __attribute__((always_inline)) {
-            if (wave < 2) asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            unsigned off[PASSES];
-            pool_rows(t + 2, off);
-            pool_gather_v(off, lds_addr(v_s[0]) + vo_prev);
+            if (wave < 2) asm volatile("s_waitcnt vmcnt(5) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            pool_gather_v(off, lds_addr(v_s[(b + 3) & 3]));
             pool_rows(t + 4, off);
             pool_gather_k(off, lds_addr(k_s[b]));
             if (wave == 0) issue_idx(t + 6);
             if (wave == 1) issue_rot(t + 4);
-            const unsigned vo_next = 3u * kTileBytes - vo_cur - vo_prev;
-            vo_prev = vo_cur;
-            vo_cur = vo_next;
         };
         if (wave_idle) {
             for (int t = 0; t < n_tiles; ++t) {
@@ -753,7 +742,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
             auto tile_a = [&](int t, int b) __attribute__((always_inline)) {
                 s_phase(b);
                 softmax_phase(t);
-                pv_phase(0, vo_cur);
+                pv_phase(b);
                 pool_rotate(t + 1, (b + 1) & 3);
                 end_of_tile_z(t, b);
             };
@@ -768,7 +757,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
         } else {
             // order B: PV(t-1), rotate K(t+1), S(t), softmax(t)
             auto tile_b = [&](int t, int b) __attribute__((always_inline)) {
-                pv_phase(0, vo_prev);
+                pv_phase((b + 3) & 3);
                 pool_rotate(t + 1, (b + 1) & 3);
                 s_phase(b);
                 softmax_phase(t);
@@ -786,7 +775,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
                 tile_b(t + 3, 0);
             }
             for (; t < n_tiles; ++t) tile_b(t, t & 3);
-            pv_phase(0, vo_prev);
+            pv_phase((n_tiles - 1) & 3);
         }
     } else {
     issue_k(2);
@@ -860,7 +849,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_mfma_kernel(AttnFormArgs<FORM
     typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
     auto stage_row = [&](int r) __attribute__((always_inline)) -> char* {
         if (POOL) return k_s[r >> 3] + wave * 1024 + (r & 7) * 128;
-        return lds_all + (kNBuf + kVBuf) * kTileBytes + kPoolBytes + wave * 4096 + r * 128;
+        return lds_all + 2 * kNBuf * kTileBytes + kPoolBytes + wave * 4096 + r * 128;
     };
     const int row0 = row_tile * kAttnRowTile + wave * NR * 32;  // first row of this wavefront
     char* const obase = (char*)p.part_o + ((((int64_t)split * p.n_kv_heads + hk) * rows + row0) * kD) * 2;
