@@ -1,5 +1,5 @@
 // Host side of libadapshot: contexts, argument validation, the integer plan
-// (prefix sums -> tile descriptors) and kernel launches.  No device code here.
+// (prefix sums -> shot lists) and kernel launches.  No device code here.
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -192,7 +192,7 @@ extern "C" adapshot_status adapshot_create(const adapshot_model_desc* desc, adap
     ctx->row_bytes = (int64_t)desc->n_kv_heads * desc->head_dim * ctx->elem_bytes;
     ctx->max_position = desc->max_position ? desc->max_position : ((int64_t)1 << 20);
     ctx->desc.max_position = ctx->max_position;
-    // tokens of a tile per assemble workgroup: about 16 KB per layer and operand
+    // tokens per assemble workgroup: about 16 KB per layer and operand
     int wg_tok = kTileTok;
     while (wg_tok > 1 && (int64_t)wg_tok * ctx->row_bytes > 16384) wg_tok /= 2;
     ctx->assemble_wg_tok = wg_tok;
@@ -252,6 +252,7 @@ extern "C" void adapshot_destroy(adapshot_ctx* ctx) {
     (void)hipDeviceSynchronize();
     ctx->prof.release();
     ctx->tile_ring.release();
+    ctx->run_lists.release();
     ctx->q_rot.release();
     ctx->part_o.release();
     ctx->part_ml.release();
@@ -305,8 +306,8 @@ extern "C" adapshot_status adapshot_pool_register(adapshot_ctx* ctx, const void*
 // descriptor from host memory).  Many layers: the host cuts the shots into pieces of wg_tok tokens itself, one
 // workgroup per piece and layer, what is left over of a shot joined to its last piece when the two fit a tile's
 // table -- no empty workgroups and none that runs for a handful of tokens, four times the descriptors, read again by
-// every layer's workgroups (28 layers of the decode caches -5 %, 80 layers of the 70B shape -2 %, the sweep's 32
-// layers 0 to -14 % from process to process; a single layer +5 %, and its planning would overtake the GPU).
+// every layer's workgroups (8 layers of 2 caches of 200 shots, 230 MB written, 79.2 -> 74.0 us; a single layer +5 %, and its planning would
+// overtake the GPU).
 constexpr int kAssemblePieceLayers = 8;
 static inline int64_t assemble_unit(const adapshot_ctx* ctx) {
     return ctx->desc.n_layers >= kAssemblePieceLayers ? ctx->assemble_wg_tok : kTileTok;
@@ -318,10 +319,18 @@ static inline int64_t shot_tiles(int64_t len, int64_t unit) {
     return r != 0 && unit + r > kTileTok ? q + 1 : q;
 }
 
+// One assemble job of a batch.
+struct AssembleJob {
+    adapshot_cache* cache;
+    const int32_t* shot_ids;
+    const int32_t* order;
+    int32_t m;
+    int64_t total, n_runs, n_tiles;  // n_runs: shots with tokens
+};
+
 // Validation + integer plan totals of one assemble call; nothing is launched or written.
 static adapshot_status check_assemble(adapshot_ctx* ctx, const adapshot_cache* cache, const int32_t* shot_ids,
-                                      const int32_t* order, int32_t m, int64_t pos0, int64_t* total_out,
-                                      int64_t* n_tiles_out) {
+                                      const int32_t* order, int32_t m, int64_t pos0, AssembleJob* job) {
     if (!cache) return fail(ctx, ADAPSHOT_EINVAL, "assemble: null cache");
     if (m < 0) return fail(ctx, ADAPSHOT_EINVAL, "assemble: m < 0");
     if (m > 0 && !shot_ids) return fail(ctx, ADAPSHOT_EINVAL, "assemble: null shot_ids");
@@ -332,7 +341,7 @@ static adapshot_status check_assemble(adapshot_ctx* ctx, const adapshot_cache* c
     if (cache->capacity < 0 || cache->capacity > INT32_MAX || cache->len < 0 || cache->len > cache->capacity)
         return fail(ctx, ADAPSHOT_EINVAL, "assemble: bad cache capacity/len");
     if (pos0 < 0) return fail(ctx, ADAPSHOT_EINVAL, "assemble: pos0 < 0");
-    int64_t total = 0, n_tiles = 0;
+    int64_t total = 0, n_runs = 0, n_tiles = 0;
     for (int32_t j = 0; j < m; ++j) {
         int32_t oj = order ? order[j] : j;
         if (oj < 0 || oj >= m) return fail(ctx, ADAPSHOT_ESHOT, "assemble: order[%d] = %d out of range", j, oj);
@@ -340,6 +349,7 @@ static adapshot_status check_assemble(adapshot_ctx* ctx, const adapshot_cache* c
         if (s < 0 || s >= ctx->n_shots) return fail(ctx, ADAPSHOT_ESHOT, "assemble: shot id %d out of range", s);
         int64_t len = ctx->shot_offsets[s + 1] - ctx->shot_offsets[s];
         total += len;
+        n_runs += len > 0;
         n_tiles += shot_tiles(len, assemble_unit(ctx));
     }
     if (cache->len + total > cache->capacity)
@@ -349,19 +359,11 @@ static adapshot_status check_assemble(adapshot_ctx* ctx, const adapshot_cache* c
         return fail(ctx, ADAPSHOT_ECAPACITY, "assemble: position %lld exceeds max_position %lld",
                     (long long)(pos0 + cache->len + total), (long long)ctx->max_position);
     if (n_tiles > INT32_MAX) return fail(ctx, ADAPSHOT_EINVAL, "assemble: too many tiles");
-    *total_out = total;
-    *n_tiles_out = n_tiles;
+    job->total = total;
+    job->n_runs = n_runs;
+    job->n_tiles = n_tiles;
     return ADAPSHOT_OK;
 }
-
-// One validated assemble job of a batch.
-struct AssembleJob {
-    adapshot_cache* cache;
-    const int32_t* shot_ids;
-    const int32_t* order;
-    int32_t m;
-    int64_t total, n_tiles;
-};
 
 static AssembleDst assemble_dst(const adapshot_ctx* ctx, const adapshot_cache& c, int64_t pos0) {
     AssembleDst d;
@@ -375,99 +377,164 @@ static AssembleDst assemble_dst(const adapshot_ctx* ctx, const adapshot_cache& c
     return d;
 }
 
-// Plan (prefix sums -> tile descriptors) and launch of validated assemble jobs: one launch per group of
-// up to kAssembleBatch caches, the tiles of a group's caches in one descriptor list.  A group of one cache and few shots
-// needs no descriptors: its shot list is a kernel argument.
-static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_t n_jobs, int64_t pos0,
+// What a launch without tiles has of jobs whose shots go into `runs`, cache after cache: add(run, cache) takes them.
+template <typename F>
+static void plan_shots(const adapshot_ctx* ctx, const AssembleJob* jobs, int32_t n_jobs, int64_t pos0, ShotsHead& h, ShotsDst* dst, F&& add) {
+    h = ShotsHead{};
+    h.k_pool = (const char*)ctx->k_pool;
+    h.v_pool = (const char*)ctx->v_pool;
+    h.tab_lo = ctx->tab_lo;
+    h.tab_hi = ctx->tab_hi;
+    h.pool_layer_stride_bytes = ctx->pool_layer_stride_tokens * ctx->row_bytes;
+    h.n_layers = ctx->desc.n_layers;
+    h.wg_tok = ctx->assemble_wg_tok;
+    h.local = ctx->desc.key_state == ADAPSHOT_KEYS_ROTATED_LOCAL ? 1 : 0;
+    h.n_kv_heads = ctx->desc.n_kv_heads;
+    h.head_dim = ctx->desc.head_dim;
+    h.dtype = ctx->desc.dtype;
+    for (int32_t b = 0; b < n_jobs; ++b) {
+        const AssembleJob& jb = jobs[b];
+        if (jb.total == 0) continue;
+        ShotsDst& d = dst[h.n_caches];
+        (AssembleDst&)d = assemble_dst(ctx, *jb.cache, pos0);
+        d.slot0 = (int32_t)jb.cache->len;
+        d.n_tokens = (int32_t)jb.total;
+        d.run0 = h.n_runs;
+        d.n_runs = (int32_t)jb.n_runs;
+        d.block0 = h.n_blocks;
+        d.pad = 0;
+        int32_t slot = 0;  // a shot starts at the sum of the lengths before it
+        for (int32_t j = 0; j < jb.m; ++j) {
+            const int32_t s = jb.shot_ids[jb.order ? jb.order[j] : j];
+            const int32_t len = (int32_t)(ctx->shot_offsets[s + 1] - ctx->shot_offsets[s]);
+            if (len == 0) continue;
+            add(ShotRun{slot, (int32_t)ctx->shot_offsets[s], s}, h.n_caches);
+            ++h.n_runs;
+            slot += len;
+        }
+        h.n_tokens += jb.total;
+        h.n_blocks += (int32_t)((jb.total + h.wg_tok - 1) / h.wg_tok);
+        ++h.n_caches;
+    }
+}
+
+// The list in the kernel arguments.
+template <typename P>
+static hipError_t assemble_by_args(adapshot_ctx* ctx, const AssembleJob* jobs, int32_t n_jobs, int64_t pos0, hipStream_t stream) {
+    P p;
+    plan_shots(ctx, jobs, n_jobs, pos0, p.h, p.dst, [&](const ShotRun& r, int32_t) { p.shots[p.h.n_runs] = r; });
+    return timed_launch(ctx, ADAPSHOT_KERNEL_ASSEMBLE, stream, [&] { return launch_assemble_shots(p, stream); });
+}
+
+// The list by way of pinned memory: it and what is made of it in device memory belong to the call until the assembly has ended.
+static hipError_t assemble_by_list(adapshot_ctx* ctx, const AssembleJob* jobs, int32_t n_jobs, int64_t pos0, int64_t n_runs, int64_t n_blocks,
+                                   hipStream_t stream) {
+    int slot;
+    void* host;
+    hipError_t e = ctx->tile_ring.acquire((size_t)n_runs * sizeof(ListRun), &slot, &host);
+    if (e != hipSuccess) return e;
+    size_t each = std::max(ctx->run_list_bytes, (size_t)1 << 16);
+    while (each < (size_t)n_runs * sizeof(ListRun) + (size_t)n_blocks * sizeof(AssembleBlock)) each *= 2;
+    e = ctx->run_lists.reserve(PinnedRing::kSlots * each, ctx->retired);
+    if (e != hipSuccess) return e;
+    ctx->run_list_bytes = each;
+    AssembleMany p;
+    ListRun* const runs = (ListRun*)host;
+    plan_shots(ctx, jobs, n_jobs, pos0, p.h, p.dst, [&](const ShotRun& r, int32_t cache) { runs[p.h.n_runs] = ListRun{r, cache}; });
+    p.h.host_list = runs;
+    p.h.list = (ListRun*)((char*)ctx->run_lists.p + (size_t)slot * each);
+    p.h.blocks = (AssembleBlock*)(p.h.list + n_runs);
+    e = launch_assemble_list(p, stream);
+    if (e != hipSuccess) return e;
+    e = timed_launch(ctx, ADAPSHOT_KERNEL_ASSEMBLE, stream,
+                     [&] { return ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_assemble_shots(p, stream); }); });
+    // (nothing behind the list's kernel: the slot is free when that has ended)
+    if (e != hipSuccess) (void)ctx->tile_ring.launch_reader(slot, stream, [] { return hipSuccess; });
+    return e;
+}
+
+// Up to kAssembleBatch jobs by tiles, whose descriptors the kernel reads in pinned memory.
+static hipError_t assemble_by_tiles(adapshot_ctx* ctx, const AssembleJob* jobs, int32_t n_jobs, int64_t pos0, int64_t n_tiles,
                                     hipStream_t stream) {
     const bool local = ctx->desc.key_state == ADAPSHOT_KEYS_ROTATED_LOCAL;
+    int slot;
+    void* host;
+    const hipError_t e = ctx->tile_ring.acquire((size_t)n_tiles * sizeof(TileDesc), &slot, &host);
+    if (e != hipSuccess) return e;
+    TileDesc* tiles = (TileDesc*)host;
+    AssembleParams p;
+    const int64_t unit = assemble_unit(ctx);
+    int64_t nt = 0;
+    for (int32_t b = 0; b < n_jobs; ++b) {
+        const AssembleJob& jb = jobs[b];
+        p.dst[b] = assemble_dst(ctx, *jb.cache, pos0);
+        // slot group j starts at off_j = sum of the lengths before it
+        int64_t slot0 = jb.cache->len;
+        for (int32_t j = 0; j < jb.m; ++j) {
+            const int32_t s = jb.shot_ids[jb.order ? jb.order[j] : j];
+            const int64_t src = ctx->shot_offsets[s], len = ctx->shot_offsets[s + 1] - src;
+            const int64_t n_here = shot_tiles(len, unit);
+            for (int64_t i = 0, t0 = 0; i < n_here; ++i, t0 += unit) {
+                TileDesc& d = tiles[nt++];
+                d.src_tok = (int32_t)(src + t0);
+                d.dst_slot = (int32_t)(slot0 + t0);
+                d.angle0 = (int32_t)(local ? pos0 + slot0 : pos0 + slot0 + t0);
+                d.angle_step = local ? 0 : 1;
+                d.n_tok = (int32_t)(i + 1 == n_here ? len - t0 : unit);  // the last tile takes what is left
+                d.shot = s;
+                d.tok0 = (int32_t)t0;
+                d.cache = b;
+            }
+            slot0 += len;
+        }
+    }
+    for (int32_t i = n_jobs; i < kAssembleBatch; ++i) p.dst[i] = AssembleDst{};
+    p.k_pool = (const char*)ctx->k_pool;
+    p.v_pool = (const char*)ctx->v_pool;
+    p.tiles = tiles;
+    p.tab_lo = ctx->tab_lo;
+    p.tab_hi = ctx->tab_hi;
+    p.pool_layer_stride_bytes = ctx->pool_layer_stride_tokens * ctx->row_bytes;
+    p.n_tiles = (int32_t)nt;
+    p.n_layers = ctx->desc.n_layers;
+    p.n_dst = n_jobs;
+    p.wg_tok = unit == kTileTok ? ctx->assemble_wg_tok : kTileTok;  // pieces cut by the host: one workgroup each
+    p.n_kv_heads = ctx->desc.n_kv_heads;
+    p.head_dim = ctx->desc.head_dim;
+    p.dtype = ctx->desc.dtype;
+    return timed_launch(ctx, ADAPSHOT_KERNEL_ASSEMBLE, stream, [&] {
+        return ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_assemble(p, stream); });
+    });
+}
+
+// Plan (prefix sums) and launch of validated assemble jobs, up to kAssembleBatch caches a launch.  Lists that fit the kernel arguments
+// go there: no pinned buffer, no event, no other kernel (2 caches of 16 shots 11.9 -> 11.2 us, 4 of 64 short ones 19.4 -> 14.8).  A longer
+// one goes through device memory where the launch writes more than the last-level cache holds, else as tiles: the kernel ahead of the
+// launch costs 4 us, and what it saves grows with the bytes.  MB written, by tiles / by list, us: one layer 171 57.6 / 61.6, 217 71.9
+// / 74.9, 341 130.2 / 129.0, 549 207 / 200, 1759 732 / 630; two layers 108 42.0 / 44.2, 269 104.7 / 105.2, 407 156 / 153, 1066 396 / 376;
+// 8 layers 2113 770 / 751, 28 layers 7441 2708 / 2618.  (Lists cut into launches with arguments: each costs 4.5 us.)
+static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_t n_jobs, int64_t pos0,
+                                    hipStream_t stream) {
     for (int32_t j0 = 0; j0 < n_jobs; j0 += kAssembleBatch) {
-        const int32_t j1 = std::min<int32_t>(n_jobs, j0 + kAssembleBatch);
-        int64_t group_tiles = 0;
-        for (int32_t b = j0; b < j1; ++b) group_tiles += jobs[b].n_tiles;
-        if (group_tiles == 0) continue;
-        if (j1 - j0 == 1 && jobs[j0].m <= kAssembleShots) {
-            const AssembleJob& jb = jobs[j0];
-            AssembleShotsParams p;
-            p.k_pool = (const char*)ctx->k_pool;
-            p.v_pool = (const char*)ctx->v_pool;
-            p.tab_lo = ctx->tab_lo;
-            p.tab_hi = ctx->tab_hi;
-            p.pool_layer_stride_bytes = ctx->pool_layer_stride_tokens * ctx->row_bytes;
-            p.dst = assemble_dst(ctx, *jb.cache, pos0);
-            p.slot0 = (int32_t)jb.cache->len;
-            p.n_tokens = (int32_t)jb.total;
-            p.n_shots = jb.m;
-            p.n_layers = ctx->desc.n_layers;
-            p.wg_tok = ctx->assemble_wg_tok;
-            p.local = local ? 1 : 0;
-            p.n_kv_heads = ctx->desc.n_kv_heads;
-            p.head_dim = ctx->desc.head_dim;
-            p.dtype = ctx->desc.dtype;
-            int32_t slot = 0;
-            for (int32_t j = 0; j < jb.m; ++j) {
-                const int32_t s = jb.shot_ids[jb.order ? jb.order[j] : j];
-                p.shots[j] = ShotRun{slot, (int32_t)ctx->shot_offsets[s], s};
-                slot += (int32_t)(ctx->shot_offsets[s + 1] - ctx->shot_offsets[s]);
-            }
-            const hipError_t e = timed_launch(ctx, ADAPSHOT_KERNEL_ASSEMBLE, stream, [&] { return launch_assemble_shots(p, stream); });
-            if (e != hipSuccess) return fail_hip(ctx, "assemble: launch", e);
-            jb.cache->len += jb.total;
-            continue;
+        const int32_t n = std::min<int32_t>(n_jobs - j0, kAssembleBatch);
+        int64_t n_caches = 0, n_tok = 0, n_runs = 0, n_tiles = 0, n_blocks = 0;
+        for (int32_t b = j0; b < j0 + n; ++b) {
+            n_caches += jobs[b].total > 0;
+            n_tok += jobs[b].total;
+            n_runs += jobs[b].n_runs;
+            n_tiles += jobs[b].n_tiles;
+            n_blocks += (jobs[b].total + ctx->assemble_wg_tok - 1) / ctx->assemble_wg_tok;
         }
-        if (group_tiles > INT32_MAX / kTileTok) return fail(ctx, ADAPSHOT_EINVAL, "assemble: too many tiles");
-        int slot;
-        void* host;
-        hipError_t e = ctx->tile_ring.acquire((size_t)group_tiles * sizeof(TileDesc), &slot, &host);
-        if (e != hipSuccess) return fail_hip(ctx, "assemble: pinned tile buffer", e);
-        TileDesc* tiles = (TileDesc*)host;
-        AssembleParams p;
-        const int64_t unit = assemble_unit(ctx);
-        int64_t nt = 0, n_tok_group = 0;
-        for (int32_t b = j0; b < j1; ++b) {
-            const AssembleJob& jb = jobs[b];
-            p.dst[b - j0] = assemble_dst(ctx, *jb.cache, pos0);
-            // slot group j starts at off_j = sum of the lengths before it
-            int64_t slot0 = jb.cache->len;
-            for (int32_t j = 0; j < jb.m; ++j) {
-                const int32_t s = jb.shot_ids[jb.order ? jb.order[j] : j];
-                const int64_t src = ctx->shot_offsets[s], len = ctx->shot_offsets[s + 1] - src;
-                const int64_t n_here = shot_tiles(len, unit);
-                for (int64_t i = 0, t0 = 0; i < n_here; ++i, t0 += unit) {
-                    TileDesc& d = tiles[nt++];
-                    d.src_tok = (int32_t)(src + t0);
-                    d.dst_slot = (int32_t)(slot0 + t0);
-                    d.angle0 = (int32_t)(local ? pos0 + slot0 : pos0 + slot0 + t0);
-                    d.angle_step = local ? 0 : 1;
-                    d.n_tok = (int32_t)(i + 1 == n_here ? len - t0 : unit);  // the last tile takes what is left
-                    d.shot = s;
-                    d.tok0 = (int32_t)t0;
-                    d.cache = b - j0;
-                }
-                slot0 += len;
-                n_tok_group += len;
-            }
-        }
-        for (int32_t i = j1 - j0; i < kAssembleBatch; ++i) p.dst[i] = AssembleDst{};
-        p.k_pool = (const char*)ctx->k_pool;
-        p.v_pool = (const char*)ctx->v_pool;
-        p.tiles = tiles;
-        p.tab_lo = ctx->tab_lo;
-        p.tab_hi = ctx->tab_hi;
-        p.pool_layer_stride_bytes = ctx->pool_layer_stride_tokens * ctx->row_bytes;
-        p.n_tiles = (int32_t)nt;
-        p.n_tokens = n_tok_group;
-        p.n_layers = ctx->desc.n_layers;
-        p.n_dst = j1 - j0;
-        p.wg_tok = unit == kTileTok ? ctx->assemble_wg_tok : kTileTok;  // pieces cut by the host: one workgroup each
-        p.n_kv_heads = ctx->desc.n_kv_heads;
-        p.head_dim = ctx->desc.head_dim;
-        p.dtype = ctx->desc.dtype;
-        e = timed_launch(ctx, ADAPSHOT_KERNEL_ASSEMBLE, stream, [&] {
-            return ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_assemble(p, stream); });
-        });
+        if (n_tok == 0) continue;
+        if (n_tiles > INT32_MAX / kTileTok) return fail(ctx, ADAPSHOT_EINVAL, "assemble: too many tiles");
+        const int64_t written = 2 * n_tok * ctx->row_bytes * ctx->desc.n_layers;
+        hipError_t e;
+        if (n_caches == 1 && n_runs <= kAssembleShots) e = assemble_by_args<AssembleOne>(ctx, jobs + j0, n, pos0, stream);
+        else if (n_caches <= kAssembleFewCaches && n_runs <= kAssembleFewShots) e = assemble_by_args<AssembleFew>(ctx, jobs + j0, n, pos0, stream);
+        else if (written > kAssembleStreamBytes) e = assemble_by_list(ctx, jobs + j0, n, pos0, n_runs, n_blocks, stream);
+        else e = assemble_by_tiles(ctx, jobs + j0, n, pos0, n_tiles, stream);
         if (e != hipSuccess) return fail_hip(ctx, "assemble: launch", e);
-        for (int32_t b = j0; b < j1; ++b) jobs[b].cache->len += jobs[b].total;
+        for (int32_t b = j0; b < j0 + n; ++b) jobs[b].cache->len += jobs[b].total;
     }
     return ADAPSHOT_OK;
 }
@@ -475,8 +542,8 @@ static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_
 extern "C" adapshot_status adapshot_assemble(adapshot_ctx* ctx, adapshot_cache* cache, const int32_t* shot_ids,
                                              const int32_t* order, int32_t m, int64_t pos0, void* hip_stream) {
     if (!ctx) return ADAPSHOT_EINVAL;
-    AssembleJob job{cache, shot_ids, order, m, 0, 0};
-    adapshot_status st = check_assemble(ctx, cache, shot_ids, order, m, pos0, &job.total, &job.n_tiles);
+    AssembleJob job{cache, shot_ids, order, m, 0, 0, 0};
+    adapshot_status st = check_assemble(ctx, cache, shot_ids, order, m, pos0, &job);
     if (st != ADAPSHOT_OK) return st;
     st = run_assemble(ctx, &job, 1, pos0, (hipStream_t)hip_stream);
     if (st == ADAPSHOT_OK) ctx->last_error.clear();
@@ -494,9 +561,8 @@ extern "C" adapshot_status adapshot_assemble_batched(adapshot_ctx* ctx, adapshot
         for (int32_t c = 0; c < b; ++c)
             if (caches[c].k == caches[b].k || caches[c].v == caches[b].v)
                 return fail(ctx, ADAPSHOT_EINVAL, "assemble_batched: caches %d and %d share a buffer", c, b);
-        jobs[(size_t)b] = AssembleJob{&caches[b], shot_ids[b], orders ? orders[b] : nullptr, m[b], 0, 0};
-        adapshot_status st = check_assemble(ctx, &caches[b], shot_ids[b], orders ? orders[b] : nullptr, m[b], pos0,
-                                            &jobs[(size_t)b].total, &jobs[(size_t)b].n_tiles);
+        jobs[(size_t)b] = AssembleJob{&caches[b], shot_ids[b], orders ? orders[b] : nullptr, m[b], 0, 0, 0};
+        adapshot_status st = check_assemble(ctx, &caches[b], shot_ids[b], orders ? orders[b] : nullptr, m[b], pos0, &jobs[(size_t)b]);
         if (st != ADAPSHOT_OK) return st;
     }
     adapshot_status st = run_assemble(ctx, jobs.data(), n_caches, pos0, (hipStream_t)hip_stream);

@@ -34,7 +34,7 @@ inline FastDiv fast_div(int32_t d) {
     return FastDiv{(uint32_t)((((uint64_t)1 << (31 + s)) + (uint64_t)d - 1) / (uint64_t)d), s};
 }
 
-// ---- assemble tiles -------------------------------------------------------------
+// ---- assemble -------------------------------------------------------------------
 // One tile = up to kTileTok consecutive tokens of ONE shot: contiguous in the pool
 // and contiguous in the cache.  Angle of token tau in the tile: angle0 + tau*angle_step.
 // A launch serves up to kAssembleBatch caches: a tile names its cache, and the caches'
@@ -70,7 +70,6 @@ struct AssembleParams {
     const float2* tab_lo;
     const float2* tab_hi;
     int64_t pool_layer_stride_bytes;
-    int64_t n_tokens;      // tokens of all tiles together
     int32_t n_tiles;
     int32_t n_layers;
     int32_t n_dst;         // caches of this launch (entries of dst in use)
@@ -83,30 +82,68 @@ struct AssembleParams {
 };
 hipError_t launch_assemble(const AssembleParams& p, hipStream_t stream);
 
-// The same for one cache and up to kAssembleShots shots, whose list travels in the kernel arguments: workgroups are cut by
-// cache slots, wg_tok consecutive ones each, and look their shots up in the list.
-constexpr int kAssembleShots = 320;
+// Launches that write more than the last-level cache holds: non-temporal stores, and lists of any length by blocks instead of tiles.
+constexpr int64_t kAssembleStreamBytes = 256ll << 20;
+// Without tiles: workgroups are cut by cache slots, wg_tok consecutive ones each, cache after cache, and look their shots up.
 struct ShotRun {
-    int32_t slot;     // first slot of the shot, counted from the call's first slot; not decreasing
-    int32_t src_tok;  // its first pool token
+    int32_t slot;     // first slot of the shot, counted from the call's first slot in this cache; increasing, the first one 0
+    int32_t src_tok;  // its first pool token (index inside a layer)
     int32_t shot;     // pool shot id
 };
-struct AssembleShotsParams {
+struct ShotsDst : AssembleDst {
+    int32_t slot0;         // first slot of the call
+    int32_t n_tokens;      // > 0
+    int32_t run0, n_runs;  // its part of the list
+    int32_t block0;        // its first workgroup of the launch, of every layer
+    int32_t pad;
+};
+// A launch whose list does not fit the kernel arguments finds both in device memory, written by a kernel ahead of it: the runs, and for
+// every workgroup what it would look up.
+struct AssembleBlock {
+    int32_t src_tok;  // pool token of its first slot
+    int32_t run;      // the run of that slot
+    int32_t skip;     // slots of the run before it
+    int32_t what;     // cache | kBlockOneRun: all its slots are the run's
+};
+constexpr int32_t kBlockOneRun = 1 << 8;
+struct ListRun {
+    ShotRun run;
+    int32_t cache;
+};
+struct ShotsHead {
     const char* k_pool;
     const char* v_pool;
     const float2* tab_lo;
     const float2* tab_hi;
     int64_t pool_layer_stride_bytes;
-    AssembleDst dst;
-    int32_t slot0;    // first slot of the call
-    int32_t n_tokens, n_shots, n_layers;
-    int32_t wg_tok;   // a power of two <= kTileTok
-    int32_t local;    // 1: keys rotated at local positions (angle = position of the shot's first slot), 0: un-rotated (angle = position)
+    const ListRun* host_list;  // pinned host memory, read by the kernel that writes the next two
+    ListRun* list;             // device memory
+    AssembleBlock* blocks;
+    int64_t n_tokens;     // of all caches together
+    int32_t n_caches, n_layers, n_blocks, n_runs;
+    int32_t wg_tok;  // slots of a workgroup: a power of two <= kTileTok
+    int32_t local;   // 1: keys rotated at local positions (angle = position of the shot's first slot), 0: un-rotated (angle = position)
     int32_t n_kv_heads, head_dim, dtype;
-    ShotRun shots[kAssembleShots];
 };
-static_assert(sizeof(AssembleShotsParams) <= 4096, "kernel arguments");
-hipError_t launch_assemble_shots(const AssembleShotsParams& p, hipStream_t stream);
+// Kernel arguments end at 4 KB: one cache and a list of kAssembleShots, kAssembleFewCaches and kAssembleFewShots in all, or
+// kAssembleBatch caches and the list in device memory (NS = 0).
+constexpr int kAssembleShots = 320;
+constexpr int kAssembleFewCaches = 8, kAssembleFewShots = 272;
+static_assert(kAssembleBatch <= kBlockOneRun, "a block's cache");
+template <int NC, int NS>
+struct AssembleShotsParams {
+    ShotsHead h;
+    ShotsDst dst[NC];
+    ShotRun shots[NS > 0 ? NS : 1];
+};
+typedef AssembleShotsParams<1, kAssembleShots> AssembleOne;
+typedef AssembleShotsParams<kAssembleFewCaches, kAssembleFewShots> AssembleFew;
+typedef AssembleShotsParams<kAssembleBatch, 0> AssembleMany;
+static_assert(sizeof(AssembleOne) <= 4096 && sizeof(AssembleFew) <= 4096 && sizeof(AssembleMany) <= 4096, "kernel arguments");
+hipError_t launch_assemble_shots(const AssembleOne& p, hipStream_t stream);
+hipError_t launch_assemble_shots(const AssembleFew& p, hipStream_t stream);
+hipError_t launch_assemble_shots(const AssembleMany& p, hipStream_t stream);
+hipError_t launch_assemble_list(const AssembleMany& p, hipStream_t stream);  // ahead of the last one: list and blocks from host_list
 
 // One decode step: cache i of this launch receives token row [layer][first + i] of k_new / v_new at
 // slot[i], the key rotated to pos[i].  Pointer tables travel in the kernel arguments.
@@ -510,6 +547,8 @@ struct adapshot_ctx {
     float* static_ent = nullptr;  // this device's copy of the static entropy scratch array (not owned)
     // scratch
     adapshot::PinnedRing tile_ring;
+    adapshot::DevBuf run_lists;  // shot lists of assemble calls, run_list_bytes for every slot of tile_ring
+    size_t run_list_bytes = 0;
     adapshot::DevBuf q_rot, part_o, part_ml, ent_part, batch_tab, pool_src, pool_rot;
     // What the device-side tables of the last batched attention call (batch_tab) and of the last zero-copy plan
     // (pool_src, pool_rot) were built from: a call with the same inputs -- the next layer of the same batch --

@@ -7,6 +7,7 @@
 // the kernel reads one K row and one V row and writes one of each.
 //
 //   blockIdx.x = (tile, part of the tile), blockIdx.y = layer, blockIdx.z = 0: K, 1: V.
+// Without tiles (assemble_shots_kernel) the workgroups are cut by cache slots, whatever shots these belong to: none is empty or ragged.
 // One layer per workgroup, layer slowest in the dispatch order: the workgroups in flight then work on one or two
 // layers, i.e. on two narrow address windows, instead of walking all layers each at its own pace (a multi-layer
 // gather copy of the same blocks: 5.47 TB/s against 5.10 TB/s; this kernel on 28..32 layers: +1.5 .. +6 %).
@@ -29,8 +30,6 @@ namespace adapshot {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int64_t kAssembleStreamBytes = 256ll << 20;  // launches that write more than this use non-temporal stores
 
 __device__ __forceinline__ u32x4 ld16(const char* p) { return __builtin_nontemporal_load((const u32x4*)p); }
 // Plain stores when what the launch writes fits the 256 MB last-level cache (attention reads the cache next, and
@@ -205,7 +204,7 @@ __device__ __forceinline__ void rotate_k(const char* pool, const Rows& rows, cha
     }
 }
 
-template <int DTYPE, int CH, bool NT>
+template <int DTYPE, int CH>
 __global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p) {
     constexpr int HALF = CH * (DTYPE == ADAPSHOT_BF16 ? 8 : 4);
     __shared__ float2 cs[kTileTok * HALF];
@@ -225,7 +224,7 @@ __global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p
     const int64_t pool_off = (int64_t)blockIdx.y * p.pool_layer_stride_bytes;
 
     if (blockIdx.z == 1) {
-        copy_v<NT>(p.v_pool + pool_off, rows, dc.v_out + dst_off, n_tok, row_bytes);
+        copy_v<false>(p.v_pool + pool_off, rows, dc.v_out + dst_off, n_tok, row_bytes);
         return;
     }
     if (blockIdx.y == 0 && tid < n_tok) {
@@ -234,61 +233,101 @@ __global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p
         if (dc.slot_tok) dc.slot_tok[slot] = td.tok0 + t_first + tid;
         if (dc.slot_pos) dc.slot_pos[slot] = dc.pos0 + slot;
     }
-    rotate_k<DTYPE, CH, NT>(p.k_pool + pool_off, rows, dc.k_out + dst_off, n_tok, p.n_kv_heads, p.tab_lo, p.tab_hi, cs,
-                            [&](int tau) __attribute__((always_inline)) { return td.angle0 + (t_first + tau) * td.angle_step; });
+    rotate_k<DTYPE, CH, false>(p.k_pool + pool_off, rows, dc.k_out + dst_off, n_tok, p.n_kv_heads, p.tab_lo, p.tab_hi, cs,
+                               [&](int tau) __attribute__((always_inline)) { return td.angle0 + (t_first + tau) * td.angle_step; });
 }
 
-// One cache, the shot list in the kernel arguments (a read there takes 0.25 us, one of a descriptor in host memory 1.3 to 1.8
-// us, and 4.5 once thousands of workgroups ask), and workgroups cut by cache slots: none of them is empty or ragged.  Every
-// wavefront finds the shots of its workgroup's first and last slot by itself: the list's starts a lane each, and the
-// number of starts at or before a slot from ballots.  Where the two differ (one in ten at 100 tokens a shot and 8 a
-// workgroup) the rows are looked up one by one.  Bound by the launch and three round trips below 1000 tokens, by the copy's
-// rate from 10000 on.  Descriptors / this list, kernel (call after call, with the event that guards the descriptors), us:
-//   fp32 4/2 x 64, 225 tokens 4.2 / 4.1 (7.5 / 6.0)              bf16 32/8 x 128, 644 tokens 4.8 / 4.3 (8.0 / 5.5)
-//   the same, 3.2k tokens 8.0 / 6.4 (10.4 / 6.6)                 32/8 x 64, 2 layers of 6.5k 15.0 / 12.3 (18.4 / 13.0)
-//   32/8 x 128, 25.5k tokens 36.4 / 35.8 (41.1 / 36.9)           28 layers of 26.5k 1088 / 1041 (5.6 / 5.8 TB/s)
-template <int DTYPE, int CH, bool NT>
-__global__ __launch_bounds__(256) void assemble_shots_kernel(AssembleShotsParams p) {
+// Ahead of a launch whose list is in pinned host memory: 16 lanes bring a run to device memory and write the blocks whose first slot
+// lies in it.  (With the runs alone and the look-up, by probes of every 64th part of the list, in every workgroup: 8 layers of 127k tokens 669 us, tiles
+// 657, this 2 % less than tiles.)  4 us, two round trips to host memory.
+__global__ __launch_bounds__(256) void assemble_list_kernel(AssembleMany p) {
+    const int i = (int)blockIdx.x * 16 + ((int)threadIdx.x >> 4), l16 = (int)threadIdx.x & 15;
+    if (i >= p.h.n_runs) return;
+    const ListRun r = p.h.host_list[i];
+    const ShotsDst& dst = p.dst[r.cache];
+    const bool last = i + 1 == dst.run0 + dst.n_runs;
+    const int end = last ? dst.n_tokens : p.h.host_list[i + 1 < p.h.n_runs ? i + 1 : i].run.slot;
+    if (l16 == 0) p.h.list[i] = r;
+    const int wt = p.h.wg_tok;
+    for (int64_t b = (r.run.slot + (int64_t)wt - 1) / wt + l16; b * wt < end; b += 16) {
+        const int s0 = (int)b * wt, s1 = s0 + wt < dst.n_tokens ? s0 + wt : dst.n_tokens;
+        p.h.blocks[dst.block0 + b] = AssembleBlock{r.run.src_tok + s0 - r.run.slot, i, s0 - r.run.slot, r.cache | (s1 <= end ? kBlockOneRun : 0)};
+    }
+}
+
+// NC caches; NS > 0: the shot list is a kernel argument (a read there takes 0.25 us, and no other kernel or event goes with the call),
+// and every wavefront finds the shots of its workgroup's first and last slot by itself, the list's starts a lane each and the number of
+// starts at or before a slot from ballots; NS = 0: what the kernel above wrote.  Where the two differ (one workgroup in ten at 100
+// tokens a shot and 8 a workgroup) the rows are looked up one by one.
+// Bound by the launch and three round trips below 1000 tokens, by the copy's rate from 10000 on.  Tiles / list in the arguments, call
+// after call with the event that guards the tiles, us: fp32 4/2 x 64, 225 tokens 7.5 / 6.0; bf16 32/8 x 128, 644 tokens 8.0 / 5.5,
+// 3.2k 10.4 / 6.6, 25.5k 41.1 / 36.9; 32/8 x 64, 2 layers of 6.5k 18.4 / 13.0; 4 caches of 64 shots, 8k tokens 19.4 / 14.8; 28 layers of
+// 26.5k 5.6 / 5.8 TB/s.  Tiles / list in device memory, kernel alone: 8 caches of 53k tokens, two layers 1346 / 1190 (5.2 / 5.9
+// TB/s), 127k tokens, two layers 405 / 367.
+template <int DTYPE, int CH, bool NT, int NC, int NS>
+__global__ __launch_bounds__(256) void assemble_shots_kernel(AssembleShotsParams<NC, NS> p) {
     constexpr int HALF = CH * (DTYPE == ADAPSHOT_BF16 ? 8 : 4);
     __shared__ float2 cs[kTileTok * HALF];
     __shared__ int32_t row_tok[kTileTok], row_angle[kTileTok];
 
+    const ShotsHead& h = p.h;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int s0 = (int)blockIdx.x * p.wg_tok;  // this workgroup's slots, counted from the call's first: s0 .. s0 + n_tok - 1
-    const int n_tok = p.n_tokens - s0 < p.wg_tok ? p.n_tokens - s0 : p.wg_tok;
-    int i0 = -1, i1 = -1;  // shots of the first and the last slot: one less than the number of starts at or before it
-    for (int b = 0; b < p.n_shots; b += 64) {
-        const int start = b + lane < p.n_shots ? p.shots[b + lane].slot : INT32_MAX;
-        const int n0 = (int)__popcll(__builtin_amdgcn_ballot_w64(start <= s0));
-        const int n1 = (int)__popcll(__builtin_amdgcn_ballot_w64(start <= s0 + n_tok - 1));
-        i0 += n0;
-        i1 += n1;
-        if (n1 < 64) break;  // starts do not decrease
+    AssembleBlock block = {};
+    int cache = 0;
+    if (NS == 0) {
+        block = h.blocks[blockIdx.x];
+        cache = block.what & (kBlockOneRun - 1);
+    } else if (NC > 1) {
+        const int start = lane < h.n_caches ? p.dst[lane % NC].block0 : INT32_MAX;
+        cache = (int)__popcll(__builtin_amdgcn_ballot_w64(start <= (int)blockIdx.x)) - 1;
     }
-    i0 = __builtin_amdgcn_readfirstlane(i0);
-    i1 = __builtin_amdgcn_readfirstlane(i1);
-    const ShotRun first = p.shots[i0];
-    const int64_t row_bytes = (int64_t)p.n_kv_heads * (2 * CH * 16);
-    const int64_t dst_off = (int64_t)(p.slot0 + s0) * row_bytes + (int64_t)blockIdx.y * p.dst.layer_stride_bytes;
-    const char* const pool = (blockIdx.z == 1 ? p.v_pool : p.k_pool) + (int64_t)blockIdx.y * p.pool_layer_stride_bytes;
-    char* const out = (blockIdx.z == 1 ? p.dst.v_out : p.dst.k_out) + dst_off;
-    const int pos = (int)p.dst.pos0 + p.slot0 + s0;  // of the first slot (below max_position <= 2^30)
-    const bool one = i0 == i1;
-    const DenseRows dense{(int64_t)(first.src_tok + s0 - first.slot) * row_bytes, row_bytes};
+    const ShotsDst& dst = p.dst[__builtin_amdgcn_readfirstlane(cache)];
+    const int s0 = ((int)blockIdx.x - dst.block0) * h.wg_tok;  // this workgroup's slots, counted from the call's first: s0 .. s0 + n_tok - 1
+    const int n_tok = dst.n_tokens - s0 < h.wg_tok ? dst.n_tokens - s0 : h.wg_tok;
+    int run, run_end;  // of the first slot; one past the last slot's, or any later one's
+    bool one;
+    if (NS == 0) {
+        run = block.run;
+        run_end = dst.run0 + dst.n_runs;
+        one = (block.what & kBlockOneRun) != 0;
+    } else {
+        int i0 = dst.run0 - 1, i1 = dst.run0 - 1;
+        for (int b = 0; b < dst.n_runs; b += 64) {
+            const int start = b + lane < dst.n_runs ? p.shots[dst.run0 + b + lane].slot : INT32_MAX;
+            const int n0 = (int)__popcll(__builtin_amdgcn_ballot_w64(start <= s0));
+            const int n1 = (int)__popcll(__builtin_amdgcn_ballot_w64(start <= s0 + n_tok - 1));
+            i0 += n0;
+            i1 += n1;
+            if (n1 < 64) break;  // starts increase
+        }
+        run = __builtin_amdgcn_readfirstlane(i0);
+        run_end = __builtin_amdgcn_readfirstlane(i1) + 1;
+        one = run + 1 == run_end;
+        const ShotRun first = p.shots[run];
+        block.skip = s0 - first.slot;
+        block.src_tok = first.src_tok + block.skip;
+    }
+    auto run_at = [&](int i) __attribute__((always_inline)) -> ShotRun { return NS == 0 ? h.list[i].run : p.shots[NS > 0 ? i : 0]; };
+    const int64_t row_bytes = (int64_t)h.n_kv_heads * (2 * CH * 16);
+    const int64_t dst_off = (int64_t)(dst.slot0 + s0) * row_bytes + (int64_t)blockIdx.y * dst.layer_stride_bytes;
+    const char* const pool = (blockIdx.z == 1 ? h.v_pool : h.k_pool) + (int64_t)blockIdx.y * h.pool_layer_stride_bytes;
+    char* const out = (blockIdx.z == 1 ? dst.v_out : dst.k_out) + dst_off;
+    const int pos = (int)dst.pos0 + dst.slot0 + s0;  // of the first slot (below max_position <= 2^30)
+    const DenseRows dense{(int64_t)block.src_tok * row_bytes, row_bytes};
     const GatheredRows gathered{row_tok, row_bytes};
     if (!one || (blockIdx.y == 0 && blockIdx.z == 0)) {
         if (tid < n_tok) {
-            int i = i0;
-            while (i < i1 && p.shots[i + 1].slot <= s0 + tid) ++i;
-            const ShotRun run = p.shots[i];
-            const int t = s0 + tid - run.slot;
-            row_tok[tid] = run.src_tok + t;
-            row_angle[tid] = p.local ? pos - s0 + run.slot : pos + tid;
+            int i = run;
+            while (i + 1 < run_end && run_at(i + 1).slot <= s0 + tid) ++i;
+            const ShotRun r = run_at(i);
+            const int t = s0 + tid - r.slot;
+            row_tok[tid] = r.src_tok + t;
+            row_angle[tid] = h.local ? pos - s0 + r.slot : pos + tid;
             if (blockIdx.y == 0 && blockIdx.z == 0) {
-                const int slot = p.slot0 + s0 + tid;
-                if (p.dst.slot_shot) p.dst.slot_shot[slot] = run.shot;
-                if (p.dst.slot_tok) p.dst.slot_tok[slot] = t;
-                if (p.dst.slot_pos) p.dst.slot_pos[slot] = p.dst.pos0 + slot;
+                const int slot = dst.slot0 + s0 + tid;
+                if (dst.slot_shot) dst.slot_shot[slot] = r.shot;
+                if (dst.slot_tok) dst.slot_tok[slot] = t;
+                if (dst.slot_pos) dst.slot_pos[slot] = dst.pos0 + slot;
             }
         }
         if (!one) __syncthreads();
@@ -298,45 +337,41 @@ __global__ __launch_bounds__(256) void assemble_shots_kernel(AssembleShotsParams
         else copy_v<NT>(pool, gathered, out, n_tok, row_bytes);
         return;
     }
-    const int angle0 = p.local ? pos - s0 + first.slot : pos, step = p.local ? 0 : 1;
+    const int angle0 = h.local ? pos - block.skip : pos, step = h.local ? 0 : 1;
     if (one)
-        rotate_k<DTYPE, CH, NT>(pool, dense, out, n_tok, p.n_kv_heads, p.tab_lo, p.tab_hi, cs,
+        rotate_k<DTYPE, CH, NT>(pool, dense, out, n_tok, h.n_kv_heads, h.tab_lo, h.tab_hi, cs,
                                 [&](int tau) __attribute__((always_inline)) { return angle0 + tau * step; });
     else
-        rotate_k<DTYPE, CH, NT>(pool, gathered, out, n_tok, p.n_kv_heads, p.tab_lo, p.tab_hi, cs,
+        rotate_k<DTYPE, CH, NT>(pool, gathered, out, n_tok, h.n_kv_heads, h.tab_lo, h.tab_hi, cs,
                                 [&](int tau) __attribute__((always_inline)) { return row_angle[tau]; });
 }
 
 template <int DTYPE, int CH>
 static hipError_t launch_t(const AssembleParams& p, hipStream_t stream) {
     dim3 grid((unsigned)p.n_tiles * (unsigned)(kTileTok / p.wg_tok), (unsigned)p.n_layers, 2);
-    // what the launch writes, K and V
-    const int64_t e = DTYPE == ADAPSHOT_BF16 ? 2 : 4;
-    const int64_t written = 2 * p.n_tokens * p.n_kv_heads * p.head_dim * e * p.n_layers;
-    if (written > kAssembleStreamBytes)
-        launch_kernel((assemble_reencode_kernel<DTYPE, CH, true>), grid, dim3(256), stream, p);
-    else
-        launch_kernel((assemble_reencode_kernel<DTYPE, CH, false>), grid, dim3(256), stream, p);
+    launch_kernel((assemble_reencode_kernel<DTYPE, CH>), grid, dim3(256), stream, p);
     return hipGetLastError();
 }
 
-template <int DTYPE, int CH>
-static hipError_t launch_t(const AssembleShotsParams& p, hipStream_t stream) {
-    const dim3 grid((unsigned)((p.n_tokens + p.wg_tok - 1) / p.wg_tok), (unsigned)p.n_layers, 2);
+template <int DTYPE, int CH, int NC, int NS>
+static hipError_t launch_t(const AssembleShotsParams<NC, NS>& p, hipStream_t stream) {
+    const dim3 grid((unsigned)p.h.n_blocks, (unsigned)p.h.n_layers, 2);
+    // what the launch writes, K and V (a list in device memory: always enough)
     const int64_t e = DTYPE == ADAPSHOT_BF16 ? 2 : 4;
-    if (2 * (int64_t)p.n_tokens * p.n_kv_heads * p.head_dim * e * p.n_layers > kAssembleStreamBytes)
-        launch_kernel((assemble_shots_kernel<DTYPE, CH, true>), grid, dim3(256), stream, p);
+    if (NS == 0 || 2 * p.h.n_tokens * p.h.n_kv_heads * p.h.head_dim * e * p.h.n_layers > kAssembleStreamBytes)
+        launch_kernel((assemble_shots_kernel<DTYPE, CH, true, NC, NS>), grid, dim3(256), stream, p);
     else
-        launch_kernel((assemble_shots_kernel<DTYPE, CH, false>), grid, dim3(256), stream, p);
+        launch_kernel((assemble_shots_kernel<DTYPE, CH, NS == 0, NC, NS>), grid, dim3(256), stream, p);
     return hipGetLastError();
 }
 
-template <typename P>
-static hipError_t launch_by_shape(const P& p, hipStream_t stream) {
-    const int e = p.dtype == ADAPSHOT_BF16 ? 2 : 4;
-    const int ch = p.head_dim / 2 * e / 16;
-    if (p.wg_tok < 1 || p.wg_tok > kTileTok || (p.wg_tok & (p.wg_tok - 1)) != 0) return hipErrorInvalidValue;
-    if (p.dtype == ADAPSHOT_BF16) {
+// h: where p has its shape
+template <typename H, typename P>
+static hipError_t launch_by_shape(const H& h, const P& p, hipStream_t stream) {
+    if (h.wg_tok < 1 || h.wg_tok > kTileTok || (h.wg_tok & (h.wg_tok - 1)) != 0) return hipErrorInvalidValue;
+    const int e = h.dtype == ADAPSHOT_BF16 ? 2 : 4;
+    const int ch = h.head_dim / 2 * e / 16;
+    if (h.dtype == ADAPSHOT_BF16) {
         switch (ch) {
             case 1: return launch_t<ADAPSHOT_BF16, 1>(p, stream);
             case 2: return launch_t<ADAPSHOT_BF16, 2>(p, stream);
@@ -359,13 +394,21 @@ static hipError_t launch_by_shape(const P& p, hipStream_t stream) {
 hipError_t launch_assemble(const AssembleParams& p, hipStream_t stream) {
     if (p.n_tiles <= 0) return hipSuccess;
     if (p.wg_tok > 0 && (int64_t)p.n_tiles * (kTileTok / p.wg_tok) > INT32_MAX) return hipErrorInvalidValue;
-    return launch_by_shape(p, stream);
+    return launch_by_shape(p, p, stream);
 }
 
-hipError_t launch_assemble_shots(const AssembleShotsParams& p, hipStream_t stream) {
-    if (p.n_tokens <= 0) return hipSuccess;
-    if (p.n_shots < 1 || p.n_shots > kAssembleShots || p.shots[0].slot != 0) return hipErrorInvalidValue;
-    return launch_by_shape(p, stream);
+template <int NC, int NS>
+static hipError_t launch_shots(const AssembleShotsParams<NC, NS>& p, hipStream_t stream) {
+    if (p.h.n_caches < 1 || p.h.n_caches > NC || p.h.n_blocks < 1 || (NS == 0 && (!p.h.list || !p.h.blocks))) return hipErrorInvalidValue;
+    return launch_by_shape(p.h, p, stream);
+}
+hipError_t launch_assemble_shots(const AssembleOne& p, hipStream_t stream) { return launch_shots(p, stream); }
+hipError_t launch_assemble_shots(const AssembleFew& p, hipStream_t stream) { return launch_shots(p, stream); }
+hipError_t launch_assemble_shots(const AssembleMany& p, hipStream_t stream) { return launch_shots(p, stream); }
+hipError_t launch_assemble_list(const AssembleMany& p, hipStream_t stream) {
+    if (p.h.n_runs < 1 || !p.h.host_list || !p.h.list || !p.h.blocks) return hipErrorInvalidValue;
+    launch_kernel(assemble_list_kernel, dim3((unsigned)((p.h.n_runs + 15) / 16)), dim3(256), stream, p);
+    return hipGetLastError();
 }
 
 // ---- decode append ------------------------------------------------------------------------------
