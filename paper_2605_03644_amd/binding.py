@@ -143,6 +143,18 @@ def _stream_ptr(stream: Optional[torch.cuda.Stream] = None) -> int:
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
+_NO_BYTES = ctypes.c_char * 0
+
+
+def _host_addr(a: np.ndarray) -> int:
+    """Where a contiguous array's data lie.  (a.ctypes makes a Python object for it: 0.6 to 1.1 us an array, this 0.25; a call on a small
+    problem is 4 us of host work and as many on the GPU.)"""
+    try:
+        return ctypes.addressof(_NO_BYTES.from_buffer(a))
+    except (TypeError, ValueError, BufferError):  # read-only memory
+        return a.ctypes.data
+
+
 def _torch_dtype(dtype: int) -> torch.dtype:
     return torch.float32 if dtype == F32 else torch.bfloat16
 
@@ -230,8 +242,8 @@ class Context:
                  pos0: int = 0, stream: Optional[torch.cuda.Stream] = None) -> None:
         ids = np.ascontiguousarray(shot_ids, dtype=np.int32)
         od = None if order is None else np.ascontiguousarray(order, dtype=np.int32)
-        self._check(self.lib.adapshot_assemble(self._h, ctypes.byref(cache.c), ids.ctypes.data,
-                                               None if od is None else od.ctypes.data, ids.shape[0], pos0,
+        self._check(self.lib.adapshot_assemble(self._h, ctypes.byref(cache.c), _host_addr(ids),
+                                               None if od is None else _host_addr(od), ids.shape[0], pos0,
                                                _stream_ptr(stream)))
 
     # -- adapshot_query_attn
@@ -255,8 +267,8 @@ class Context:
         od = None if order is None else np.ascontiguousarray(order, dtype=np.int32)
         if out is None:
             out = torch.empty_like(q)
-        self._check(self.lib.adapshot_query_attn_pool(self._h, layer, ids.ctypes.data,
-                                                      None if od is None else od.ctypes.data, ids.shape[0], pos0,
+        self._check(self.lib.adapshot_query_attn_pool(self._h, layer, _host_addr(ids),
+                                                      None if od is None else _host_addr(od), ids.shape[0], pos0,
                                                       q.data_ptr(), k_self.data_ptr(), v_self.data_ptr(), q.shape[0],
                                                       q_pos0, out.data_ptr(), _stream_ptr(stream)))
         return out
@@ -294,7 +306,7 @@ class Context:
             out = torch.empty(rows, dtype=torch.float32, device=logits.device)
         self._check(self.lib.adapshot_probe_entropy_tokens(
             self._h, logits.data_ptr(), logits.stride(0) if rows > 1 else vocab, rows, vocab,
-            ids.ctypes.data_as(ctypes.c_void_p), int(ids.size), int(mode), out.data_ptr(), _stream_ptr(stream)))
+            _host_addr(ids), int(ids.size), int(mode), out.data_ptr(), _stream_ptr(stream)))
         return out
 
     # -- adapshot_rank_shots / adapshot_top_k
@@ -342,13 +354,13 @@ class Context:
         n = len(caches)
         ids = [np.ascontiguousarray(x, dtype=np.int32) for x in shot_ids]
         ods = None if orders is None else [None if o is None else np.ascontiguousarray(o, dtype=np.int32) for o in orders]
-        id_ptrs = (ctypes.c_void_p * n)(*[x.ctypes.data for x in ids])
-        od_ptrs = None if ods is None else (ctypes.c_void_p * n)(*[None if o is None else o.ctypes.data for o in ods])
+        id_ptrs = (ctypes.c_void_p * n)(*[_host_addr(x) for x in ids])
+        od_ptrs = None if ods is None else (ctypes.c_void_p * n)(*[None if o is None else _host_addr(o) for o in ods])
         m = np.array([x.shape[0] for x in ids], dtype=np.int32)
         arr = self._pack_caches(caches)
         st = self.lib.adapshot_assemble_batched(self._h, arr, n, ctypes.cast(id_ptrs, ctypes.c_void_p),
                                                 None if od_ptrs is None else ctypes.cast(od_ptrs, ctypes.c_void_p),
-                                                m.ctypes.data, pos0, _stream_ptr(stream))
+                                                _host_addr(m), pos0, _stream_ptr(stream))
         self._unpack_lens(caches, arr)
         self._check(st)
 
@@ -377,8 +389,8 @@ class Context:
         n = len(shot_ids)
         ids = [np.ascontiguousarray(x, dtype=np.int32) for x in shot_ids]
         ods = None if orders is None else [None if o is None else np.ascontiguousarray(o, dtype=np.int32) for o in orders]
-        id_ptrs = (ctypes.c_void_p * n)(*[x.ctypes.data for x in ids])
-        od_ptrs = None if ods is None else (ctypes.c_void_p * n)(*[None if o is None else o.ctypes.data for o in ods])
+        id_ptrs = (ctypes.c_void_p * n)(*[_host_addr(x) for x in ids])
+        od_ptrs = None if ods is None else (ctypes.c_void_p * n)(*[None if o is None else _host_addr(o) for o in ods])
         m = np.array([x.shape[0] for x in ids], dtype=np.int32)
         return (ids, ods, id_ptrs, od_ptrs, m)
 
@@ -392,7 +404,7 @@ class Context:
         its = items if isinstance(items, ctypes.Array) else self.pack_attn_items(items)
         self._check(self.lib.adapshot_query_attn_pool_batched(
             self._h, layer, ctypes.cast(id_ptrs, ctypes.c_void_p),
-            None if od_ptrs is None else ctypes.cast(od_ptrs, ctypes.c_void_p), m.ctypes.data, m.shape[0], pos0,
+            None if od_ptrs is None else ctypes.cast(od_ptrs, ctypes.c_void_p), _host_addr(m), m.shape[0], pos0,
             its, len(its), _stream_ptr(stream)))
 
     # -- adapshot_decode_append: k_new, v_new [L, n_caches, H_kv, d]

@@ -1,6 +1,7 @@
 """What the binding hands to the library: attention items packed in one piece, and the stream of a call."""
 import ctypes
 
+import numpy as np
 import pytest
 import torch
 
@@ -22,6 +23,16 @@ def test_a_strided_item_is_refused():
     x = torch.empty(4, 4, 16)
     with pytest.raises(AssertionError):
         ad.Context.pack_attn_items([(0, 1, x[..., :8], x, x, 0, x)])
+
+
+@pytest.mark.parametrize("n", [0, 1, 7])
+@pytest.mark.parametrize("writable", [True, False])
+def test_the_address_of_an_array(n, writable):
+    base = np.arange(n + 3, dtype=np.int32)
+    a = base[2:2 + n]
+    a.flags.writeable = writable
+    assert n == 0 or ad._host_addr(a) == a.ctypes.data == base.ctypes.data + 8
+    assert isinstance(ad._host_addr(a), int)
 
 
 @pytest.mark.gpu
