@@ -214,7 +214,8 @@ extern "C" adapshot_status adapshot_create(const adapshot_model_desc* desc, adap
     // RoPE tables in fp64, rounded once to fp32.
     const int half = desc->head_dim / 2;
     const int64_t n_hi = (ctx->max_position + kRopeLo - 1) / kRopeLo + 1;
-    std::vector<float2> lo((size_t)(2 * kRopeLo) * half), hi((size_t)n_hi * half);
+    const int64_t n_mid = attn_mfma_supported(ctx->desc) ? n_hi : 0;  // tab_mid: the zero-copy tile kernel's
+    std::vector<float2> lo((size_t)(2 * kRopeLo) * half), hi((size_t)n_hi * half), mid((size_t)n_mid * half);
     std::vector<double> theta(half);
     for (int i = 0; i < half; ++i) theta[i] = pow(desc->rope_theta, -2.0 * (double)i / (double)desc->head_dim);
     for (int r = 0; r < 2 * kRopeLo; ++r)
@@ -222,15 +223,27 @@ extern "C" adapshot_status adapshot_create(const adapshot_model_desc* desc, adap
             double a = (r < kRopeLo ? (double)r : (double)(r - kRopeLo) + 0.5) * theta[i];
             lo[(size_t)r * half + i] = make_float2((float)cos(a), (float)sin(a));
         }
+    std::vector<double> cos_mid(half), sin_mid(half);
+    for (int i = 0; i < half; ++i) {
+        cos_mid[i] = cos(0.5 * (kRopeLo - 1) * theta[i]);
+        sin_mid[i] = sin(0.5 * (kRopeLo - 1) * theta[i]);
+    }
     for (int64_t r = 0; r < n_hi; ++r)
         for (int i = 0; i < half; ++i) {
             double a = (double)(r * kRopeLo) * theta[i];
-            hi[(size_t)r * half + i] = make_float2((float)cos(a), (float)sin(a));
+            const double c = cos(a), s = sin(a);
+            hi[(size_t)r * half + i] = make_float2((float)c, (float)s);
+            if (r < n_mid) {
+                const double mc = cos_mid[i], ms = sin_mid[i];
+                mid[(size_t)r * half + i] = make_float2((float)(c * mc - s * ms), (float)(s * mc + c * ms));
+            }
         }
     e = hipMalloc((void**)&ctx->tab_lo, lo.size() * sizeof(float2));
     if (e == hipSuccess) e = hipMalloc((void**)&ctx->tab_hi, hi.size() * sizeof(float2));
     if (e == hipSuccess) e = hipMemcpy(ctx->tab_lo, lo.data(), lo.size() * sizeof(float2), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(ctx->tab_hi, hi.data(), hi.size() * sizeof(float2), hipMemcpyHostToDevice);
+    if (e == hipSuccess && n_mid > 0) e = hipMalloc((void**)&ctx->tab_mid, mid.size() * sizeof(float2));
+    if (e == hipSuccess && n_mid > 0) e = hipMemcpy(ctx->tab_mid, mid.data(), mid.size() * sizeof(float2), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc((void**)&ctx->stream_counters, kStreamUnits * sizeof(unsigned));
     const std::vector<unsigned> zeros(kStreamUnits, 0u);
     if (e == hipSuccess) e = hipMemcpy(ctx->stream_counters, zeros.data(), zeros.size() * sizeof(unsigned), hipMemcpyHostToDevice);
@@ -267,6 +280,7 @@ extern "C" void adapshot_destroy(adapshot_ctx* ctx) {
     ctx->retired.clear();
     if (ctx->tab_lo) (void)hipFree(ctx->tab_lo);
     if (ctx->tab_hi) (void)hipFree(ctx->tab_hi);
+    if (ctx->tab_mid) (void)hipFree(ctx->tab_mid);
     if (ctx->stream_counters) (void)hipFree(ctx->stream_counters);
     delete ctx;
 }
@@ -1193,7 +1207,7 @@ extern "C" adapshot_status adapshot_query_attn_pool(adapshot_ctx* ctx, int32_t l
     pp.slot_src = (int32_t*)ctx->pool_src.p;
     pp.tile_rot = (float2*)ctx->pool_rot.p;
     pp.tab_lo = ctx->tab_lo;
-    pp.tab_hi = ctx->tab_hi;
+    pp.tab_mid = ctx->tab_mid;
     pp.pos0 = pos0;
     pp.n_segs = n_segs;
     pp.n_tiles = (int32_t)n_tiles;
@@ -1338,7 +1352,7 @@ extern "C" adapshot_status adapshot_query_attn_pool_batched(adapshot_ctx* ctx, i
         pp.slot_src = (int32_t*)ctx->pool_src.p;
         pp.tile_rot = (float2*)ctx->pool_rot.p;
         pp.tab_lo = ctx->tab_lo;
-        pp.tab_hi = ctx->tab_hi;
+        pp.tab_mid = ctx->tab_mid;
         pp.pos0 = pos0;
         pp.n_segs = ns;
         pp.n_tiles = (int32_t)n_tiles;

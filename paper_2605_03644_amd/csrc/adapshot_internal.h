@@ -280,7 +280,7 @@ struct PoolPlanParams {
     int32_t* slot_src;
     float2* tile_rot;
     const float2* tab_lo;
-    const float2* tab_hi;
+    const float2* tab_mid;
     int64_t pos0;
     int32_t n_segs, n_tiles, head_dim;
 };
@@ -543,6 +543,7 @@ struct adapshot_ctx {
     // tables
     float2* tab_lo = nullptr;
     float2* tab_hi = nullptr;
+    float2* tab_mid = nullptr;  // (cos, sin)((64 i + 31.5) theta_f), where the tile kernel serves the model
     unsigned* stream_counters = nullptr;  // arrival counters of split streaming launches, zero between launches
     float* static_ent = nullptr;  // this device's copy of the static entropy scratch array (not owned)
     // scratch
