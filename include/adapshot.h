@@ -20,16 +20,16 @@
  *     are ordinary host memory read before the call returns.
  *   - `hip_stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     All kernels of a call are enqueued on it; calls return without waiting for
- *     the GPU.  A context owns device scratch (RoPE tables, shot lists,
+ *     the GPU.  A context owns device scratch (RoPE tables, shot lists, tile descriptors,
  *     split partials), so calls on ONE context must be issued in stream order on
  *     one stream at a time; use one context per concurrent stream.
  *   - Allocation and waiting.  adapshot_create allocates the RoPE tables and 16 KiB of arrival counters
  *     (hipMalloc, blocking copies, and a wait for them).  adapshot_query_attn, adapshot_query_attn_pool, the batched attention calls, adapshot_probe_entropy,
  *     adapshot_probe_entropy_tokens, adapshot_rank_shots and assembly of more shots than its kernel arguments hold (320 for one cache,
- *     280 for up to 8) keep grow-only workspaces: a call that
+ *     272 for up to 8) that writes more than 256 MiB keep grow-only workspaces: a call that
  *     needs more than any earlier call on the context calls hipMalloc (an outgrown buffer is kept
  *     until adapshot_destroy, never freed in a call, so no call waits for the device); a call that
- *     fits the existing workspaces allocates nothing.  Such an assembly, adapshot_query_attn_pool, the batched attention
+ *     fits the existing workspaces allocates nothing.  Assembly of more shots than that, adapshot_query_attn_pool, the batched attention
  *     calls and adapshot_rank_shots write small tables into a ring of 8 pinned host buffers (hipHostMalloc
  *     when one must grow); the ninth such call in flight waits for the first one's kernels.  No
  *     call synchronises the device or the stream otherwise.  adapshot_probe_entropy_static is the

@@ -524,7 +524,7 @@ static hipError_t assemble_by_tiles(adapshot_ctx* ctx, const AssembleJob* jobs, 
 // Plan (prefix sums) and launch of validated assemble jobs, up to kAssembleBatch caches a launch.  Lists that fit the kernel arguments
 // go there: no pinned buffer, no event, no other kernel (2 caches of 16 shots 11.9 -> 11.2 us, 4 of 64 short ones 19.4 -> 14.8).  A longer
 // one goes through device memory where the launch writes more than the last-level cache holds, else as tiles: the kernel ahead of the
-// launch costs 4 us, and what it saves grows with the bytes.  MB written, by tiles / by list, us: one layer 171 57.6 / 61.6, 217 71.9
+// launch costs 4 to 7 us, and what it saves grows with the bytes.  MB written, by tiles / by list, us: one layer 171 57.6 / 61.6, 217 71.9
 // / 74.9, 341 130.2 / 129.0, 549 207 / 200, 1759 732 / 630; two layers 108 42.0 / 44.2, 269 104.7 / 105.2, 407 156 / 153, 1066 396 / 376;
 // 8 layers 2113 770 / 751, 28 layers 7441 2708 / 2618.  (Lists cut into launches with arguments: each costs 4.5 us.)
 static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_t n_jobs, int64_t pos0,
