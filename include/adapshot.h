@@ -326,14 +326,14 @@ adapshot_status adapshot_set_attn_splits(adapshot_ctx* ctx, int32_t n_split);
 adapshot_status adapshot_attn_split_plan(const adapshot_model_desc* desc, int32_t n_compute_units, int32_t t_q,
                                          int64_t n_ctx, int32_t* n_split, int64_t* keys_per_split);
 
-/* Measurement aid (not a step of the method).  While enabled, every kernel the context
- * launches carries a pair of HIP events attached to its dispatch on the launch stream, whose
+/* Measurement aid (not a step of the method).  While enabled, every kernel the context launches, but for the copies of
+ * tables from pinned host memory (a few us ahead of the first layer of a large batch or of a ranking), carries a pair of HIP events attached to its dispatch on the launch stream, whose
  * difference is the kernel's own execution time (events recorded before and after a launch
  * would add about 2.5 us of command-processor round trips).  adapshot_profile_read waits for
  * the recorded launches of one kernel kind, returns their summed duration in milliseconds
  * and their count, and forgets them.  Whole-path throughput is measured with profiling off. */
 typedef enum {
-    ADAPSHOT_KERNEL_ASSEMBLE = 0,       /* fused gather + re-encode */
+    ADAPSHOT_KERNEL_ASSEMBLE = 0,       /* fused gather + re-encode; a shot list in device memory is written by a launch of its own */
     ADAPSHOT_KERNEL_ROPE_ROWS = 1,      /* rotation of the query rows (ranking); plan of a zero-copy context */
     ADAPSHOT_KERNEL_ATTN = 2,           /* split-K attention proper */
     ADAPSHOT_KERNEL_ATTN_COMBINE = 3,   /* merge of the split partials (matrix-core kernel) */

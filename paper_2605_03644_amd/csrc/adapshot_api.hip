@@ -458,7 +458,7 @@ static hipError_t assemble_by_list(adapshot_ctx* ctx, const AssembleJob* jobs, i
     p.h.host_list = runs;
     p.h.list = (ListRun*)((char*)ctx->run_lists.p + (size_t)slot * each);
     p.h.blocks = (AssembleBlock*)(p.h.list + n_runs);
-    e = launch_assemble_list(p, stream);
+    e = timed_launch(ctx, ADAPSHOT_KERNEL_ASSEMBLE, stream, [&] { return launch_assemble_list(p, stream); });
     if (e != hipSuccess) return e;
     e = timed_launch(ctx, ADAPSHOT_KERNEL_ASSEMBLE, stream,
                      [&] { return ctx->tile_ring.launch_reader(slot, stream, [&] { return launch_assemble_shots(p, stream); }); });

@@ -25,6 +25,24 @@ def test_lists_in_device_memory(layers, hkv, d, dtype, n_caches, m, lens_hi, loc
     assert written > 256 << 20
 
 
+# arguments: one launch; tiles: one; a list in device memory: the launch that writes it, and the assembly
+@pytest.mark.parametrize("n_caches,m,layers,launches", [(1, 300, 2, 1), (2, 200, 2, 1), (1, 1100, 2, 2), (49, 30, 2, 3)])
+def test_every_launch_is_recorded(n_caches, m, layers, launches):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2605_03644_amd import binding as ad
+    ctx = ad.Context(layers, 8, 8, 128, 1.0e4, ad.BF16, max_position=1 << 19)
+    off = (35 * np.arange(1201)).astype(np.int64)
+    k, v = (wl.normal_tensor((layers, int(off[-1]), 8, 128), torch.bfloat16, "cuda", s) for s in (1, 2))
+    ctx.pool_register(k, v, off)
+    caches = [ad.Cache(ctx, 35 * m, with_index=False) for _ in range(n_caches)]
+    ctx.profile_enable(True)
+    ctx.assemble_batched(caches, [np.arange(m, dtype=np.int32)] * n_caches)
+    ms, n = ctx.profile_read()["assemble_reencode"]
+    assert n == launches and ms > 0
+    ctx.close()
+
+
 def _check(layers, hkv, d, dtype, n_caches, m, lens_hi, local, index):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
