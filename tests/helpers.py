@@ -1,4 +1,7 @@
 """Shared pieces of the GPU parity tests: tolerance checks written out once."""
+import os
+import re
+
 import numpy as np
 import torch
 
@@ -54,3 +57,10 @@ def storage_to_f64(a: np.ndarray) -> np.ndarray:
     if a.dtype == np.uint16:
         return (a.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
     return a.astype(np.float64)
+
+
+def constant(name: str, header: str = "adapshot_internal.h") -> int:
+    """A whole-number limit of the library, from the header that defines it: a test that is about one side of it says so in numbers."""
+    text = open(os.path.join(os.path.dirname(wl.__file__), "csrc", header)).read()
+    a, shift = re.search(r"\b" + name + r" = (\d+)(?:ll)?(?: << (\d+))?[,;]", text).groups()
+    return int(a) << int(shift or 0)
