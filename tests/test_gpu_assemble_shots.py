@@ -1,11 +1,12 @@
-"""Assembly of one cache with its shot list in the kernel arguments, against the descriptor path that a batch of caches takes:
-the same bits and the same index arrays, for shots shorter than a workgroup, empty ones, lists up to and beyond the
-argument's length, caches that already hold tokens, both key states."""
+"""Assembly of one cache with its shot list in the kernel arguments, against the lists of a batch there and against the tiles of a batch
+of more caches than the arguments hold: the same bits and the same index arrays, for shots shorter than a workgroup, empty ones,
+lists up to and beyond the argument's length, caches that already hold tokens, both key states."""
 import numpy as np
 import pytest
 import torch
 
 from paper_2605_03644_amd import workloads as wl
+from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
 
@@ -41,16 +42,23 @@ def test_the_list_in_the_arguments_gives_what_descriptors_give(ad, dtype, hq, hk
     ctx.pool_register(k, v, off)
     ids, order = rng.permutation(n_pool)[:m].astype(np.int32), rng.permutation(m).astype(np.int32)
     total = int(np.sum(off[ids + 1] - off[ids]))
-    first = np.flatnonzero(np.diff(off))[:1].astype(np.int32)  # a shot with tokens, for the second cache of the batch
-    one, two, other = (ad.Cache(ctx, have + total + 2, with_index=True) for _ in range(3))
-    other = ad.Cache(ctx, have + int(off[first[0] + 1] - off[first[0]]), with_index=False)
-    for c in (one, two, other):
+    first = np.flatnonzero(np.diff(off))[:1].astype(np.int32)  # a shot with tokens, for the other caches of the batches
+    n_first = int(off[first[0] + 1] - off[first[0]])
+    one, two, tiles = (ad.Cache(ctx, have + total + 2, with_index=True) for _ in range(3))
+    others = [ad.Cache(ctx, have + n_first, with_index=False) for _ in range(H.constant("kAssembleFewCaches"))]
+    assert 2 * (total + len(others) * n_first) * layers * hkv * d * k.element_size() <= H.constant("kAssembleStreamBytes")  # (no list in device memory)
+    for c in [one, two, tiles] + others:
         c.c.len = have
     ctx.assemble(one, ids, order, pos0=11)
-    ctx.assemble_batched([two, other], [ids, first], [order, None], pos0=11)
+    ctx.assemble_batched([two, others[0]], [ids, first], [order, None], pos0=11)
+    others[0].c.len = have
+    ctx.assemble_batched([tiles] + others, [ids] + [first] * len(others), [order] + [None] * len(others), pos0=11)
     torch.cuda.synchronize()
-    assert one.len == two.len == have + total
-    for a, b in ((one.k, two.k), (one.v, two.v), (one.slot_shot, two.slot_shot), (one.slot_tok, two.slot_tok), (one.slot_pos, two.slot_pos)):
-        assert torch.equal(a, b)
+    assert total > 0 and one.len == two.len == tiles.len == have + total
+    for x in (two, tiles):
+        for a, b in ((one.k, x.k), (one.v, x.v), (one.slot_shot, x.slot_shot), (one.slot_tok, x.slot_tok), (one.slot_pos, x.slot_pos)):
+            assert torch.equal(a, b)
+    for x in others:
+        assert x.len == have + n_first and torch.equal(x.v[:, have:], v[:, off[first[0]]:off[first[0] + 1]])
     if total:
         assert int(one.slot_pos[have + total - 1]) == 11 + have + total - 1 and int(one.slot_pos[have + total]) == -1

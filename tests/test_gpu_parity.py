@@ -108,9 +108,26 @@ def test_assemble_qwen_shape_bf16_two_layers(ad, oracle_mod):
 
 @pytest.mark.parametrize("key_state", [0, 1])
 def test_assemble_many_layers_host_cut_pieces(ad, oracle_mod, key_state):
-    """From 8 layers on the host cuts every shot into one-workgroup pieces (8 tokens for this row size) and joins
-    what is left over to the last piece: shot lengths 1..70 cover shots shorter than a piece, shots with no
-    remainder and every remainder 1..7; three appends."""
+    """From 8 layers on the host cuts every shot of a list beyond the kernel arguments that writes no more than 256 MB into
+    one-workgroup pieces (8 tokens for this row size) and joins what is left over to the last piece: shot lengths 1..22 cover shots
+    shorter than a piece, shots with no remainder and every remainder 1..7; two appends."""
+    import dataclasses
+    w = dataclasses.replace(wl.WORKLOADS["llama8b_1layer"], name="llama8b_pieces", n_layers=8, n_shots=800, len_lo=1,
+                            len_hi=22, m_select=650)
+    lens = wl.shot_lengths(w)
+    assert lens.min() == 1 and lens.max() == 22 and len({int(x) % 8 for x in lens}) == 8
+    ids, order = wl.selection(w)
+    picked = lens[ids[order]]
+    for part in (picked[:325], picked[325:]):
+        assert len(part) > H.constant("kAssembleShots")
+        assert 2 * int(part.sum()) * 8 * w.n_kv_heads * w.head_dim * 2 <= H.constant("kAssembleStreamBytes")
+    r = _run_assemble_case(ad, oracle_mod, w, key_state, 5, [0.5], ids=ids, order=order)
+    assert r["total"] > 1000
+
+
+@pytest.mark.parametrize("key_state", [0, 1])
+def test_assemble_many_layers(ad, oracle_mod, key_state):
+    """The same number of layers with lists in the kernel arguments: shot lengths 1..70, three appends."""
     import dataclasses
     w = dataclasses.replace(wl.WORKLOADS["llama8b_1layer"], name="llama8b_pieces", n_layers=8, n_shots=90, len_lo=1,
                             len_hi=70, m_select=60)
