@@ -164,7 +164,7 @@ adapshot_status adapshot_query_attn(adapshot_ctx* ctx, const adapshot_cache* cac
  * rounding: the attention kernel gathers every 64-slot tile of the context row by row through a slot -> pool
  * token table and rotates its keys to the positions pos0 + slot inside the key loop, in LDS, before the first
  * product reads them (Position Decoupling and Re-encoding: R(a)R(b) = R(a+b), so the rotation of a tile's
- * first position and the rotation of the row's index inside the tile compose; Eq. rope_compensation).  Worth
+ * centre and the rotation of the row's distance from it compose; Eq. rope_compensation).  Worth
  * it for a context that is attended once; a context that is attended again (further layers' probes, every
  * decode step) is cheaper assembled once.  shot_ids, order: HOST int32[m] as in adapshot_assemble; q, k_self,
  * v_self, out, q_pos0 as in adapshot_query_attn.  A small launch expands the plan, a second one attends, a third one

@@ -816,7 +816,7 @@ struct PoolBatch {
     const char* v_layer;
     const int32_t* slot_src;    // device: the lists' slot tables, one after the other
     const int64_t* list_base;   // host: first entry of every list in slot_src
-    const float2* tile_rot;     // device: (cos, sin) of position pos0 + 64 i for every 64-slot tile, shared by the lists
+    const float2* tile_rot;     // device: (cos, sin) of pos0 + 64 i + 31.5, the centre of 64-slot tile i, in tile_rot_place() order, shared by the lists
 };
 static adapshot_status run_query_attn_batch(adapshot_ctx* ctx, const adapshot_cache* caches, int32_t layer,
                                             const adapshot_attn_item* items, int32_t n_items, hipStream_t stream,

@@ -54,11 +54,6 @@ __device__ __forceinline__ void stream_store2(float* p, float a, float b) {
     const u64 v = (u64)__float_as_uint(a) | ((u64)__float_as_uint(b) << 32);
     __hip_atomic_store((u64*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ f32x2 stream_load2(const float* p) {
-    const u64 v = __hip_atomic_load((const u64*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const f32x2 r = {__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32))};
-    return r;
-}
 
 template <int DTYPE, int D, int NR, bool POOL, int NI>
 __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamArgs<NI> p) {
