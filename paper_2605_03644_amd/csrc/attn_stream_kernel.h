@@ -478,9 +478,16 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         const bool self = s >= n_cs;
 #pragma unroll
         for (int kb = 0; kb < NK; ++kb) {
-            // (blocks past the own tokens are masked, whatever they hold)
-            if (self) {
-                if (SK * (s - n_cs) + 16 * kb < n_self) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16);
+            // Blocks past the own tokens are masked, whatever they hold, and not turned, but for the gathered forms that are slower with the
+            // branch: fp32, and bf16 from 64 columns on, which do best with one rotation of either kind of keys.  With / without it,
+            // us: fp32 x 128, 32/8 heads, 100 tokens over 7.9k slots 336 / 280, 8/2 heads, 64 over 7.9k 52.0 / 43.8, 24 over 154 11.8 / 10.9;
+            // fp32 x 64, 4/2 heads, 24 over 154 7.7 / 6.9; bf16 x 64, 24 over 260 8.7 / 8.0.  (bf16 x 16 and x 32 with one rotation: registers for
+            // half the workgroups, 256 tokens of 32/8 heads over 24k 270 -> 301 and 552 -> 569.)
+            const bool seen = SK * (s - n_cs) + 16 * kb < n_self;
+            if (POOL && BF && D >= 64) {
+                rotate(k[kb], (self ? (int64_t)it.q_pos0 + SK * (s - n_cs) : p.ctx_pos0 + k0 + SK * s) + 16 * kb + l16);
+            } else if (self) {
+                if ((POOL && !BF) || seen) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16);
             } else if (POOL) {
                 rotate(k[kb], p.ctx_pos0 + k0 + SK * s + 16 * kb + l16);
             }
