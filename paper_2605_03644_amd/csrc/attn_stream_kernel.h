@@ -85,14 +85,14 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     constexpr int TR = 16 * NR;
     constexpr int NS = NR * DB;  // 1 KB pieces of a wavefront's output state
     static_assert(D == 8 || D % 16 == 0, "head dimensions");
-    // Keys of an assembled context come through LDS (dma_k), two steps per wavefront, where these and the states fit and the loads are
+    // Keys of an assembled context come through LDS (dma_k), two steps per wavefront, in bf16 models where these and the states fit: the loads are
     // what the loop waits for.  Calls over contexts that no cache held, straight into the lanes / through LDS, us: bf16 x 64, 64 tokens over
-    // 6.6k slots 22.3 / 19.5, 32/8 heads x 128, 24 tokens over 830 10.3 / 9.7, fp32 x 64, 16 tokens over 1k 8.3 / 8.1; not fp32 x 128, whose
-    // matrix instructions take longer than its loads (32 tokens over 2k 13.5 / 13.7), nor two row blocks of fp32 x 64 (200 over 2k 44.3 / 46.7).
+    // 6.6k slots 22.3 / 19.5, 32/8 heads x 128, 24 tokens over 830 10.3 / 9.7.  Not fp32, whose matrix instructions take longer than its loads:
+    // x 128, 32 tokens over 2k 13.5 / 13.7, x 64, 100 tokens of 32/8 heads over 24k 214 / 222, 16 over 24k 32.5 / 33.1, one of 4/2 over 154 4.7 / 4.5.
     constexpr int RB = D * E;                                        // bytes of a row
     constexpr int KS_BYTES = SK * RB;                                // keys of a step
     constexpr int OS_BYTES = NS * 1024 > KS_BYTES ? NS * 1024 : KS_BYTES;
-    constexpr bool KL = !POOL && RB >= 128 && W * (OS_BYTES + KS_BYTES) <= 128 * 1024 && (BF || (D == 64 && NR == 1));
+    constexpr bool KL = BF && !POOL && RB >= 128 && W * (OS_BYTES + KS_BYTES) <= 128 * 1024;
     constexpr int RI = KL ? 1024 / RB : 1;                           // rows of one load instruction
     constexpr int CR = RB >= 16 ? RB / 16 : 1;                       // 16-byte chunks of a row
     constexpr int RG = RB < 256 ? 256 / RB : 1, CM = CR < 16 ? CR - 1 : 15;  // row r keeps chunk c at place c ^ (r / RG & CM)
