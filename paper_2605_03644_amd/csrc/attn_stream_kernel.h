@@ -819,9 +819,13 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     const int n_rows = rows - row0 < TR ? rows - row0 : TR;
     const int e4 = n_rows * (D / 4);  // 16-byte pieces of the output rows
     constexpr int PB = 8;             // splits in flight per thread, twice
-    // Threads in groups of a power of two, one for every piece of a pass; the groups take the splits between them.
+    // Threads in groups of a power of two, one for every piece of a pass; the groups take the splits between them, up to 8 splits one group.  No
+    // round of loads behind the last one, and that one's sum outside the loop.  With eight groups and a round more whatever there is / now, us: 4/2
+    // fp32 heads x 64, 32 queries of one token over 250 to 500 slots, 4 splits 8.5 / 7.9 (before the merge lost its branches 8.2); 8/2 x 128, 32
+    // tokens over 2.5k, 16 splits 11.8 / 11.4, 28/4 heads, one over 20k, 32 splits 11.8 / 11.6 (the round behind a branch in the loop: 12.2, 12.3).
     const int lg_t = 31 - __builtin_clz(T), lg_e = e4 > 1 ? 32 - __builtin_clz(e4 - 1) : 0;
-    const int lg_pe = lg_e < lg_t - 3 ? lg_t - 3 : lg_e < lg_t ? lg_e : lg_t;
+    const int lg_g = n_split > PB ? 32 - __builtin_clz((n_split - 1) / PB) : 0;
+    const int lg_pe = lg_e < lg_t - lg_g ? lg_t - lg_g : lg_e < lg_t ? lg_e : lg_t;
     const int pe = 1 << lg_pe, ng = T >> lg_pe;  // pieces of a pass; at most 8 groups
     const int grp = tid >> lg_pe, ei = tid & (pe - 1);
     const unsigned split_bytes = TR * D * 4;
@@ -853,18 +857,24 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         const int row = e / (D / 4);
         if (e0 != 0) pieces(e, 0, x);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int s0 = 0; s0 < n_split; s0 += PB * ng) {  // (s0 + grp + b * ng < 64: PB * ng divides it)
-            f32x4 y[PB];
-            pieces(e, s0 + PB * ng, y);
+        auto add = [&](int s0) __attribute__((always_inline)) {  // (s0 + grp + b * ng < 64: PB * ng divides it)
             const float* wr = &sw[s0 + grp][row < TR ? row : 0];
 #pragma unroll
             for (int b = 0; b < PB; ++b) {
                 const float w = wr[b * ng * TR];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[i] += w * x[b][i];
-                x[b] = y[b];
             }
+        };
+        int s0 = 0;
+        for (; s0 + PB * ng < n_split; s0 += PB * ng) {
+            f32x4 y[PB];
+            pieces(e, s0 + PB * ng, y);
+            add(s0);
+#pragma unroll
+            for (int b = 0; b < PB; ++b) x[b] = y[b];
         }
+        add(s0);
         if (ng > 1) {  // (then this is the only pass)
             red[tid] = acc;
             __syncthreads();

@@ -1,6 +1,7 @@
 """The streaming attention kernel where its keys come through LDS and where its splits are merged: contexts that end on either
 side of a 32-key step, of the eight wavefronts' first steps and of their second ones, own tokens that fill a key block or run
-over it, and split counts around the eight that a thread of the merge has in flight, for one row up to a full row block."""
+over it, and split counts around the eight that a thread of the merge has in flight and around those where its threads
+form two, four and eight groups, for one row up to a full row block."""
 import dataclasses
 
 import pytest
@@ -17,7 +18,7 @@ BARS = {"f32": dict(max_abs=1e-4, rel_fro=1e-5), "bf16": dict(max_abs=2e-2, rel_
 
 @pytest.mark.parametrize("dtype,d,hq,hkv", [("bf16", 128, 4, 4), ("bf16", 128, 28, 4), ("bf16", 64, 8, 2), ("f32", 64, 4, 2), ("f32", 128, 8, 2)])
 @pytest.mark.parametrize("n_ctx,t_q,splits", [(31, 1, 1), (33, 2, 1), (256, 1, 1), (257, 16, 1), (513, 17, 1), (1100, 4, 2), (1100, 1, 9),
-                                              (2200, 2, 17), (4096, 1, 64)])
+                                              (2200, 2, 17), (4096, 1, 64), (600, 3, 8), (1100, 5, 16), (2112, 4, 32), (2240, 2, 33)])
 def test_steps_and_merges(oracle_mod, dtype, d, hq, hkv, n_ctx, t_q, splits):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
