@@ -522,12 +522,7 @@ static hipError_t assemble_by_tiles(adapshot_ctx* ctx, const AssembleJob* jobs, 
     });
 }
 
-// Plan (prefix sums) and launch of validated assemble jobs, up to kAssembleBatch caches a launch.  Lists that fit the kernel arguments
-// go there: no pinned buffer, no event, no other kernel (2 caches of 16 shots 11.9 -> 11.2 us, 4 of 64 short ones 19.4 -> 14.8).  A longer
-// one goes through device memory where the launch writes more than the last-level cache holds, else as tiles: the kernel ahead of the
-// launch costs 4 to 7 us, and what it saves grows with the bytes.  MB written, by tiles / by list, us: one layer 171 57.6 / 61.6, 217 71.9
-// / 74.9, 341 130.2 / 129.0, 549 207 / 200, 1759 732 / 630; two layers 108 42.0 / 44.2, 269 104.7 / 105.2, 407 156 / 153, 1066 396 / 376;
-// 8 layers 2113 770 / 751, 28 layers 7441 2708 / 2618.  (Lists cut into launches with arguments: each costs 4.5 us.)
+// Plan (prefix sums) and launch of validated assemble jobs, up to kAssembleBatch caches a launch.
 static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_t n_jobs, int64_t pos0,
                                     hipStream_t stream) {
     for (int32_t j0 = 0; j0 < n_jobs; j0 += kAssembleBatch) {
@@ -542,12 +537,13 @@ static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_
         }
         if (n_tok == 0) continue;
         if (n_tiles > INT32_MAX / kTileTok) return fail(ctx, ADAPSHOT_EINVAL, "assemble: too many tiles");
-        const int64_t written = 2 * n_tok * ctx->row_bytes * ctx->desc.n_layers;
         hipError_t e;
-        if (n_caches == 1 && n_runs <= kAssembleShots) e = assemble_by_args<AssembleOne>(ctx, jobs + j0, n, pos0, stream);
-        else if (n_caches <= kAssembleFewCaches && n_runs <= kAssembleFewShots) e = assemble_by_args<AssembleFew>(ctx, jobs + j0, n, pos0, stream);
-        else if (written > kAssembleStreamBytes) e = assemble_by_list(ctx, jobs + j0, n, pos0, n_runs, n_blocks, stream);
-        else e = assemble_by_tiles(ctx, jobs + j0, n, pos0, n_tiles, stream);
+        switch (assemble_route(ctx->desc, n_caches, n_runs, n_tok, n_blocks)) {
+            case kAssembleOneByArgs: e = assemble_by_args<AssembleOne>(ctx, jobs + j0, n, pos0, stream); break;
+            case kAssembleFewByArgs: e = assemble_by_args<AssembleFew>(ctx, jobs + j0, n, pos0, stream); break;
+            case kAssembleByList: e = assemble_by_list(ctx, jobs + j0, n, pos0, n_runs, n_blocks, stream); break;
+            default: e = assemble_by_tiles(ctx, jobs + j0, n, pos0, n_tiles, stream); break;
+        }
         if (e != hipSuccess) return fail_hip(ctx, "assemble: launch", e);
         for (int32_t b = j0; b < j0 + n; ++b) jobs[b].cache->len += jobs[b].total;
     }

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "adapshot.h"
+#include "assemble_plan.h"
 #include "attn_plan.h"
 
 namespace adapshot {
@@ -39,7 +40,6 @@ inline FastDiv fast_div(int32_t d) {
 // and contiguous in the cache.  Angle of token tau in the tile: angle0 + tau*angle_step.
 // A launch serves up to kAssembleBatch caches: a tile names its cache, and the caches'
 // buffers travel in the kernel arguments.
-constexpr int kTileTok = 32;
 struct TileDesc {
     int32_t src_tok;     // first pool token (index inside a layer)
     int32_t dst_slot;    // first cache slot; the token's new position is the cache's pos0 + slot
@@ -52,7 +52,6 @@ struct TileDesc {
 };
 static_assert(sizeof(TileDesc) == 32, "TileDesc is read as two 16-byte words");
 
-constexpr int kAssembleBatch = 48;
 struct AssembleDst {  // one cache of the launch
     char* k_out;
     char* v_out;
@@ -82,8 +81,6 @@ struct AssembleParams {
 };
 hipError_t launch_assemble(const AssembleParams& p, hipStream_t stream);
 
-// Launches that write more than the last-level cache holds: non-temporal stores, and lists of any length by blocks instead of tiles.
-constexpr int64_t kAssembleStreamBytes = 256ll << 20;
 // Without tiles: workgroups are cut by cache slots, wg_tok consecutive ones each, cache after cache, and look their shots up.
 struct ShotRun {
     int32_t slot;     // first slot of the shot, counted from the call's first slot in this cache; increasing, the first one 0
@@ -127,8 +124,6 @@ struct ShotsHead {
 };
 // Kernel arguments end at 4 KB: one cache and a list of kAssembleShots, kAssembleFewCaches and kAssembleFewShots in all, or
 // kAssembleBatch caches and the list in device memory (NS = 0).
-constexpr int kAssembleShots = 320;
-constexpr int kAssembleFewCaches = 8, kAssembleFewShots = 272;
 static_assert(kAssembleBatch <= kBlockOneRun, "a block's cache");
 template <int NC, int NS>
 struct AssembleShotsParams {

@@ -59,8 +59,9 @@ def storage_to_f64(a: np.ndarray) -> np.ndarray:
     return a.astype(np.float64)
 
 
-def constant(name: str, header: str = "adapshot_internal.h") -> int:
-    """A whole-number limit of the library, from the header that defines it: a test that is about one side of it says so in numbers."""
-    text = open(os.path.join(os.path.dirname(wl.__file__), "csrc", header)).read()
+def constant(name: str) -> int:
+    """A whole-number limit of the library, from the source that defines it: a test that is about one side of it says so in numbers."""
+    csrc = os.path.join(os.path.dirname(wl.__file__), "csrc")
+    text = "".join(open(os.path.join(csrc, f)).read() for f in sorted(os.listdir(csrc)))
     a, shift = re.search(r"\b" + name + r" = (\d+)(?:ll)?(?: << (\d+))?[,;]", text).groups()
     return int(a) << int(shift or 0)

@@ -101,7 +101,7 @@ def test_lists_of_calls_in_flight(ad, profiled):
     k, v = (wl.normal_tensor((layers, int(offsets[-1]), hkv, d), torch.bfloat16, "cuda", s) for s in (1, 2))
     ctx.pool_register(k, v, offsets)
     token_bytes = layers * hkv * d * 2
-    assert layers >= H.constant("kAssemblePieceLayers", "adapshot_api.hip")
+    assert layers >= H.constant("kAssemblePieceLayers")
     wg_tok = 16384 // (hkv * d * 2)
     calls, sizes = [], []
     for m in (1500, 1600, 1500, 2800, 1700, 1500, 1500, 5600, 1600, 2900, 1500, 1500, 1500):
