@@ -323,7 +323,6 @@ extern "C" adapshot_status adapshot_pool_register(adapshot_ctx* ctx, const void*
 // table -- no empty workgroups and none that runs for a handful of tokens, four times the descriptors, read again by
 // every layer's workgroups (8 layers of 2 caches of 200 shots, 230 MB written, 79.2 -> 74.0 us; a single layer +5 %, and its planning would
 // overtake the GPU).
-constexpr int kAssemblePieceLayers = 8;
 static inline int64_t assemble_unit(const adapshot_ctx* ctx) {
     return ctx->desc.n_layers >= kAssemblePieceLayers ? ctx->assemble_wg_tok : kTileTok;
 }
@@ -470,7 +469,7 @@ static hipError_t assemble_by_list(adapshot_ctx* ctx, const AssembleJob* jobs, i
 
 // Up to kAssembleBatch jobs by tiles, whose descriptors the kernel reads in pinned memory.
 static hipError_t assemble_by_tiles(adapshot_ctx* ctx, const AssembleJob* jobs, int32_t n_jobs, int64_t pos0, int64_t n_tiles,
-                                    hipStream_t stream) {
+                                    int64_t n_tok, hipStream_t stream) {
     const bool local = ctx->desc.key_state == ADAPSHOT_KEYS_ROTATED_LOCAL;
     int slot;
     void* host;
@@ -511,6 +510,7 @@ static hipError_t assemble_by_tiles(adapshot_ctx* ctx, const AssembleJob* jobs, 
     p.tab_hi = ctx->tab_hi;
     p.pool_layer_stride_bytes = ctx->pool_layer_stride_tokens * ctx->row_bytes;
     p.n_tiles = (int32_t)nt;
+    p.n_tokens = n_tok;
     p.n_layers = ctx->desc.n_layers;
     p.n_dst = n_jobs;
     p.wg_tok = unit == kTileTok ? ctx->assemble_wg_tok : kTileTok;  // pieces cut by the host: one workgroup each
@@ -538,11 +538,11 @@ static adapshot_status run_assemble(adapshot_ctx* ctx, AssembleJob* jobs, int32_
         if (n_tok == 0) continue;
         if (n_tiles > INT32_MAX / kTileTok) return fail(ctx, ADAPSHOT_EINVAL, "assemble: too many tiles");
         hipError_t e;
-        switch (assemble_route(ctx->desc, n_caches, n_runs, n_tok, n_blocks)) {
+        switch (assemble_route(ctx->desc, n_caches, n_runs, n_tok, n_blocks, n_tiles)) {
             case kAssembleOneByArgs: e = assemble_by_args<AssembleOne>(ctx, jobs + j0, n, pos0, stream); break;
             case kAssembleFewByArgs: e = assemble_by_args<AssembleFew>(ctx, jobs + j0, n, pos0, stream); break;
             case kAssembleByList: e = assemble_by_list(ctx, jobs + j0, n, pos0, n_runs, n_blocks, stream); break;
-            default: e = assemble_by_tiles(ctx, jobs + j0, n, pos0, n_tiles, stream); break;
+            default: e = assemble_by_tiles(ctx, jobs + j0, n, pos0, n_tiles, n_tok, stream); break;
         }
         if (e != hipSuccess) return fail_hip(ctx, "assemble: launch", e);
         for (int32_t b = j0; b < j0 + n; ++b) jobs[b].cache->len += jobs[b].total;

@@ -69,6 +69,7 @@ struct AssembleParams {
     const float2* tab_lo;
     const float2* tab_hi;
     int64_t pool_layer_stride_bytes;
+    int64_t n_tokens;      // tokens of all tiles together
     int32_t n_tiles;
     int32_t n_layers;
     int32_t n_dst;         // caches of this launch (entries of dst in use)

@@ -204,7 +204,7 @@ __device__ __forceinline__ void rotate_k(const char* pool, const Rows& rows, cha
     }
 }
 
-template <int DTYPE, int CH>
+template <int DTYPE, int CH, bool NT>
 __global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p) {
     constexpr int HALF = CH * (DTYPE == ADAPSHOT_BF16 ? 8 : 4);
     __shared__ float2 cs[kTileTok * HALF];
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p
     const int64_t pool_off = (int64_t)blockIdx.y * p.pool_layer_stride_bytes;
 
     if (blockIdx.z == 1) {
-        copy_v<false>(p.v_pool + pool_off, rows, dc.v_out + dst_off, n_tok, row_bytes);
+        copy_v<NT>(p.v_pool + pool_off, rows, dc.v_out + dst_off, n_tok, row_bytes);
         return;
     }
     if (blockIdx.y == 0 && tid < n_tok) {
@@ -233,8 +233,8 @@ __global__ __launch_bounds__(256) void assemble_reencode_kernel(AssembleParams p
         if (dc.slot_tok) dc.slot_tok[slot] = td.tok0 + t_first + tid;
         if (dc.slot_pos) dc.slot_pos[slot] = dc.pos0 + slot;
     }
-    rotate_k<DTYPE, CH, false>(p.k_pool + pool_off, rows, dc.k_out + dst_off, n_tok, p.n_kv_heads, p.tab_lo, p.tab_hi, cs,
-                               [&](int tau) __attribute__((always_inline)) { return td.angle0 + (t_first + tau) * td.angle_step; });
+    rotate_k<DTYPE, CH, NT>(p.k_pool + pool_off, rows, dc.k_out + dst_off, n_tok, p.n_kv_heads, p.tab_lo, p.tab_hi, cs,
+                            [&](int tau) __attribute__((always_inline)) { return td.angle0 + (t_first + tau) * td.angle_step; });
 }
 
 // Ahead of a launch whose list is in pinned host memory: 16 lanes bring a run to device memory and write the blocks whose first slot
@@ -346,19 +346,26 @@ __global__ __launch_bounds__(256) void assemble_shots_kernel(AssembleShotsParams
                                 [&](int tau) __attribute__((always_inline)) { return row_angle[tau]; });
 }
 
+// What a launch writes, K and V.
+template <int DTYPE, typename H>
+static int64_t written_bytes(const H& h, int64_t n_tokens) {
+    return 2 * n_tokens * h.n_kv_heads * h.head_dim * (DTYPE == ADAPSHOT_BF16 ? 2 : 4) * h.n_layers;
+}
+
 template <int DTYPE, int CH>
 static hipError_t launch_t(const AssembleParams& p, hipStream_t stream) {
     dim3 grid((unsigned)p.n_tiles * (unsigned)(kTileTok / p.wg_tok), (unsigned)p.n_layers, 2);
-    launch_kernel((assemble_reencode_kernel<DTYPE, CH>), grid, dim3(256), stream, p);
+    if (written_bytes<DTYPE>(p, p.n_tokens) > kAssembleStreamBytes)
+        launch_kernel((assemble_reencode_kernel<DTYPE, CH, true>), grid, dim3(256), stream, p);
+    else
+        launch_kernel((assemble_reencode_kernel<DTYPE, CH, false>), grid, dim3(256), stream, p);
     return hipGetLastError();
 }
 
 template <int DTYPE, int CH, int NC, int NS>
 static hipError_t launch_t(const AssembleShotsParams<NC, NS>& p, hipStream_t stream) {
     const dim3 grid((unsigned)p.h.n_blocks, (unsigned)p.h.n_layers, 2);
-    // what the launch writes, K and V (a list in device memory: always enough)
-    const int64_t e = DTYPE == ADAPSHOT_BF16 ? 2 : 4;
-    if (NS == 0 || 2 * p.h.n_tokens * p.h.n_kv_heads * p.h.head_dim * e * p.h.n_layers > kAssembleStreamBytes)
+    if (NS == 0 || written_bytes<DTYPE>(p.h, p.h.n_tokens) > kAssembleStreamBytes)  // (a list in device memory: always)
         launch_kernel((assemble_shots_kernel<DTYPE, CH, true, NC, NS>), grid, dim3(256), stream, p);
     else
         launch_kernel((assemble_shots_kernel<DTYPE, CH, NS == 0, NC, NS>), grid, dim3(256), stream, p);

@@ -21,7 +21,7 @@ def test_small_batches(n_caches, m, lens_hi, local, index):
     (28, 1, 256, "bf16", 1, 4200, 4, 1), (28, 1, 256, "bf16", 48, 34, 12, 0), (28, 1, 256, "bf16", 49, 34, 12, 1),
     (2, 8, 128, "bf16", 1, 1100, 70, 1), (2, 8, 128, "bf16", 3, 380, 70, 0), (2, 16, 128, "f32", 9, 40, 70, 0), (1, 8, 128, "bf16", 8, 400, 55, 0)])
 def test_lists_in_device_memory(layers, hkv, d, dtype, n_caches, m, lens_hi, local):
-    written = _check(layers, hkv, d, dtype, n_caches, m, lens_hi, local, True)
+    written = _check(layers, hkv, d, dtype, n_caches, m, lens_hi, local, True, 2 if n_caches <= 48 else 3)  # (a 49th cache: a launch of its own)
     assert written > 256 << 20
 
 
@@ -43,7 +43,14 @@ def test_every_launch_is_recorded(n_caches, m, layers, launches):
     ctx.close()
 
 
-def _check(layers, hkv, d, dtype, n_caches, m, lens_hi, local, index):
+# the same rows by tiles: more than 256 MB of long shots in pieces cut by the host, fp32 shots of more than a tile
+@pytest.mark.parametrize("layers,hkv,d,dtype,n_caches,m,lens_hi,local", [(8, 8, 128, "bf16", 9, 40, 70, 0), (2, 8, 128, "f32", 3, 130, 120, 1)])
+def test_tiles_past_the_cache(layers, hkv, d, dtype, n_caches, m, lens_hi, local):
+    written = _check(layers, hkv, d, dtype, n_caches, m, lens_hi, local, True, 1)
+    assert 256 << 20 < written <= 512 << 20
+
+
+def _check(layers, hkv, d, dtype, n_caches, m, lens_hi, local, index, launches=None):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2605_03644_amd import binding as ad
@@ -62,7 +69,11 @@ def _check(layers, hkv, d, dtype, n_caches, m, lens_hi, local, index):
     got, want = ([ad.Cache(ctx, 5 + t + 2, with_index=index) for t in totals] for _ in range(2))
     for c in got + want:
         c.c.len = 5
+    ctx.profile_enable(launches is not None)
     ctx.assemble_batched(got, ids, [None] * n_caches, pos0=9)
+    if launches is not None:  # the route: a list is a launch of its own
+        assert ctx.profile_read()["assemble_reencode"][1] == launches
+        ctx.profile_enable(False)
     for c, i in zip(want, ids):
         for a in range(0, m, 300):
             ctx.assemble(c, i[a:a + 300], None, pos0=9)

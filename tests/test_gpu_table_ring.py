@@ -96,7 +96,7 @@ def test_lists_of_calls_in_flight(ad, profiled):
     ctx = ad.Context(layers, 8, hkv, d, 1.0e4, ad.BF16, max_position=1 << 17)
     rng = np.random.default_rng(6)
     n_pool = 6000
-    lens = rng.integers(0, 13, n_pool).astype(np.int64)
+    lens = rng.integers(0, 41, n_pool).astype(np.int64)
     offsets = np.concatenate([[0], np.cumsum(lens)])
     k, v = (wl.normal_tensor((layers, int(offsets[-1]), hkv, d), torch.bfloat16, "cuda", s) for s in (1, 2))
     ctx.pool_register(k, v, offsets)
@@ -104,10 +104,10 @@ def test_lists_of_calls_in_flight(ad, profiled):
     assert layers >= H.constant("kAssemblePieceLayers")
     wg_tok = 16384 // (hkv * d * 2)
     calls, sizes = [], []
-    for m in (1500, 1600, 1500, 2800, 1700, 1500, 1500, 5600, 1600, 2900, 1500, 1500, 1500):
+    for m in (900, 950, 900, 2200, 1000, 900, 900, 4400, 950, 1200, 900, 900, 900):
         shots = rng.permutation(n_pool)[:m].astype(np.int32)
         n = int(lens[shots].sum())
-        assert not _by_tiles(1, m, n, token_bytes) and 2 * n * token_bytes > H.constant("kAssembleStreamBytes")
+        assert m > H.constant("kAssembleShots") and 2 * n * token_bytes > 2 * H.constant("kAssembleStreamBytes")
         sizes.append(16 * (int((lens[shots] > 0).sum()) + -(-n // wg_tok)))
         calls.append(([ad.Cache(ctx, n + 3)], [shots]))
         lists = [rng.permutation(n_pool)[:170].astype(np.int32) for _ in range(2)]
