@@ -25,15 +25,15 @@
  *     one stream at a time; use one context per concurrent stream.
  *   - Allocation and waiting.  adapshot_create allocates the RoPE tables and 16 KiB of arrival counters
  *     (hipMalloc, blocking copies, and a wait for them).  adapshot_query_attn, adapshot_query_attn_pool, the batched attention calls, adapshot_probe_entropy,
- *     adapshot_probe_entropy_tokens, adapshot_rank_shots and assembly of more shots than its kernel arguments hold (320 for one cache,
- *     272 for up to 8) that writes more than 256 MiB keep grow-only workspaces: a call that
+ *     adapshot_probe_entropy_tokens, adapshot_rank_shots and assembly of a long shot list that writes more than 256 MiB keep grow-only workspaces: a call that
  *     needs more than any earlier call on the context calls hipMalloc (an outgrown buffer is kept
  *     until adapshot_destroy, never freed in a call, so no call waits for the device); a call that
- *     fits the existing workspaces allocates nothing.  Assembly of more shots than that, adapshot_query_attn_pool, the batched attention
+ *     fits the existing workspaces allocates nothing.  Assembly of a long shot list, adapshot_query_attn_pool, the batched attention
  *     calls and adapshot_rank_shots write small tables into a ring of 8 pinned host buffers (hipHostMalloc
  *     when one must grow); the ninth such call in flight waits for the first one's kernels.  No
- *     call synchronises the device or the stream otherwise.  adapshot_probe_entropy_static is the
- *     variant of the entropy call that never allocates.
+ *     call synchronises the device or the stream otherwise.  (A long shot list: one that does not travel in the kernel arguments.  Up to 320 shots of one
+ *     cache do, and up to 272 of 2 to 8 caches, but for large launches whose rows are below 512 bytes.  Batched attention of up to 32 items
+ *     mostly travels there too.)  adapshot_probe_entropy_static is the variant of the entropy call that never allocates.
  *   - Every function validates its arguments on the host BEFORE launching
  *     anything: a call that returns an error has written nothing to device
  *     memory.  The reason is kept per context (adapshot_last_error).

@@ -299,7 +299,8 @@ struct CombineWork {  // one workgroup of the batched combine kernel: 16 (kv hea
 };
 // A smaller batch travels in the kernel arguments, which costs neither the table copy (4.2 us) nor the wait of the kernel behind it for its
 // completion event (4.5 us): a decode step of 32 queries of 16k slots 185 -> 180 us a layer, passes of probe sweeps over one to
-// three layers 235 -> 203 and 170 -> 145.  An entry of work is an (item, split, row tile), served by n_kv_heads workgroups, the
+// three layers 235 -> 203 and 170 -> 145.  What goes beyond them is as before: 24 tokens of 32/8 heads over 1k slots, 32 items 51.6 ->
+// 46.5 us, 33 items 67.  An entry of work is an (item, split, row tile), served by n_kv_heads workgroups, the
 // kv head fastest as in the tables.  Kernel arguments end at 4 KB.
 constexpr int kBatchArgItems = 32, kBatchArgWork = 352;
 struct BatchArgItem {

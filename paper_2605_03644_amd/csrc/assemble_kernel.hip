@@ -262,8 +262,8 @@ __global__ __launch_bounds__(256) void assemble_list_kernel(AssembleMany p) {
 // Bound by the launch and three round trips below 1000 tokens, by the copy's rate from 10000 on.  Tiles / list in the arguments, call
 // after call with the event that guards the tiles, us: fp32 4/2 x 64, 225 tokens 7.5 / 6.0; bf16 32/8 x 128, 644 tokens 8.0 / 5.5,
 // 3.2k 10.4 / 6.6, 25.5k 41.1 / 36.9; 32/8 x 64, 2 layers of 6.5k 18.4 / 13.0; 4 caches of 64 shots, 8k tokens 19.4 / 14.8; 28 layers of
-// 26.5k 5.6 / 5.8 TB/s.  Tiles / list in device memory, kernel alone: 8 caches of 53k tokens, two layers 1346 / 1190 (5.2 / 5.9
-// TB/s), 127k tokens, two layers 405 / 367.
+// 26.5k 5.6 / 5.8 TB/s.  Tiles / list in device memory with the kernel ahead of it: 8 caches of 53k tokens, two layers 1335 / 1239
+// (5.3 / 5.7 TB/s), 127k tokens, two layers 400 / 380.
 template <int DTYPE, int CH, bool NT, int NC, int NS>
 __global__ __launch_bounds__(256) void assemble_shots_kernel(AssembleShotsParams<NC, NS> p) {
     constexpr int HALF = CH * (DTYPE == ADAPSHOT_BF16 ? 8 : 4);

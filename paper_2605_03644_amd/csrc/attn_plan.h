@@ -112,8 +112,9 @@ inline int64_t stream_splits(const StreamShape& s, int64_t split_tiles) {
 // for its share of the keys: 2.4 TB/s to 64 workgroups, 3.4 to 128, 6.1 to 256; rows of one kv head in several units are drawn
 // from it half of the time.  Splits cost their merge by the last workgroup: 3.2 us, 0.15 for every round of its loads and 19 ns per KB.
 // Fitted to 1294 calls over contexts that no cache held, each with up to 20 split counts (single calls of 11 models, 1 to 256 tokens over
-// 60 to 32k slots; decode steps of 2 to 32 queries of 5 models): the counts chosen here take 0.8 % longer than the best ones, at
-// most 18 % (a price fitted to repeated calls over one context: 4 %, at most 54 %).
+// 60 to 32k slots; decode steps of 2 to 32 queries of 5 models), with a merge that took splits one branch at a time: the counts chosen took 0.8 %
+// longer than the best ones.  The merge has become shorter since and the price has not: over 107 such calls of 8 models the counts chosen take
+// 6.1 % longer, at most 25 % (64/8 heads x 128, 8 tokens over 330 slots 7.9 us, in one split 6.3; 28/4 heads, one over 16k, 42 splits 12.5 to 12.8, 51 and 63 12.4).
 inline double stream_price(const adapshot_model_desc& d, int64_t n_cu, const StreamShape* shapes, int32_t n_shapes, int32_t row_blocks,
                            int64_t split_tiles) {
     const int64_t e = d.dtype == ADAPSHOT_BF16 ? 2 : 4, sk = stream_step_keys(d);
@@ -194,17 +195,18 @@ inline StreamPlan plan_stream(const adapshot_model_desc& d, int64_t n_cu, int32_
 }
 
 // Which kernel: the 256-row tile kernel for bf16 models of head dimension 128 where it is the cheaper one.  It reads a context
-// once per 256 rows and draws 6.1 TB/s, but is two launches (a batch: three), leaves wavefronts without rows idle and
-// writes a partial for every split; the streaming kernel reads it once per 16 rows, in one launch.
+// once per 256 rows and draws 6.1 TB/s, but is two launches (a batch whose tables do not fit the kernel arguments: three), leaves wavefronts
+// without rows idle and writes a partial for every split; the streaming kernel reads it once per 16 rows, in one launch.
 constexpr int64_t kStreamBytes = 200000000;
 inline int64_t context_bytes(const adapshot_model_desc& d, int64_t slots) { return slots * d.n_kv_heads * d.head_dim * 4; }
 
 // A single call compares prices, but keeps the streaming kernel's fp32 partials where it has few rows.  The tile kernel's price: 10.8 us
 // for the two launches, 0.83 us per MB of partials, 0.08 per split, and per tile of a workgroup and turn 0.35 or (more than 128 rows)
-// 0.57 us, or 7.3 MB/us.  Over 358 calls (5 models, 1 to 256 tokens over 60 to 32k slots that no cache held) the kernel chosen is 0.2 %
-// slower than the better one, at most 14 %.  Us, tile kernel / streaming: 32/8 heads, 8 tokens over 250 / 2k / 4k slots
-// 11.3 / 14.9 / 16.4 and 7.0 / 11.2 / 12.8; 32 tokens over 1k / 4k 15.8 / 19.1 and 11.5 / 19.7; 64 tokens over 250 / 1k / 4k 13.9 / 18.4 / 21.9
-// and 7.8 / 15.1 / 30.4; 28/4 heads, 16 / 64 tokens over 4k 21.7 / 22.4 and 14.8 / 29.0; 64/8 heads, 8 tokens over 8k 20.0 and 22.6.
+// 0.57 us, or 7.3 MB/us.  Fitted to 358 calls (5 models, 1 to 256 tokens over 60 to 32k slots that no cache held); the streaming kernel's merge has become
+// shorter since: over 121 such calls the kernel chosen is 1.5 % slower than the better one, at most 39 % (8/2 heads, 58 tokens over 12k 25.5 by
+// tiles, 18.3 by streaming; 28/4 heads, 76 over 1.8k 20.0 and 14.5).  Us a call, call after call, tile kernel / streaming: 32/8 heads, 8 tokens over
+// 250 / 2k / 4k slots 11.4 / 15.3 / 16.7 and 6.2 / 9.0 / 10.4; 32 tokens over 1k / 4k 15.8 / 19.5 and 9.6 / 17.4; 64 tokens over 250 / 1k / 4k
+// 14.2 / 18.0 / 23.5 and 7.4 / 11.2 / 24.5; 28/4 heads, 16 / 64 tokens over 4k 21.6 / 22.3 and 12.5 / 23.1; 64/8 heads, 8 tokens over 8k 20.0 and 19.3.
 inline bool single_by_tiles(const adapshot_model_desc& d, int32_t t_q, int64_t n_ctx, bool zero_copy, int64_t n_cu = 256) {
     if (!attn_mfma_supported(d)) return false;
     if (zero_copy || context_bytes(d, n_ctx) > kStreamBytes) return true;  // (no gathered form of the streaming kernel for these models)
@@ -225,10 +227,11 @@ inline bool single_by_tiles(const adapshot_model_desc& d, int32_t t_q, int64_t n
 
 // A batch of these models: the streaming kernel if every item has at most 16 rows per kv head, all contexts together at most 1.5 times
 // kStreamBytes, and every context is read by one item -- items that share one find its tiles in the L2 when the tile kernel orders
-// them by cache and split.  Per layer of a decode step over contexts that no cache held, tables made for every call (tile kernel with
-// table copy and merge / streaming kernel, us): 28/4 heads, 12 queries of 8k slots 197 MB 48.7 / 41.3, 8 of 16k 262 MB 59.5 / 53.4, 20
-// of 8k 328 MB 66.9 / 65.3, 12 of 16k 393 MB 74.5 / 75.8, 16 of 16k 524 MB 95.0 / 99.2; 32/8 heads, 4 tokens, 8 of 8k 262 MB
-// 56.1 / 56.2, 12 of 8k 393 MB 84.6 / 84.7, 6 of 16k 393 MB 73.1 / 79.1.  A batch of one takes it where a single call does, too.
+// them by cache and split.  Per layer of a decode step over contexts that no cache held, planned anew in every call (tile kernel, its tables in the
+// kernel arguments, and merge / streaming kernel, us): 28/4 heads, 16 queries of 4k slots 131 MB 33.1 / 29.1, 12 of 8k 197 MB 44.2 / 40.4, 30 of 4k 246 MB
+// 53.7 / 49.9, 8 of 16k 262 MB 50.9 / 53.0, 20 of 8k 328 MB 65.5 / 62.5, 12 of 16k 393 MB 74.8 / 73.9, 16 of 16k 524 MB 96.6 / 97.3; 32/8 heads,
+// 4 tokens, 8 of 8k 262 MB 54.3 / 52.8, 12 of 8k 393 MB 76.2 / 78.4, 6 of 16k 393 MB 74.3 / 74.3.  With tables (33 queries of 28/4 heads): of 4k
+// 270 MB 70.3 / 60.5, of 8k 541 MB 116.1 / 106.1.  A batch of one takes it where a single call does, too.
 inline bool batch_by_stream(const adapshot_model_desc& d, const adapshot_attn_item* items, int32_t n_items, int64_t n_cu) {
     if (!attn_mfma_supported(d)) return true;
     if (n_items == 1 && !single_by_tiles(d, items[0].t_q, items[0].n_ctx, false, n_cu)) return true;

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     // Keys of an assembled context come through LDS (dma_k), two steps per wavefront, in bf16 models where these and the states fit: the loads are
     // what the loop waits for.  Calls over contexts that no cache held, straight into the lanes / through LDS, us: bf16 x 64, 64 tokens over
     // 6.6k slots 22.3 / 19.5, 32/8 heads x 128, 24 tokens over 830 10.3 / 9.7.  Not fp32, whose matrix instructions take longer than its loads:
-    // x 128, 32 tokens over 2k 13.5 / 13.7, x 64, 100 tokens of 32/8 heads over 24k 214 / 222, 16 over 24k 32.5 / 33.1, one of 4/2 over 154 4.7 / 4.5.
+    // x 128, 32 tokens over 2k 13.5 / 13.7, x 64, 100 tokens of 32/8 heads over 24k 214 / 222, 16 over 24k 32.5 / 33.1, one of 4/2 over 154 4.7 / 4.5, 16 over 224 6.6 / 6.1.
     constexpr int RB = D * E;                                        // bytes of a row
     constexpr int KS_BYTES = SK * RB;                                // keys of a step
     constexpr int OS_BYTES = NS * 1024 > KS_BYTES ? NS * 1024 : KS_BYTES;
