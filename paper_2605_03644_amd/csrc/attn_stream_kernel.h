@@ -473,8 +473,8 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
     clear();
 
     // keys that come un-rotated, turned to their positions; loads return in order, and behind the next step's rows the tables' entries
-    // are waited for with them
-    auto turn = [&](int s, unsigned (&k)[NK][NJ][KR]) __attribute__((always_inline)) {
+    // are waited for with them; all: blocks that no row sees as well
+    auto turn = [&](int s, unsigned (&k)[NK][NJ][KR], bool all = false) __attribute__((always_inline)) {
         const bool self = s >= n_cs;
 #pragma unroll
         for (int kb = 0; kb < NK; ++kb) {
@@ -487,7 +487,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
             if (POOL && BF && D >= 64) {
                 rotate(k[kb], (self ? (int64_t)it.q_pos0 + SK * (s - n_cs) : p.ctx_pos0 + k0 + SK * s) + 16 * kb + l16);
             } else if (self) {
-                if ((POOL && !BF) || seen) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16);
+                if ((POOL && !BF) || all || seen) rotate(k[kb], (int64_t)it.q_pos0 + SK * (s - n_cs) + 16 * kb + l16);
             } else if (POOL) {
                 rotate(k[kb], p.ctx_pos0 + k0 + SK * s + 16 * kb + l16);
             }
@@ -656,9 +656,12 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
         // compiler wait at its head for loads that only that way out leaves behind, and a wavefront with one step loads no
         // second one (one step per wavefront: 7.2 -> 6.6 us of a call, 10.3 -> 9.6).
         int s = wave;
+        // (bf16 x 32 turns blocks that no row sees, but for the step behind the loop: 32/8 heads, 94 tokens over 6.4k slots 28.1 -> 27.3 us, 111 over 7.2k
+        // 31.2 -> 30.6, before any block was left out 27.6 and 30.8; small calls lose 1 to 2 % of the 10 that this gave them.)
+        constexpr bool kLoopTurnsAll = BF && D == 32 && !POOL;
         auto step = [&](int b) __attribute__((always_inline)) {
             const int kb = KL ? 0 : b;
-            if (!LATE && !KL) turn(s, kf[kb]);
+            if (!LATE && !KL) turn(s, kf[kb], kLoopTurnsAll);
             if (NBV == 1) {
                 load_v(s, vf[0]);
                 fetch_tok(s + W);
@@ -675,7 +678,7 @@ __global__ __launch_bounds__(kStreamWaves * 64) void attn_stream_kernel(StreamAr
                 __builtin_amdgcn_sched_barrier(0);  // the next step's loads first
                 take_k(b == 0 ? kw0 : kw1, kf[0]);
             }
-            if (LATE || KL) turn(s, kf[kb]);
+            if (LATE || KL) turn(s, kf[kb], kLoopTurnsAll);
             compute(s, kf[kb], vf[b % NBV], std::false_type{});
             s += W;
         };
